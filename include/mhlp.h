@@ -68,11 +68,11 @@ typedef struct {
     double tol;         /* stop when ||g - A mu||_2 / ||g||_2 <= tol (true residual) */
     int32_t max_iter;   /* total Arnoldi steps                                        */
     int32_t restart;    /* Krylov dimension before a restart (<= 512)                 */
-    int32_t precision;  /* MHLP_FP64 or MHLP_MIXED (mixed: FP32 far-field inner solves
-                           inside FP64 iterative refinement: each cycle's Arnoldi steps
-                           use the FP32 far field and stop at 0.5e-6 of the residual
-                           the cycle started from; each cycle ends with the FP64 true
-                           residual, from which the next starts)                      */
+    int32_t precision;  /* MHLP_FP64 or MHLP_MIXED (mixed: inner solves of iterative
+                           refinement: each cycle's Arnoldi steps stop at 0.5e-6 of
+                           the residual the cycle started from; each cycle ends with
+                           the FP64 true residual, from which the next starts; the
+                           operator itself is FP64 in both)                           */
     int32_t use_x0;     /* 1: mu holds the initial guess on entry; 0: zero guess      */
 } mhlp_gmres_opts;
 
@@ -140,12 +140,11 @@ mhlp_status mhlp_plan_info(const mhlp_plan *plan, int64_t *n_targets, int64_t *n
    panels evaluated by separate blocks (partial sums added in fixed order, so
    results do not depend on nsplit beyond rounding); the default aims at about
    8192 blocks of 256 targets with at least 2 panels per split.  The FP64
-   single and double layers do not use it: they run as a stream of
-   (256 targets, one panel) units spread evenly over one launch of as many
-   blocks as the chip holds, and the FP64 double layer of an on-surface scalar
-   plan of up to 8192 nodes (the BIE operator, GMRES) evaluates each unordered
-   pair once on tiles of its own.  set_split may reallocate the plan's
-   partial-sum buffer (it synchronises the device then).
+   single and double layers do not use it: each group of 64 targets takes the
+   panels far from it through expansions of clusters of up to 16 panels
+   (truncated below rounding) and the others pair by pair, from lists built
+   with the plan.  set_split may reallocate the plan's partial-sum buffer (it
+   synchronises the device then).
    mhlp_plan_autotune times the far evaluation (layers: 1 SLP, 2 DLP, 3 both,
    4 the on-surface BIE operator, 5 the gradients of both, off-surface, 6 the
    stresslet operator of a stokes plan, 7 the stresslet target gradient of an
@@ -154,8 +153,7 @@ mhlp_status mhlp_plan_info(const mhlp_plan *plan, int64_t *n_targets, int64_t *n
    with HIP events on `stream`, keeps the fewest splits within 1% of the
    fastest and reports it with its time (host outputs; cand/cand_ms receive up
    to cap candidates and their ms per launch).  Where the FP64 launch does not
-   use the split (layers 1-3, and 4 on a symmetric on-surface plan), FP64
-   requests time the MIXED launch of the same layers, the one the split
+   use the split (layers 1-4), FP64 requests time the MIXED launch of the same layers, the one the split
    serves.  Synchronises the stream.  Errors: MHLP_INVALID_ARG. */
 mhlp_status mhlp_plan_set_split(mhlp_plan *plan, int32_t nsplit);
 mhlp_status mhlp_plan_get_split(const mhlp_plan *plan, int32_t *nsplit);

@@ -18,9 +18,12 @@
  *                    panels (some node within 1.2 h), Newton preimage, Bernstein
  *                    radius < 3.5 (Sec. 4.5.1).
  *   near_weights     one thread per listed pair: correction weights (nearfield.h).
- *   far_eval_fp64    one thread per target, sources streamed through LDS in tiles
- *                    of 16 panels; listed panels are skipped and their corrected
- *                    contribution added in the epilogue (no add-then-subtract).
+ *   far_tree         FP64 far field (tree.h): far panels through cluster expansions,
+ *                    the others pair by pair; listed panels are skipped and their
+ *                    corrected contribution added in the epilogue (no
+ *                    add-then-subtract).
+ *   far_eval_mixed   FP32 far field, one thread per target, sources streamed
+ *                    through LDS in tiles of 16 panels.
  *   gmres_*          BLAS-1 pieces of the Arnoldi process.
  */
 #include <hip/hip_runtime.h>
@@ -97,6 +100,7 @@ static_assert(sizeof(GState) <= 64, "the state and the tail state share the firs
 
 namespace mhlp {
 struct FmmTree;
+struct TreeDev;
 }
 
 struct mhlp_plan {
@@ -115,15 +119,14 @@ struct mhlp_plan {
     bool stokes = false;      /* modified-Stokes (stresslet) plan: operator on [2][N] densities */
     double *wstk = nullptr;   /* stokes: [4][nnz][16] stresslet weights (D11, D12, D21, D22)   */
     mhlp::FmmTree *fmm = nullptr; /* off-surface scalar plans: FMM far field (mhlp_plan_set_fmm) */
-    /* on-surface scalar plans up to SYM_NMAX nodes: the double layer's far sum
-       with each unordered pair evaluated once (sym_far_kernel) */
+    /* on-surface stresslet plans up to SYM_NMAX nodes: the far sum with each
+       unordered pair evaluated once (stk_sym_kernel) */
     int2 *sym_tiles = nullptr;   /* (row block, column chunk) of each tile */
     int32_t sym_ntiles = 0;
     double *sym_p1 = nullptr;    /* [column chunks][N] row sums */
     double *sym_p2 = nullptr;    /* [row blocks][N] column sums */
     uint32_t *sym_bits = nullptr; /* [N][sym_nw] near panels of each node as bits */
     int32_t sym_nw = 0;
-    uint8_t *sym_cls = nullptr;   /* [4 row blocks][Np] piece class of each (row wave, column panel) */
     double *wstkg = nullptr;  /* stokes, off-surface, built on first use: [8][nnz][16] stresslet
                                  gradient weights, block (2a + l) 2 + j = d u_a/d x_l per mu_j */
     double *stk_flux = nullptr; /* stokes: device scalar sum_j w_j mu_j.n_j / |Gamma|           */
@@ -133,13 +136,12 @@ struct mhlp_plan {
     int nsplit = 1;           /* source splits of the far field (small M)   */
     int32_t pps = 0;          /* panels per split                           */
     double *part = nullptr;   /* [2][nsplit][M] partial sums ([4][..] off-surface, for gradients) */
-    /* FP64 far field as a stream of (target block, panel) units (far_eval_fp64) */
-    uint8_t *wcls = nullptr;  /* [M/64 waves][Np] fine piece + 1 of each (wave, panel) */
+    uint8_t *wcls = nullptr;  /* [M/64 waves][Np] fine piece + 1 of each (wave, panel): mixed precision,
+                                 gradients, stresslet */
     double *fqd = nullptr;    /* [2][KQ_NP] fine-piece scales at alpha (fine_scales) */
-    int32_t sk_P[3] = {0, 0, 0}; /* blocks of the launch (resident blocks of the chip) for SLP+DLP, SLP, DLP */
-    int32_t sk_S = 0;            /* partial slots per target block, the largest over the three */
-    int32_t sk_stride = 1;       /* unit order within a target block (coprime to Np)            */
-    double *skpart = nullptr;    /* [2][sk_S][M] */
+    mhlp::TreeDev *tree = nullptr; /* scalar plans: clusters, item lists, moments (tree.h) */
+    int tr_waves = 0, tr_split = 1; /* waves per block and blocks per group of far_tree_kernel */
+    double *trpart = nullptr;  /* [2][tr_split][M] partial sums when tr_split > 1 */
     NearParams np{};
     double near_factor = 1.2;
     int64_t part_cap = 0;     /* capacity of part (doubles)                 */
@@ -513,16 +515,7 @@ struct FarArgs {
     int64_t jstride;
     const int32_t *perm; /* output index of internal target i (NULL: identity) */
     const double *pcx, *pcy, *prad; /* bounding circle of each panel */
-    /* FP64 far field as a stream of (target block, panel) units: the launch's
-       skP blocks take equal contiguous ranges of the skU = TB Np units and
-       leave one partial sum per target block they touch, slot = block - first
-       block of that target block ([layer][skS][M]); wcls[wave Np + p] - 1 is
-       the fine piece every pair of the wave with panel p lies in (plan time) */
-    int64_t skU;
-    int32_t skP, skS;
-    int32_t skStride; /* unit j of a target block is panel (j skStride) mod Np */
-    double *skps, *skpd;
-    const uint8_t *wcls = nullptr;
+    const uint8_t *wcls = nullptr; /* [M/64 waves][Np] fine piece + 1 of each (wave, panel): mixed precision */
     const double *fq = nullptr; /* [2][KQ_NP] scales of the fine pieces at the plan's alpha (fine_scales) */
 };
 
@@ -657,16 +650,16 @@ __device__ __forceinline__ double wave_sum_dpp(double v)
     return __hiloint2double(hi, lo);
 }
 
-/* ---- on-surface double layer, each unordered far pair once ----
-   K1(z)/r depends on the pair only through r, so one evaluation serves the
-   term of source j at node i and of source i at node j.  Tiles pair a block of
+/* ---- on-surface stresslet operator, each unordered far pair once ----
+   The A1..A3 of a pair depend on it only through r, so one evaluation serves
+   the term of source j at node i and of source i at node j.  Tiles pair a block of
    SYM_R = 256 row nodes (16 panels) with a chunk of SYM_C = 16 column nodes
    (one panel; small tiles keep enough blocks in flight); tile (I, J) exists
    when the chunk does not start before the block (column panels >= 16 I), and on the block's own chunks only row < column
    counts.  The row node takes the column terms (unless the column panel is
    listed near it) into p1[J][i]; each column node takes the row terms (unless
-   the row's panel is listed near the column node), summed over lanes by a
-   butterfly and over waves in order, into p2[I][j].  Every pair of distinct
+   the row's panel is listed near the column node), summed over lanes and over
+   waves in order, into p2[I][j].  Every pair of distinct
    nodes is evaluated in exactly one tile. */
 constexpr int SYM_R = 256, SYM_C = 16, SYM_RP = SYM_R / 16, SYM_CP = SYM_C / 16, SYM_NMAX = 8192;
 
@@ -678,15 +671,6 @@ __device__ __forceinline__ double gsf_wave_sum(double v)
 }
 
 
-struct SymArgs {
-    FarArgs A;
-    const int2 *tiles;
-    double *p1, *p2;
-    const uint32_t *bits; /* [N][nw] near panels of each node */
-    int nw;
-    const uint8_t *cls;   /* [N/64 row waves][Np] fine piece + 1 of every pair of (wave, column panel); bit 7:
-                             some pair of them is near on either side */
-};
 static_assert(SYM_RP == 16 && SYM_CP == 1, "the near masks below read 16 row panels and one column panel");
 
 /* per node, its near panels as a bit set of nw words */
@@ -700,489 +684,6 @@ __global__ void near_bits_kernel(const int32_t *__restrict__ nptr, const int32_t
     for (int32_t q = nptr[i]; q < nptr[i + 1]; ++q) {
         const int32_t p = npan[q];
         if (p >= 0) b[p >> 5] |= 1u << (p & 31);
-    }
-}
-
-/* the column loop of sym_far_kernel for 16 columns, two at a time, with the
-   fine piece PC (-1: z <= 2; KQ_NP: per-pair selection) of the wave and column
-   panel.  MASK: the wave has near pairs (on either side) or is on the diagonal
-   block, where only row < column counts.  The row terms accumulate in the
-   returned sum; the column terms go to colv[s][t] for the block's reduction. */
-template <int PC, bool MASK>
-__device__ __forceinline__ double sym_columns(const FarArgs &A, const FarConst &fc, int ncol, int64_t i, int64_t j0,
-                                              bool valid, bool diag, double x, double y, double dix, double diy,
-                                              uint32_t rnear, int kp, const double *cx, const double *cy,
-                                              const double *cdx, const double *cdy, const uint32_t *cmask,
-                                              double (*colv)[SYM_R])
-{
-    constexpr int K = PC < 0 || PC >= KQ_NP ? 0 : PC;
-    const FarTab T = far_table();
-    double qa, qk;
-    fine_q<K>(A.fq, qa, qk);
-    const int t = threadIdx.x;
-    double acc = 0.0;
-#pragma unroll 1
-    for (int s = 0; s < ncol; s += 2) {
-        const int64_t ja = j0 + s, jb = ja + 1;
-        const double ex0 = x - cx[s], ey0 = y - cy[s], ex1 = x - cx[s + 1], ey1 = y - cy[s + 1];
-        double r20 = fma(ex0, ex0, ey0 * ey0), r21 = fma(ex1, ex1, ey1 * ey1);
-        bool r0 = valid, r1 = valid, c0 = valid, c1 = valid;
-        if (MASK) {
-            /* row and column terms wanted for the two columns (s, s + 1 share a panel) */
-            const bool rfar = valid && !(rnear & 1u);
-            r0 = rfar && (!diag || i < ja);
-            r1 = rfar && (!diag || i < jb);
-            c0 = valid && !((cmask[s] >> kp) & 1u) && (!diag || i < ja);
-            c1 = valid && !((cmask[s + 1] >> kp) & 1u) && (!diag || i < jb);
-            r20 = (r0 || c0) ? r20 : 1.0; /* unused pairs (the node itself among them) */
-            r21 = (r1 || c1) ? r21 : 1.0;
-        }
-        K01 o0, o1;
-        if constexpr (PC >= KQ_NP)
-            k01_far2<false, true, true, true>(T, fc, r20, r21, o0, o1);
-        else
-            k01_far2_fixed<false, true, PC>(T, fc, qa, qk, r20, r21, o0, o1);
-        const double f0 = fma(ex0, cdx[s], ey0 * cdy[s]), f1 = fma(ex1, cdx[s + 1], ey1 * cdy[s + 1]);
-        const double g0 = -fma(ex0, dix, ey0 * diy), g1 = -fma(ex1, dix, ey1 * diy);
-        if (MASK) {
-            if (r0) acc = fma(o0.ak1r, f0, acc);
-            if (r1) acc = fma(o1.ak1r, f1, acc);
-            colv[s][t] = c0 ? o0.ak1r * g0 : 0.0;
-            colv[s + 1][t] = c1 ? o1.ak1r * g1 : 0.0;
-        } else {
-            acc = fma(o1.ak1r, f1, fma(o0.ak1r, f0, acc));
-            colv[s][t] = o0.ak1r * g0;
-            colv[s + 1][t] = o1.ak1r * g1;
-        }
-    }
-    return acc;
-}
-
-template <bool MASK>
-__device__ __forceinline__ double sym_columns_pc(int pc, const FarArgs &A, const FarConst &fc, int ncol, int64_t i,
-                                                 int64_t j0, bool valid, bool diag, double x, double y, double dix,
-                                                 double diy, uint32_t rnear, int kp, const double *cx,
-                                                 const double *cy, const double *cdx, const double *cdy,
-                                                 const uint32_t *cmask, double (*colv)[SYM_R])
-{
-    switch (pc) {
-#define MHLP_SYM_PC(PCV)                                                                                   \
-    case PCV:                                                                                              \
-        return sym_columns<PCV, MASK>(A, fc, ncol, i, j0, valid, diag, x, y, dix, diy, rnear, kp, cx, cy, cdx, \
-                                      cdy, cmask, colv);
-        MHLP_SYM_PC(-1)
-        MHLP_SYM_PC(0)
-        MHLP_SYM_PC(1)
-        MHLP_SYM_PC(2)
-        MHLP_SYM_PC(3)
-        MHLP_SYM_PC(4)
-        MHLP_SYM_PC(5)
-        MHLP_SYM_PC(6)
-        MHLP_SYM_PC(7)
-        MHLP_SYM_PC(8)
-        MHLP_SYM_PC(9)
-        MHLP_SYM_PC(10)
-        MHLP_SYM_PC(11)
-        MHLP_SYM_PC(12)
-        MHLP_SYM_PC(13)
-        MHLP_SYM_PC(14)
-#undef MHLP_SYM_PC
-    default:
-        return sym_columns<KQ_NP, MASK>(A, fc, ncol, i, j0, valid, diag, x, y, dix, diy, rnear, kp, cx, cy, cdx,
-                                        cdy, cmask, colv);
-    }
-}
-
-/* One tile: 256 row nodes (block I) against the 16 nodes of column panel J.
-   The row sums go to p1[J][i]; the column terms of the tile's 256 rows are
-   reduced through LDS (each thread adds 16 rows of one column, 16 lanes then
-   combine by a fixed butterfly) into p2[I][j].  Each wave takes the fine piece
-   of its (row wave, column panel) from the plan's class table and checks near
-   masks only when that pair of wave and panel has near pairs on either side or
-   lies on the diagonal block. */
-__global__ __launch_bounds__(SYM_R) void sym_far_kernel(SymArgs S)
-{
-    const FarArgs &A = S.A;
-    __shared__ double cx[SYM_C], cy[SYM_C], cdx[SYM_C], cdy[SYM_C];
-    __shared__ uint32_t cmask[SYM_C];
-    __shared__ double colv[SYM_C][SYM_R];
-    const double *mu;
-    if (!far_density(A, mu)) return; /* the same for the whole launch */
-    const int2 tl = S.tiles[blockIdx.x];
-    const int I = tl.x, J = tl.y, t = threadIdx.x;
-    const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int64_t N = A.N, i = (int64_t)I * SYM_R + t, j0 = (int64_t)J * SYM_C;
-    const int pb = SYM_RP * I; /* first panel of the row block */
-    if (t < SYM_C) {
-        const int64_t j = j0 + t;
-        double xj = 0.0, yj = 0.0, dx = 0.0, dy = 0.0;
-        uint32_t msk = 0;
-        if (j < N) {
-            xj = A.sx[j];
-            yj = A.sy[j];
-            const double m = (A.alpha * A.sw[j]) * mu[j];
-            dx = m * A.snx[j];
-            dy = m * A.sny[j];
-            msk = (S.bits[j * S.nw + (pb >> 5)] >> (pb & 31)) & 0xFFFFu; /* the block's 16 panels */
-        }
-        cx[t] = xj;
-        cy[t] = yj;
-        cdx[t] = dx;
-        cdy[t] = dy;
-        cmask[t] = msk;
-    }
-    const bool valid = i < N;
-    double x = 0.0, y = 0.0, dix = 0.0, diy = 0.0;
-    uint32_t rnear = 0; /* bit 0: column panel J listed near row i */
-    int kp = 0;         /* row panel within the block */
-    if (valid) {
-        x = A.sx[i];
-        y = A.sy[i];
-        const double m = (A.alpha * A.sw[i]) * mu[i];
-        dix = m * A.snx[i];
-        diy = m * A.sny[i];
-        kp = (int)(i / 16) - pb;
-        rnear = (S.bits[i * S.nw + (J >> 5)] >> (J & 31)) & 1u;
-    }
-    const bool diag = SYM_CP * J < pb + SYM_RP; /* the chunk lies in the row block */
-    __syncthreads();
-    const FarConst fc = far_const(A.alpha);
-    const int ncol = (int)min((int64_t)SYM_C, N - j0);
-    const int cw = S.cls[((int64_t)I * (SYM_R / 64) + wv) * A.Np + J];
-    const int pc = (cw & 0x7f) - 1;
-    const double acc = (diag || (cw & 0x80))
-                           ? sym_columns_pc<true>(pc, A, fc, ncol, i, j0, valid, diag, x, y, dix, diy, rnear, kp,
-                                                  cx, cy, cdx, cdy, cmask, colv)
-                           : sym_columns_pc<false>(pc, A, fc, ncol, i, j0, valid, diag, x, y, dix, diy, rnear, kp,
-                                                   cx, cy, cdx, cdy, cmask, colv);
-    __syncthreads();
-    /* column c = t / 16: thread (c, g) adds rows g, g + 16, ..., g + 240, then the
-       16 lanes of the column combine */
-    {
-        const int c = t >> 4, g = t & 15;
-        double sc = 0.0;
-        if (c < ncol)
-            for (int r = g; r < SYM_R; r += 16) sc += colv[c][r];
-        for (int off = 8; off > 0; off >>= 1) sc += __shfl_xor(sc, off);
-        if (g == 0 && c < ncol) S.p2[(int64_t)I * N + j0 + c] = sc;
-    }
-    if (valid) S.p1[(int64_t)J * N + i] = acc;
-}
-
-/* Plan time, symmetric on-surface plans: for every (wave of 64 row nodes,
-   column panel) the fine piece that holds z for every pair the tile evaluates
-   (row i < column j, and not near on both sides; exact extreme distances; a
-   two-neighbour piece when they straddle one boundary, KQ_NP + 1 otherwise),
-   plus bit 7 when some such pair is near on either side (the row node lists
-   the column panel, or the column node lists the row node's panel).  Pairs
-   with j <= i are never evaluated by tile (row block of i, column panel of j),
-   which exists only for column panels from 16 x the row block on. */
-__global__ __launch_bounds__(256) void sym_class_kernel(const double *__restrict__ x, const double *__restrict__ y,
-                                                        int64_t N, int64_t Np, double alpha,
-                                                        const uint32_t *__restrict__ bits, int nw,
-                                                        uint8_t *__restrict__ cls)
-{
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    const bool valid = i < N;
-    const int64_t iv = valid ? i : N - 1;
-    const int64_t w = i >> 6, pi = iv / 16;
-    const double xi = x[iv], yi = y[iv];
-    for (int64_t p = 0; p < Np; ++p) {
-        double r2lo = 1e300, r2hi = -1.0;
-        const bool rn = ((bits[iv * nw + (p >> 5)] >> (p & 31)) & 1u) != 0;
-        bool near = false;
-        for (int jj = 0; jj < 16; ++jj) {
-            const int64_t j = 16 * p + jj;
-            if (!valid || j <= i) continue;
-            const bool cn = ((bits[j * nw + (pi >> 5)] >> (pi & 31)) & 1u) != 0;
-            near = near || rn || cn;
-            if (rn && cn) continue; /* neither term is taken */
-            const double ex = xi - x[j], ey = yi - y[j];
-            const double r2 = fma(ex, ex, ey * ey);
-            r2lo = fmin(r2lo, r2);
-            r2hi = fmax(r2hi, r2);
-        }
-        int lo = KQ_NB + 1, hi = -1; /* lanes without pairs do not vote */
-        if (r2hi >= 0.0) {
-            const double zlo = alpha * sqrt(r2lo), zhi = alpha * sqrt(r2hi);
-            lo = 0;
-            hi = 0;
-            for (int b = 0; b < KQ_NB; ++b) {
-                lo += zlo > KQ_B[b] ? 1 : 0;
-                hi += zhi > KQ_B[b] ? 1 : 0;
-            }
-        }
-        for (int off = 32; off > 0; off >>= 1) {
-            lo = min(lo, __shfl_xor(lo, off));
-            hi = max(hi, __shfl_xor(hi, off));
-        }
-        int c = KQ_NP + 1;
-        if (hi < 0)
-            c = KQ_NP + 1;
-        else if (lo == hi)
-            c = lo; /* piece lo - 1 (0: z <= 2) */
-        else if (lo >= 1 && hi == lo + 1 && lo <= KQ_NB - 1)
-            c = KQ_NB + lo; /* pieces lo - 1 and lo */
-        if (__ballot(near) != 0) c |= 0x80;
-        if ((threadIdx.x & 63) == 0) cls[w * Np + p] = (uint8_t)c;
-    }
-}
-
-/* node n: row sums of the chunks from its block on, column sums of the blocks
-   up to its own, then the near corrections, 1/(2 pi) and the identity term;
-   FZ_L lanes per node and FZ_TG nodes per block as in far_finalize.  Every
-   thread of the block returns. */
-__device__ __forceinline__ void sym_finalize_body(const SymArgs &S, const double *mu, int nchunk,
-                                                  double (&red)[2][FZ_L][FZ_TG])
-{
-    const FarArgs &A = S.A;
-    const int g = threadIdx.x % FZ_TG, l = threadIdx.x / FZ_TG;
-    const int64_t n = blockIdx.x * (int64_t)FZ_TG + g;
-    double fd = 0.0, nd = 0.0;
-    if (n < A.N) {
-        const int B = (int)(n / SYM_R);
-#pragma unroll 4
-        for (int c = SYM_RP * B / SYM_CP + l; c < nchunk; c += FZ_L) fd += S.p1[(int64_t)c * A.N + n];
-        for (int b = l; b <= B; b += FZ_L) fd += S.p2[(int64_t)b * A.N + n];
-        for (int32_t q = A.nptr[n]; q < A.nptr[n + 1]; ++q) {
-            const int64_t p = A.npan[q];
-            if (p < 0) continue;
-            nd = fma(A.wdl[16 * (int64_t)q + l], mu[16 * p + l], nd);
-        }
-    }
-    red[0][l][g] = fd;
-    red[1][l][g] = nd;
-    __syncthreads();
-    if (l == 0 && n < A.N) {
-        for (int q = 1; q < FZ_L; ++q) {
-            fd += red[0][q][g];
-            nd += red[1][q][g];
-        }
-        double v = fma(INV_2PI, fd, nd);
-        if (A.half_term != 0.0) v = fma(A.half_term, mu[n], v);
-        A.ud[n] = v;
-    }
-}
-
-__global__ __launch_bounds__(FZ_TG *FZ_L) void sym_finalize(SymArgs S, int nchunk)
-{
-    __shared__ double red[2][FZ_L][FZ_TG];
-    const double *mu;
-    if (!far_density(S.A, mu)) return;
-    sym_finalize_body(S, mu, nchunk, red);
-}
-
-/* the 16 sources of one LDS panel (offset l0) against the lane's target: PC the
-   fine piece (-1: z <= 2; KQ_NP: per-pair selection over the three-piece fits) */
-template <bool SLP, bool DLP, int PC>
-__device__ __forceinline__ void far_panel_fp64(const FarArgs &A, const FarConst &fc, double x, double y,
-                                               const double *lx, const double *ly, const double *lq,
-                                               const double *ldx, const double *ldy, int l0, double &accs,
-                                               double &accd)
-{
-    constexpr int K = PC < 0 || PC >= KQ_NP ? 0 : PC;
-    /* the table pointer once per panel: the piece's coefficients stay in
-       scalar registers for its 8 loop trips */
-    const FarTab T = far_table();
-    double qa, qk;
-    fine_q<K>(A.fq, qa, qk);
-#pragma unroll 1
-    for (int s = 0; s < 16; s += 2) {
-        const int a0 = l0 + s, a1 = a0 + 1;
-        const double ex0 = x - lx[a0], ey0 = y - ly[a0];
-        const double ex1 = x - lx[a1], ey1 = y - ly[a1];
-        const double r20 = fma(ex0, ex0, ey0 * ey0), r21 = fma(ex1, ex1, ey1 * ey1);
-        K01 o0, o1;
-        if constexpr (PC >= KQ_NP)
-            k01_far2<SLP, DLP, true, true>(T, fc, r20, r21, o0, o1);
-        else
-            k01_far2_fixed<SLP, DLP, PC>(T, fc, qa, qk, r20, r21, o0, o1);
-        if (SLP) accs = fma(o1.k0, lq[a1], fma(o0.k0, lq[a0], accs));
-        if (DLP)
-            accd = fma(o1.ak1r, fma(ex1, ldx[a1], ey1 * ldy[a1]), fma(o0.ak1r, fma(ex0, ldx[a0], ey0 * ldy[a0]), accd));
-    }
-}
-
-/* waves per SIMD the FP64 far kernel is compiled for (96 registers per lane) */
-constexpr int SK_WAVES = 4;
-
-/* The stream position of hardware block b of a P-block launch.  The chip's
-   dispatcher deals blocks to its 8 XCDs (each with its own L2) in turn, block b
-   to XCD b mod 8; numbering the stream XCD by XCD gives each XCD one
-   contiguous stretch of it, so the blocks that share a target block share an
-   L2 and read its targets and class rows from there.  A bijection of
-   [0, P) for every P. */
-__device__ __forceinline__ int64_t xcd_major(int64_t b, int64_t P)
-{
-    const int64_t q = P >> 3, r = P & 7, x = b & 7, k = b >> 3;
-    return x * q + (x < r ? x : r) + k;
-}
-
-/* first unit of block b of the stream decomposition, and the block that holds unit u */
-__host__ __device__ inline int64_t sk_start(int64_t U, int P, int64_t b) { return (U * b) / P; }
-__host__ __device__ inline int64_t sk_block_of(int64_t U, int P, int64_t u)
-{
-    int64_t b = (u * P) / U;
-    while (b > 0 && sk_start(U, P, b) > u) --b;
-    while (b + 1 < P && sk_start(U, P, b + 1) <= u) ++b;
-    return b;
-}
-
-/* The FP64 far field as a stream of units (target block of FT_THREADS targets,
-   one panel): block b takes units sk_start(b) .. sk_start(b+1) - 1 in order,
-   i.e. a run of units of one target block, then possibly the start of the
-   next, and so on; every block has the same number of units.  Unit j of a
-   target block is panel (j skStride) mod Np, a stride near 0.618 Np coprime to
-   Np, so that each block's run mixes panels near and far from its targets and
-   the blocks cost about the same.  For each target block it touches, the block
-   sums its panels (a target skips the panels it lists as near) and writes the
-   partial sums of its targets into slot (b - first block of the target block);
-   far_sk_finalize adds the slots in order with the near corrections.  Sources
-   are staged in LDS 16 panels at a time; each panel is evaluated with the fine
-   piece the plan-time class table gives for (wave, panel) (low 7 bits: piece
-   + 1, KQ_NP + 1 for the per-pair selection; bit 7: some target of the wave
-   lists the panel, only then do the lanes look it up in their lists). */
-template <bool SLP, bool DLP>
-__global__ __launch_bounds__(FT_THREADS, SK_WAVES) void far_eval_fp64(FarArgs A)
-{
-    __shared__ double lx[FT_SRC], ly[FT_SRC], lq[FT_SRC], ldx[FT_SRC], ldy[FT_SRC];
-    __shared__ int32_t lp[16];
-    const double *mu;
-    if (!far_density(A, mu)) return;
-    const int64_t Np = A.Np;
-    const int64_t blk = xcd_major(blockIdx.x, A.skP);
-    int64_t u = sk_start(A.skU, A.skP, blk);
-    const int64_t uend = sk_start(A.skU, A.skP, blk + 1);
-    const FarConst fc = far_const(A.alpha);
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    while (u < uend) {
-        const int64_t tb = u / Np;
-        const int64_t jb = u - tb * Np;
-        const int64_t je = min(Np, uend - tb * Np);
-        const int64_t i = tb * FT_THREADS + threadIdx.x;
-        const bool valid = i < A.M;
-        /* lanes past the last target repeat its position (results discarded) */
-        const int64_t iv = valid ? i : A.M - 1;
-        const double x = A.tx[iv], y = A.ty[iv];
-        const int32_t k0 = A.nptr[iv], k1 = A.nptr[iv + 1];
-        const uint8_t *cls = A.wcls + (tb * (FT_THREADS / 64) + wv) * Np;
-        double accs = 0.0, accd = 0.0;
-        for (int64_t jt = jb; jt < je; jt += 16) {
-            const int npl = (je - jt) < 16 ? (int)(je - jt) : 16;
-            __syncthreads();
-            if (threadIdx.x < 16 * npl) {
-                const int64_t p = ((jt + (threadIdx.x >> 4)) * A.skStride) % Np;
-                const int64_t jn = 16 * p + (threadIdx.x & 15);
-                const double wj = A.sw[jn];
-                lx[threadIdx.x] = A.sx[jn];
-                ly[threadIdx.x] = A.sy[jn];
-                if (SLP) lq[threadIdx.x] = wj * A.sigma[jn];
-                if (DLP) {
-                    /* alpha goes with the dipole: the pair evaluates K1(z)/r */
-                    const double m = (A.alpha * wj) * mu[jn];
-                    ldx[threadIdx.x] = m * A.snx[jn];
-                    ldy[threadIdx.x] = m * A.sny[jn];
-                }
-                if ((threadIdx.x & 15) == 0) lp[threadIdx.x >> 4] = (int32_t)p;
-            }
-            __syncthreads();
-            for (int pl = 0; pl < npl; ++pl) {
-                const int32_t p = lp[pl];
-                const int cw = cls[p];
-                if (cw & 0x80) { /* some target of the wave lists the panel */
-                    bool listed = false;
-                    for (int32_t q = k0; q < k1; ++q) listed = listed || A.npan[q] == p;
-                    if (listed) continue;
-                }
-                const int pc = (cw & 0x7f) - 1;
-                const int l0 = pl * 16;
-                switch (pc) {
-#define MHLP_FAR_PANEL(PCV)                                                                               \
-    case PCV:                                                                                              \
-        far_panel_fp64<SLP, DLP, PCV>(A, fc, x, y, lx, ly, lq, ldx, ldy, l0, accs, accd);                  \
-        break;
-                    MHLP_FAR_PANEL(-1)
-                    MHLP_FAR_PANEL(0)
-                    MHLP_FAR_PANEL(1)
-                    MHLP_FAR_PANEL(2)
-                    MHLP_FAR_PANEL(3)
-                    MHLP_FAR_PANEL(4)
-                    MHLP_FAR_PANEL(5)
-                    MHLP_FAR_PANEL(6)
-                    MHLP_FAR_PANEL(7)
-                    MHLP_FAR_PANEL(8)
-                    MHLP_FAR_PANEL(9)
-                    MHLP_FAR_PANEL(10)
-                    MHLP_FAR_PANEL(11)
-                    MHLP_FAR_PANEL(12)
-                    MHLP_FAR_PANEL(13)
-                    MHLP_FAR_PANEL(14)
-#undef MHLP_FAR_PANEL
-                default:
-                    far_panel_fp64<SLP, DLP, KQ_NP>(A, fc, x, y, lx, ly, lq, ldx, ldy, l0, accs, accd);
-                }
-            }
-        }
-        const int64_t slot = blk - sk_block_of(A.skU, A.skP, tb * Np);
-        if (valid) {
-            if (SLP) A.skps[slot * A.M + i] = accs;
-            if (DLP) A.skpd[slot * A.M + i] = accd;
-        }
-        u = (tb + 1) * Np;
-    }
-}
-
-/* Sum of the stream partials of each target (slots of its target block in
-   order), near corrections, 1/(2 pi) and the identity term; lanes as in
-   far_finalize (L per target). */
-template <bool SLP, bool DLP, int L>
-__global__ __launch_bounds__(L == 1 ? 256 : FZ_TG * L) void far_sk_finalize(FarArgs A)
-{
-    constexpr int TG = L == 1 ? 256 : FZ_TG;
-    __shared__ double red[4][L == 1 ? 1 : L][L == 1 ? 1 : TG]; /* far S, near S, far D, near D */
-    const double *mu;
-    if (!far_density(A, mu)) return;
-    const int g = threadIdx.x % TG, l = L == 1 ? 0 : threadIdx.x / TG;
-    const int64_t i = blockIdx.x * (int64_t)TG + g;
-    double fs = 0.0, ns = 0.0, fd = 0.0, nd = 0.0;
-    if (i < A.M) {
-        const int64_t tb = i / FT_THREADS;
-        const int64_t b0 = sk_block_of(A.skU, A.skP, tb * A.Np);
-        const int64_t nseg = sk_block_of(A.skU, A.skP, tb * A.Np + A.Np - 1) - b0 + 1;
-        for (int64_t q = l; q < nseg; q += L) {
-            if (SLP) fs += A.skps[q * A.M + i];
-            if (DLP) fd += A.skpd[q * A.M + i];
-        }
-        for (int32_t q = A.nptr[i]; q < A.nptr[i + 1]; ++q) {
-            const int64_t p = A.npan[q];
-            if (p < 0) continue;
-            for (int jj = l; jj < 16; jj += L) {
-                if (SLP) ns = fma(A.wsl[16 * (int64_t)q + jj], A.sigma[16 * p + jj], ns);
-                if (DLP) nd = fma(A.wdl[16 * (int64_t)q + jj], mu[16 * p + jj], nd);
-            }
-        }
-    }
-    if (L > 1) {
-        red[0][l][g] = fs;
-        red[1][l][g] = ns;
-        red[2][l][g] = fd;
-        red[3][l][g] = nd;
-        __syncthreads();
-        if (l != 0) return;
-        for (int q = 1; q < L; ++q) {
-            fs += red[0][q][g];
-            ns += red[1][q][g];
-            fd += red[2][q][g];
-            nd += red[3][q][g];
-        }
-    }
-    if (i >= A.M) return;
-    const int64_t o = A.perm ? (int64_t)A.perm[i] : i;
-    if (SLP) A.us[o] = fma(INV_2PI, fs, ns);
-    if (DLP) {
-        double v = fma(INV_2PI, fd, nd);
-        if (A.half_term != 0.0) v = fma(A.half_term, mu[i], v);
-        A.ud[o] = v;
     }
 }
 
@@ -1339,6 +840,8 @@ __global__ __launch_bounds__(FT_THREADS) void far_eval_mixed(FarArgs A)
         far_epilogue<SLP, DLP>(A, mu, i, accs, accd);
     }
 }
+
+#include "tree.h"
 
 /* ------------------------------------------------------------------------ */
 /* volume sum over a tensor grid (all pairs) with the self-cell correction   */
@@ -1842,7 +1345,7 @@ __global__ void stkg_finalize(StkGArgs A, int nsplit)
    with A1, A2, A3 = alpha^2 T1, alpha^4 T2, alpha^2 T3 of |e| (App. B), the
    contraction of far_stokes_fp64.  F is odd in e, so one evaluation of the A_k
    serves both terms of the pair: source j at node i and +F(e; n_i, m_i) for
-   source i at node j.  Tiles, near bit set and order rules as sym_far_kernel;
+   source i at node j.  Tiles, near bit set and order rules as above;
    the column terms of a tile are summed over each row of 16 lanes by DPP
    moves, then the 16 row sums of a column in order through LDS. */
 struct StkSymArgs {
@@ -3276,42 +2779,41 @@ extern "C" mhlp_status mhlp_plan_destroy(mhlp_plan *P)
     if (P->cap_stream) (void)hipStreamDestroy(P->cap_stream);
     void *ptrs[] = {P->near_ptr, P->near_panel, P->near_tgt, P->near_ts, P->wslp,  P->wdlp,    P->ws,
                     P->hdev,     P->part,       P->gdev,     P->perm,    P->wgrad, P->wstk,    P->stk_flux,
-                    P->wstkg,    P->sym_tiles,  P->sym_p1,   P->sym_p2,  P->sym_bits, P->wcls, P->skpart,
-                    P->sym_cls,  P->fqd};
+                    P->wstkg,    P->sym_tiles,  P->sym_p1,   P->sym_p2,  P->sym_bits, P->wcls, P->trpart,
+                    P->fqd};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     delete P->fmm;
+    if (P->tree) {
+        void *tp[] = {P->tree->cc, P->tree->rmin, P->tree->mom, P->tree->st, P->tree->items, P->tree->cnt, P->tree->order};
+        for (void *p : tp)
+            if (p) (void)hipFree(p);
+        delete P->tree;
+    }
     if (P->hhost) (void)hipHostFree(P->hhost);
     if (P->gstate_host) (void)hipHostFree(P->gstate_host);
     delete P;
     return MHLP_OK;
 }
 
-/* Blocks of far_eval_fp64<SLP, DLP> the chip holds at once (per CU times CUs). */
-template <bool SLP, bool DLP>
-static mhlp_status far_resident_blocks(int *out)
+/* The fine pieces' scales at the plan's alpha (read by every far kernel). */
+static mhlp_status far_scales_setup(mhlp_plan *P, hipStream_t st)
 {
-    int dev = 0, cus = 0, nb = 0;
-    HIPCHECK(hipGetDevice(&dev));
-    HIPCHECK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    HIPCHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, far_eval_fp64<SLP, DLP>, FT_THREADS, 0));
-    *out = (nb > 0 ? nb : 1) * (cus > 0 ? cus : 1);
+    double fq[2 * KQ_NP];
+    fine_scales(P->alpha, fq);
+    TRY(dalloc(&P->fqd, 2 * KQ_NP));
+    HIPCHECK(hipMemcpyAsync(P->fqd, fq, sizeof(fq), hipMemcpyHostToDevice, st));
+    HIPCHECK(hipStreamSynchronize(st)); /* fq ends here */
     return MHLP_OK;
 }
 
-/* The (wave of 64 targets, panel) class table of the far-field tiles and the
-   fine pieces' scales at the plan's alpha (built on the stream after the near
-   lists, which it reads); the fused evaluation, the gradients and the
-   stresslet kernels read it. */
+/* The (wave of 64 targets, panel) class table of the mixed-precision, gradient
+   and stresslet tiles (built on the stream after the near lists, which it reads). */
 static mhlp_status far_class_setup(mhlp_plan *P, hipStream_t st)
 {
     const int64_t M = P->M, Np = P->g->Np;
     const int64_t TB = (M + FT_THREADS - 1) / FT_THREADS;
     TRY(dalloc(&P->wcls, TB * (FT_THREADS / 64) * Np));
-    double fq[2 * KQ_NP];
-    fine_scales(P->alpha, fq);
-    TRY(dalloc(&P->fqd, 2 * KQ_NP));
-    HIPCHECK(hipMemcpyAsync(P->fqd, fq, sizeof(fq), hipMemcpyHostToDevice, st)); /* fq lives until the sync below */
     far_class_kernel<<<(unsigned)TB, FT_THREADS, 0, st>>>(P->tx, P->ty, M, P->g->soa, P->g->soa + P->g->N, Np,
                                                           P->alpha, P->near_ptr, P->near_panel, P->wcls);
     HIPCHECK(hipGetLastError());
@@ -3319,41 +2821,54 @@ static mhlp_status far_class_setup(mhlp_plan *P, hipStream_t st)
     return MHLP_OK;
 }
 
-/* The FP64 far field's launch shape: one block per resident slot of the chip
-   for each layer variant (at most one per unit), the partial slots a target
-   block can need, their buffer, and the (wave, panel) class table (built on the
-   stream after the near lists, which it reads). */
-/* blocks of the stream launch per block the chip holds at once: later waves
-   of blocks let the hardware dispatcher even out what the equal unit counts
-   leave uneven (measured on config 2 at alpha = 5: 1.49 / 1.39 / 1.35 / 1.36 ms
-   for 1, 2, 4, 8) */
-constexpr int SK_OVERSUB = 4;
-static mhlp_status far_stream_setup(mhlp_plan *P, hipStream_t st)
+/* Clusters, item lists and buffers of a scalar plan's far field (tree.h), on
+   the stream after the near lists, which the item lists read. */
+static mhlp_status tree_setup(mhlp_plan *P, hipStream_t st)
 {
-    const int64_t M = P->M, Np = P->g->Np;
-    const int64_t TB = (M + FT_THREADS - 1) / FT_THREADS, U = TB * Np;
-    int res[3] = {0, 0, 0};
-    TRY((far_resident_blocks<true, true>(&res[0])));
-    TRY((far_resident_blocks<true, false>(&res[1])));
-    TRY((far_resident_blocks<false, true>(&res[2])));
-    int32_t smax = 1;
-    for (int v = 0; v < 3; ++v) {
-        const int Pv = (int)std::min<int64_t>((int64_t)SK_OVERSUB * res[v], U);
-        P->sk_P[v] = Pv;
-        for (int64_t tb = 0; tb < TB; ++tb) {
-            const int64_t n = sk_block_of(U, Pv, tb * Np + Np - 1) - sk_block_of(U, Pv, tb * Np) + 1;
-            smax = (int32_t)std::max<int64_t>(smax, n);
-        }
+    const mhlp_geometry *g = P->g;
+    const int64_t M = P->M, Np = g->Np, G = (M + 63) / 64;
+    P->tree = new mhlp::TreeDev();
+    mhlp::TreeDev &T = *P->tree;
+    T.Np = Np;
+    while (T.nlev < mhlp::TR_LEV && ((int64_t)1 << T.nlev) <= Np) {
+        T.off[T.nlev] = T.ncl;
+        T.ncl += (Np + ((int64_t)1 << T.nlev) - 1) >> T.nlev;
+        ++T.nlev;
     }
-    P->sk_S = smax;
-    {
-        int64_t st_ = std::llround(0.6180339887498949 * (double)Np);
-        if (st_ < 1) st_ = 1;
-        while (std::gcd(st_, Np) != 1) ++st_;
-        P->sk_stride = (int32_t)(st_ % Np == 0 ? 1 : st_ % Np);
-    }
-    TRY(dalloc(&P->skpart, 2 * (int64_t)smax * M));
-    return far_class_setup(P, st);
+    TRY(dalloc(&T.cc, 2 * T.ncl));
+    TRY(dalloc(&T.rmin, mhlp::TR_RM * T.ncl));
+    TRY(dalloc(&T.mom, T.ncl * mhlp::tr_stride(2)));
+    TRY(dalloc(&T.st, 48 * Np));
+    TRY(dalloc(&T.items, G * Np));
+    TRY(dalloc(&T.cnt, G));
+    TRY(dalloc(&T.order, G));
+    /* waves per group of 64 targets (blocks of 8, 16 or 4 waves; direct items
+       cut into 2^cut units), by the number of groups: enough waves to fill the
+       chip.  Measured us per evaluation (starfish, 4096 sources, alpha = 5) with
+       4 / 16 / 32 / 64 / 128 waves: 52 groups 114/72/35/31/28, 106 groups
+       98/64/35/31/34, 425 groups 94/63/46/52/71, 853 groups 79/54/58/78/117,
+       1709 groups 69/85/-/-/161; the on-surface operator (targets in panel order,
+       eight direct panels a group) with 16 / 32 / 64: 64 groups 21.5/18.1/18.4
+       (alpha = 50: 39/24/22). */
+    if (G >= 1200)
+        P->tr_waves = 4, T.cut = 0;
+    else if (G >= 640)
+        P->tr_waves = 16, T.cut = 2;
+    else if (G >= 170)
+        P->tr_waves = 8, P->tr_split = 4, T.cut = 2;
+    else if (G >= 85 || P->onsurf)
+        P->tr_waves = 8, P->tr_split = 8, T.cut = 2;
+    else
+        P->tr_waves = 8, P->tr_split = 16, T.cut = 3;
+    if (P->tr_split > 1) TRY(dalloc(&P->trpart, 2 * (int64_t)P->tr_split * M));
+    mhlp::tree_clusters_kernel<<<nblocks(T.ncl, 4), 256, 0, st>>>(T, g->soa, g->soa + g->N, g->ph, P->alpha,
+                                                                  P->near_factor);
+    mhlp::tree_lists_kernel<<<nblocks(G, 4), 256, 0, st>>>(T, P->tx, P->ty, M, g->soa, g->soa + g->N, g->ph,
+                                                           P->near_factor, P->alpha, P->near_ptr, P->near_panel);
+    mhlp::tree_order_kernel<<<1, 1024, 0, st>>>(T, G);
+    HIPCHECK(hipGetLastError());
+    HIPCHECK(hipStreamSynchronize(st)); /* later calls may come on other streams */
+    return MHLP_OK;
 }
 
 static mhlp_status plan_create_impl(const mhlp_geometry *g, double alpha, const double *tx, const double *ty,
@@ -3463,11 +2978,10 @@ static mhlp_status plan_create_impl(const mhlp_geometry *g, double alpha, const 
             return s;
         }
     }
-    if (P->onsurf && g->N <= SYM_NMAX && g->N % 16 == 0) {
-        /* tiles of the symmetric on-surface double layer, scalar or stresslet
-           (row block I, column chunk J from the block's first panel on); the
-           stresslet keeps two components per partial sum and no piece table */
-        const int64_t ncomp = P->stokes ? 2 : 1;
+    if (P->onsurf && P->stokes && g->N <= SYM_NMAX) {
+        /* tiles of the symmetric on-surface stresslet operator (row block I,
+           column chunk J from the block's first panel on), two components */
+        const int64_t ncomp = 2;
         const int64_t nrb = (g->N + SYM_R - 1) / SYM_R, ncc = (g->N + SYM_C - 1) / SYM_C;
         std::vector<int2> tiles;
         for (int64_t I = 0; I < nrb; ++I)
@@ -3476,8 +2990,7 @@ static mhlp_status plan_create_impl(const mhlp_geometry *g, double alpha, const 
         P->sym_nw = (int32_t)((g->Np + 31) / 32);
         if ((s = dalloc(&P->sym_tiles, (int64_t)tiles.size())) || (s = dalloc(&P->sym_p1, ncomp * ncc * g->N)) ||
             (s = dalloc(&P->sym_p2, ncomp * nrb * g->N)) ||
-            (s = dalloc(&P->sym_bits, (int64_t)P->sym_nw * g->N)) ||
-            (!P->stokes && (s = dalloc(&P->sym_cls, nrb * (SYM_R / 64) * g->Np)))) {
+            (s = dalloc(&P->sym_bits, (int64_t)P->sym_nw * g->N))) {
             mhlp_plan_destroy(P);
             return s;
         }
@@ -3561,15 +3074,13 @@ static mhlp_status plan_create_impl(const mhlp_geometry *g, double alpha, const 
         P->fill_mismatch = mism;
     }
     (void)hipFree(cnt);
-    if ((s = stokes ? far_class_setup(P, st) : far_stream_setup(P, st))) {
+    if ((s = far_scales_setup(P, st)) || (!stokes && (s = tree_setup(P, st))) ||
+        (s = far_class_setup(P, st))) {
         mhlp_plan_destroy(P);
         return s;
     }
     if (P->sym_bits) {
         near_bits_kernel<<<nblocks(M, 256), 256, 0, st>>>(P->near_ptr, P->near_panel, M, P->sym_nw, P->sym_bits);
-        if (P->sym_cls)
-            sym_class_kernel<<<nblocks(M, SYM_R), SYM_R, 0, st>>>(P->g->soa, P->g->soa + P->g->N, M, P->g->Np,
-                                                                   P->alpha, P->sym_bits, P->sym_nw, P->sym_cls);
         hipError_t eb = hipGetLastError();
         if (eb == hipSuccess) eb = hipStreamSynchronize(st); /* later calls may come on other streams */
         if (eb != hipSuccess) {
@@ -3626,24 +3137,27 @@ extern "C" mhlp_status mhlp_plan_info(const mhlp_plan *P, int64_t *n_targets, in
 /* evaluation                                                                */
 /* ------------------------------------------------------------------------ */
 template <bool SLP, bool DLP>
-static void launch_far_t(FarArgs A, const mhlp_plan *P, int nsplit, int32_t precision, hipStream_t st)
+static void launch_far_t(FarArgs A, const mhlp_plan *P, int32_t precision, hipStream_t st)
 {
-    const unsigned nb = nblocks(A.M, FT_THREADS);
+    int nsplit;
     if (precision == MHLP_FP64) {
-        A.skP = P->sk_P[SLP && DLP ? 0 : SLP ? 1 : 2];
-        far_eval_fp64<SLP, DLP><<<(unsigned)A.skP, FT_THREADS, 0, st>>>(A);
-        if (A.M <= FZ_SHORT)
-            far_sk_finalize<SLP, DLP, FZ_L><<<nblocks(A.M, FZ_TG), FZ_TG * FZ_L, 0, st>>>(A);
+        const mhlp::TreeDev &T = *P->tree;
+        nsplit = P->tr_split;
+        A.part_s = P->trpart;
+        mhlp::tree_moments_kernel<SLP, DLP>
+            <<<dim3(nblocks(A.Np, 16), (unsigned)T.nlev, mhlp::TR_GROUPS), 256, 0, st>>>(A, T);
+        A.part_d = P->trpart + (int64_t)nsplit * A.M;
+        mhlp::far_tree_kernel<SLP, DLP>
+            <<<dim3(nblocks(A.M, 64), (unsigned)nsplit), 64 * P->tr_waves, 0, st>>>(A, T);
+    } else {
+        nsplit = P->nsplit;
+        const dim3 grid(nblocks(A.M, FT_THREADS), (unsigned)nsplit);
+        if (nsplit <= 1)
+            far_eval_mixed<SLP, DLP, false><<<grid, FT_THREADS, 0, st>>>(A);
         else
-            far_sk_finalize<SLP, DLP, 1><<<nblocks(A.M, 256), 256, 0, st>>>(A);
-        return;
+            far_eval_mixed<SLP, DLP, true><<<grid, FT_THREADS, 0, st>>>(A);
     }
-    if (nsplit <= 1) {
-        far_eval_mixed<SLP, DLP, false><<<nb, FT_THREADS, 0, st>>>(A);
-        return;
-    }
-    dim3 grid(nb, nsplit);
-    far_eval_mixed<SLP, DLP, true><<<grid, FT_THREADS, 0, st>>>(A);
+    if (nsplit <= 1) return;
     if (A.M <= FZ_SHORT)
         far_finalize<SLP, DLP, FZ_L><<<nblocks(A.M, FZ_TG), FZ_TG * FZ_L, 0, st>>>(A, nsplit);
     else
@@ -3685,22 +3199,9 @@ static FarArgs far_args(const mhlp_plan *P, const double *sigma, const double *m
     A.pcx = g->pcx;
     A.pcy = g->pcy;
     A.prad = g->prad;
-    A.skU = (int64_t)((P->M + FT_THREADS - 1) / FT_THREADS) * g->Np;
-    A.skP = P->sk_P[0];
-    A.skS = P->sk_S;
-    A.skStride = P->sk_stride;
-    A.skps = P->skpart;
-    A.skpd = P->skpart + (int64_t)P->sk_S * P->M;
     A.wcls = P->wcls;
     A.fq = P->fqd;
     return A;
-}
-
-/* The symmetric on-surface operator's launches (FP64, scalar plan with
-   symmetric tiles) */
-static SymArgs sym_args(const mhlp_plan *P, const FarArgs &A)
-{
-    return SymArgs{A, P->sym_tiles, P->sym_p1, P->sym_p2, P->sym_bits, P->sym_nw, P->sym_cls};
 }
 
 static mhlp_status launch_far(const mhlp_plan *P, const double *sigma, const double *mu, double *us, double *ud,
@@ -3713,13 +3214,6 @@ static mhlp_status launch_far(const mhlp_plan *P, const double *sigma, const dou
     if (half_term != 0.0 && (!P->onsurf || P->M != g->N))
         return fail(MHLP_INVALID_ARG, "identity term needs an on-surface plan");
     const FarArgs A = far_args(P, sigma, mu, us, ud, half_term, gs, jstride);
-    if (P->sym_tiles && !sigma && mu && precision == MHLP_FP64) {
-        const SymArgs S = sym_args(P, A);
-        sym_far_kernel<<<(unsigned)P->sym_ntiles, SYM_R, 0, st>>>(S);
-        sym_finalize<<<nblocks(A.M, FZ_TG), FZ_TG * FZ_L, 0, st>>>(S, (int)((g->N + SYM_C - 1) / SYM_C));
-        HIPCHECK(hipGetLastError());
-        return MHLP_OK;
-    }
     if (P->fmm && precision == MHLP_FP64 && !gs) {
         if (sigma && mu)
             fmm_far_t<true, true>(P->fmm, A, st);
@@ -3731,11 +3225,11 @@ static mhlp_status launch_far(const mhlp_plan *P, const double *sigma, const dou
         return MHLP_OK;
     }
     if (sigma && mu)
-        launch_far_t<true, true>(A, P, P->nsplit, precision, st);
+        launch_far_t<true, true>(A, P, precision, st);
     else if (sigma)
-        launch_far_t<true, false>(A, P, P->nsplit, precision, st);
+        launch_far_t<true, false>(A, P, precision, st);
     else
-        launch_far_t<false, true>(A, P, P->nsplit, precision, st);
+        launch_far_t<false, true>(A, P, precision, st);
     HIPCHECK(hipGetLastError());
     return MHLP_OK;
 }
@@ -3788,12 +3282,10 @@ extern "C" mhlp_status mhlp_plan_autotune(mhlp_plan *P, int32_t layers, int32_t 
     if (cap < 0 || (cap > 0 && (!cand || !cand_ms))) return fail(MHLP_INVALID_ARG, "candidate arrays");
     hipStream_t st = (hipStream_t)stream;
     const int64_t N = P->g->N, M = P->M, Np = P->g->Np;
-    /* The FP64 single and double layers run as a stream of (target block, panel)
-       units and the FP64 operator of a symmetric on-surface plan on its own
-       tiles: neither uses the split.  For them the split serves the MIXED
-       launch of the same layers (potentials, and the inner operator of mixed
-       GMRES refinement), which is what gets timed. */
-    if (precision == MHLP_FP64 && (layers <= 3 || (layers == 4 && P->sym_tiles))) precision = MHLP_MIXED;
+    /* The FP64 single and double layers run by cluster expansions (tree.h) and
+       do not use the split.  For them the split serves the MIXED launch of the
+       same layers, which is what gets timed. */
+    if (precision == MHLP_FP64 && layers <= 4) precision = MHLP_MIXED;
     std::vector<int> cs;
     for (int64_t ns = 1; ns <= Np && ns <= 256; ns *= 2) cs.push_back((int)ns);
     if (std::find(cs.begin(), cs.end(), P->nsplit) == cs.end()) cs.push_back(P->nsplit);
@@ -4119,7 +3611,11 @@ static mhlp_status apply_op(mhlp_plan *P, const double *x, double *out, int32_t 
                             const GState *gs = nullptr, int64_t jstride = 0)
 {
     if (P->stokes) return launch_stokes(P, x, out, P->g->N, true, st, gs, jstride);
-    return launch_far(P, nullptr, x, nullptr, out, 0.5, prec, st, gs, jstride);
+    /* also the inner steps of a mixed-precision solve: the FP64 operator by
+       expansions takes a third of the FP32 tiles' time (N = 4096: 18 against
+       61 + 5 us) and is the more accurate */
+    (void)prec;
+    return launch_far(P, nullptr, x, nullptr, out, 0.5, MHLP_FP64, st, gs, jstride);
 }
 
 static mhlp_status ensure_ws(mhlp_plan *P, int64_t cols)
@@ -4533,8 +4029,7 @@ static mhlp_status gmres_solve_impl(const mhlp_plan *Pc, const double *g, double
     double rel = 1.0;
     /* the solve runs on its own copies of g and mu (xw, bw), which the captured
        graphs refer to; the start kernel of a device-normed solve makes them,
-       else they are copied here.  Mixed precision: Arnoldi steps on the FP32
-       far field, each cycle an inner solve to 1e-6 of the residual it started
+       else they are copied here.  Mixed precision: each cycle an inner solve to 1e-6 of the residual it started
        from, its end the FP64 true residual (iterative refinement). */
     if (!bnorm_dev) HIPCHECK(hipMemcpyAsync(bw, g, sizeof(double) * N, hipMemcpyDeviceToDevice, st));
     TRY(gmres_core(P, bw, bnorm, xw, opts->tol, opts->restart, opts->max_iter, mixed ? MHLP_MIXED : MHLP_FP64, st,

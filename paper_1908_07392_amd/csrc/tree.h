@@ -1,0 +1,712 @@
+/* Far field of the layer potentials by cluster expansions (FP64), for every
+   far sum over the panels of a plan.
+
+   Clusters are runs of 1, 2, 4, 8 or 16 consecutive panels (level 0..4, aligned
+   at their size).  The field of a cluster's charges q_j and dipoles d_j at y_j,
+       sum_j q_j K0(alpha |x - y_j|) + d_j . grad_y K0(alpha |x - y_j|),
+   is, by Graf's addition theorem about the cluster's centre c,
+       Re sum_{n=0..p} M_n K_n(alpha r) e^{i n theta},   x - c = r e^{i theta},
+       M_n = (2 - delta_n0) sum_j q_j B_n(y_j - c),  B_n(d) = I_n(alpha |d|) e^{-i n arg d},
+       dipoles: M_n = (2 - delta_n0)(alpha/2) sum_j [conj(d_j) B_{n-1} + d_j B_{n+1}]  (n >= 1),
+                M_0 = alpha sum_j Re(d_j B_1).
+   A wave of 64 targets takes each panel once: through the largest cluster whose
+   expansion of an order up to TR_PMAX reaches rounding at all its targets
+   (tree_order_ratio), else directly (the class-table tiles of the far
+   kernels).  The lists are built with the plan (tree_lists_kernel); the moments
+   of every evaluation come from tree_moments_kernel, which also stages the
+   charges and dipoles of the direct part.
+
+   Why this split: a pair costs 55-75 FP64 instructions directly, an order of a
+   cluster 10 for both layers and about 50 once per cluster, so a panel of 16
+   sources costs about 1100 directly and 130-370 through its own expansion, and
+   far clusters hold up to 16 panels.  alpha R <= TR_AMAX keeps the terms of the
+   expansion within e^{2 alpha R} of its value (wider clusters would lose digits
+   to cancellation, and need more orders than they have panels). */
+#pragma once
+
+namespace mhlp {
+
+constexpr int TR_LEV = 5;                    /* cluster levels: 1, 2, 4, 8, 16 panels */
+constexpr int TR_PMIN = 8, TR_PSTEP = 2, TR_NP = 13, TR_PMAX = TR_PMIN + TR_PSTEP * (TR_NP - 1);
+constexpr int TR_ROWS = TR_PMAX + 1;         /* orders 0..TR_PMAX of a moment table */
+constexpr int TR_RM = 16;                    /* distances kept per cluster: TR_NP orders, the underflow's last */
+/* doubles of a cluster's moment table: rows of 2 NF values, padded to the 32 doubles of a row load */
+constexpr int tr_stride(int nf) { return (TR_ROWS * 2 * nf + 31) / 32 * 32; }
+constexpr double TR_AMIN = 1e-6, TR_AMAX = 2.0; /* alpha R of an expansion (below: K_n, I_n leave the range of a double) */
+constexpr double TR_ZZERO = 746.0;           /* e^{-z} is exactly 0 in double from here on (also scaled by 2^-1074) */
+constexpr double TR_EPS = 0x1p-54;           /* truncation of an expansion, relative to its smallest pair */
+
+struct TreeDev {
+    int64_t Np = 0;
+    int nlev = 0;
+    int64_t off[TR_LEV] = {0, 0, 0, 0, 0};   /* first cluster of each level */
+    int64_t ncl = 0;
+    int cut = 0;                             /* a direct item is 2^cut units of work (16/2^cut sources each) */
+    double *cc = nullptr;                    /* [ncl][2] centres */
+    double *rmin = nullptr;                  /* [ncl][TR_RM]: distance from which order TR_PMIN + TR_PSTEP k serves
+                                                (k < TR_NP; INFINITY: never); last: from which every pair underflows */
+    double *mom = nullptr;                   /* [ncl][tr_stride]: rows of (2 Re M, -2 Im M) per field */
+    double *st = nullptr;                    /* staged sources [Np][3][16]: w sigma, alpha w mu n_x, alpha w mu n_y */
+    uint2 *items = nullptr;                  /* [groups][Np]: direct items from the front, expansions from the back */
+    int2 *cnt = nullptr;                     /* [groups]: their numbers */
+    int32_t *order = nullptr;                /* [groups] launch order: the groups with the most work first */
+};
+
+/* item: x = cluster, y = piece + 1 (bits 0-4) | order (bits 8-13) | flags */
+constexpr uint32_t TR_NEAR = 1u << 16; /* direct: some target of the wave lists the panel */
+constexpr uint32_t TR_ZERO = 1u << 17; /* every pair underflows to zero: only non-finite densities matter */
+
+/* Truncation of an order-p expansion with alpha R = a at distance t R from the
+   centre: bound of sum_{n>p} alpha (I_{n-1} + I_{n+1})(a) K_n(a t), the
+   neglected field of a unit dipole on the cluster's rim (a charge's is
+   smaller), over alpha K_1(a t + a), that dipole's smallest field.
+   I_p(a) <= (a/2)^p/p! e^{a^2/(4(p+1))}; K_{p+1}/K_1 by the upward ratios;
+   K_1(b)/K_1(b + a) <= e^a (1 + a/b). */
+__host__ __device__ inline float tree_truncation(int p, float a, float t)
+{
+    const float b = a * t;
+    float prod = 1.0f, h = 2.0f / b + 1.0f;
+    for (int n = 1; n <= p; ++n) {
+        prod *= (0.5f * a / (float)n) * h;
+        h = (float)(2 * (n + 1)) / b + 1.0f / h;
+    }
+    return prod * expf(a + 0.25f * a * a / (float)(p + 1)) * (1.0f + 1.0f / t) / (1.0f - 1.0f / t);
+}
+
+/* the smallest t = r/R (to 2%, rounded up) from which order p serves; single
+   precision is enough for a bound */
+__host__ __device__ inline double tree_order_ratio(int p, double alphaR)
+{
+    constexpr float TMIN = 1.5f, TMAX = 300.0f, EPS = (float)(0.999 * TR_EPS);
+    const float a = (float)alphaR;
+    if (!(alphaR >= TR_AMIN && alphaR <= TR_AMAX) || !(tree_truncation(p, a, TMAX) <= EPS)) return INFINITY;
+    float lo = logf(TMIN), hi = logf(TMAX);
+    for (int k = 0; k < 8; ++k) {
+        const float mid = 0.5f * (lo + hi);
+        if (tree_truncation(p, a, expf(mid)) <= EPS)
+            hi = mid;
+        else
+            lo = mid;
+    }
+    return (double)expf(hi) * (1.0 + 1e-5);
+}
+
+__device__ __forceinline__ float tr_dpp_f(float v, float old, int sel)
+{
+    const int o = __float_as_int(old), i = __float_as_int(v);
+    int r;
+    switch (sel) {
+    case 0: r = __builtin_amdgcn_update_dpp(o, i, 0x111, 0xf, 0xf, false); break;
+    case 1: r = __builtin_amdgcn_update_dpp(o, i, 0x112, 0xf, 0xf, false); break;
+    case 2: r = __builtin_amdgcn_update_dpp(o, i, 0x114, 0xf, 0xf, false); break;
+    case 3: r = __builtin_amdgcn_update_dpp(o, i, 0x118, 0xf, 0xf, false); break;
+    case 4: r = __builtin_amdgcn_update_dpp(o, i, 0x142, 0xa, 0xf, false); break;
+    default: r = __builtin_amdgcn_update_dpp(o, i, 0x143, 0xc, 0xf, false); break;
+    }
+    return __int_as_float(r);
+}
+/* smallest and largest value over the wave's 64 lanes (NaN lanes do not count) */
+__device__ __forceinline__ float wave_min_f(float v)
+{
+#pragma unroll
+    for (int k = 0; k < 6; ++k) v = fminf(v, tr_dpp_f(v, INFINITY, k));
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+__device__ __forceinline__ float wave_max_f(float v)
+{
+#pragma unroll
+    for (int k = 0; k < 6; ++k) v = fmaxf(v, tr_dpp_f(v, -INFINITY, k));
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+
+__device__ __forceinline__ int tree_level_of(const TreeDev &T, int64_t c)
+{
+    int k = 0;
+    while (k + 1 < T.nlev && c >= T.off[k + 1]) ++k;
+    return k;
+}
+
+/* plan time: centre (of the bounding box), and the distances rmin of each
+   cluster; one wave per cluster.  A cluster is far enough from every target
+   that could list one of its panels: a listed panel has a node within
+   near_factor h, so r >= R + near_factor max h rules it out. */
+__global__ __launch_bounds__(256) void tree_clusters_kernel(TreeDev T, const double *__restrict__ x,
+                                                            const double *__restrict__ y,
+                                                            const double *__restrict__ ph, double alpha,
+                                                            double near_factor)
+{
+    const int64_t c = blockIdx.x * (int64_t)4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (c >= T.ncl) return;
+    const int k = tree_level_of(T, c);
+    const int64_t p0 = (c - T.off[k]) << k, p1 = min(T.Np, p0 + (1 << k));
+    double xl = INFINITY, xh = -INFINITY, yl = INFINITY, yh = -INFINITY, h = 0.0;
+    for (int64_t j = 16 * p0 + lane; j < 16 * p1; j += 64) {
+        xl = fmin(xl, x[j]), xh = fmax(xh, x[j]);
+        yl = fmin(yl, y[j]), yh = fmax(yh, y[j]);
+        h = fmax(h, ph[j >> 4]);
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        xl = fmin(xl, __shfl_xor(xl, o)), xh = fmax(xh, __shfl_xor(xh, o));
+        yl = fmin(yl, __shfl_xor(yl, o)), yh = fmax(yh, __shfl_xor(yh, o));
+        h = fmax(h, __shfl_xor(h, o));
+    }
+    const double cx = 0.5 * (xl + xh), cy = 0.5 * (yl + yh);
+    double R = 0.0;
+    for (int64_t j = 16 * p0 + lane; j < 16 * p1; j += 64) R = fmax(R, hypot(x[j] - cx, y[j] - cy));
+    for (int o = 32; o > 0; o >>= 1) R = fmax(R, __shfl_xor(R, o));
+    R *= 1.0 + 1e-12;
+    if (lane == 0) {
+        T.cc[2 * c] = cx;
+        T.cc[2 * c + 1] = cy;
+    }
+    if (lane < TR_RM) {
+        const double clear = R + near_factor * h * (1.0 + 1e-12);
+        double v;
+        if (lane < TR_NP)
+            v = fmax(R * tree_order_ratio(TR_PMIN + TR_PSTEP * lane, alpha * R), clear);
+        else
+            v = fmax(R + TR_ZZERO * (1.0 + 1e-12) / alpha, clear);
+        T.rmin[TR_RM * c + lane] = v;
+    }
+}
+
+/* the piece class of z in [zlo, zhi] (0: z <= 2, piece + 1, KQ_NP + 1: per-pair) */
+__device__ __forceinline__ int tree_piece(double zlo, double zhi)
+{
+    int lo = 0, hi = 0;
+    for (int b = 0; b < KQ_NB; ++b) {
+        lo += zlo > KQ_B[b] ? 1 : 0;
+        hi += zhi > KQ_B[b] ? 1 : 0;
+    }
+    if (lo == hi) return lo;
+    if (lo >= 1 && hi == lo + 1 && lo <= KQ_NB - 1) return KQ_NB + lo;
+    return KQ_NP + 1;
+}
+
+/* plan time: the item lists of each group of 64 targets, one wave per group.
+   Panels are visited in order; at each, the largest aligned cluster is tried
+   first, then its halves. */
+__global__ __launch_bounds__(256) void tree_lists_kernel(TreeDev T, const double *__restrict__ tx,
+                                                         const double *__restrict__ ty, int64_t M,
+                                                         const double *__restrict__ sx, const double *__restrict__ sy,
+                                                         const double *__restrict__ ph, double near_factor,
+                                                         double alpha, const int32_t *__restrict__ nptr,
+                                                         const int32_t *__restrict__ npan)
+{
+    const int64_t g = blockIdx.x * (int64_t)4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (64 * g >= M) return;
+    const int64_t i = min(64 * g + lane, M - 1);
+    const double x = tx[i], y = ty[i];
+    const int32_t k0 = nptr[i], k1 = nptr[i + 1];
+    uint2 *items = T.items + g * T.Np;
+    int nd = 0, nf = 0;
+    for (int64_t p = 0; p < T.Np;) {
+        int k = p == 0 ? T.nlev - 1 : min(T.nlev - 1, __builtin_ctz((uint32_t)p));
+        for (;; --k) {
+            const int64_t c = T.off[k] + (p >> k);
+            const double dx = x - T.cc[2 * c], dy = y - T.cc[2 * c + 1], r = sqrt(fma(dx, dx, dy * dy));
+            /* extreme distances, widened past the rounding to float */
+            const double rlo = (double)wave_min_f((float)r) * (1.0 - 3e-7);
+            const double rhi = (double)wave_max_f((float)r) * (1.0 + 3e-7);
+            const double *rm = T.rmin + TR_RM * c;
+            uint32_t y_ = 0xffffffffu;
+            if (rlo >= rm[TR_RM - 1]) {
+                y_ = TR_ZERO;
+            } else {
+                for (int q = TR_NP - 1; q >= 0 && rlo >= rm[q]; --q) /* rm falls with the order */
+                    y_ = (uint32_t)(TR_PMIN + TR_PSTEP * q) << 8;
+                if (y_ != 0xffffffffu) y_ |= (uint32_t)tree_piece(alpha * rlo, alpha * rhi);
+            }
+            if (y_ != 0xffffffffu) {
+                if (lane == 0) items[T.Np - 1 - nf] = make_uint2((uint32_t)c, y_);
+                ++nf;
+                break;
+            }
+            if (k > 0) continue;
+            /* direct: the piece of the targets that do not list the panel */
+            bool listed = false;
+            for (int32_t q = k0; q < k1; ++q) listed = listed || npan[q] == (int32_t)p;
+            const bool any = __ballot(listed) != 0;
+            if (__ballot(!listed) != 0) {
+                double r2lo = INFINITY, r2hi = 0.0;
+                for (int j = 0; j < 16; ++j) {
+                    const double ex = x - sx[16 * p + j], ey = y - sy[16 * p + j];
+                    const double r2 = fma(ex, ex, ey * ey);
+                    r2lo = fmin(r2lo, r2);
+                    r2hi = fmax(r2hi, r2);
+                }
+                const double dlo = (double)wave_min_f(listed ? INFINITY : (float)sqrt(r2lo)) * (1.0 - 3e-7);
+                const double dhi = (double)wave_max_f(listed ? -INFINITY : (float)sqrt(r2hi)) * (1.0 + 3e-7);
+                if (lane == 0)
+                    items[nd] = make_uint2((uint32_t)c, (uint32_t)tree_piece(alpha * dlo, alpha * dhi) |
+                                                            (any ? TR_NEAR : 0u));
+                ++nd;
+            }
+            break;
+        }
+        p += (int64_t)1 << k;
+    }
+    if (lane == 0) T.cnt[g] = make_int2(nd, nf);
+}
+
+/* plan time: the groups by falling work (a direct item costs about three
+   expansions), one block, a counting sort: blocks start in this order, so the
+   groups next to the curve, with up to five times the work of the others, do
+   not start last */
+constexpr int TR_BINS = 1024;
+__global__ __launch_bounds__(1024) void tree_order_kernel(TreeDev T, int64_t G)
+{
+    __shared__ int32_t pos[TR_BINS];
+    auto bin = [&](int64_t g) { return TR_BINS - 1 - min(TR_BINS - 1, 3 * T.cnt[g].x + T.cnt[g].y); };
+    const int t = threadIdx.x;
+    pos[t] = 0;
+    __syncthreads();
+    for (int64_t g = t; g < G; g += 1024) atomicAdd(&pos[bin(g)], 1);
+    __syncthreads();
+    for (int o = 1; o < TR_BINS; o <<= 1) {
+        const int32_t v = t >= o ? pos[t - o] : 0;
+        __syncthreads();
+        pos[t] += v;
+        __syncthreads();
+    }
+    const int32_t before = t ? pos[t - 1] : 0;
+    __syncthreads();
+    pos[t] = before;
+    __syncthreads();
+    for (int64_t g = t; g < G; g += 1024) T.order[atomicAdd(&pos[bin(g)], 1)] = (int32_t)g;
+}
+
+/* ------------------------------------------------------------------------ */
+/* moments of one evaluation                                                 */
+/* ------------------------------------------------------------------------ */
+/* A block takes 256 sources (16 panels) at one level (blockIdx.y) and TR_NG
+   orders (blockIdx.z).  With w = (alpha/2) conj(y - c) and q = |w|^2,
+   B_n = w^n/n! S_n(q), S_n = sum_k q^k/(k! (n+1)..(n+k)), from the backward
+   recurrence S_{n-1} = S_n + q/(n(n+1)) S_{n+1} (all terms positive: stable)
+   started by the series; no root, division or angle per source.  The sources
+   of a panel are added through LDS in a fixed order, panels of a cluster by a
+   fixed tree.  Latency bound (config 2: 240 blocks, 14 MFLOP): the split over
+   orders keeps a block at three short rounds. */
+constexpr int TR_NG = 12, TR_GROUPS = (TR_ROWS + TR_NG - 1) / TR_NG;
+constexpr int TR_RO = 4;   /* orders per LDS round */
+constexpr int TR_PAD = 17; /* LDS row of a panel's 16 sources */
+
+template <int N0, int CNT>
+__device__ __forceinline__ void tree_regular(double wr, double wi, double q, double (&br)[CNT], double (&bi)[CNT])
+{
+    /* B_n, n = N0 .. N0 + CNT - 1 */
+    constexpr int top = N0 + CNT - 1;
+    double s1 = 1.0, s0 = 1.0; /* S_{top+1}, S_top by Horner, 10 terms (q <= 1) */
+#pragma unroll
+    for (int k = 10; k >= 1; --k) {
+        s1 = fma(q * (1.0 / ((double)k * (top + 1 + k))), s1, 1.0);
+        s0 = fma(q * (1.0 / ((double)k * (top + k))), s0, 1.0);
+    }
+#pragma unroll
+    for (int n = top; n >= N0; --n) {
+        br[n - N0] = s0;
+        if (n > 0) {
+            const double t = fma(q * (1.0 / ((double)n * (n + 1))), s1, s0);
+            s1 = s0;
+            s0 = t;
+        }
+    }
+    double pr = 1.0, pi = 0.0;
+#pragma unroll
+    for (int n = 1; n <= top; ++n) {
+        if (n - 1 >= N0) {
+            bi[n - 1 - N0] = pi * br[n - 1 - N0];
+            br[n - 1 - N0] *= pr;
+        }
+        const double a = wr * (1.0 / n), b = wi * (1.0 / n);
+        const double t = fma(pr, a, -pi * b);
+        pi = fma(pr, b, pi * a);
+        pr = t;
+    }
+    bi[CNT - 1] = pi * br[CNT - 1];
+    br[CNT - 1] *= pr;
+}
+
+template <bool SLP, bool DLP, int Z>
+__device__ __forceinline__ void tree_moments_body(const FarArgs &A, const TreeDev &T, const double *mu,
+                                                  double (*buf)[16 * TR_PAD])
+{
+    constexpr int NV = (SLP ? 2 : 0) + (DLP ? 2 : 0), N0 = Z * TR_NG;
+    constexpr int LO = N0 == 0 ? 0 : N0 - 1, CNT = N0 + TR_NG - LO + 1; /* orders N0 - 1 .. N0 + TR_NG */
+    const int k = blockIdx.y, t = threadIdx.x;
+    const int64_t p0 = (int64_t)blockIdx.x * 16, j = 16 * p0 + t;
+    const bool have = j < A.N;
+    const int64_t js = have ? j : A.N - 1, ps = js >> 4;
+    const int64_t c = T.off[k] + (ps >> k);
+    const double dx = A.sx[js] - T.cc[2 * c], dy = A.sy[js] - T.cc[2 * c + 1];
+    const double wj = have ? A.sw[js] : 0.0;
+    double q = 0.0, ex = 0.0, ey = 0.0;
+    if (SLP) q = have ? wj * A.sigma[js] : 0.0;
+    if (DLP) {
+        const double m = have ? (A.alpha * wj) * mu[js] : 0.0; /* alpha goes with the dipole */
+        ex = m * A.snx[js];
+        ey = m * A.sny[js];
+    }
+    if (Z == 0 && k == 0 && have) {
+        double *s = T.st + (j >> 4) * 48 + (j & 15);
+        if (SLP) s[0] = q;
+        if (DLP) {
+            s[16] = ex;
+            s[32] = ey;
+        }
+    }
+    /* clusters too wide to expand (the same test as tree_order_ratio through rmin) */
+    const bool live = T.rmin[TR_RM * c + TR_NP - 1] < INFINITY;
+    if (__syncthreads_or(live ? 1 : 0) == 0) return;
+    const double ah = 0.5 * A.alpha, wr = live ? ah * dx : 0.0, wi = live ? -ah * dy : 0.0;
+    double br[CNT], bi[CNT];
+    tree_regular<LO, CNT>(wr, wi, fma(wr, wr, wi * wi), br, bi);
+    const int cb = t >> 4, pp = t & 15;
+#pragma unroll
+    for (int r = 0; r < TR_NG; r += TR_RO) {
+        if (N0 + r > TR_PMAX) break;
+#pragma unroll
+        for (int o = 0; o < TR_RO; ++o) {
+            const int n = N0 + r + o, b = n - LO; /* compile-time */
+            const double f = n == 0 ? 1.0 : 2.0;
+            int v = o * NV;
+            const int at = (t >> 4) * TR_PAD + (t & 15);
+            if (SLP) {
+                buf[v++][at] = f * q * br[b];
+                buf[v++][at] = -f * q * bi[b];
+            }
+            if (DLP) {
+                /* ex, ey carry alpha: the factor is (2 - delta)/2 */
+                double re, im;
+                if (n == 0) {
+                    re = fma(ex, br[b + 1], -ey * bi[b + 1]);
+                    im = 0.0;
+                } else {
+                    const int bm = b > 0 ? b - 1 : 0;
+                    re = fma(ex, br[bm] + br[b + 1], ey * (bi[bm] - bi[b + 1]));
+                    im = fma(ex, bi[bm] + bi[b + 1], ey * (br[b + 1] - br[bm]));
+                }
+                buf[v++][at] = re;
+                buf[v++][at] = -im;
+            }
+        }
+        __syncthreads();
+        if (cb < TR_RO * NV) {
+            const double *row = buf[cb] + pp * TR_PAD;
+            double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+            for (int l = 0; l < 16; l += 2) {
+                s0 += row[l];
+                s1 += row[l + 1];
+            }
+            double s = s0 + s1;
+            for (int o = 1; o < (1 << k); o <<= 1) s += __shfl_xor(s, o);
+            const int n = N0 + r + cb / NV;
+            const int64_t p = p0 + pp;
+            if ((pp & ((1 << k) - 1)) == 0 && p < T.Np && n <= TR_PMAX)
+                T.mom[(T.off[k] + (p >> k)) * tr_stride(NV / 2) + n * NV + cb % NV] = s;
+        }
+        __syncthreads();
+    }
+}
+
+template <bool SLP, bool DLP>
+__global__ __launch_bounds__(256) void tree_moments_kernel(FarArgs A, TreeDev T)
+{
+    constexpr int NV = (SLP ? 2 : 0) + (DLP ? 2 : 0);
+    __shared__ double buf[TR_RO * NV][16 * TR_PAD];
+    const double *mu;
+    if (!far_density(A, mu)) return;
+    switch (blockIdx.z) {
+    case 0: tree_moments_body<SLP, DLP, 0>(A, T, mu, buf); break;
+    case 1: tree_moments_body<SLP, DLP, 1>(A, T, mu, buf); break;
+    default: tree_moments_body<SLP, DLP, 2>(A, T, mu, buf); break;
+    }
+}
+static_assert(TR_GROUPS == 3, "tree_moments_kernel has a case for each group of orders");
+
+/* ------------------------------------------------------------------------ */
+/* evaluation                                                                */
+/* ------------------------------------------------------------------------ */
+/* K0, K1 at distance^2 r2 in piece PC (-1: z <= 2; KQ_NP: per-lane), and 1/r */
+template <int PC>
+__device__ __forceinline__ void tree_k01(const FarConst &fc, const double *fq, double r2, double &ri, double &k0,
+                                         double &k1)
+{
+    constexpr int K = PC < 0 || PC >= KQ_NP ? 0 : PC;
+    const FarTab T = far_table();
+    if constexpr (PC >= 0 && PC < KQ_NP) {
+        double qa, qk, d;
+        fine_q<K>(fq, qa, qk);
+        ri = lean_rsq(r2);
+        const double z = fc.a * (r2 * ri);
+        const double e = lean_exp_neg(T, z) * lean_rsq(z);
+        k0 = e * far_piece_fine<true, true, K>(T, qa, qk, ri, d);
+        k1 = e * d;
+    } else {
+        K01 o, o2;
+        if constexpr (PC < 0)
+            o = k01_far_small<true, true, true>(T, r2, fc);
+        else
+            k01_far2<true, true, true, true>(T, fc, r2, r2, o, o2);
+        ri = lean_rsq(r2);
+        k0 = o.k0;
+        k1 = o.ak1r * (r2 * ri);
+    }
+}
+
+__device__ __forceinline__ void tree_k01_pc(int pc, const FarConst &fc, const double *fq, double r2, double &ri,
+                                            double &k0, double &k1)
+{
+    switch (pc) {
+#define MHLP_TREE_PC(PCV) \
+    case PCV: tree_k01<PCV>(fc, fq, r2, ri, k0, k1); break;
+        MHLP_PC_CASES(MHLP_TREE_PC)
+#undef MHLP_TREE_PC
+    default: tree_k01<KQ_NP>(fc, fq, r2, ri, k0, k1);
+    }
+}
+
+/* f += (v of lane L of the lane's row of 16) * s: the moments of an expansion
+   sit 32 to a pair of registers, repeated in every row of 16 lanes, and reach
+   the FMA as its broadcast operand.  v comes from a load and is never written
+   by the VALU before (no DPP hazard). */
+template <int L>
+__device__ __forceinline__ void fmac_row(double &f, double v, double s)
+{
+    asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(f) : "v"(v), "v"(s), "n"(L));
+}
+
+template <int NF, int N, int F>
+__device__ __forceinline__ void tree_row(const double2 *m, double kc, double ks, double (&f0)[NF], double (&f1)[NF])
+{
+    if constexpr (F < NF) {
+        constexpr int at = N * 2 * NF + 2 * F;
+        fmac_row<(at % 32) / 2>(f0[F], m[at / 32].x, kc);
+        if (N > 0) fmac_row<(at % 32) / 2>(f1[F], m[at / 32].y, ks);
+        tree_row<NF, N, F + 1>(m, kc, ks, f0, f1);
+    }
+}
+
+/* orders N, N + 1 and on to `order` (even) */
+template <int NF, int N>
+__device__ __forceinline__ void tree_rows(int order, const double2 *m, double c2, double h, double b, double km,
+                                          double k, double cp, double cn, double sp, double sn, double (&f0)[NF],
+                                          double (&f1)[NF])
+{
+    if constexpr (N < TR_PMAX) {
+        if (N > order) return;
+        tree_row<NF, N, 0>(m, k * cn, k * sn, f0, f1);
+        km = fma(b, k, km);
+        cp = fma(c2, cn, -cp);
+        sp = fma(c2, sn, -sp);
+        b += h;
+        tree_row<NF, N + 1, 0>(m, km * cp, km * sp, f0, f1);
+        k = fma(b, km, k);
+        cn = fma(c2, cp, -cn);
+        sn = fma(c2, sp, -sn);
+        tree_rows<NF, N + 2>(order, m, c2, h, b + h, km, k, cp, cn, sp, sn, f0, f1);
+    }
+}
+
+/* NF fields of one cluster expansion at the lane's target.  K_n
+   by the upward recurrence (stable), cos and sin of n theta by theirs; the
+   n-th term falls like (R/r)^n, so the growth of their rounding with n does not
+   show.  The moments are loaded whole (a row of 16 lanes holds 32 doubles per
+   load) while K0 and K1 are formed: reading them order by order through the
+   scalar cache left the kernel waiting (its 16 KB serve two CUs). */
+template <int NF>
+__device__ __forceinline__ void tree_expand(const FarConst &fc, const double *fq, const TreeDev &T, uint32_t c,
+                                            int pc, int order, double x, double y, double (&f0)[NF])
+{
+    constexpr int NL = tr_stride(NF) / 32;
+    const double2 *mp = (const double2 *)(T.mom + (int64_t)c * tr_stride(NF)) + (threadIdx.x & 15);
+    double2 m[NL];
+#pragma unroll
+    for (int l = 0; l < NL; ++l) m[l] = mp[16 * l];
+    const MHLP_CAS double *cc = (const MHLP_CAS double *)T.cc + 2 * (int64_t)c;
+    const double ex = x - cc[0], ey = y - cc[1];
+    double ri, k0, k1;
+    tree_k01_pc(pc, fc, fq, fma(ex, ex, ey * ey), ri, k0, k1);
+    const double ct = ex * ri, st = ey * ri, h = 2.0 * fc.ia * ri;
+    double f1[NF];
+#pragma unroll
+    for (int f = 0; f < NF; ++f) f0[f] = f1[f] = 0.0;
+    tree_row<NF, 0, 0>(m, k0, 0.0, f0, f1);
+    tree_rows<NF, 1>(order, m, 2.0 * ct, h, h, k0, k1, 1.0, ct, 0.0, st, f0, f1);
+#pragma unroll
+    for (int f = 0; f < NF; ++f) f0[f] += f1[f];
+}
+
+/* whether a staged charge or dipole of the cluster is infinite or NaN */
+template <bool SLP, bool DLP>
+__device__ __forceinline__ bool tree_bad(const TreeDev &T, int64_t p0, int64_t p1)
+{
+    double s = 0.0;
+    for (int64_t j = 16 * p0 + (threadIdx.x & 63); j < 16 * p1; j += 64) {
+        const double *q = T.st + (j >> 4) * 48 + (j & 15);
+        if (SLP) s = fma(0.0, q[0], s);
+        if (DLP) s = fma(0.0, q[16], fma(0.0, q[32], s));
+    }
+    return __ballot(!(s == 0.0)) != 0;
+}
+
+/* staged sources s0..s1-1 of one panel against the lane's target, in piece PC;
+   sources come through the scalar cache, two at a time */
+template <bool SLP, bool DLP, int PC>
+__device__ __forceinline__ void tree_panel(const FarArgs &A, const FarConst &fc, const TreeDev &D, int64_t p, int s0,
+                                           int s1, double x, double y, double &accs, double &accd)
+{
+    const MHLP_CAS double *sx = (const MHLP_CAS double *)A.sx + 16 * p;
+    const MHLP_CAS double *sy = (const MHLP_CAS double *)A.sy + 16 * p;
+    const MHLP_CAS double *st = (const MHLP_CAS double *)D.st + 48 * p;
+    constexpr int K = PC < 0 || PC >= KQ_NP ? 0 : PC;
+    const FarTab T = far_table();
+    double qa, qk;
+    fine_q<K>(A.fq, qa, qk);
+#pragma unroll 1
+    for (int s = s0; s < s1; s += 2) {
+        const double ex0 = x - sx[s], ey0 = y - sy[s];
+        const double ex1 = x - sx[s + 1], ey1 = y - sy[s + 1];
+        const double r20 = fma(ex0, ex0, ey0 * ey0), r21 = fma(ex1, ex1, ey1 * ey1);
+        K01 o0, o1;
+        if constexpr (PC >= KQ_NP)
+            k01_far2<SLP, DLP, true, true>(T, fc, r20, r21, o0, o1);
+        else
+            k01_far2_fixed<SLP, DLP, PC>(T, fc, qa, qk, r20, r21, o0, o1);
+        if (SLP) accs = fma(o1.k0, st[s + 1], fma(o0.k0, st[s], accs));
+        if (DLP)
+            accd = fma(o1.ak1r, fma(ex1, st[16 + s + 1], ey1 * st[32 + s + 1]),
+                       fma(o0.ak1r, fma(ex0, st[16 + s], ey0 * st[32 + s]), accd));
+    }
+}
+
+constexpr int TR_WMAX = 16; /* waves of a block at most */
+
+/* One block per group of 64 targets (lane = target), in the order of the
+   groups' work; the waves of the gridDim.y blocks of a group share its items:
+   direct ones in units of 16 / 2^cut sources in turn, expansions in equal
+   runs, starting from the other end, so that no wave gets more than its share
+   of both.  One block per group: the wave sums are added in wave order with
+   the near corrections, which the waves share by node.  Several: each leaves
+   its sum in slot blockIdx.y for far_finalize.  A cluster whose expansion is
+   not finite (an infinite or NaN density) or whose pairs all underflow with
+   such a density is summed directly, pair by pair.
+
+   Bound by VALU FP64 (109,314 targets, 4096 sources, alpha = 5: 15.6e3
+   instructions per group against 304e3 for the direct sum of all pairs, 68 us
+   against 1.07 ms; alpha = 500, all pairs direct: within 5% of the issue rate).
+   Waves per group (tree_setup): four for many groups; up to 128 for few,
+   where the longest wave (a direct panel in one wave takes about 20 us) sets
+   the time. */
+template <bool SLP, bool DLP>
+__global__ __launch_bounds__(64 * TR_WMAX) void far_tree_kernel(FarArgs A, TreeDev T)
+{
+    constexpr int NF = (SLP ? 1 : 0) + (DLP ? 1 : 0);
+    __shared__ double red[NF][TR_WMAX][64];
+    const double *mu;
+    if (!far_density(A, mu)) return;
+    const int lane = threadIdx.x & 63, W = blockDim.x >> 6;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t g = T.order[blockIdx.x];
+    const int64_t i = 64 * g + lane;
+    const bool valid = i < A.M;
+    const int64_t iv = valid ? i : A.M - 1; /* lanes past the last target repeat it, as in the lists */
+    const double x = A.tx[iv], y = A.ty[iv];
+    const int32_t k0 = A.nptr[iv], k1 = A.nptr[iv + 1];
+    const int NW = W * gridDim.y, wg = w * gridDim.y + blockIdx.y;
+    const int2 cnt = T.cnt[g];
+    const uint2 *items = T.items + g * T.Np;
+    const FarConst fc = far_const(A.alpha);
+    double acc[NF];
+#pragma unroll
+    for (int f = 0; f < NF; ++f) acc[f] = 0.0;
+    const int nsrc = 16 >> T.cut;
+    for (int k = wg; k < (cnt.x << T.cut); k += NW) {
+        const uint2 it = items[k >> T.cut];
+        const int s0 = (k & ((1 << T.cut) - 1)) * nsrc, s1 = s0 + nsrc;
+        const uint32_t p = __builtin_amdgcn_readfirstlane(it.x), fl = __builtin_amdgcn_readfirstlane(it.y);
+        bool listed = false;
+        if (fl & TR_NEAR)
+            for (int32_t q = k0; q < k1; ++q) listed = listed || A.npan[q] == (int32_t)p;
+        if (listed) continue;
+        double ps = 0.0, pd = 0.0;
+        switch ((int)(fl & 31) - 1) {
+#define MHLP_TREE_PANEL(PCV)                                                                               \
+    case PCV: tree_panel<SLP, DLP, PCV>(A, fc, T, p, s0, s1, x, y, ps, pd); break;
+            MHLP_PC_CASES(MHLP_TREE_PANEL)
+#undef MHLP_TREE_PANEL
+        default: tree_panel<SLP, DLP, KQ_NP>(A, fc, T, p, s0, s1, x, y, ps, pd);
+        }
+        if (SLP) acc[0] += ps;
+        if (DLP) acc[NF - 1] += pd;
+    }
+    const int fb = cnt.y * (NW - 1 - wg) / NW, fe = cnt.y * (NW - wg) / NW;
+    for (int k = fb; k < fe; ++k) {
+        const uint2 it = items[T.Np - 1 - k];
+        const uint32_t c = __builtin_amdgcn_readfirstlane(it.x), fl = __builtin_amdgcn_readfirstlane(it.y);
+        double f[NF];
+        bool direct = false;
+        if (fl & TR_ZERO) {
+#pragma unroll
+            for (int n = 0; n < NF; ++n) f[n] = 0.0;
+            const int lv = tree_level_of(T, c);
+            const int64_t p0 = ((int64_t)c - T.off[lv]) << lv;
+            direct = tree_bad<SLP, DLP>(T, p0, min(T.Np, p0 + (1 << lv)));
+        } else {
+            tree_expand<NF>(fc, A.fq, T, c, (int)(fl & 31) - 1, (int)(fl >> 8) & 63, x, y, f);
+            bool fin = true;
+#pragma unroll
+            for (int n = 0; n < NF; ++n) fin = fin && __builtin_isfinite(f[n]);
+            direct = __ballot(!fin) != 0;
+        }
+        if (direct) {
+            const int lv = tree_level_of(T, c);
+            const int64_t p0 = ((int64_t)c - T.off[lv]) << lv, p1 = min(T.Np, p0 + (1 << lv));
+            double ps = 0.0, pd = 0.0;
+            for (int64_t p = p0; p < p1; ++p)
+                tree_panel<SLP, DLP, KQ_NP>(A, fc, T, p, 0, 16, x, y, ps, pd);
+            if (SLP) f[0] = ps;
+            if (DLP) f[NF - 1] = pd;
+        }
+#pragma unroll
+        for (int n = 0; n < NF; ++n) acc[n] += f[n];
+    }
+    if (gridDim.y > 1) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) red[f][w][lane] = acc[f];
+        __syncthreads();
+        if (w >= NF || !valid) return;
+        double s = 0.0;
+        for (int v = 0; v < W; ++v) s += red[w][v][lane];
+        ((SLP && w == 0) ? A.part_s : A.part_d)[blockIdx.y * A.M + i] = s;
+        return;
+    }
+    /* near corrections: this wave's nodes of each listed panel */
+    double ns = 0.0, nd = 0.0;
+    for (int32_t q = k0; q < k1; ++q) {
+        const int64_t p = A.npan[q];
+        if (p < 0) continue;
+        for (int jj = w; jj < 16; jj += W) {
+            if (SLP) ns = fma(A.wsl[16 * (int64_t)q + jj], A.sigma[16 * p + jj], ns);
+            if (DLP) nd = fma(A.wdl[16 * (int64_t)q + jj], mu[16 * p + jj], nd);
+        }
+    }
+    if (SLP) red[0][w][lane] = fma(INV_2PI, acc[0], ns);
+    if (DLP) red[NF - 1][w][lane] = fma(INV_2PI, acc[NF - 1], nd);
+    __syncthreads();
+    if (w >= NF || !valid) return;
+    double s = 0.0;
+    for (int v = 0; v < W; ++v) s += red[w][v][lane];
+    const int64_t o = A.perm ? (int64_t)A.perm[i] : i;
+    if (SLP && w == 0) {
+        A.us[o] = s;
+    } else {
+        if (A.half_term != 0.0) s = fma(A.half_term, mu[i], s);
+        A.ud[o] = s;
+    }
+}
+
+} // namespace mhlp

@@ -1,0 +1,116 @@
+"""GPU tests of the cluster-expansion far field (csrc/tree.h) at the sizes where its lists and splits can
+go wrong: ragged clusters, one target to many, every regime of alpha R.
+
+Off the near panels the result is the plain Nystrom sum, which scipy's K0 and K1 give pair by pair.  The
+bound of a term is 3e-14 + 5e-16 z of its absolute value: about 10 roundings of 2.2e-16 per term and
+partial sum, times the spread of the kernel over a cluster (I0(2) = 2.3 on average over its charges),
+with a margin of six, and two roundings of the argument of e^{-z} on either side; 1e-300 covers values next
+to underflow.  In mixed precision a term is
+good to 1e-6 plus 2e-7 z (three roundings of 2^-24 in the argument of e^{-z}); below 1e-36 of the charges
+it is flushed to zero."""
+import numpy as np
+import pytest
+import scipy.special as sp
+import torch
+
+from paper_1908_07392_amd import mhlp
+from paper_1908_07392_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def _t(a):
+    return torch.as_tensor(np.ascontiguousarray(a), dtype=torch.float64, device="cuda:0")
+
+
+def _setup(panels, m, seed):
+    """An ellipse, random densities, targets inside and outside further than 1.25 panel lengths from it."""
+    rng = np.random.default_rng(seed)
+    g = wl.discretize(wl.Curve("ellipse", a=1.2, b=0.7), panels)
+    clear = 1.3 * g.weights.reshape(-1, 16).sum(axis=1).max()
+    tx, ty = rng.uniform(-3.0, 3.0, 40 * m + 400), rng.uniform(-2.0, 2.0, 40 * m + 400)
+    tx[: tx.size // 2] *= 0.3
+    ty[: ty.size // 2] *= 0.3
+    keep = np.ones(tx.size, bool)
+    for j in range(0, g.n_nodes, 3):
+        keep &= np.hypot(tx - g.x[j], ty - g.y[j]) > clear
+    tx, ty = tx[keep], ty[keep]
+    pick = rng.permutation(tx.size)[:m]
+    assert pick.size == m
+    return g, tx[pick], ty[pick], rng.standard_normal(g.n_nodes), rng.standard_normal(g.n_nodes)
+
+
+def _plain(g, alpha, tx, ty, sg, mu):
+    """The sums, and the sums of the terms' absolute values times the FP64 and the mixed bound of a term."""
+    ex, ey = tx[:, None] - g.x, ty[:, None] - g.y
+    r = np.hypot(ex, ey)
+    nx, ny = g.normals
+    s = sp.k0(alpha * r) * (g.weights * sg) / (2 * np.pi)
+    d = alpha * sp.k1(alpha * r) / r * (ex * nx + ey * ny) * (g.weights * mu) / (2 * np.pi)
+    dabs = alpha * sp.k1(alpha * r) * np.abs(g.weights * mu) / (2 * np.pi)
+    f64, f32 = 3e-14 + 5e-16 * alpha * r, 1e-6 + 2e-7 * alpha * r
+    return (s.sum(axis=1), (np.abs(s) * f64).sum(axis=1), (np.abs(s) * f32).sum(axis=1),
+            d.sum(axis=1), (dabs * f64).sum(axis=1), (dabs * f32).sum(axis=1))
+
+
+# alpha R of a panel from 1e-7 (below the expansions' range: all direct) through the expansions to beyond
+# them; at 900 the farthest pairs underflow.  Target counts on both sides of a group of 64 and of every
+# split of the groups over waves and blocks.
+@pytest.mark.parametrize("panels,m,alpha", [(24, 1, 3.0), (40, 63, 1e-6), (40, 65, 0.05), (47, 64, 3.0), (33, 1000, 8.0),
+                                            (64, 5500, 20.0), (31, 11000, 60.0), (40, 41000, 12.0), (48, 300, 900.0),
+                                            (37, 77000, 2.0)])
+def test_tree_potentials_vs_plain_sums(panels, m, alpha):
+    g, tx, ty, sg, mu = _setup(panels, m, panels + m)
+    P = mhlp.Plan(mhlp.Geometry(_t(g.node_soa())), alpha, _t(tx), _t(ty))
+    assert P.n_near_pairs == 0
+    sel = np.unique(np.linspace(0, m - 1, min(m, 400)).astype(int))
+    s, sa, sm, d, da, dm = _plain(g, alpha, tx[sel], ty[sel], sg, mu)
+    for prec in (mhlp.FP64, mhlp.MIXED):
+        us, ud = mhlp.eval_layer(P, sigma=_t(sg), mu=_t(mu), precision=prec)
+        us1, ud1 = mhlp.eval_slp(P, _t(sg), precision=prec), mhlp.eval_dlp(P, _t(mu), precision=prec)
+        for u, ref, a64, a32 in ((us, s, sa, sm), (us1, s, sa, sm), (ud, d, da, dm), (ud1, d, da, dm)):
+            bound = a64 + 1e-300 if prec == mhlp.FP64 else a32 + 1e-36 * alpha
+            assert (np.abs(u.cpu().numpy()[sel] - ref) <= bound).all()
+
+
+def test_tree_clusters_leave_listed_panels_direct():
+    """A near factor that lists panels far from their targets: no cluster may cover a listed panel.  On a
+    resolved curve with a smooth density the corrected panels give the plain rule's value."""
+    g, tx, ty, _, _ = _setup(96, 700, 5)
+    sg = np.cos(3 * g.theta) + 0.5
+    G = mhlp.Geometry(_t(g.node_soa()))
+    plain = mhlp.Plan(G, 6.0, _t(tx), _t(ty))
+    wide = mhlp.Plan(G, 6.0, _t(tx), _t(ty), params=dict(near_factor=9.0, rho_direct=200.0))
+    assert plain.n_near_pairs == 0 and wide.n_near_pairs > 700
+    for a, b in zip(mhlp.eval_layer(plain, sigma=_t(sg), mu=_t(sg)), mhlp.eval_layer(wide, sigma=_t(sg), mu=_t(sg))):
+        assert float((a - b).abs().max()) < 1e-9 * float(a.abs().max())
+
+
+@pytest.mark.parametrize("alpha", [5.0, 900.0])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_tree_non_finite_densities_reach_every_target(alpha, bad):
+    """A NaN or infinite charge makes every target non-finite, also where its pairs underflow; an infinite
+    one gives +inf wherever K0 is not zero, as the sum pair by pair does."""
+    g, tx, ty, sg, _ = _setup(48, 300, 7)
+    P = mhlp.Plan(mhlp.Geometry(_t(g.node_soa())), alpha, _t(tx), _t(ty))
+    sg[100] = bad
+    u = mhlp.eval_slp(P, _t(sg)).cpu().numpy()
+    if np.isnan(bad):
+        assert np.isnan(u).all()
+    else:
+        z = alpha * np.hypot(tx - g.x[100], ty - g.y[100])
+        assert (u[z < 700.0] == np.inf).all() and not np.isfinite(u).any()
+
+
+@pytest.mark.parametrize("panels", [3, 17, 96, 170, 700])
+@pytest.mark.parametrize("alpha", [2.0, 40.0])
+def test_tree_onsurface_operator_on_the_circle(panels, alpha):
+    """cos(n theta) is an eigenfunction of 1/2 I + D on the circle, with -alpha I_n K_n'."""
+    g = wl.discretize(wl.Curve("circle", R=1.0), panels)
+    P = mhlp.Plan(mhlp.Geometry(_t(g.node_soa())), alpha)
+    n = 2
+    lam = -alpha * sp.ive(n, alpha) * np.exp(alpha) * sp.kvp(n, alpha)
+    mu = np.cos(n * g.theta)
+    for prec, tol in ((mhlp.FP64, 1e-11 if panels > 3 else 1e-6), (mhlp.MIXED, 1e-6)):
+        out = mhlp.apply_bie(P, _t(mu), precision=prec).cpu().numpy()
+        assert np.max(np.abs(out - lam * mu)) < tol * abs(lam)
