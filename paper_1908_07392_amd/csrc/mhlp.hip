@@ -141,7 +141,6 @@ struct mhlp_plan {
     double *fqd = nullptr;    /* [2][KQ_NP] fine-piece scales at alpha (fine_scales) */
     mhlp::TreeDev *tree = nullptr; /* scalar plans: clusters, item lists, moments (tree.h) */
     int tr_waves = 0, tr_split = 1; /* waves per block and blocks per group of far_tree_kernel */
-    double *trpart = nullptr;  /* [2][tr_split][M] partial sums when tr_split > 1 */
     NearParams np{};
     double near_factor = 1.2;
     int64_t part_cap = 0;     /* capacity of part (doubles)                 */
@@ -506,6 +505,9 @@ struct FarArgs {
     double alpha;
     double half_term; /* 0.5 for (1/2 I + D) on an on-surface plan, else 0 */
     double *us, *ud;
+    const double *wg = nullptr;       /* gradients: correction weights [4][nnz][16] ... */
+    int64_t nnz = 0;
+    double *gout[4] = {nullptr, nullptr, nullptr, nullptr}; /* ... and outputs d_x S, d_y S, d_x D, d_y D */
     int64_t Np;
     int32_t pps;      /* panels per source split (blockIdx.y) */
     double *part_s, *part_d; /* [nsplit][M] partial far sums when split */
@@ -848,197 +850,6 @@ __global__ __launch_bounds__(FT_THREADS) void far_eval_mixed(FarArgs A)
 /*   u_i = sum_{j != i} K0(alpha r_ij)/(2 pi) w_j f_j + (w_i/h^2) Wcell f_i    */
 /* Sources are targets; the self pair (r == 0) is skipped in the sum.        */
 /* ------------------------------------------------------------------------ */
-/* ------------------------------------------------------------------------ */
-/* target gradients of the layer potentials, FP64 (off-surface plans)        */
-/*   grad S:  -(1/2pi) sum_j alpha K1(alpha r)/r (x - y_j) w_j sigma_j        */
-/*   grad D:  (1/2pi) sum_j [A n_j - ((x - y_j).n_j)(x - y_j)(alpha^2 K0 + 2A)/r^2] w_j mu_j, */
-/*            A = alpha K1(alpha r)/r                                          */
-/* with the listed near panels replaced by their gradient correction weights. */
-/* ------------------------------------------------------------------------ */
-struct GradArgs {
-    const double *sx, *sy, *sw, *snx, *sny;
-    const double *sigma, *mu;
-    const double *tx, *ty;
-    int64_t M, Np, nnz;
-    const int32_t *nptr, *npan, *perm;
-    const double *wg;  /* [4][nnz][16] */
-    double alpha;
-    int32_t pps;
-    double *part;      /* [4][nsplit][M] when split */
-    double *out[4];    /* d/dx1 S, d/dx2 S, d/dx1 D, d/dx2 D (caller order) */
-    const uint8_t *wcls = nullptr; /* the plan's (wave, panel) fine-piece classes, if any */
-    const double *fq = nullptr;    /* the fine pieces' scales at the plan's alpha */
-};
-
-template <bool GS, bool GD>
-__device__ __forceinline__ void grad_epilogue(const GradArgs &A, int64_t i, const double *acc)
-{
-    double c[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int32_t q = A.nptr[i]; q < A.nptr[i + 1]; ++q) {
-        const int64_t p = A.npan[q];
-        if (p < 0) continue;
-        for (int jj = 0; jj < 16; ++jj) {
-            const int64_t o = 16 * (int64_t)q + jj;
-            if (GS) {
-                const double sg = A.sigma[16 * p + jj];
-                c[0] = fma(A.wg[o], sg, c[0]);
-                c[1] = fma(A.wg[A.nnz * 16 + o], sg, c[1]);
-            }
-            if (GD) {
-                const double m = A.mu[16 * p + jj];
-                c[2] = fma(A.wg[2 * A.nnz * 16 + o], m, c[2]);
-                c[3] = fma(A.wg[3 * A.nnz * 16 + o], m, c[3]);
-            }
-        }
-    }
-    const int64_t o = A.perm ? (int64_t)A.perm[i] : i;
-    if (GS) {
-        A.out[0][o] = fma(-INV_2PI, acc[0], c[0]);
-        A.out[1][o] = fma(-INV_2PI, acc[1], c[1]);
-    }
-    if (GD) {
-        A.out[2][o] = fma(INV_2PI, acc[2], c[2]);
-        A.out[3][o] = fma(INV_2PI, acc[3], c[3]);
-    }
-}
-
-template <bool GS, bool GD>
-__global__ void grad_finalize(GradArgs A, int nsplit)
-{
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= A.M) return;
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int k = 0; k < nsplit; ++k)
-        for (int b = 0; b < 4; ++b)
-            if ((b < 2 && GS) || (b >= 2 && GD)) acc[b] += A.part[((int64_t)b * nsplit + k) * A.M + i];
-    grad_epilogue<GS, GD>(A, i, acc);
-}
-
-/* the 16 sources of one LDS panel (offset l0) against the lane's target for
-   the gradients: PC the fine piece of the plan's class table (-1: z <= 2;
-   KQ_NP: per-pair selection over the three-piece fits) */
-template <bool GS, bool GD, int PC>
-__device__ __forceinline__ void grad_panel_fp64(const GradArgs &A, const FarConst &fc, double x, double y,
-                                                const double *lx, const double *ly, const double *lq,
-                                                const double *ldx, const double *ldy, int l0, double &sx,
-                                                double &sy, double &dx, double &dy)
-{
-    constexpr int K = PC < 0 || PC >= KQ_NP ? 0 : PC;
-    const FarTab T = far_table();
-    double qa, qk;
-    fine_q<K>(A.fq, qa, qk);
-#pragma unroll 1
-    for (int s = 0; s < 16; s += 2) {
-        const int l0s = l0 + s, l1 = l0s + 1;
-        const double ex0 = x - lx[l0s], ey0 = y - ly[l0s];
-        const double ex1 = x - lx[l1], ey1 = y - ly[l1];
-        const double r20 = fma(ex0, ex0, ey0 * ey0), r21 = fma(ex1, ex1, ey1 * ey1);
-        K01 o0, o1; /* ak1r holds K1(z)/r; the staged densities carry alpha */
-        if constexpr (PC >= KQ_NP)
-            k01_far2<GD, true, true, true>(T, fc, r20, r21, o0, o1);
-        else
-            k01_far2_fixed<GD, true, PC>(T, fc, qa, qk, r20, r21, o0, o1);
-        if (GS) {
-            const double c0 = o0.ak1r * lq[l0s], c1 = o1.ak1r * lq[l1];
-            sx = fma(c1, ex1, fma(c0, ex0, sx));
-            sy = fma(c1, ey1, fma(c0, ey0, sy));
-        }
-        if (GD) {
-            /* (alpha^2 K0 + 2 alpha K1/r) (x-y).d / r^2, alpha from the dipole */
-            const double n0 = fma(ex0, ldx[l0s], ey0 * ldy[l0s]), n1 = fma(ex1, ldx[l1], ey1 * ldy[l1]);
-            const double b0 = n0 * fma(A.alpha, o0.k0, 2.0 * o0.ak1r) * o0.ri2;
-            const double b1 = n1 * fma(A.alpha, o1.k0, 2.0 * o1.ak1r) * o1.ri2;
-            dx = fma(-b1, ex1, fma(o1.ak1r, ldx[l1], fma(-b0, ex0, fma(o0.ak1r, ldx[l0s], dx))));
-            dy = fma(-b1, ey1, fma(o1.ak1r, ldy[l1], fma(-b0, ey0, fma(o0.ak1r, ldy[l0s], dy))));
-        }
-    }
-}
-
-/* Each panel takes the fine piece of the plan's (wave, panel) class table, the
-   one the fused evaluation uses (targets in the same order, waves of 64);
-   lanes past the last target repeat it, as the table assumes. */
-template <bool GS, bool GD, bool SPLIT>
-__global__ __launch_bounds__(FT_THREADS) void far_grad_fp64(GradArgs A)
-{
-    __shared__ double lx[FT_SRC], ly[FT_SRC], lq[FT_SRC], ldx[FT_SRC], ldy[FT_SRC];
-    const int64_t i = blockIdx.x * (int64_t)FT_THREADS + threadIdx.x;
-    const bool valid = i < A.M;
-    const int64_t iv = valid ? i : A.M - 1;
-    const double x = A.tx[iv], y = A.ty[iv];
-    const int64_t pb = SPLIT ? (int64_t)blockIdx.y * A.pps : 0;
-    const int64_t pe = SPLIT ? min(A.Np, pb + A.pps) : A.Np;
-    int32_t k = A.nptr[iv];
-    const int32_t kend = A.nptr[iv + 1];
-    while (k < kend && A.npan[k] >= 0 && A.npan[k] < pb) ++k;
-    int32_t nxt = (k < kend) ? A.npan[k] : INT_MAX;
-    const FarConst fc = far_const(A.alpha);
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint8_t *cls = A.wcls ? A.wcls + ((int64_t)blockIdx.x * (FT_THREADS / 64) + wv) * A.Np : nullptr;
-    double sx = 0.0, sy = 0.0, dx = 0.0, dy = 0.0;
-    for (int64_t base = 16 * pb; base < 16 * pe; base += FT_SRC) {
-        __syncthreads();
-        const int64_t j = base + threadIdx.x;
-        if (j < 16 * pe) {
-            /* alpha goes with the charges and dipoles: the pair evaluates K1(z)/r */
-            const double wj = A.alpha * A.sw[j];
-            lx[threadIdx.x] = A.sx[j];
-            ly[threadIdx.x] = A.sy[j];
-            if (GS) lq[threadIdx.x] = wj * A.sigma[j];
-            if (GD) {
-                const double m = wj * A.mu[j];
-                ldx[threadIdx.x] = m * A.snx[j];
-                ldy[threadIdx.x] = m * A.sny[j];
-            }
-        }
-        __syncthreads();
-        const int32_t p0 = (int32_t)(base / 16);
-        const int npl = (pe - p0) < 16 ? (int)(pe - p0) : 16;
-        for (int pl = 0; pl < npl; ++pl) {
-            if (p0 + pl == nxt) {
-                ++k;
-                nxt = (k < kend) ? A.npan[k] : INT_MAX;
-                continue;
-            }
-            const int pc = cls ? (cls[p0 + pl] & 0x7f) - 1 : KQ_NP;
-            const int l0 = pl * 16;
-            switch (pc) {
-#define MHLP_GRAD_PANEL(PCV)                                                                              \
-    case PCV:                                                                                              \
-        grad_panel_fp64<GS, GD, PCV>(A, fc, x, y, lx, ly, lq, ldx, ldy, l0, sx, sy, dx, dy);               \
-        break;
-                MHLP_GRAD_PANEL(-1)
-                MHLP_GRAD_PANEL(0)
-                MHLP_GRAD_PANEL(1)
-                MHLP_GRAD_PANEL(2)
-                MHLP_GRAD_PANEL(3)
-                MHLP_GRAD_PANEL(4)
-                MHLP_GRAD_PANEL(5)
-                MHLP_GRAD_PANEL(6)
-                MHLP_GRAD_PANEL(7)
-                MHLP_GRAD_PANEL(8)
-                MHLP_GRAD_PANEL(9)
-                MHLP_GRAD_PANEL(10)
-                MHLP_GRAD_PANEL(11)
-                MHLP_GRAD_PANEL(12)
-                MHLP_GRAD_PANEL(13)
-                MHLP_GRAD_PANEL(14)
-#undef MHLP_GRAD_PANEL
-            default:
-                grad_panel_fp64<GS, GD, KQ_NP>(A, fc, x, y, lx, ly, lq, ldx, ldy, l0, sx, sy, dx, dy);
-            }
-        }
-    }
-    if (!valid) return;
-    const double acc[4] = {sx, sy, dx, dy};
-    if (SPLIT) {
-        const int ns = gridDim.y;
-        for (int b = 0; b < 4; ++b)
-            if ((b < 2 && GS) || (b >= 2 && GD)) A.part[((int64_t)b * ns + blockIdx.y) * A.M + i] = acc[b];
-    } else {
-        grad_epilogue<GS, GD>(A, i, acc);
-    }
-}
-
 /* ------------------------------------------------------------------------ */
 /* modified-Stokes double layer, FP64 (stokes plans)                         */
 /*   u_i(x) = sum_j D_ij(x, y_j) w_j mu_j,                                     */
@@ -2779,13 +2590,13 @@ extern "C" mhlp_status mhlp_plan_destroy(mhlp_plan *P)
     if (P->cap_stream) (void)hipStreamDestroy(P->cap_stream);
     void *ptrs[] = {P->near_ptr, P->near_panel, P->near_tgt, P->near_ts, P->wslp,  P->wdlp,    P->ws,
                     P->hdev,     P->part,       P->gdev,     P->perm,    P->wgrad, P->wstk,    P->stk_flux,
-                    P->wstkg,    P->sym_tiles,  P->sym_p1,   P->sym_p2,  P->sym_bits, P->wcls, P->trpart,
-                    P->fqd};
+                    P->wstkg,    P->sym_tiles,  P->sym_p1,   P->sym_p2,  P->sym_bits, P->wcls, P->fqd};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     delete P->fmm;
     if (P->tree) {
-        void *tp[] = {P->tree->cc, P->tree->rmin, P->tree->mom, P->tree->st, P->tree->items, P->tree->cnt, P->tree->order};
+        void *tp[] = {P->tree->cc, P->tree->rmin, P->tree->mom, P->tree->st, P->tree->items, P->tree->cnt, P->tree->order,
+                      P->tree->part};
         for (void *p : tp)
             if (p) (void)hipFree(p);
         delete P->tree;
@@ -2837,7 +2648,7 @@ static mhlp_status tree_setup(mhlp_plan *P, hipStream_t st)
     }
     TRY(dalloc(&T.cc, 2 * T.ncl));
     TRY(dalloc(&T.rmin, mhlp::TR_RM * T.ncl));
-    TRY(dalloc(&T.mom, T.ncl * mhlp::tr_stride(2)));
+    TRY(dalloc(&T.mom, T.ncl * mhlp::tr_stride(P->onsurf ? 2 : 4)));
     TRY(dalloc(&T.st, 48 * Np));
     TRY(dalloc(&T.items, G * Np));
     TRY(dalloc(&T.cnt, G));
@@ -2860,7 +2671,7 @@ static mhlp_status tree_setup(mhlp_plan *P, hipStream_t st)
         P->tr_waves = 8, P->tr_split = 8, T.cut = 2;
     else
         P->tr_waves = 8, P->tr_split = 16, T.cut = 3;
-    if (P->tr_split > 1) TRY(dalloc(&P->trpart, 2 * (int64_t)P->tr_split * M));
+    if (P->tr_split > 1) TRY(dalloc(&T.part, (P->onsurf ? 2 : 4) * (int64_t)P->tr_split * M));
     mhlp::tree_clusters_kernel<<<nblocks(T.ncl, 4), 256, 0, st>>>(T, g->soa, g->soa + g->N, g->ph, P->alpha,
                                                                   P->near_factor);
     mhlp::tree_lists_kernel<<<nblocks(G, 4), 256, 0, st>>>(T, P->tx, P->ty, M, g->soa, g->soa + g->N, g->ph,
@@ -3136,28 +2947,34 @@ extern "C" mhlp_status mhlp_plan_info(const mhlp_plan *P, int64_t *n_targets, in
 /* ------------------------------------------------------------------------ */
 /* evaluation                                                                */
 /* ------------------------------------------------------------------------ */
-template <bool SLP, bool DLP>
-static void launch_far_t(FarArgs A, const mhlp_plan *P, int32_t precision, hipStream_t st)
+/* The launches of one far sum by cluster expansions: Op what it evaluates,
+   <SLP, DLP, GRAD> the moments it reads. */
+template <class Op, bool SLP, bool DLP, bool GRAD>
+static void launch_tree(const FarArgs &A, const mhlp_plan *P, hipStream_t st)
 {
-    int nsplit;
+    const mhlp::TreeDev &T = *P->tree;
+    mhlp::tree_moments_kernel<SLP, DLP, GRAD>
+        <<<dim3(nblocks(A.Np, 16), (unsigned)T.nlev, mhlp::TR_GROUPS), 256, 0, st>>>(A, T);
+    mhlp::far_tree_kernel<Op>
+        <<<dim3(nblocks(A.M, 64), (unsigned)P->tr_split), 64 * P->tr_waves, 0, st>>>(A, T);
+    if (P->tr_split > 1)
+        mhlp::tree_finalize<Op><<<dim3(nblocks(A.M, 64), (unsigned)Op::NF), 64, 0, st>>>(A, T, P->tr_split);
+}
+
+template <bool SLP, bool DLP>
+static void launch_far_t(const FarArgs &A, const mhlp_plan *P, int32_t precision, hipStream_t st)
+{
     if (precision == MHLP_FP64) {
-        const mhlp::TreeDev &T = *P->tree;
-        nsplit = P->tr_split;
-        A.part_s = P->trpart;
-        mhlp::tree_moments_kernel<SLP, DLP>
-            <<<dim3(nblocks(A.Np, 16), (unsigned)T.nlev, mhlp::TR_GROUPS), 256, 0, st>>>(A, T);
-        A.part_d = P->trpart + (int64_t)nsplit * A.M;
-        mhlp::far_tree_kernel<SLP, DLP>
-            <<<dim3(nblocks(A.M, 64), (unsigned)nsplit), 64 * P->tr_waves, 0, st>>>(A, T);
-    } else {
-        nsplit = P->nsplit;
-        const dim3 grid(nblocks(A.M, FT_THREADS), (unsigned)nsplit);
-        if (nsplit <= 1)
-            far_eval_mixed<SLP, DLP, false><<<grid, FT_THREADS, 0, st>>>(A);
-        else
-            far_eval_mixed<SLP, DLP, true><<<grid, FT_THREADS, 0, st>>>(A);
+        launch_tree<mhlp::TreePot<SLP, DLP>, SLP, DLP, false>(A, P, st);
+        return;
     }
-    if (nsplit <= 1) return;
+    const int nsplit = P->nsplit;
+    const dim3 grid(nblocks(A.M, FT_THREADS), (unsigned)nsplit);
+    if (nsplit <= 1) {
+        far_eval_mixed<SLP, DLP, false><<<grid, FT_THREADS, 0, st>>>(A);
+        return;
+    }
+    far_eval_mixed<SLP, DLP, true><<<grid, FT_THREADS, 0, st>>>(A);
     if (A.M <= FZ_SHORT)
         far_finalize<SLP, DLP, FZ_L><<<nblocks(A.M, FZ_TG), FZ_TG * FZ_L, 0, st>>>(A, nsplit);
     else
@@ -3399,18 +3216,6 @@ static mhlp_status ensure_grad_weights(mhlp_plan *P, hipStream_t st)
     return MHLP_OK;
 }
 
-template <bool GS, bool GD>
-static void launch_grad_t(const GradArgs &A, int nsplit, hipStream_t st)
-{
-    const unsigned nb = nblocks(A.M, FT_THREADS);
-    if (nsplit <= 1) {
-        far_grad_fp64<GS, GD, false><<<nb, FT_THREADS, 0, st>>>(A);
-        return;
-    }
-    far_grad_fp64<GS, GD, true><<<dim3(nb, nsplit), FT_THREADS, 0, st>>>(A);
-    grad_finalize<GS, GD><<<nblocks(A.M, 256), 256, 0, st>>>(A, nsplit);
-}
-
 extern "C" mhlp_status mhlp_eval_grad(const mhlp_plan *Pc, const double *sigma, const double *mu, double *gs_x,
                                       double *gs_y, double *gd_x, double *gd_y, void *stream)
 {
@@ -3424,39 +3229,17 @@ extern "C" mhlp_status mhlp_eval_grad(const mhlp_plan *Pc, const double *sigma, 
     mhlp_plan *P = const_cast<mhlp_plan *>(Pc); /* gradient weights are built on first use */
     hipStream_t st = (hipStream_t)stream;
     TRY(ensure_grad_weights(P, st));
-    const mhlp_geometry *g = P->g;
-    GradArgs A;
-    A.sx = g->soa;
-    A.sy = g->soa + g->N;
-    A.sw = g->w;
-    A.snx = g->nx;
-    A.sny = g->ny;
-    A.sigma = sigma;
-    A.mu = mu;
-    A.tx = P->tx;
-    A.ty = P->ty;
-    A.M = P->M;
-    A.Np = g->Np;
-    A.nnz = P->nnz;
-    A.nptr = P->near_ptr;
-    A.npan = P->near_panel;
-    A.perm = P->perm;
+    FarArgs A = far_args(P, sigma, mu, nullptr, nullptr, 0.0, nullptr, 0);
     A.wg = P->wgrad;
-    A.alpha = P->alpha;
-    A.pps = P->pps;
-    A.part = P->part;
-    A.wcls = P->wcls;
-    A.fq = P->fqd;
-    A.out[0] = gs_x;
-    A.out[1] = gs_y;
-    A.out[2] = gd_x;
-    A.out[3] = gd_y;
+    A.nnz = P->nnz;
+    double *out[4] = {gs_x, gs_y, gd_x, gd_y};
+    for (int f = 0; f < 4; ++f) A.gout[f] = out[f];
     if (gs && gd)
-        launch_grad_t<true, true>(A, P->nsplit, st);
+        launch_tree<mhlp::TreeGrad<true, true>, true, true, true>(A, P, st);
     else if (gs)
-        launch_grad_t<true, false>(A, P->nsplit, st);
+        launch_tree<mhlp::TreeGrad<true, false>, true, false, true>(A, P, st);
     else
-        launch_grad_t<false, true>(A, P->nsplit, st);
+        launch_tree<mhlp::TreeGrad<false, true>, false, true, true>(A, P, st);
     HIPCHECK(hipGetLastError());
     return MHLP_OK;
 }

@@ -28,7 +28,8 @@ namespace mhlp {
 
 constexpr int TR_LEV = 5;                    /* cluster levels: 1, 2, 4, 8, 16 panels */
 constexpr int TR_PMIN = 8, TR_PSTEP = 2, TR_NP = 13, TR_PMAX = TR_PMIN + TR_PSTEP * (TR_NP - 1);
-constexpr int TR_ROWS = TR_PMAX + 1;         /* orders 0..TR_PMAX of a moment table */
+constexpr int TR_GRAD = 2;                   /* orders a gradient takes beyond the potential's */
+constexpr int TR_ROWS = TR_PMAX + TR_GRAD + 1; /* orders of a moment table */
 constexpr int TR_RM = 16;                    /* distances kept per cluster: TR_NP orders, the underflow's last */
 /* doubles of a cluster's moment table: rows of 2 NF values, padded to the 32 doubles of a row load */
 constexpr int tr_stride(int nf) { return (TR_ROWS * 2 * nf + 31) / 32 * 32; }
@@ -49,6 +50,7 @@ struct TreeDev {
     double *st = nullptr;                    /* staged sources [Np][3][16]: w sigma, alpha w mu n_x, alpha w mu n_y */
     uint2 *items = nullptr;                  /* [groups][Np]: direct items from the front, expansions from the back */
     int2 *cnt = nullptr;                     /* [groups]: their numbers */
+    double *part = nullptr;                  /* [fields][blocks per group][M] sums of split groups */
     int32_t *order = nullptr;                /* [groups] launch order: the groups with the most work first */
 };
 
@@ -124,6 +126,13 @@ __device__ __forceinline__ int tree_level_of(const TreeDev &T, int64_t c)
     int k = 0;
     while (k + 1 < T.nlev && c >= T.off[k + 1]) ++k;
     return k;
+}
+
+__device__ __forceinline__ void tree_panels_of(const TreeDev &T, int64_t c, int64_t &p0, int64_t &p1)
+{
+    const int k = tree_level_of(T, c);
+    p0 = (c - T.off[k]) << k;
+    p1 = min(T.Np, p0 + (1 << k));
 }
 
 /* plan time: centre (of the bounding box), and the distances rmin of each
@@ -290,7 +299,6 @@ __global__ __launch_bounds__(1024) void tree_order_kernel(TreeDev T, int64_t G)
    fixed tree.  Latency bound (config 2: 240 blocks, 14 MFLOP): the split over
    orders keeps a block at three short rounds. */
 constexpr int TR_NG = 12, TR_GROUPS = (TR_ROWS + TR_NG - 1) / TR_NG;
-constexpr int TR_RO = 4;   /* orders per LDS round */
 constexpr int TR_PAD = 17; /* LDS row of a panel's 16 sources */
 
 template <int N0, int CNT>
@@ -329,12 +337,125 @@ __device__ __forceinline__ void tree_regular(double wr, double wi, double q, dou
     br[CNT - 1] *= pr;
 }
 
-template <bool SLP, bool DLP, int Z>
+/* B_n is kept for n = N0 - H .. N0 + TR_NG - 1 + H: the potential of a dipole
+   takes the neighbours of order n (H = 1), its gradient the next ones too */
+template <bool GRAD, int Z>
+struct TreeB {
+    static constexpr int H = GRAD ? 2 : 1, N0 = Z * TR_NG, LO = N0 < H ? 0 : N0 - H, CNT = N0 + TR_NG + H - LO;
+    double br[CNT], bi[CNT];
+    /* M_n (n >= 0, without the factor 2 of n > 0) of a unit charge, and of the dipole (ex, ey)/alpha */
+    template <int N>
+    __device__ __forceinline__ void dipole(double ex, double ey, double &re, double &im) const
+    {
+        constexpr int b = N - LO;
+        if constexpr (N == 0) {
+            re = fma(ex, br[1], -ey * bi[1]);
+            im = 0.0;
+        } else {
+            re = 0.5 * fma(ex, br[b - 1] + br[b + 1], ey * (bi[b - 1] - bi[b + 1]));
+            im = 0.5 * fma(ex, bi[b - 1] + bi[b + 1], ey * (br[b + 1] - br[b - 1]));
+        }
+    }
+};
+
+/* row n of one layer: the potential's (2 Re M, -2 Im M), or the same of its x
+   and y derivatives: (d_x + i d_y) sum_n M_n K_n e^{i n theta} =
+   -alpha sum_n M_n K_{n+1} e^{i (n+1) theta} over all n, M_{-n} = conj M_n. */
+template <bool GRAD, int N, class M>
+__device__ __forceinline__ void tree_row_values(const M &m, double alpha, double (*v)[16 * TR_PAD], int at)
+{
+    double a, b;
+    if constexpr (!GRAD) {
+        m.template at<N>(a, b);
+        v[0][at] = N == 0 ? a : 2.0 * a;
+        v[1][at] = N == 0 ? 0.0 : -2.0 * b;
+    } else {
+        double c, d;
+        m.template at<N + 1>(c, d);
+        if constexpr (N == 0) {
+            v[0][at] = -alpha * c;
+            v[1][at] = 0.0;
+            v[2][at] = alpha * d;
+            v[3][at] = 0.0;
+        } else {
+            m.template at<N - 1>(a, b);
+            v[0][at] = -alpha * (a + c);
+            v[1][at] = alpha * (b + d);
+            v[2][at] = -alpha * (b - d);
+            v[3][at] = -alpha * (a - c);
+        }
+    }
+}
+
+template <class B>
+struct TreeCharge {
+    const B &b;
+    double q;
+    template <int N>
+    __device__ __forceinline__ void at(double &re, double &im) const
+    {
+        re = q * b.br[N - B::LO];
+        im = q * b.bi[N - B::LO];
+    }
+};
+template <class B>
+struct TreeDipole {
+    const B &b;
+    double ex, ey;
+    template <int N>
+    __device__ __forceinline__ void at(double &re, double &im) const
+    {
+        b.template dipole<N>(ex, ey, re, im);
+    }
+};
+
+template <bool SLP, bool DLP, bool GRAD, int Z, int R, class B>
+__device__ __forceinline__ void tree_moments_rounds(const TreeDev &T, int k, int64_t p0, const B &b, double alpha,
+                                                    double q, double ex, double ey, double (*buf)[16 * TR_PAD])
+{
+    constexpr int NL = GRAD ? 4 : 2, NV = NL * ((SLP ? 1 : 0) + (DLP ? 1 : 0)), RO = NV > 4 ? 2 : 4; /* orders a round */
+    constexpr int N = Z * TR_NG + R;
+    if constexpr (R < TR_NG && N < TR_ROWS) {
+        const int t = threadIdx.x, at = (t >> 4) * TR_PAD + (t & 15), pp = t & 15;
+        const TreeCharge<B> mc{b, q};
+        const TreeDipole<B> md{b, ex, ey};
+        double(*bd)[16 * TR_PAD] = buf + (SLP ? NL : 0);
+        if (SLP) tree_row_values<GRAD, N>(mc, alpha, buf, at);
+        if (DLP) tree_row_values<GRAD, N>(md, alpha, bd, at);
+        if (SLP) tree_row_values<GRAD, N + 1>(mc, alpha, buf + NV, at);
+        if (DLP) tree_row_values<GRAD, N + 1>(md, alpha, bd + NV, at);
+        if constexpr (RO > 2) {
+            if (SLP) tree_row_values<GRAD, N + 2>(mc, alpha, buf + 2 * NV, at);
+            if (DLP) tree_row_values<GRAD, N + 2>(md, alpha, bd + 2 * NV, at);
+            if (SLP) tree_row_values<GRAD, N + 3>(mc, alpha, buf + 3 * NV, at);
+            if (DLP) tree_row_values<GRAD, N + 3>(md, alpha, bd + 3 * NV, at);
+        }
+        __syncthreads();
+        const int cb = t >> 4;
+        if (cb < RO * NV) {
+            const double *row = buf[cb] + pp * TR_PAD;
+            double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+            for (int l = 0; l < 16; l += 2) {
+                s0 += row[l];
+                s1 += row[l + 1];
+            }
+            double s = s0 + s1;
+            for (int o = 1; o < (1 << k); o <<= 1) s += __shfl_xor(s, o);
+            const int n = N + cb / NV;
+            const int64_t p = p0 + pp;
+            if ((pp & ((1 << k) - 1)) == 0 && p < T.Np && n < TR_ROWS)
+                T.mom[(T.off[k] + (p >> k)) * tr_stride(NV / 2) + n * NV + cb % NV] = s;
+        }
+        __syncthreads();
+        tree_moments_rounds<SLP, DLP, GRAD, Z, R + RO>(T, k, p0, b, alpha, q, ex, ey, buf);
+    }
+}
+
+template <bool SLP, bool DLP, bool GRAD, int Z>
 __device__ __forceinline__ void tree_moments_body(const FarArgs &A, const TreeDev &T, const double *mu,
                                                   double (*buf)[16 * TR_PAD])
 {
-    constexpr int NV = (SLP ? 2 : 0) + (DLP ? 2 : 0), N0 = Z * TR_NG;
-    constexpr int LO = N0 == 0 ? 0 : N0 - 1, CNT = N0 + TR_NG - LO + 1; /* orders N0 - 1 .. N0 + TR_NG */
     const int k = blockIdx.y, t = threadIdx.x;
     const int64_t p0 = (int64_t)blockIdx.x * 16, j = 16 * p0 + t;
     const bool have = j < A.N;
@@ -351,7 +472,7 @@ __device__ __forceinline__ void tree_moments_body(const FarArgs &A, const TreeDe
     }
     if (Z == 0 && k == 0 && have) {
         double *s = T.st + (j >> 4) * 48 + (j & 15);
-        if (SLP) s[0] = q;
+        if (SLP) s[0] = GRAD ? A.alpha * q : q; /* a gradient pair evaluates K1(z)/r of both */
         if (DLP) {
             s[16] = ex;
             s[32] = ey;
@@ -361,68 +482,22 @@ __device__ __forceinline__ void tree_moments_body(const FarArgs &A, const TreeDe
     const bool live = T.rmin[TR_RM * c + TR_NP - 1] < INFINITY;
     if (__syncthreads_or(live ? 1 : 0) == 0) return;
     const double ah = 0.5 * A.alpha, wr = live ? ah * dx : 0.0, wi = live ? -ah * dy : 0.0;
-    double br[CNT], bi[CNT];
-    tree_regular<LO, CNT>(wr, wi, fma(wr, wr, wi * wi), br, bi);
-    const int cb = t >> 4, pp = t & 15;
-#pragma unroll
-    for (int r = 0; r < TR_NG; r += TR_RO) {
-        if (N0 + r > TR_PMAX) break;
-#pragma unroll
-        for (int o = 0; o < TR_RO; ++o) {
-            const int n = N0 + r + o, b = n - LO; /* compile-time */
-            const double f = n == 0 ? 1.0 : 2.0;
-            int v = o * NV;
-            const int at = (t >> 4) * TR_PAD + (t & 15);
-            if (SLP) {
-                buf[v++][at] = f * q * br[b];
-                buf[v++][at] = -f * q * bi[b];
-            }
-            if (DLP) {
-                /* ex, ey carry alpha: the factor is (2 - delta)/2 */
-                double re, im;
-                if (n == 0) {
-                    re = fma(ex, br[b + 1], -ey * bi[b + 1]);
-                    im = 0.0;
-                } else {
-                    const int bm = b > 0 ? b - 1 : 0;
-                    re = fma(ex, br[bm] + br[b + 1], ey * (bi[bm] - bi[b + 1]));
-                    im = fma(ex, bi[bm] + bi[b + 1], ey * (br[b + 1] - br[bm]));
-                }
-                buf[v++][at] = re;
-                buf[v++][at] = -im;
-            }
-        }
-        __syncthreads();
-        if (cb < TR_RO * NV) {
-            const double *row = buf[cb] + pp * TR_PAD;
-            double s0 = 0.0, s1 = 0.0;
-#pragma unroll
-            for (int l = 0; l < 16; l += 2) {
-                s0 += row[l];
-                s1 += row[l + 1];
-            }
-            double s = s0 + s1;
-            for (int o = 1; o < (1 << k); o <<= 1) s += __shfl_xor(s, o);
-            const int n = N0 + r + cb / NV;
-            const int64_t p = p0 + pp;
-            if ((pp & ((1 << k) - 1)) == 0 && p < T.Np && n <= TR_PMAX)
-                T.mom[(T.off[k] + (p >> k)) * tr_stride(NV / 2) + n * NV + cb % NV] = s;
-        }
-        __syncthreads();
-    }
+    TreeB<GRAD, Z> b;
+    tree_regular<TreeB<GRAD, Z>::LO, TreeB<GRAD, Z>::CNT>(wr, wi, fma(wr, wr, wi * wi), b.br, b.bi);
+    tree_moments_rounds<SLP, DLP, GRAD, Z, 0>(T, k, p0, b, A.alpha, q, ex, ey, buf);
 }
 
-template <bool SLP, bool DLP>
+template <bool SLP, bool DLP, bool GRAD>
 __global__ __launch_bounds__(256) void tree_moments_kernel(FarArgs A, TreeDev T)
 {
-    constexpr int NV = (SLP ? 2 : 0) + (DLP ? 2 : 0);
-    __shared__ double buf[TR_RO * NV][16 * TR_PAD];
+    constexpr int NV = (GRAD ? 4 : 2) * ((SLP ? 1 : 0) + (DLP ? 1 : 0));
+    __shared__ double buf[(NV > 4 ? 2 : 4) * NV][16 * TR_PAD];
     const double *mu;
     if (!far_density(A, mu)) return;
     switch (blockIdx.z) {
-    case 0: tree_moments_body<SLP, DLP, 0>(A, T, mu, buf); break;
-    case 1: tree_moments_body<SLP, DLP, 1>(A, T, mu, buf); break;
-    default: tree_moments_body<SLP, DLP, 2>(A, T, mu, buf); break;
+    case 0: tree_moments_body<SLP, DLP, GRAD, 0>(A, T, mu, buf); break;
+    case 1: tree_moments_body<SLP, DLP, GRAD, 1>(A, T, mu, buf); break;
+    default: tree_moments_body<SLP, DLP, GRAD, 2>(A, T, mu, buf); break;
     }
 }
 static_assert(TR_GROUPS == 3, "tree_moments_kernel has a case for each group of orders");
@@ -496,7 +571,7 @@ __device__ __forceinline__ void tree_rows(int order, const double2 *m, double c2
                                           double k, double cp, double cn, double sp, double sn, double (&f0)[NF],
                                           double (&f1)[NF])
 {
-    if constexpr (N < TR_PMAX) {
+    if constexpr (N + 1 < TR_ROWS) {
         if (N > order) return;
         tree_row<NF, N, 0>(m, k * cn, k * sn, f0, f1);
         km = fma(b, k, km);
@@ -553,33 +628,141 @@ __device__ __forceinline__ bool tree_bad(const TreeDev &T, int64_t p0, int64_t p
     return __ballot(!(s == 0.0)) != 0;
 }
 
-/* staged sources s0..s1-1 of one panel against the lane's target, in piece PC;
-   sources come through the scalar cache, two at a time */
-template <bool SLP, bool DLP, int PC>
-__device__ __forceinline__ void tree_panel(const FarArgs &A, const FarConst &fc, const TreeDev &D, int64_t p, int s0,
-                                           int s1, double x, double y, double &accs, double &accd)
-{
-    const MHLP_CAS double *sx = (const MHLP_CAS double *)A.sx + 16 * p;
-    const MHLP_CAS double *sy = (const MHLP_CAS double *)A.sy + 16 * p;
-    const MHLP_CAS double *st = (const MHLP_CAS double *)D.st + 48 * p;
-    constexpr int K = PC < 0 || PC >= KQ_NP ? 0 : PC;
-    const FarTab T = far_table();
-    double qa, qk;
-    fine_q<K>(A.fq, qa, qk);
+/* What a far sum evaluates.  NF fields, EXTRA orders beyond the list's;
+   panel<PC>: staged sources s0..s1-1 of panel p against the lane's target in
+   piece PC (-1: z <= 2; KQ_NP: per pair), added to f (sources come through the
+   scalar cache, two at a time); near: the correction of node jj of the listed
+   pair q; store: field f of target i.  The sums carry no 1/(2 pi) until they
+   leave the wave. */
+template <bool SLP, bool DLP>
+struct TreePot {
+    static constexpr int NF = (SLP ? 1 : 0) + (DLP ? 1 : 0), EXTRA = 0;
+    template <int PC>
+    static __device__ __forceinline__ void panel(const FarArgs &A, const FarConst &fc, const TreeDev &D, int64_t p,
+                                                 int s0, int s1, double x, double y, double (&f)[NF])
+    {
+        constexpr int K = PC < 0 || PC >= KQ_NP ? 0 : PC;
+        const MHLP_CAS double *sx = (const MHLP_CAS double *)A.sx + 16 * p;
+        const MHLP_CAS double *sy = (const MHLP_CAS double *)A.sy + 16 * p;
+        const MHLP_CAS double *st = (const MHLP_CAS double *)D.st + 48 * p;
+        const FarTab T = far_table();
+        double qa, qk;
+        fine_q<K>(A.fq, qa, qk);
 #pragma unroll 1
-    for (int s = s0; s < s1; s += 2) {
-        const double ex0 = x - sx[s], ey0 = y - sy[s];
-        const double ex1 = x - sx[s + 1], ey1 = y - sy[s + 1];
-        const double r20 = fma(ex0, ex0, ey0 * ey0), r21 = fma(ex1, ex1, ey1 * ey1);
-        K01 o0, o1;
-        if constexpr (PC >= KQ_NP)
-            k01_far2<SLP, DLP, true, true>(T, fc, r20, r21, o0, o1);
-        else
-            k01_far2_fixed<SLP, DLP, PC>(T, fc, qa, qk, r20, r21, o0, o1);
-        if (SLP) accs = fma(o1.k0, st[s + 1], fma(o0.k0, st[s], accs));
-        if (DLP)
-            accd = fma(o1.ak1r, fma(ex1, st[16 + s + 1], ey1 * st[32 + s + 1]),
-                       fma(o0.ak1r, fma(ex0, st[16 + s], ey0 * st[32 + s]), accd));
+        for (int s = s0; s < s1; s += 2) {
+            const double ex0 = x - sx[s], ey0 = y - sy[s];
+            const double ex1 = x - sx[s + 1], ey1 = y - sy[s + 1];
+            const double r20 = fma(ex0, ex0, ey0 * ey0), r21 = fma(ex1, ex1, ey1 * ey1);
+            K01 o0, o1;
+            if constexpr (PC >= KQ_NP)
+                k01_far2<SLP, DLP, true, true>(T, fc, r20, r21, o0, o1);
+            else
+                k01_far2_fixed<SLP, DLP, PC>(T, fc, qa, qk, r20, r21, o0, o1);
+            if (SLP) f[0] = fma(o1.k0, st[s + 1], fma(o0.k0, st[s], f[0]));
+            if (DLP)
+                f[NF - 1] = fma(o1.ak1r, fma(ex1, st[16 + s + 1], ey1 * st[32 + s + 1]),
+                                fma(o0.ak1r, fma(ex0, st[16 + s], ey0 * st[32 + s]), f[NF - 1]));
+        }
+    }
+    static __device__ __forceinline__ void near(const FarArgs &A, const double *mu, int64_t q, int64_t p, int jj,
+                                                double (&n)[NF])
+    {
+        if (SLP) n[0] = fma(A.wsl[16 * q + jj], A.sigma[16 * p + jj], n[0]);
+        if (DLP) n[NF - 1] = fma(A.wdl[16 * q + jj], mu[16 * p + jj], n[NF - 1]);
+    }
+    static __device__ __forceinline__ void store(const FarArgs &A, const double *mu, int64_t i, int f, double v)
+    {
+        const int64_t o = A.perm ? (int64_t)A.perm[i] : i;
+        if (SLP && f == 0) {
+            A.us[o] = v;
+        } else {
+            if (A.half_term != 0.0) v = fma(A.half_term, mu[i], v);
+            A.ud[o] = v;
+        }
+    }
+    static __device__ __forceinline__ bool bad(const TreeDev &T, int64_t p0, int64_t p1)
+    {
+        return tree_bad<SLP, DLP>(T, p0, p1);
+    }
+};
+
+/* the target gradients: d_x S, d_y S, d_x D, d_y D (without the absent layer's) */
+template <bool SLP, bool DLP>
+struct TreeGrad {
+    static constexpr int NF = (SLP ? 2 : 0) + (DLP ? 2 : 0), EXTRA = TR_GRAD;
+    template <int PC>
+    static __device__ __forceinline__ void panel(const FarArgs &A, const FarConst &fc, const TreeDev &D, int64_t p,
+                                                 int s0, int s1, double x, double y, double (&f)[NF])
+    {
+        constexpr int K = PC < 0 || PC >= KQ_NP ? 0 : PC;
+        const MHLP_CAS double *sx = (const MHLP_CAS double *)A.sx + 16 * p;
+        const MHLP_CAS double *sy = (const MHLP_CAS double *)A.sy + 16 * p;
+        const MHLP_CAS double *st = (const MHLP_CAS double *)D.st + 48 * p;
+        const FarTab T = far_table();
+        double qa, qk;
+        fine_q<K>(A.fq, qa, qk);
+#pragma unroll 1
+        for (int s = s0; s < s1; s += 2) {
+            const double ex0 = x - sx[s], ey0 = y - sy[s];
+            const double ex1 = x - sx[s + 1], ey1 = y - sy[s + 1];
+            const double r20 = fma(ex0, ex0, ey0 * ey0), r21 = fma(ex1, ex1, ey1 * ey1);
+            K01 o0, o1; /* ak1r holds K1(z)/r; the staged charges and dipoles carry alpha */
+            if constexpr (PC >= KQ_NP)
+                k01_far2<DLP, true, true, true>(T, fc, r20, r21, o0, o1);
+            else
+                k01_far2_fixed<DLP, true, PC>(T, fc, qa, qk, r20, r21, o0, o1);
+            if (SLP) {
+                const double c0 = o0.ak1r * st[s], c1 = o1.ak1r * st[s + 1];
+                f[0] = fma(-c1, ex1, fma(-c0, ex0, f[0]));
+                f[1] = fma(-c1, ey1, fma(-c0, ey0, f[1]));
+            }
+            if (DLP) {
+                /* (alpha^2 K0 + 2 alpha K1/r) (x-y).d / r^2, alpha from the dipole */
+                const double n0 = fma(ex0, st[16 + s], ey0 * st[32 + s]);
+                const double n1 = fma(ex1, st[16 + s + 1], ey1 * st[32 + s + 1]);
+                const double b0 = n0 * fma(A.alpha, o0.k0, 2.0 * o0.ak1r) * o0.ri2;
+                const double b1 = n1 * fma(A.alpha, o1.k0, 2.0 * o1.ak1r) * o1.ri2;
+                double &gx = f[NF - 2], &gy = f[NF - 1];
+                gx = fma(-b1, ex1, fma(o1.ak1r, st[16 + s + 1], fma(-b0, ex0, fma(o0.ak1r, st[16 + s], gx))));
+                gy = fma(-b1, ey1, fma(o1.ak1r, st[32 + s + 1], fma(-b0, ey0, fma(o0.ak1r, st[32 + s], gy))));
+            }
+        }
+    }
+    static __device__ __forceinline__ void near(const FarArgs &A, const double *mu, int64_t q, int64_t p, int jj,
+                                                double (&n)[NF])
+    {
+        const int64_t o = 16 * q + jj, block = 16 * A.nnz;
+        if (SLP) {
+            const double sg = A.sigma[16 * p + jj];
+            n[0] = fma(A.wg[o], sg, n[0]);
+            n[1] = fma(A.wg[block + o], sg, n[1]);
+        }
+        if (DLP) {
+            const double m = mu[16 * p + jj];
+            n[NF - 2] = fma(A.wg[2 * block + o], m, n[NF - 2]);
+            n[NF - 1] = fma(A.wg[3 * block + o], m, n[NF - 1]);
+        }
+    }
+    static __device__ __forceinline__ void store(const FarArgs &A, const double *, int64_t i, int f, double v)
+    {
+        A.gout[SLP ? f : f + 2][A.perm ? (int64_t)A.perm[i] : i] = v;
+    }
+    static __device__ __forceinline__ bool bad(const TreeDev &T, int64_t p0, int64_t p1)
+    {
+        return tree_bad<SLP, DLP>(T, p0, p1);
+    }
+};
+
+template <class Op, class Args>
+__device__ __forceinline__ void tree_panel(int pc, const Args &A, const FarConst &fc, const TreeDev &T, int64_t p,
+                                           int s0, int s1, double x, double y, double (&f)[Op::NF])
+{
+    switch (pc) {
+#define MHLP_TREE_PANEL(PCV) \
+    case PCV: Op::template panel<PCV>(A, fc, T, p, s0, s1, x, y, f); break;
+        MHLP_PC_CASES(MHLP_TREE_PANEL)
+#undef MHLP_TREE_PANEL
+    default: Op::template panel<KQ_NP>(A, fc, T, p, s0, s1, x, y, f);
     }
 }
 
@@ -589,22 +772,22 @@ constexpr int TR_WMAX = 16; /* waves of a block at most */
    groups' work; the waves of the gridDim.y blocks of a group share its items:
    direct ones in units of 16 / 2^cut sources in turn, expansions in equal
    runs, starting from the other end, so that no wave gets more than its share
-   of both.  One block per group: the wave sums are added in wave order with
-   the near corrections, which the waves share by node.  Several: each leaves
-   its sum in slot blockIdx.y for far_finalize.  A cluster whose expansion is
-   not finite (an infinite or NaN density) or whose pairs all underflow with
-   such a density is summed directly, pair by pair.
+   of both, and the near corrections by node.  The wave sums are added
+   in wave order; with several blocks a group they go to slot blockIdx.y for
+   tree_finalize.  A cluster whose expansion is not finite (an infinite or NaN
+   density), or whose pairs all underflow with such a density, is summed
+   directly, pair by pair.
 
    Bound by VALU FP64 (109,314 targets, 4096 sources, alpha = 5: 15.6e3
-   instructions per group against 304e3 for the direct sum of all pairs, 68 us
+   instructions per group against 304e3 for the direct sum of all pairs, 66 us
    against 1.07 ms; alpha = 500, all pairs direct: within 5% of the issue rate).
    Waves per group (tree_setup): four for many groups; up to 128 for few,
    where the longest wave (a direct panel in one wave takes about 20 us) sets
    the time. */
-template <bool SLP, bool DLP>
+template <class Op>
 __global__ __launch_bounds__(64 * TR_WMAX) void far_tree_kernel(FarArgs A, TreeDev T)
 {
-    constexpr int NF = (SLP ? 1 : 0) + (DLP ? 1 : 0);
+    constexpr int NF = Op::NF;
     __shared__ double red[NF][TR_WMAX][64];
     const double *mu;
     if (!far_density(A, mu)) return;
@@ -626,22 +809,18 @@ __global__ __launch_bounds__(64 * TR_WMAX) void far_tree_kernel(FarArgs A, TreeD
     const int nsrc = 16 >> T.cut;
     for (int k = wg; k < (cnt.x << T.cut); k += NW) {
         const uint2 it = items[k >> T.cut];
-        const int s0 = (k & ((1 << T.cut) - 1)) * nsrc, s1 = s0 + nsrc;
+        const int s0 = (k & ((1 << T.cut) - 1)) * nsrc;
         const uint32_t p = __builtin_amdgcn_readfirstlane(it.x), fl = __builtin_amdgcn_readfirstlane(it.y);
         bool listed = false;
         if (fl & TR_NEAR)
             for (int32_t q = k0; q < k1; ++q) listed = listed || A.npan[q] == (int32_t)p;
         if (listed) continue;
-        double ps = 0.0, pd = 0.0;
-        switch ((int)(fl & 31) - 1) {
-#define MHLP_TREE_PANEL(PCV)                                                                               \
-    case PCV: tree_panel<SLP, DLP, PCV>(A, fc, T, p, s0, s1, x, y, ps, pd); break;
-            MHLP_PC_CASES(MHLP_TREE_PANEL)
-#undef MHLP_TREE_PANEL
-        default: tree_panel<SLP, DLP, KQ_NP>(A, fc, T, p, s0, s1, x, y, ps, pd);
-        }
-        if (SLP) acc[0] += ps;
-        if (DLP) acc[NF - 1] += pd;
+        double f[NF];
+#pragma unroll
+        for (int n = 0; n < NF; ++n) f[n] = 0.0;
+        tree_panel<Op>((int)(fl & 31) - 1, A, fc, T, p, s0, s0 + nsrc, x, y, f);
+#pragma unroll
+        for (int n = 0; n < NF; ++n) acc[n] += f[n];
     }
     const int fb = cnt.y * (NW - 1 - wg) / NW, fe = cnt.y * (NW - wg) / NW;
     for (int k = fb; k < fe; ++k) {
@@ -652,61 +831,64 @@ __global__ __launch_bounds__(64 * TR_WMAX) void far_tree_kernel(FarArgs A, TreeD
         if (fl & TR_ZERO) {
 #pragma unroll
             for (int n = 0; n < NF; ++n) f[n] = 0.0;
-            const int lv = tree_level_of(T, c);
-            const int64_t p0 = ((int64_t)c - T.off[lv]) << lv;
-            direct = tree_bad<SLP, DLP>(T, p0, min(T.Np, p0 + (1 << lv)));
+            int64_t p0, p1;
+            tree_panels_of(T, c, p0, p1);
+            direct = Op::bad(T, p0, p1);
         } else {
-            tree_expand<NF>(fc, A.fq, T, c, (int)(fl & 31) - 1, (int)(fl >> 8) & 63, x, y, f);
+            tree_expand<NF>(fc, A.fq, T, c, (int)(fl & 31) - 1, ((int)(fl >> 8) & 63) + Op::EXTRA, x, y, f);
             bool fin = true;
 #pragma unroll
             for (int n = 0; n < NF; ++n) fin = fin && __builtin_isfinite(f[n]);
             direct = __ballot(!fin) != 0;
         }
         if (direct) {
-            const int lv = tree_level_of(T, c);
-            const int64_t p0 = ((int64_t)c - T.off[lv]) << lv, p1 = min(T.Np, p0 + (1 << lv));
-            double ps = 0.0, pd = 0.0;
-            for (int64_t p = p0; p < p1; ++p)
-                tree_panel<SLP, DLP, KQ_NP>(A, fc, T, p, 0, 16, x, y, ps, pd);
-            if (SLP) f[0] = ps;
-            if (DLP) f[NF - 1] = pd;
+#pragma unroll
+            for (int n = 0; n < NF; ++n) f[n] = 0.0;
+            int64_t p0, p1;
+            tree_panels_of(T, c, p0, p1);
+            for (int64_t p = p0; p < p1; ++p) Op::template panel<KQ_NP>(A, fc, T, p, 0, 16, x, y, f);
         }
 #pragma unroll
         for (int n = 0; n < NF; ++n) acc[n] += f[n];
     }
-    if (gridDim.y > 1) {
+    double nr[NF];
 #pragma unroll
-        for (int f = 0; f < NF; ++f) red[f][w][lane] = acc[f];
-        __syncthreads();
-        if (w >= NF || !valid) return;
-        double s = 0.0;
-        for (int v = 0; v < W; ++v) s += red[w][v][lane];
-        ((SLP && w == 0) ? A.part_s : A.part_d)[blockIdx.y * A.M + i] = s;
-        return;
-    }
-    /* near corrections: this wave's nodes of each listed panel */
-    double ns = 0.0, nd = 0.0;
-    for (int32_t q = k0; q < k1; ++q) {
-        const int64_t p = A.npan[q];
-        if (p < 0) continue;
-        for (int jj = w; jj < 16; jj += W) {
-            if (SLP) ns = fma(A.wsl[16 * (int64_t)q + jj], A.sigma[16 * p + jj], ns);
-            if (DLP) nd = fma(A.wdl[16 * (int64_t)q + jj], mu[16 * p + jj], nd);
+    for (int f = 0; f < NF; ++f) nr[f] = 0.0;
+    if (wg < 16)
+        for (int32_t q = k0; q < k1; ++q) {
+            const int64_t p = A.npan[q];
+            if (p < 0) continue;
+            for (int jj = wg; jj < 16; jj += NW) Op::near(A, mu, q, p, jj, nr);
         }
-    }
-    if (SLP) red[0][w][lane] = fma(INV_2PI, acc[0], ns);
-    if (DLP) red[NF - 1][w][lane] = fma(INV_2PI, acc[NF - 1], nd);
+#pragma unroll
+    for (int f = 0; f < NF; ++f) red[f][w][lane] = fma(INV_2PI, acc[f], nr[f]);
     __syncthreads();
-    if (w >= NF || !valid) return;
-    double s = 0.0;
-    for (int v = 0; v < W; ++v) s += red[w][v][lane];
-    const int64_t o = A.perm ? (int64_t)A.perm[i] : i;
-    if (SLP && w == 0) {
-        A.us[o] = s;
-    } else {
-        if (A.half_term != 0.0) s = fma(A.half_term, mu[i], s);
-        A.ud[o] = s;
+    if (!valid) return;
+    for (int f = w; f < NF; f += W) {
+        double s = 0.0;
+        for (int v = 0; v < W; ++v) s += red[f][v][lane];
+        if (gridDim.y > 1)
+            T.part[((int64_t)f * gridDim.y + blockIdx.y) * A.M + i] = s;
+        else
+            Op::store(A, mu, i, f, s);
     }
+}
+
+/* the slots of a group split over several blocks, in order; one thread per
+   target and field */
+template <class Op>
+__global__ __launch_bounds__(64) void tree_finalize(FarArgs A, TreeDev T, int nsplit)
+{
+    const double *mu;
+    if (!far_density(A, mu)) return;
+    const int64_t i = blockIdx.x * (int64_t)64 + threadIdx.x;
+    if (i >= A.M) return;
+    const int f = blockIdx.y;
+    const double *part = T.part + (int64_t)f * nsplit * A.M + i;
+    double s = 0.0;
+#pragma unroll 4
+    for (int k = 0; k < nsplit; ++k) s += part[k * A.M];
+    Op::store(A, mu, i, f, s);
 }
 
 } // namespace mhlp

@@ -114,3 +114,28 @@ def test_tree_onsurface_operator_on_the_circle(panels, alpha):
     for prec, tol in ((mhlp.FP64, 1e-11 if panels > 3 else 1e-6), (mhlp.MIXED, 1e-6)):
         out = mhlp.apply_bie(P, _t(mu), precision=prec).cpu().numpy()
         assert np.max(np.abs(out - lam * mu)) < tol * abs(lam)
+
+
+@pytest.mark.parametrize("panels,m,alpha", [(29, 1, 4.0), (33, 900, 8.0), (64, 5500, 25.0), (31, 11000, 60.0),
+                                            (40, 41000, 3.0), (37, 77000, 12.0)])
+def test_tree_gradients_vs_plain_sums(panels, m, alpha):
+    """Each component against the closed forms, to the potentials' bound times alpha (the size of a derivative)
+    and the dipole's second derivative."""
+    g, tx, ty, sg, mu = _setup(panels, m, panels + m)
+    P = mhlp.Plan(mhlp.Geometry(_t(g.node_soa())), alpha, _t(tx), _t(ty))
+    sel = np.unique(np.linspace(0, m - 1, min(m, 400)).astype(int))
+    ex, ey = tx[sel][:, None] - g.x, ty[sel][:, None] - g.y
+    r = np.hypot(ex, ey)
+    k0, k1 = sp.k0(alpha * r), sp.k1(alpha * r)
+    nx, ny = g.normals
+    q, d = g.weights * sg / (2 * np.pi), g.weights * mu / (2 * np.pi)
+    A, f64 = alpha * k1 / r, 3e-14 + 5e-16 * alpha * r
+    B = (ex * nx + ey * ny) * (alpha ** 2 * k0 + 2 * A) / r ** 2
+    gs, gd = mhlp.eval_grad(P, sigma=_t(sg), mu=_t(mu))
+    gs1, gd1 = mhlp.eval_grad(P, sigma=_t(sg))[0], mhlp.eval_grad(P, mu=_t(mu))[1]
+    for u, v in ((gs, gd), (gs1, gd1)):
+        for c, (e, n) in enumerate(((ex, nx), (ey, ny))):
+            bs = (A * r * np.abs(q) * f64).sum(axis=1)
+            bd = ((alpha ** 2 * k0 + 3 * A) * np.abs(d) * f64).sum(axis=1)
+            assert (np.abs(u[c].cpu().numpy()[sel] + (A * e * q).sum(axis=1)) <= bs + 1e-300).all()
+            assert (np.abs(v[c].cpu().numpy()[sel] - ((A * n - B * e) * d).sum(axis=1)) <= bd + 1e-300).all()
