@@ -135,16 +135,16 @@ mhlp_status mhlp_plan_destroy(mhlp_plan *plan);
 mhlp_status mhlp_plan_info(const mhlp_plan *plan, int64_t *n_targets, int64_t *n_sources, int64_t *n_near_pairs,
                            double *alpha);
 
-/* Far-field launch shape.  The mixed-precision far field, the gradients and
-   the stresslet split the direct sum over sources into nsplit ranges of
-   panels evaluated by separate blocks (partial sums added in fixed order, so
-   results do not depend on nsplit beyond rounding); the default aims at about
-   8192 blocks of 256 targets with at least 2 panels per split.  The FP64
-   single and double layers do not use it: each group of 64 targets takes the
-   panels far from it through expansions of clusters of up to 16 panels
-   (truncated below rounding) and the others pair by pair, from lists built
-   with the plan.  set_split may reallocate the plan's partial-sum buffer (it
-   synchronises the device then).
+/* Far-field launch shape.  The mixed-precision far field splits the direct sum
+   over sources into nsplit ranges of panels evaluated by separate blocks
+   (partial sums added in fixed order, so results do not depend on nsplit
+   beyond rounding); the default aims at about 8192 blocks of 256 targets with
+   at least 2 panels per split.  The FP64 launches (potentials, gradients,
+   stresslet) do not use it: each group of 64 targets takes the panels far from
+   it through expansions of clusters of up to 16 panels (truncated below
+   rounding) and the others pair by pair, from lists built with the plan.
+   set_split may reallocate the plan's partial-sum buffer (it synchronises the
+   device then).
    mhlp_plan_autotune times the far evaluation (layers: 1 SLP, 2 DLP, 3 both,
    4 the on-surface BIE operator, 5 the gradients of both, off-surface, 6 the
    stresslet operator of a stokes plan, 7 the stresslet target gradient of an
@@ -154,7 +154,7 @@ mhlp_status mhlp_plan_info(const mhlp_plan *plan, int64_t *n_targets, int64_t *n
    fastest and reports it with its time (host outputs; cand/cand_ms receive up
    to cap candidates and their ms per launch).  Where the FP64 launch does not
    use the split (layers 1-4), FP64 requests time the MIXED launch of the same layers, the one the split
-   serves.  Synchronises the stream.  Errors: MHLP_INVALID_ARG. */
+   serves (layers 5-7 time the same launch for every candidate).  Synchronises the stream.  Errors: MHLP_INVALID_ARG. */
 mhlp_status mhlp_plan_set_split(mhlp_plan *plan, int32_t nsplit);
 mhlp_status mhlp_plan_get_split(const mhlp_plan *plan, int32_t *nsplit);
 mhlp_status mhlp_plan_autotune(mhlp_plan *plan, int32_t layers, int32_t precision, int32_t reps, void *stream,
@@ -194,9 +194,7 @@ mhlp_status mhlp_apply_bie_operator(const mhlp_plan *onsurf, const double *mu, d
      T_ijk = alpha^2 T1 (d_jk r_i + d_ik r_j + d_ij r_k) + alpha^4 T2 r_i r_j r_k
              + alpha^2 T3 d_ik r_j,   r = x - y, n into the domain.
    A stokes plan has the near lists of mhlp_plan_create, 64 stresslet
-   correction weights per near pair (2x2 blocks on the panel's 16 nodes) and,
-   like a scalar plan, one byte per (64 targets, panel) naming the far-field
-   fit that serves those pairs; it
+   correction weights per near pair (2x2 blocks on the panel's 16 nodes); it
    serves only the mhlp_stokes_* calls (the scalar calls reject it and vice
    versa).  Densities and outputs are component-major: mu [2][N] (mu_1 at
    mu[0..N), mu_2 at mu[N..2N)), u [2][M].  FP64 throughout.

@@ -119,27 +119,18 @@ struct mhlp_plan {
     bool stokes = false;      /* modified-Stokes (stresslet) plan: operator on [2][N] densities */
     double *wstk = nullptr;   /* stokes: [4][nnz][16] stresslet weights (D11, D12, D21, D22)   */
     mhlp::FmmTree *fmm = nullptr; /* off-surface scalar plans: FMM far field (mhlp_plan_set_fmm) */
-    /* on-surface stresslet plans up to SYM_NMAX nodes: the far sum with each
-       unordered pair evaluated once (stk_sym_kernel) */
-    int2 *sym_tiles = nullptr;   /* (row block, column chunk) of each tile */
-    int32_t sym_ntiles = 0;
-    double *sym_p1 = nullptr;    /* [column chunks][N] row sums */
-    double *sym_p2 = nullptr;    /* [row blocks][N] column sums */
-    uint32_t *sym_bits = nullptr; /* [N][sym_nw] near panels of each node as bits */
-    int32_t sym_nw = 0;
     double *wstkg = nullptr;  /* stokes, off-surface, built on first use: [8][nnz][16] stresslet
                                  gradient weights, block (2a + l) 2 + j = d u_a/d x_l per mu_j */
-    double *stk_flux = nullptr; /* stokes: device scalar sum_j w_j mu_j.n_j / |Gamma|           */
     double inv_len = 0.0;     /* 1 / |Gamma| */
     int64_t nnz = 0;
     int32_t fill_mismatch = 0;
     int nsplit = 1;           /* source splits of the far field (small M)   */
     int32_t pps = 0;          /* panels per split                           */
     double *part = nullptr;   /* [2][nsplit][M] partial sums ([4][..] off-surface, for gradients) */
-    uint8_t *wcls = nullptr;  /* [M/64 waves][Np] fine piece + 1 of each (wave, panel): mixed precision,
-                                 gradients, stresslet */
-    double *fqd = nullptr;    /* [2][KQ_NP] fine-piece scales at alpha (fine_scales) */
-    mhlp::TreeDev *tree = nullptr; /* scalar plans: clusters, item lists, moments (tree.h) */
+    uint8_t *wcls = nullptr;  /* scalar plans: [M/64 waves][Np] fine piece + 1 of each (wave, panel) for the
+                                 mixed-precision tiles */
+    double *fqd = nullptr;    /* [FINE_SCALES] fine-piece scales and constants at alpha (fine_scales) */
+    mhlp::TreeDev *tree = nullptr; /* clusters, item lists, moments (tree.h) */
     int tr_waves = 0, tr_split = 1; /* waves per block and blocks per group of far_tree_kernel */
     NearParams np{};
     double near_factor = 1.2;
@@ -505,9 +496,11 @@ struct FarArgs {
     double alpha;
     double half_term; /* 0.5 for (1/2 I + D) on an on-surface plan, else 0 */
     double *us, *ud;
-    const double *wg = nullptr;       /* gradients: correction weights [4][nnz][16] ... */
+    /* gradients, stresslet: correction weights [blocks][nnz][16] and the outputs of the fields */
+    const double *wg = nullptr;
     int64_t nnz = 0;
-    double *gout[4] = {nullptr, nullptr, nullptr, nullptr}; /* ... and outputs d_x S, d_y S, d_x D, d_y D */
+    double *gout[4] = {nullptr, nullptr, nullptr, nullptr};
+    double inv_len = 0.0; /* 1/|Gamma| (on-surface stresslet operator) */
     int64_t Np;
     int32_t pps;      /* panels per source split (blockIdx.y) */
     double *part_s, *part_d; /* [nsplit][M] partial far sums when split */
@@ -518,7 +511,7 @@ struct FarArgs {
     const int32_t *perm; /* output index of internal target i (NULL: identity) */
     const double *pcx, *pcy, *prad; /* bounding circle of each panel */
     const uint8_t *wcls = nullptr; /* [M/64 waves][Np] fine piece + 1 of each (wave, panel): mixed precision */
-    const double *fq = nullptr; /* [2][KQ_NP] scales of the fine pieces at the plan's alpha (fine_scales) */
+    const double *fq = nullptr; /* scales of the fine pieces and constants at the plan's alpha (fine_scales) */
 };
 
 
@@ -652,19 +645,6 @@ __device__ __forceinline__ double wave_sum_dpp(double v)
     return __hiloint2double(hi, lo);
 }
 
-/* ---- on-surface stresslet operator, each unordered far pair once ----
-   The A1..A3 of a pair depend on it only through r, so one evaluation serves
-   the term of source j at node i and of source i at node j.  Tiles pair a block of
-   SYM_R = 256 row nodes (16 panels) with a chunk of SYM_C = 16 column nodes
-   (one panel; small tiles keep enough blocks in flight); tile (I, J) exists
-   when the chunk does not start before the block (column panels >= 16 I), and on the block's own chunks only row < column
-   counts.  The row node takes the column terms (unless the column panel is
-   listed near it) into p1[J][i]; each column node takes the row terms (unless
-   the row's panel is listed near the column node), summed over lanes and over
-   waves in order, into p2[I][j].  Every pair of distinct
-   nodes is evaluated in exactly one tile. */
-constexpr int SYM_R = 256, SYM_C = 16, SYM_RP = SYM_R / 16, SYM_CP = SYM_C / 16, SYM_NMAX = 8192;
-
 /* sum over the 64 lanes of a wave by a fixed butterfly (every lane gets it) */
 __device__ __forceinline__ double gsf_wave_sum(double v)
 {
@@ -672,22 +652,6 @@ __device__ __forceinline__ double gsf_wave_sum(double v)
     return v;
 }
 
-
-static_assert(SYM_RP == 16 && SYM_CP == 1, "the near masks below read 16 row panels and one column panel");
-
-/* per node, its near panels as a bit set of nw words */
-__global__ void near_bits_kernel(const int32_t *__restrict__ nptr, const int32_t *__restrict__ npan, int64_t M,
-                                 int nw, uint32_t *__restrict__ bits)
-{
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= M) return;
-    uint32_t *b = bits + i * nw;
-    for (int k = 0; k < nw; ++k) b[k] = 0u;
-    for (int32_t q = nptr[i]; q < nptr[i + 1]; ++q) {
-        const int32_t p = npan[q];
-        if (p >= 0) b[p >> 5] |= 1u << (p & 31);
-    }
-}
 
 /* Plan time: the fine piece of every (wave of 64 targets, panel) for the FP64
    far field (low 7 bits: piece + 1, 0 for z <= 2 everywhere, KQ_NP + 1 when
@@ -850,616 +814,6 @@ __global__ __launch_bounds__(FT_THREADS) void far_eval_mixed(FarArgs A)
 /*   u_i = sum_{j != i} K0(alpha r_ij)/(2 pi) w_j f_j + (w_i/h^2) Wcell f_i    */
 /* Sources are targets; the self pair (r == 0) is skipped in the sum.        */
 /* ------------------------------------------------------------------------ */
-/* ------------------------------------------------------------------------ */
-/* modified-Stokes double layer, FP64 (stokes plans)                         */
-/*   u_i(x) = sum_j D_ij(x, y_j) w_j mu_j,                                     */
-/*   D_ij = -[A1 (n_i r_j + r_i n_j + d_ij r.n) + A2 r_i r_j r.n + A3 r_i n_j], */
-/*   r = x - y, A1 = alpha^2 T1, A2 = alpha^4 T2, A3 = alpha^2 T3            */
-/* with the listed near panels replaced by their stresslet weights, and on    */
-/* on-surface plans (BIE) the 1/2 mu and W mu = n sum_j w_j mu_j.n_j / |Gamma| */
-/* terms.  Densities and outputs are [2][N] / [2][M] (component-major).       */
-/* ------------------------------------------------------------------------ */
-struct StkArgs {
-    const double *sx, *sy, *sw, *snx, *sny;
-    const double *mu; /* [2][N] (or the GMRES basis, column j at mu + j*jstride) */
-    int64_t N;
-    const double *tx, *ty;
-    int64_t M, Np, nnz;
-    const int32_t *nptr, *npan, *perm;
-    const double *wst; /* [4][nnz][16] */
-    double alpha;
-    int32_t pps;
-    double *part;      /* [2][nsplit][M] */
-    double *u;         /* u1 = u[o], u2 = u[ustride + o] */
-    int64_t ustride;
-    int32_t bie;
-    const double *flux; /* sum_j w_j mu_j.n_j / |Gamma| (bie) */
-    const GState *gs;
-    int64_t jstride;
-    const uint8_t *wcls = nullptr; /* the plan's (wave, panel) fine-piece classes, if any */
-    const double *fq = nullptr;    /* the fine pieces' scales at the plan's alpha */
-};
-
-__device__ __forceinline__ bool stk_density(const StkArgs &A, const double *&mu)
-{
-    mu = A.mu;
-    if (A.gs) {
-        if (A.gs->done) return false;
-        mu += (int64_t)A.gs->j * A.jstride;
-    }
-    return true;
-}
-
-__device__ __forceinline__ void stk_epilogue(const StkArgs &A, const double *__restrict__ mu, int64_t i, double a1,
-                                             double a2)
-{
-    for (int32_t q = A.nptr[i]; q < A.nptr[i + 1]; ++q) {
-        const int64_t p = A.npan[q];
-        if (p < 0) continue;
-        for (int jj = 0; jj < 16; ++jj) {
-            const int64_t o = 16 * (int64_t)q + jj;
-            const double m1 = mu[16 * p + jj], m2 = mu[A.N + 16 * p + jj];
-            a1 = fma(A.wst[o], m1, fma(A.wst[A.nnz * 16 + o], m2, a1));
-            a2 = fma(A.wst[2 * A.nnz * 16 + o], m1, fma(A.wst[3 * A.nnz * 16 + o], m2, a2));
-        }
-    }
-    if (A.bie) {
-        const double f = A.flux[0];
-        a1 = fma(0.5, mu[i], fma(A.snx[i], f, a1));
-        a2 = fma(0.5, mu[A.N + i], fma(A.sny[i], f, a2));
-    }
-    const int64_t o = A.perm ? (int64_t)A.perm[i] : i;
-    A.u[o] = a1;
-    A.u[A.ustride + o] = a2;
-}
-
-/* Split partials + the epilogue, laid out as far_finalize: L = FZ_L lanes per
-   target (lane l: partials l, l + L, ..., node l of each near panel, lane sums
-   added in lane order) for short target lists, one thread per target
-   otherwise. */
-template <int L>
-__global__ __launch_bounds__(L == 1 ? 256 : FZ_TG * L) void stk_finalize(StkArgs A, int nsplit)
-{
-    if (L == 1) {
-        const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-        const double *mu;
-        if (i >= A.M || !stk_density(A, mu)) return;
-        double a1 = 0.0, a2 = 0.0;
-        for (int k = 0; k < nsplit; ++k) {
-            a1 += A.part[(int64_t)k * A.M + i];
-            a2 += A.part[((int64_t)nsplit + k) * A.M + i];
-        }
-        stk_epilogue(A, mu, i, a1, a2);
-        return;
-    }
-    __shared__ double red[4][L][FZ_TG]; /* far 1, near 1, far 2, near 2 */
-    const double *mu;
-    if (!stk_density(A, mu)) return; /* the same for every thread of the launch */
-    const int g = threadIdx.x % FZ_TG, l = threadIdx.x / FZ_TG;
-    const int64_t i = blockIdx.x * (int64_t)FZ_TG + g;
-    double f1 = 0.0, n1 = 0.0, f2 = 0.0, n2 = 0.0;
-    if (i < A.M) {
-        for (int k = l; k < nsplit; k += L) {
-            f1 += A.part[(int64_t)k * A.M + i];
-            f2 += A.part[((int64_t)nsplit + k) * A.M + i];
-        }
-        for (int32_t q = A.nptr[i]; q < A.nptr[i + 1]; ++q) {
-            const int64_t p = A.npan[q];
-            if (p < 0) continue;
-            const int64_t o = 16 * (int64_t)q + l;
-            const double m1 = mu[16 * p + l], m2 = mu[A.N + 16 * p + l];
-            n1 = fma(A.wst[o], m1, fma(A.wst[A.nnz * 16 + o], m2, n1));
-            n2 = fma(A.wst[2 * A.nnz * 16 + o], m1, fma(A.wst[3 * A.nnz * 16 + o], m2, n2));
-        }
-    }
-    red[0][l][g] = f1;
-    red[1][l][g] = n1;
-    red[2][l][g] = f2;
-    red[3][l][g] = n2;
-    __syncthreads();
-    if (l != 0 || i >= A.M) return;
-    for (int q = 1; q < L; ++q) {
-        f1 += red[0][q][g];
-        n1 += red[1][q][g];
-        f2 += red[2][q][g];
-        n2 += red[3][q][g];
-    }
-    double a1 = f1 + n1, a2 = f2 + n2;
-    if (A.bie) {
-        const double f = A.flux[0];
-        a1 = fma(0.5, mu[i], fma(A.snx[i], f, a1));
-        a2 = fma(0.5, mu[A.N + i], fma(A.sny[i], f, a2));
-    }
-    const int64_t o = A.perm ? (int64_t)A.perm[i] : i;
-    A.u[o] = a1;
-    A.u[A.ustride + o] = a2;
-}
-
-/* flux sum_j w_j mu_j.n_j / |Gamma| of the density into flux[0]; one block,
-   fixed summation order */
-__global__ __launch_bounds__(256) void stk_flux_kernel(StkArgs A, double inv_len, double *__restrict__ flux)
-{
-    __shared__ double red[256];
-    const double *mu;
-    if (!stk_density(A, mu)) return;
-    double s = 0.0;
-    for (int64_t j = threadIdx.x; j < A.N; j += 256) s = fma(A.sw[j], fma(mu[j], A.snx[j], mu[A.N + j] * A.sny[j]), s);
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-        if (threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) flux[0] = red[0] * inv_len;
-}
-
-/* the 16 sources of one LDS panel (offset l0) against the lane's target for
-   the stresslet double layer, in piece PC of the class table */
-template <int PC>
-__device__ __forceinline__ void stk_panel_fp64(const double *fq, const FarConst &fc, double al2, double ial2, double x,
-                                               double y, const double *lx, const double *ly, const double *lm1,
-                                               const double *lm2, const double *lnx, const double *lny, int l0,
-                                               double &a1, double &a2)
-{
-    constexpr int K = PC < 0 || PC >= KQ_NP ? 0 : PC;
-    const FarTab T = far_table();
-    double qa, qk;
-    fine_q<K>(fq, qa, qk);
-#pragma unroll 1
-    for (int s = 0; s < 16; s += 2) {
-        const int l0s = l0 + s;
-        const double ex0 = x - lx[l0s], ey0 = y - ly[l0s];
-        const double ex1 = x - lx[l0s + 1], ey1 = y - ly[l0s + 1];
-        const double r20 = fma(ex0, ex0, ey0 * ey0), r21 = fma(ex1, ex1, ey1 * ey1);
-        double Ak2[2][3];
-        stk_far2_pc<PC>(T, fc, qa, qk, al2, ial2, r20, r21, Ak2[0], Ak2[1]);
-        const double ex[2] = {ex0, ex1}, ey[2] = {ey0, ey1};
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int l = l0s + u;
-            const double *Ak = Ak2[u];
-            const double nx = lnx[l], ny = lny[l], m1 = lm1[l], m2 = lm2[l];
-            const double rn = fma(ex[u], nx, ey[u] * ny);
-            const double rm = fma(ex[u], m1, ey[u] * m2);
-            const double nm = fma(nx, m1, ny * m2);
-            const double c = fma(Ak[1] * rm, rn, Ak[2] * nm);
-            a1 -= fma(Ak[0], fma(nx, rm, fma(ex[u], nm, m1 * rn)), c * ex[u]);
-            a2 -= fma(Ak[0], fma(ny, rm, fma(ey[u], nm, m2 * rn)), c * ey[u]);
-        }
-    }
-}
-
-template <bool SPLIT>
-__global__ __launch_bounds__(FT_THREADS) void far_stokes_fp64(StkArgs A)
-{
-    __shared__ double lx[FT_SRC], ly[FT_SRC], lm1[FT_SRC], lm2[FT_SRC], lnx[FT_SRC], lny[FT_SRC];
-    const double *mu;
-    if (!stk_density(A, mu)) return;
-    const int64_t i = blockIdx.x * (int64_t)FT_THREADS + threadIdx.x;
-    const bool valid = i < A.M;
-    const int64_t iv = valid ? i : A.M - 1; /* lanes past the last target repeat it */
-    const double x = A.tx[iv], y = A.ty[iv];
-    const int64_t pb = SPLIT ? (int64_t)blockIdx.y * A.pps : 0;
-    const int64_t pe = SPLIT ? min(A.Np, pb + A.pps) : A.Np;
-    int32_t k = A.nptr[iv];
-    const int32_t kend = A.nptr[iv + 1];
-    while (k < kend && A.npan[k] >= 0 && A.npan[k] < pb) ++k;
-    int32_t nxt = (k < kend) ? A.npan[k] : INT_MAX;
-    const FarConst fc = far_const(A.alpha);
-    const double al2 = A.alpha * A.alpha, ial2 = fc.ia * fc.ia;
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint8_t *cls = A.wcls ? A.wcls + ((int64_t)blockIdx.x * (FT_THREADS / 64) + wv) * A.Np : nullptr;
-    double a1 = 0.0, a2 = 0.0;
-    for (int64_t base = 16 * pb; base < 16 * pe; base += FT_SRC) {
-        __syncthreads();
-        const int64_t j = base + threadIdx.x;
-        if (j < 16 * pe) {
-            const double wj = A.sw[j];
-            lx[threadIdx.x] = A.sx[j];
-            ly[threadIdx.x] = A.sy[j];
-            lm1[threadIdx.x] = wj * mu[j];
-            lm2[threadIdx.x] = wj * mu[A.N + j];
-            lnx[threadIdx.x] = A.snx[j];
-            lny[threadIdx.x] = A.sny[j];
-        }
-        __syncthreads();
-        const int32_t p0 = (int32_t)(base / 16);
-        const int npl = (pe - p0) < 16 ? (int)(pe - p0) : 16;
-        for (int pl = 0; pl < npl; ++pl) {
-            if (p0 + pl == nxt) {
-                ++k;
-                nxt = (k < kend) ? A.npan[k] : INT_MAX;
-                continue;
-            }
-            const int pc = cls ? (cls[p0 + pl] & 0x7f) - 1 : KQ_NP;
-            const int l0 = pl * 16;
-            switch (pc) {
-#define MHLP_STK_PANEL(PCV)                                                                                \
-    case PCV:                                                                                              \
-        stk_panel_fp64<PCV>(A.fq, fc, al2, ial2, x, y, lx, ly, lm1, lm2, lnx, lny, l0, a1, a2);           \
-        break;
-                MHLP_PC_CASES(MHLP_STK_PANEL)
-#undef MHLP_STK_PANEL
-            default:
-                stk_panel_fp64<KQ_NP>(A.fq, fc, al2, ial2, x, y, lx, ly, lm1, lm2, lnx, lny, l0, a1, a2);
-            }
-        }
-    }
-    if (!valid) return;
-    if (SPLIT) {
-        const int ns = gridDim.y;
-        A.part[(int64_t)blockIdx.y * A.M + i] = a1;
-        A.part[((int64_t)ns + blockIdx.y) * A.M + i] = a2;
-    } else {
-        stk_epilogue(A, mu, i, a1, a2);
-    }
-}
-
-/* ------------------------------------------------------------------------ */
-/* target gradient of the modified-Stokes double layer, FP64 (off-surface    */
-/* stokes plans):  d u_i/d x_l = sum_j d_l D_ij(x, y_j) w_j mu_j with        */
-/*   d_l D_ij m_j = -[ r_l Pm_i + n_l (A1 m_i + A2 (r.m) r_i)                  */
-/*                     + m_l (A1 n_i + A2 (r.n) r_i)                           */
-/*                     + d_il ((A1 + A3)(n.m) + A2 (r.n)(r.m)) ],              */
-/*   Pm_i = B1 (n_i (r.m) + m_i (r.n)) + r_i (B2 (r.n)(r.m) + (B1 + B3)(n.m)), */
-/* B_k = A_k'(r)/r, and the listed near panels replaced by their weights.    */
-/* Outputs g[c][M], c = 2i + l.                                               */
-/* ------------------------------------------------------------------------ */
-struct StkGArgs {
-    const double *sx, *sy, *sw, *snx, *sny;
-    const double *mu; /* [2][N] */
-    int64_t N;
-    const double *tx, *ty;
-    int64_t M, Np, nnz;
-    const int32_t *nptr, *npan, *perm;
-    const double *wg; /* [8][nnz][16] */
-    double alpha;
-    int32_t pps;
-    double *part;     /* [4][nsplit][M] */
-    double *g;        /* [4][M] */
-    const uint8_t *wcls = nullptr; /* the plan's (wave, panel) fine-piece classes, if any */
-    const double *fq = nullptr;    /* the fine pieces' scales at the plan's alpha */
-};
-
-__device__ __forceinline__ void stkg_epilogue(const StkGArgs &A, int64_t i, const double *acc)
-{
-    double c[4] = {acc[0], acc[1], acc[2], acc[3]};
-    const int64_t bs = A.nnz * 16;
-    for (int32_t q = A.nptr[i]; q < A.nptr[i + 1]; ++q) {
-        const int64_t p = A.npan[q];
-        if (p < 0) continue;
-        for (int jj = 0; jj < 16; ++jj) {
-            const int64_t o = 16 * (int64_t)q + jj;
-            const double m1 = A.mu[16 * p + jj], m2 = A.mu[A.N + 16 * p + jj];
-#pragma unroll
-            for (int b = 0; b < 4; ++b) c[b] = fma(A.wg[(2 * b) * bs + o], m1, fma(A.wg[(2 * b + 1) * bs + o], m2, c[b]));
-        }
-    }
-    const int64_t o = A.perm ? (int64_t)A.perm[i] : i;
-#pragma unroll
-    for (int b = 0; b < 4; ++b) A.g[b * A.M + o] = c[b];
-}
-
-__global__ void stkg_finalize(StkGArgs A, int nsplit)
-{
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= A.M) return;
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int k = 0; k < nsplit; ++k)
-        for (int b = 0; b < 4; ++b) acc[b] += A.part[((int64_t)b * nsplit + k) * A.M + i];
-    stkg_epilogue(A, i, acc);
-}
-
-/* ---- on-surface stresslet double layer, each unordered far pair once ----
-   The far term of source j at node i is -F(e; n_j, m_j), e = x_i - x_j, m = w mu,
-   F(e; n, m) = A1 (n (e.m) + e (n.m) + m (e.n)) + (A2 (e.m)(e.n) + A3 (n.m)) e
-   with A1, A2, A3 = alpha^2 T1, alpha^4 T2, alpha^2 T3 of |e| (App. B), the
-   contraction of far_stokes_fp64.  F is odd in e, so one evaluation of the A_k
-   serves both terms of the pair: source j at node i and +F(e; n_i, m_i) for
-   source i at node j.  Tiles, near bit set and order rules as above;
-   the column terms of a tile are summed over each row of 16 lanes by DPP
-   moves, then the 16 row sums of a column in order through LDS. */
-struct StkSymArgs {
-    StkArgs A;
-    const int2 *tiles;
-    double *p1, *p2; /* [column panel][2][N], [row block][2][N] */
-    const uint32_t *bits;
-    int nw;
-};
-
-/* inclusive sums within each row of 16 lanes: lane 15 of a row holds its sum */
-__device__ __forceinline__ double row16_sum_dpp(double v)
-{
-#pragma unroll
-    for (int k = 0; k < 4; ++k) v = dpp_add(v, k);
-    return v;
-}
-
-__global__ __launch_bounds__(SYM_R) void stk_sym_kernel(StkSymArgs S)
-{
-    const StkArgs &A = S.A;
-    __shared__ double cx[SYM_C], cy[SYM_C], cnx[SYM_C], cny[SYM_C], cm1[SYM_C], cm2[SYM_C], cnm[SYM_C];
-    __shared__ uint32_t cmask[SYM_C];
-    __shared__ double colv[2][SYM_C][SYM_R / 16];
-    const double *mu;
-    if (!stk_density(A, mu)) return; /* the same for the whole launch */
-    const int2 tl = S.tiles[blockIdx.x];
-    const int I = tl.x, J = tl.y, t = threadIdx.x;
-    const int64_t N = A.N, i = (int64_t)I * SYM_R + t, j0 = (int64_t)J * SYM_C;
-    const int pb = SYM_RP * I; /* first panel of the row block */
-    if (t < SYM_C) {
-        const int64_t j = j0 + t;
-        double xj = 0.0, yj = 0.0, nxj = 0.0, nyj = 0.0, m1 = 0.0, m2 = 0.0;
-        uint32_t msk = 0;
-        if (j < N) {
-            xj = A.sx[j];
-            yj = A.sy[j];
-            nxj = A.snx[j];
-            nyj = A.sny[j];
-            const double wj = A.sw[j];
-            m1 = wj * mu[j];
-            m2 = wj * mu[N + j];
-            msk = (S.bits[j * S.nw + (pb >> 5)] >> (pb & 31)) & 0xFFFFu; /* the block's 16 panels */
-        }
-        cx[t] = xj;
-        cy[t] = yj;
-        cnx[t] = nxj;
-        cny[t] = nyj;
-        cm1[t] = m1;
-        cm2[t] = m2;
-        cnm[t] = fma(nxj, m1, nyj * m2);
-        cmask[t] = msk;
-    }
-    const bool valid = i < N;
-    double x = 0.0, y = 0.0, nxi = 0.0, nyi = 0.0, mi1 = 0.0, mi2 = 0.0;
-    uint32_t rnear = 0; /* bit 0: column panel J listed near row i */
-    int kp = 0;         /* row panel within the block */
-    if (valid) {
-        x = A.sx[i];
-        y = A.sy[i];
-        nxi = A.snx[i];
-        nyi = A.sny[i];
-        const double wi = A.sw[i];
-        mi1 = wi * mu[i];
-        mi2 = wi * mu[N + i];
-        kp = (int)(i / 16) - pb;
-        rnear = (S.bits[i * S.nw + (J >> 5)] >> (J & 31)) & 1u;
-    }
-    const double nmi = fma(nxi, mi1, nyi * mi2);
-    const bool diag = SYM_CP * J < pb + SYM_RP; /* the chunk lies in the row block */
-    const bool rfar = valid && !(rnear & 1u);
-    __syncthreads();
-    const FarConst fc = far_const(A.alpha);
-    const double al2 = A.alpha * A.alpha, ial2 = fc.ia * fc.ia;
-    const int ncol = (int)min((int64_t)SYM_C, N - j0);
-    const int slot = t >> 4; /* row of 16 lanes: 4 per wave */
-    double a1 = 0.0, a2 = 0.0;
-#pragma unroll 1
-    for (int s = 0; s < ncol; s += 2) {
-        const FarTab T = far_table();
-        double ex[2], ey[2], r2[2];
-        bool rw[2], cl[2];
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int c = s + u;
-            const bool order = !diag || i < j0 + c; /* on the diagonal block only row < column */
-            ex[u] = x - cx[c];
-            ey[u] = y - cy[c];
-            rw[u] = rfar && order;
-            cl[u] = valid && order && !((cmask[c] >> kp) & 1u);
-            const double d2 = fma(ex[u], ex[u], ey[u] * ey[u]);
-            r2[u] = (rw[u] || cl[u]) ? d2 : 1.0; /* unused pairs (the node itself among them) */
-        }
-        double Ak[2][3];
-        stk_far2(T, fc, al2, ial2, r2[0], r2[1], Ak[0], Ak[1]);
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int c = s + u;
-            const double *K = Ak[u];
-            if (rw[u]) {
-                const double rn = fma(ex[u], cnx[c], ey[u] * cny[c]), rm = fma(ex[u], cm1[c], ey[u] * cm2[c]);
-                const double nm = cnm[c], cf = fma(K[1] * rm, rn, K[2] * nm);
-                a1 -= fma(K[0], fma(cnx[c], rm, fma(ex[u], nm, cm1[c] * rn)), cf * ex[u]);
-                a2 -= fma(K[0], fma(cny[c], rm, fma(ey[u], nm, cm2[c] * rn)), cf * ey[u]);
-            }
-            double v1 = 0.0, v2 = 0.0;
-            if (cl[u]) {
-                const double rn = fma(ex[u], nxi, ey[u] * nyi), rm = fma(ex[u], mi1, ey[u] * mi2);
-                const double cf = fma(K[1] * rm, rn, K[2] * nmi);
-                v1 = fma(K[0], fma(nxi, rm, fma(ex[u], nmi, mi1 * rn)), cf * ex[u]);
-                v2 = fma(K[0], fma(nyi, rm, fma(ey[u], nmi, mi2 * rn)), cf * ey[u]);
-            }
-            v1 = row16_sum_dpp(v1);
-            v2 = row16_sum_dpp(v2);
-            if ((t & 15) == 15) {
-                colv[0][c][slot] = v1;
-                colv[1][c][slot] = v2;
-            }
-        }
-    }
-    __syncthreads();
-    if (t < 2 * SYM_C) {
-        const int comp = t / SYM_C, c = t % SYM_C;
-        if (c < ncol) {
-            double sc = 0.0;
-            for (int r = 0; r < SYM_R / 16; ++r) sc += colv[comp][c][r];
-            S.p2[((int64_t)I * 2 + comp) * N + j0 + c] = sc;
-        }
-    }
-    if (valid) {
-        S.p1[(int64_t)J * 2 * N + i] = a1;
-        S.p1[((int64_t)J * 2 + 1) * N + i] = a2;
-    }
-}
-
-/* node n: both components of the row sums of the chunks from its block on and
-   of the column sums of the blocks up to its own, the near corrections, and
-   on the BIE operator the flux term and mu/2; FZ_L lanes per node, FZ_TG
-   nodes per block, lane sums added in lane order. */
-__global__ __launch_bounds__(FZ_TG *FZ_L) void stk_sym_finalize(StkSymArgs S, int nchunk)
-{
-    const StkArgs &A = S.A;
-    __shared__ double red[4][FZ_L][FZ_TG]; /* far 1, near 1, far 2, near 2 */
-    const double *mu;
-    if (!stk_density(A, mu)) return; /* the same for every thread of the launch */
-    const int g = threadIdx.x % FZ_TG, l = threadIdx.x / FZ_TG;
-    const int64_t N = A.N, n = blockIdx.x * (int64_t)FZ_TG + g;
-    double f1 = 0.0, n1 = 0.0, f2 = 0.0, n2 = 0.0;
-    if (n < N) {
-        const int B = (int)(n / SYM_R);
-        for (int c = SYM_RP * B / SYM_CP + l; c < nchunk; c += FZ_L) {
-            f1 += S.p1[(int64_t)c * 2 * N + n];
-            f2 += S.p1[((int64_t)c * 2 + 1) * N + n];
-        }
-        for (int b = l; b <= B; b += FZ_L) {
-            f1 += S.p2[(int64_t)b * 2 * N + n];
-            f2 += S.p2[((int64_t)b * 2 + 1) * N + n];
-        }
-        for (int32_t q = A.nptr[n]; q < A.nptr[n + 1]; ++q) {
-            const int64_t p = A.npan[q];
-            if (p < 0) continue;
-            const int64_t o = 16 * (int64_t)q + l;
-            const double m1 = mu[16 * p + l], m2 = mu[N + 16 * p + l];
-            n1 = fma(A.wst[o], m1, fma(A.wst[A.nnz * 16 + o], m2, n1));
-            n2 = fma(A.wst[2 * A.nnz * 16 + o], m1, fma(A.wst[3 * A.nnz * 16 + o], m2, n2));
-        }
-    }
-    red[0][l][g] = f1;
-    red[1][l][g] = n1;
-    red[2][l][g] = f2;
-    red[3][l][g] = n2;
-    __syncthreads();
-    if (l != 0 || n >= N) return;
-    for (int q = 1; q < FZ_L; ++q) {
-        f1 += red[0][q][g];
-        n1 += red[1][q][g];
-        f2 += red[2][q][g];
-        n2 += red[3][q][g];
-    }
-    double a1 = f1 + n1, a2 = f2 + n2;
-    if (A.bie) {
-        const double f = A.flux[0];
-        a1 = fma(0.5, mu[n], fma(A.snx[n], f, a1));
-        a2 = fma(0.5, mu[N + n], fma(A.sny[n], f, a2));
-    }
-    const int64_t o = A.perm ? (int64_t)A.perm[n] : n;
-    A.u[o] = a1;
-    A.u[A.ustride + o] = a2;
-}
-
-/* the 16 sources of one LDS panel (offset l0) against the lane's target for
-   the stresslet target gradient, in piece PC of the class table; g: the
-   lane's four accumulators */
-template <int PC>
-__device__ __forceinline__ void stkg_panel_fp64(const double *fq, const FarConst &fc, double al2, double ial2, double x,
-                                                double y, const double *lx, const double *ly, const double *lm1,
-                                                const double *lm2, const double *lnx, const double *lny, int l0,
-                                                double *g)
-{
-    constexpr int K = PC < 0 || PC >= KQ_NP ? 0 : PC;
-    const FarTab T = far_table();
-    double qa, qk;
-    fine_q<K>(fq, qa, qk);
-#pragma unroll 1
-    for (int s = 0; s < 16; s += 2) {
-        const int l0s = l0 + s;
-        const double ex0 = x - lx[l0s], ey0 = y - ly[l0s];
-        const double ex1 = x - lx[l0s + 1], ey1 = y - ly[l0s + 1];
-        const double r20 = fma(ex0, ex0, ey0 * ey0), r21 = fma(ex1, ex1, ey1 * ey1);
-        double Ak[2][3], Bk[2][3];
-        stk_far2_ab_pc<PC>(T, fc, qa, qk, al2, ial2, r20, r21, Ak[0], Bk[0], Ak[1], Bk[1]);
-        const double ex[2] = {ex0, ex1}, ey[2] = {ey0, ey1};
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int l = l0s + u;
-            const double *a = Ak[u], *b = Bk[u];
-            const double nx = lnx[l], ny = lny[l], m1 = lm1[l], m2 = lm2[l];
-            const double rn = fma(ex[u], nx, ey[u] * ny);
-            const double rm = fma(ex[u], m1, ey[u] * m2);
-            const double nm = fma(nx, m1, ny * m2);
-            const double sr = fma(b[1] * rn, rm, (b[0] + b[2]) * nm);
-            const double p1 = fma(b[0], fma(nx, rm, m1 * rn), ex[u] * sr);
-            const double p2 = fma(b[0], fma(ny, rm, m2 * rn), ey[u] * sr);
-            const double a1 = fma(a[0], m1, a[1] * rm * ex[u]), a2 = fma(a[0], m2, a[1] * rm * ey[u]);
-            const double c1 = fma(a[0], nx, a[1] * rn * ex[u]), c2 = fma(a[0], ny, a[1] * rn * ey[u]);
-            const double d = fma(a[0] + a[2], nm, a[1] * rn * rm);
-            g[0] -= fma(ex[u], p1, fma(nx, a1, fma(m1, c1, d)));
-            g[1] -= fma(ey[u], p1, fma(ny, a1, m2 * c1));
-            g[2] -= fma(ex[u], p2, fma(nx, a2, m1 * c2));
-            g[3] -= fma(ey[u], p2, fma(ny, a2, fma(m2, c2, d)));
-        }
-    }
-}
-
-template <bool SPLIT>
-__global__ __launch_bounds__(FT_THREADS) void far_stokes_grad_fp64(StkGArgs A)
-{
-    __shared__ double lx[FT_SRC], ly[FT_SRC], lm1[FT_SRC], lm2[FT_SRC], lnx[FT_SRC], lny[FT_SRC];
-    const int64_t i = blockIdx.x * (int64_t)FT_THREADS + threadIdx.x;
-    const bool valid = i < A.M;
-    const int64_t iv = valid ? i : A.M - 1; /* lanes past the last target repeat it */
-    const double x = A.tx[iv], y = A.ty[iv];
-    const int64_t pb = SPLIT ? (int64_t)blockIdx.y * A.pps : 0;
-    const int64_t pe = SPLIT ? min(A.Np, pb + A.pps) : A.Np;
-    int32_t k = A.nptr[iv];
-    const int32_t kend = A.nptr[iv + 1];
-    while (k < kend && A.npan[k] >= 0 && A.npan[k] < pb) ++k;
-    int32_t nxt = (k < kend) ? A.npan[k] : INT_MAX;
-    const FarConst fc = far_const(A.alpha);
-    const double al2 = A.alpha * A.alpha, ial2 = fc.ia * fc.ia;
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint8_t *cls = A.wcls ? A.wcls + ((int64_t)blockIdx.x * (FT_THREADS / 64) + wv) * A.Np : nullptr;
-    double g11 = 0.0, g12 = 0.0, g21 = 0.0, g22 = 0.0;
-    for (int64_t base = 16 * pb; base < 16 * pe; base += FT_SRC) {
-        __syncthreads();
-        const int64_t j = base + threadIdx.x;
-        if (j < 16 * pe) {
-            const double wj = A.sw[j];
-            lx[threadIdx.x] = A.sx[j];
-            ly[threadIdx.x] = A.sy[j];
-            lm1[threadIdx.x] = wj * A.mu[j];
-            lm2[threadIdx.x] = wj * A.mu[A.N + j];
-            lnx[threadIdx.x] = A.snx[j];
-            lny[threadIdx.x] = A.sny[j];
-        }
-        __syncthreads();
-        const int32_t p0 = (int32_t)(base / 16);
-        const int npl = (pe - p0) < 16 ? (int)(pe - p0) : 16;
-        for (int pl = 0; pl < npl; ++pl) {
-            if (p0 + pl == nxt) {
-                ++k;
-                nxt = (k < kend) ? A.npan[k] : INT_MAX;
-                continue;
-            }
-            const int pc = cls ? (cls[p0 + pl] & 0x7f) - 1 : KQ_NP;
-            const int l0 = pl * 16;
-            double gg[4] = {g11, g12, g21, g22};
-            switch (pc) {
-#define MHLP_STKG_PANEL(PCV)                                                                               \
-    case PCV:                                                                                              \
-        stkg_panel_fp64<PCV>(A.fq, fc, al2, ial2, x, y, lx, ly, lm1, lm2, lnx, lny, l0, gg);              \
-        break;
-                MHLP_PC_CASES(MHLP_STKG_PANEL)
-#undef MHLP_STKG_PANEL
-            default:
-                stkg_panel_fp64<KQ_NP>(A.fq, fc, al2, ial2, x, y, lx, ly, lm1, lm2, lnx, lny, l0, gg);
-            }
-            g11 = gg[0];
-            g12 = gg[1];
-            g21 = gg[2];
-            g22 = gg[3];
-        }
-    }
-    if (!valid) return;
-    const double acc[4] = {g11, g12, g21, g22};
-    if (SPLIT) {
-        const int ns = gridDim.y;
-        for (int b = 0; b < 4; ++b) A.part[((int64_t)b * ns + blockIdx.y) * A.M + i] = acc[b];
-    } else {
-        stkg_epilogue(A, i, acc);
-    }
-}
-
 struct VolArgs {
     const double *x, *y, *w, *f;
     int64_t n;
@@ -2589,14 +1943,14 @@ extern "C" mhlp_status mhlp_plan_destroy(mhlp_plan *P)
         if (gp.second.exec) (void)hipGraphExecDestroy(gp.second.exec);
     if (P->cap_stream) (void)hipStreamDestroy(P->cap_stream);
     void *ptrs[] = {P->near_ptr, P->near_panel, P->near_tgt, P->near_ts, P->wslp,  P->wdlp,    P->ws,
-                    P->hdev,     P->part,       P->gdev,     P->perm,    P->wgrad, P->wstk,    P->stk_flux,
-                    P->wstkg,    P->sym_tiles,  P->sym_p1,   P->sym_p2,  P->sym_bits, P->wcls, P->fqd};
+                    P->hdev,     P->part,       P->gdev,     P->perm,    P->wgrad, P->wstk,    P->wstkg,
+                    P->wcls,     P->fqd};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     delete P->fmm;
     if (P->tree) {
         void *tp[] = {P->tree->cc, P->tree->rmin, P->tree->mom, P->tree->st, P->tree->items, P->tree->cnt, P->tree->order,
-                      P->tree->part};
+                      P->tree->part, P->tree->flux};
         for (void *p : tp)
             if (p) (void)hipFree(p);
         delete P->tree;
@@ -2610,16 +1964,15 @@ extern "C" mhlp_status mhlp_plan_destroy(mhlp_plan *P)
 /* The fine pieces' scales at the plan's alpha (read by every far kernel). */
 static mhlp_status far_scales_setup(mhlp_plan *P, hipStream_t st)
 {
-    double fq[2 * KQ_NP];
+    double fq[FINE_SCALES];
     fine_scales(P->alpha, fq);
-    TRY(dalloc(&P->fqd, 2 * KQ_NP));
+    TRY(dalloc(&P->fqd, FINE_SCALES));
     HIPCHECK(hipMemcpyAsync(P->fqd, fq, sizeof(fq), hipMemcpyHostToDevice, st));
     HIPCHECK(hipStreamSynchronize(st)); /* fq ends here */
     return MHLP_OK;
 }
 
-/* The (wave of 64 targets, panel) class table of the mixed-precision, gradient
-   and stresslet tiles (built on the stream after the near lists, which it reads). */
+/* The (wave of 64 targets, panel) class table of the mixed-precision tiles (built on the stream after the near lists, which it reads). */
 static mhlp_status far_class_setup(mhlp_plan *P, hipStream_t st)
 {
     const int64_t M = P->M, Np = P->g->Np;
@@ -2632,7 +1985,7 @@ static mhlp_status far_class_setup(mhlp_plan *P, hipStream_t st)
     return MHLP_OK;
 }
 
-/* Clusters, item lists and buffers of a scalar plan's far field (tree.h), on
+/* Clusters, item lists and buffers of a plan's far field (tree.h), on
    the stream after the near lists, which the item lists read. */
 static mhlp_status tree_setup(mhlp_plan *P, hipStream_t st)
 {
@@ -2648,7 +2001,9 @@ static mhlp_status tree_setup(mhlp_plan *P, hipStream_t st)
     }
     TRY(dalloc(&T.cc, 2 * T.ncl));
     TRY(dalloc(&T.rmin, mhlp::TR_RM * T.ncl));
-    TRY(dalloc(&T.mom, T.ncl * mhlp::tr_stride(P->onsurf ? 2 : 4)));
+    T.stokes = P->stokes ? 1 : 0;
+    TRY(dalloc(&T.mom, T.ncl * mhlp::tr_stride(P->stokes ? (P->onsurf ? 6 : 10) : (P->onsurf ? 4 : 8))));
+    if (P->stokes && P->onsurf) TRY(dalloc(&T.flux, Np));
     TRY(dalloc(&T.st, 48 * Np));
     TRY(dalloc(&T.items, G * Np));
     TRY(dalloc(&T.cnt, G));
@@ -2789,30 +2144,6 @@ static mhlp_status plan_create_impl(const mhlp_geometry *g, double alpha, const 
             return s;
         }
     }
-    if (P->onsurf && P->stokes && g->N <= SYM_NMAX) {
-        /* tiles of the symmetric on-surface stresslet operator (row block I,
-           column chunk J from the block's first panel on), two components */
-        const int64_t ncomp = 2;
-        const int64_t nrb = (g->N + SYM_R - 1) / SYM_R, ncc = (g->N + SYM_C - 1) / SYM_C;
-        std::vector<int2> tiles;
-        for (int64_t I = 0; I < nrb; ++I)
-            for (int64_t J = SYM_RP * I / SYM_CP; J < ncc; ++J) tiles.push_back(make_int2((int)I, (int)J));
-        P->sym_ntiles = (int32_t)tiles.size();
-        P->sym_nw = (int32_t)((g->Np + 31) / 32);
-        if ((s = dalloc(&P->sym_tiles, (int64_t)tiles.size())) || (s = dalloc(&P->sym_p1, ncomp * ncc * g->N)) ||
-            (s = dalloc(&P->sym_p2, ncomp * nrb * g->N)) ||
-            (s = dalloc(&P->sym_bits, (int64_t)P->sym_nw * g->N))) {
-            mhlp_plan_destroy(P);
-            return s;
-        }
-        hipError_t e = hipMemcpyAsync(P->sym_tiles, tiles.data(), sizeof(int2) * tiles.size(), hipMemcpyHostToDevice,
-                                      st);
-        if (e == hipSuccess) e = hipStreamSynchronize(st);  /* tiles is freed at the end of this block */
-        if (e != hipSuccess) {
-            mhlp_plan_destroy(P);
-            return fail(MHLP_HIP_ERROR, std::string("plan_create tile copy: ") + hipGetErrorString(e));
-        }
-    }
     int32_t *cnt = nullptr;
     if ((s = dalloc(&cnt, M + 1)) || (s = dalloc(&P->near_ptr, M + 1))) {
         if (cnt) (void)hipFree(cnt);
@@ -2885,26 +2216,12 @@ static mhlp_status plan_create_impl(const mhlp_geometry *g, double alpha, const 
         P->fill_mismatch = mism;
     }
     (void)hipFree(cnt);
-    if ((s = far_scales_setup(P, st)) || (!stokes && (s = tree_setup(P, st))) ||
-        (s = far_class_setup(P, st))) {
+    if ((s = far_scales_setup(P, st)) || (s = tree_setup(P, st)) || (!stokes && (s = far_class_setup(P, st)))) {
         mhlp_plan_destroy(P);
         return s;
     }
-    if (P->sym_bits) {
-        near_bits_kernel<<<nblocks(M, 256), 256, 0, st>>>(P->near_ptr, P->near_panel, M, P->sym_nw, P->sym_bits);
-        hipError_t eb = hipGetLastError();
-        if (eb == hipSuccess) eb = hipStreamSynchronize(st); /* later calls may come on other streams */
-        if (eb != hipSuccess) {
-            mhlp_plan_destroy(P);
-            return fail(MHLP_HIP_ERROR, std::string("plan_create near bits: ") + hipGetErrorString(eb));
-        }
-    }
     if (stokes) {
-        /* W term: device scalar for the flux, host 1/|Gamma| */
-        if ((s = dalloc(&P->stk_flux, 8))) {
-            mhlp_plan_destroy(P);
-            return s;
-        }
+        /* W term: 1/|Gamma| */
         std::vector<double> hw((size_t)g->N);
         hipError_t e2 = hipMemcpyAsync(hw.data(), g->w, sizeof(double) * g->N, hipMemcpyDeviceToHost, st);
         if (e2 == hipSuccess) e2 = hipStreamSynchronize(st);
@@ -2949,16 +2266,35 @@ extern "C" mhlp_status mhlp_plan_info(const mhlp_plan *P, int64_t *n_targets, in
 /* ------------------------------------------------------------------------ */
 /* The launches of one far sum by cluster expansions: Op what it evaluates,
    <SLP, DLP, GRAD> the moments it reads. */
+static dim3 moments_grid(const FarArgs &A, const mhlp::TreeDev &T)
+{
+    return dim3(nblocks(A.Np, 16), (unsigned)T.nlev, mhlp::TR_GROUPS);
+}
+
+template <class Op>
+static void launch_tree_far(const FarArgs &A, const mhlp_plan *P, hipStream_t st)
+{
+    const mhlp::TreeDev &T = *P->tree;
+    mhlp::far_tree_kernel<Op>
+        <<<dim3(nblocks(A.M, 64), (unsigned)P->tr_split), 64 * std::min(P->tr_waves, Op::WMAX), 0, st>>>(A, T);
+    if (P->tr_split > 1)
+        mhlp::tree_finalize<Op><<<dim3(nblocks(A.M, 64), (unsigned)Op::NF), 64, 0, st>>>(A, T, P->tr_split);
+}
+
 template <class Op, bool SLP, bool DLP, bool GRAD>
 static void launch_tree(const FarArgs &A, const mhlp_plan *P, hipStream_t st)
 {
     const mhlp::TreeDev &T = *P->tree;
-    mhlp::tree_moments_kernel<SLP, DLP, GRAD>
-        <<<dim3(nblocks(A.Np, 16), (unsigned)T.nlev, mhlp::TR_GROUPS), 256, 0, st>>>(A, T);
-    mhlp::far_tree_kernel<Op>
-        <<<dim3(nblocks(A.M, 64), (unsigned)P->tr_split), 64 * P->tr_waves, 0, st>>>(A, T);
-    if (P->tr_split > 1)
-        mhlp::tree_finalize<Op><<<dim3(nblocks(A.M, 64), (unsigned)Op::NF), 64, 0, st>>>(A, T, P->tr_split);
+    mhlp::tree_moments_kernel<SLP, DLP, GRAD><<<moments_grid(A, T), 256, 0, st>>>(A, T);
+    launch_tree_far<Op>(A, P, st);
+}
+
+template <bool GRAD>
+static void launch_tree_stokes(const FarArgs &A, const mhlp_plan *P, hipStream_t st)
+{
+    const mhlp::TreeDev &T = *P->tree;
+    mhlp::tree_stokes_kernel<GRAD><<<moments_grid(A, T), 256, 0, st>>>(A, T);
+    launch_tree_far<mhlp::TreeStokes<GRAD>>(A, P, st);
 }
 
 template <bool SLP, bool DLP>
@@ -3250,53 +2586,13 @@ extern "C" mhlp_status mhlp_eval_grad(const mhlp_plan *Pc, const double *sigma, 
 static mhlp_status launch_stokes(const mhlp_plan *P, const double *mu, double *u, int64_t ustride, bool bie,
                                  hipStream_t st, const GState *gs, int64_t jstride)
 {
-    const mhlp_geometry *g = P->g;
-    StkArgs A;
-    A.sx = g->soa;
-    A.sy = g->soa + g->N;
-    A.sw = g->w;
-    A.snx = g->nx;
-    A.sny = g->ny;
-    A.mu = mu;
-    A.N = g->N;
-    A.tx = P->tx;
-    A.ty = P->ty;
-    A.M = P->M;
-    A.Np = g->Np;
+    FarArgs A = far_args(P, nullptr, mu, nullptr, nullptr, bie ? 0.5 : 0.0, gs, jstride);
+    A.wg = P->wstk;
     A.nnz = P->nnz;
-    A.nptr = P->near_ptr;
-    A.npan = P->near_panel;
-    A.perm = P->perm;
-    A.wst = P->wstk;
-    A.alpha = P->alpha;
-    A.pps = P->pps;
-    A.part = P->part;
-    A.u = u;
-    A.ustride = ustride;
-    A.bie = bie ? 1 : 0;
-    A.flux = P->stk_flux;
-    A.gs = gs;
-    A.jstride = jstride;
-    A.wcls = P->wcls;
-    A.fq = P->fqd;
-    if (bie) stk_flux_kernel<<<1, 256, 0, st>>>(A, P->inv_len, P->stk_flux);
-    if (P->sym_tiles) { /* on-surface: each unordered far pair once */
-        const StkSymArgs S{A, P->sym_tiles, P->sym_p1, P->sym_p2, P->sym_bits, P->sym_nw};
-        stk_sym_kernel<<<(unsigned)P->sym_ntiles, SYM_R, 0, st>>>(S);
-        stk_sym_finalize<<<nblocks(g->N, FZ_TG), FZ_TG * FZ_L, 0, st>>>(S, (int)((g->N + SYM_C - 1) / SYM_C));
-        HIPCHECK(hipGetLastError());
-        return MHLP_OK;
-    }
-    const unsigned nb = nblocks(A.M, FT_THREADS);
-    if (P->nsplit <= 1) {
-        far_stokes_fp64<false><<<nb, FT_THREADS, 0, st>>>(A);
-    } else {
-        far_stokes_fp64<true><<<dim3(nb, P->nsplit), FT_THREADS, 0, st>>>(A);
-        if (A.M <= FZ_SHORT)
-            stk_finalize<FZ_L><<<nblocks(A.M, FZ_TG), FZ_TG * FZ_L, 0, st>>>(A, P->nsplit);
-        else
-            stk_finalize<1><<<nblocks(A.M, 256), 256, 0, st>>>(A, P->nsplit);
-    }
+    A.gout[0] = u;
+    A.gout[1] = u + ustride;
+    A.inv_len = P->inv_len;
+    launch_tree_stokes<false>(A, P, st);
     HIPCHECK(hipGetLastError());
     return MHLP_OK;
 }
@@ -3347,37 +2643,11 @@ extern "C" mhlp_status mhlp_stokes_eval_grad(const mhlp_plan *Pc, const double *
     mhlp_plan *P = const_cast<mhlp_plan *>(Pc); /* gradient weights are built on first use */
     hipStream_t st = (hipStream_t)stream;
     TRY(ensure_stokes_grad_weights(P, st));
-    const mhlp_geometry *geo = P->g;
-    StkGArgs A;
-    A.sx = geo->soa;
-    A.sy = geo->soa + geo->N;
-    A.sw = geo->w;
-    A.snx = geo->nx;
-    A.sny = geo->ny;
-    A.mu = mu;
-    A.N = geo->N;
-    A.tx = P->tx;
-    A.ty = P->ty;
-    A.M = P->M;
-    A.Np = geo->Np;
-    A.nnz = P->nnz;
-    A.nptr = P->near_ptr;
-    A.npan = P->near_panel;
-    A.perm = P->perm;
+    FarArgs A = far_args(P, nullptr, mu, nullptr, nullptr, 0.0, nullptr, 0);
     A.wg = P->wstkg;
-    A.alpha = P->alpha;
-    A.pps = P->pps;
-    A.part = P->part;
-    A.g = g;
-    A.wcls = P->wcls;
-    A.fq = P->fqd;
-    const unsigned nb = nblocks(A.M, FT_THREADS);
-    if (P->nsplit <= 1) {
-        far_stokes_grad_fp64<false><<<nb, FT_THREADS, 0, st>>>(A);
-    } else {
-        far_stokes_grad_fp64<true><<<dim3(nb, P->nsplit), FT_THREADS, 0, st>>>(A);
-        stkg_finalize<<<nblocks(A.M, 256), 256, 0, st>>>(A, P->nsplit);
-    }
+    A.nnz = P->nnz;
+    for (int f = 0; f < 4; ++f) A.gout[f] = g + f * P->M;
+    launch_tree_stokes<true>(A, P, st);
     HIPCHECK(hipGetLastError());
     return MHLP_OK;
 }

@@ -30,9 +30,10 @@ constexpr int TR_LEV = 5;                    /* cluster levels: 1, 2, 4, 8, 16 p
 constexpr int TR_PMIN = 8, TR_PSTEP = 2, TR_NP = 13, TR_PMAX = TR_PMIN + TR_PSTEP * (TR_NP - 1);
 constexpr int TR_GRAD = 2;                   /* orders a gradient takes beyond the potential's */
 constexpr int TR_ROWS = TR_PMAX + TR_GRAD + 1; /* orders of a moment table */
-constexpr int TR_RM = 16;                    /* distances kept per cluster: TR_NP orders, the underflow's last */
-/* doubles of a cluster's moment table: rows of 2 NF values, padded to the 32 doubles of a row load */
-constexpr int tr_stride(int nf) { return (TR_ROWS * 2 * nf + 31) / 32 * 32; }
+constexpr int TR_RM = 16;                    /* distances kept per cluster: TR_NP orders, then (last) the underflow's,
+                                                or the radius in a stresslet plan */
+/* doubles of a cluster's moment table: rows of nv values, padded to the 32 doubles of a row load */
+constexpr int tr_stride(int nv) { return (TR_ROWS * nv + 31) / 32 * 32; }
 constexpr double TR_AMIN = 1e-6, TR_AMAX = 2.0; /* alpha R of an expansion (below: K_n, I_n leave the range of a double) */
 constexpr double TR_ZZERO = 746.0;           /* e^{-z} is exactly 0 in double from here on (also scaled by 2^-1074) */
 constexpr double TR_EPS = 0x1p-54;           /* truncation of an expansion, relative to its smallest pair */
@@ -42,11 +43,14 @@ struct TreeDev {
     int nlev = 0;
     int64_t off[TR_LEV] = {0, 0, 0, 0, 0};   /* first cluster of each level */
     int64_t ncl = 0;
+    int stokes = 0;                          /* stresslet lists (tree_stokes_order) */
+    double *flux = nullptr;                  /* on-surface stresslet: [Np] sums of w mu.n */
     int cut = 0;                             /* a direct item is 2^cut units of work (16/2^cut sources each) */
     double *cc = nullptr;                    /* [ncl][2] centres */
     double *rmin = nullptr;                  /* [ncl][TR_RM]: distance from which order TR_PMIN + TR_PSTEP k serves
                                                 (k < TR_NP; INFINITY: never); last: from which every pair underflows */
-    double *mom = nullptr;                   /* [ncl][tr_stride]: rows of (2 Re M, -2 Im M) per field */
+    double *mom = nullptr;                   /* [ncl][tr_stride]: rows of the coefficients of K_n cos n theta
+                                                and K_n sin n theta per field (stresslet: then of r^-n) */
     double *st = nullptr;                    /* staged sources [Np][3][16]: w sigma, alpha w mu n_x, alpha w mu n_y */
     uint2 *items = nullptr;                  /* [groups][Np]: direct items from the front, expansions from the back */
     int2 *cnt = nullptr;                     /* [groups]: their numbers */
@@ -57,6 +61,23 @@ struct TreeDev {
 /* item: x = cluster, y = piece + 1 (bits 0-4) | order (bits 8-13) | flags */
 constexpr uint32_t TR_NEAR = 1u << 16; /* direct: some target of the wave lists the panel */
 constexpr uint32_t TR_ZERO = 1u << 17; /* every pair underflows to zero: only non-finite densities matter */
+constexpr uint32_t TR_LAP = 1u << 18;  /* stresslet: the K part of every pair is below rounding */
+
+/* Stresslet double layer by clusters.  With U = u_1 + i u_2, x - y = r e^{i theta},
+   sigma = (m_1 + i m_2)(n_1 + i n_2)/2, tau = m.n (m = w mu) and O_k = K_k(alpha r) e^{i k theta},
+   the closed forms of T1..T3 (App. B) are
+     2 pi U = conj(sigma) [8/(alpha^2 conj(x - y)^3) - alpha O_3] + sigma alpha O_{-1} + tau/conj(x - y):
+   derivatives of K0 and of log r, each of which has its expansion about the
+   cluster's centre (Graf's theorem; powers of 1/conj(x - c)).  The two parts
+   in brackets cancel like z^2/8 for small z, so a cluster is expanded only
+   from alpha (r - R) >= TR_SZ on; from TR_SLAP on the K part is below
+   rounding against the other's 1/r and left out (K_3(42) = 1e-19), for
+   clusters of any alpha R.  Order: the terms of the bracket differ by the
+   factor z^2/(4 n) once n > z^2/4, so the neglected terms are below
+   n t^{n-3}/r in every regime (t = R/r). */
+constexpr double TR_SZ = 2.0, TR_SLAP = 42.0, TR_SAMAX = 1e7;
+constexpr int TR_SNP = 12; /* orders 8..30: the gradient takes TR_SGRAD more */
+constexpr int TR_SGRAD = 4;
 
 /* Truncation of an order-p expansion with alpha R = a at distance t R from the
    centre: bound of sum_{n>p} alpha (I_{n-1} + I_{n+1})(a) K_n(a t), the
@@ -73,6 +94,14 @@ __host__ __device__ inline float tree_truncation(int p, float a, float t)
         h = (float)(2 * (n + 1)) / b + 1.0f / h;
     }
     return prod * expf(a + 0.25f * a * a / (float)(p + 1)) * (1.0f + 1.0f / t) / (1.0f - 1.0f / t);
+}
+
+/* the stresslet's t = r/R from which order p serves */
+__host__ __device__ inline double tree_stokes_ratio(int p)
+{
+    double t = pow(TR_EPS / (p + 2), 1.0 / (p - 2)); /* the bound without its 1/(1 - t)^2, then with it */
+    for (int k = 0; k < 3; ++k) t = pow(TR_EPS * (1.0 - t) * (1.0 - t) / (p + 2), 1.0 / (p - 2));
+    return 1.0 / t;
 }
 
 /* the smallest t = r/R (to 2%, rounded up) from which order p serves; single
@@ -172,7 +201,10 @@ __global__ __launch_bounds__(256) void tree_clusters_kernel(TreeDev T, const dou
     if (lane < TR_RM) {
         const double clear = R + near_factor * h * (1.0 + 1e-12);
         double v;
-        if (lane < TR_NP)
+        if (T.stokes)
+            v = lane < TR_SNP ? fmax(R * tree_stokes_ratio(TR_PMIN + TR_PSTEP * lane), clear)
+                              : (lane < TR_RM - 1 ? INFINITY : R);
+        else if (lane < TR_NP)
             v = fmax(R * tree_order_ratio(TR_PMIN + TR_PSTEP * lane, alpha * R), clear);
         else
             v = fmax(R + TR_ZZERO * (1.0 + 1e-12) / alpha, clear);
@@ -221,12 +253,18 @@ __global__ __launch_bounds__(256) void tree_lists_kernel(TreeDev T, const double
             const double rhi = (double)wave_max_f((float)r) * (1.0 + 3e-7);
             const double *rm = T.rmin + TR_RM * c;
             uint32_t y_ = 0xffffffffu;
-            if (rlo >= rm[TR_RM - 1]) {
+            bool expand = true, lap = false;
+            if (T.stokes) {
+                const double R = rm[TR_RM - 1], a = alpha * R, zc = alpha * (rlo - R);
+                lap = zc >= TR_SLAP;
+                expand = a >= TR_AMIN && (lap ? a <= TR_SAMAX : a <= TR_AMAX && zc >= TR_SZ);
+            }
+            if (!T.stokes && rlo >= rm[TR_RM - 1]) {
                 y_ = TR_ZERO;
-            } else {
-                for (int q = TR_NP - 1; q >= 0 && rlo >= rm[q]; --q) /* rm falls with the order */
+            } else if (expand) {
+                for (int q = TR_NP - 1 - T.stokes; /* the stresslet has one order fewer */ q >= 0 && rlo >= rm[q]; --q) /* rm falls with the order */
                     y_ = (uint32_t)(TR_PMIN + TR_PSTEP * q) << 8;
-                if (y_ != 0xffffffffu) y_ |= (uint32_t)tree_piece(alpha * rlo, alpha * rhi);
+                if (y_ != 0xffffffffu) y_ |= (uint32_t)tree_piece(alpha * rlo, alpha * rhi) | (lap ? TR_LAP : 0u);
             }
             if (y_ != 0xffffffffu) {
                 if (lane == 0) items[T.Np - 1 - nf] = make_uint2((uint32_t)c, y_);
@@ -445,7 +483,7 @@ __device__ __forceinline__ void tree_moments_rounds(const TreeDev &T, int k, int
             const int n = N + cb / NV;
             const int64_t p = p0 + pp;
             if ((pp & ((1 << k) - 1)) == 0 && p < T.Np && n < TR_ROWS)
-                T.mom[(T.off[k] + (p >> k)) * tr_stride(NV / 2) + n * NV + cb % NV] = s;
+                T.mom[(T.off[k] + (p >> k)) * tr_stride(NV) + n * NV + cb % NV] = s;
         }
         __syncthreads();
         tree_moments_rounds<SLP, DLP, GRAD, Z, R + RO>(T, k, p0, b, alpha, q, ex, ey, buf);
@@ -485,6 +523,163 @@ __device__ __forceinline__ void tree_moments_body(const FarArgs &A, const TreeDe
     TreeB<GRAD, Z> b;
     tree_regular<TreeB<GRAD, Z>::LO, TreeB<GRAD, Z>::CNT>(wr, wi, fma(wr, wr, wi * wi), b.br, b.bi);
     tree_moments_rounds<SLP, DLP, GRAD, Z, 0>(T, k, p0, b, A.alpha, q, ex, ey, buf);
+}
+
+/* rows of the stresslet: per complex field (the velocity; with GRAD its x and
+   y derivatives) the coefficients of K_n cos and K_n sin of its real and
+   imaginary part, then Re and Im of the power (2/z)^n e^{i n theta} (GRAD: of
+   the x derivative; the y derivative's is -i times it). */
+template <bool GRAD, int Z>
+struct TreeS {
+    static constexpr int H = GRAD ? 4 : 3, N0 = Z * TR_NG, LO = N0 < H ? 0 : N0 - H, CNT = N0 + TR_NG + H - LO;
+    double br[CNT], bi[CNT], pr[CNT], pi[CNT]; /* B_n and w^n */
+    cplx sg;                                   /* alpha sigma */
+    double tau, alpha;
+    template <int N>
+    __device__ __forceinline__ cplx b() const
+    {
+        return mk(br[N - LO], bi[N - LO]);
+    }
+    template <int N>
+    __device__ __forceinline__ cplx w() const
+    {
+        return mk(pr[N - LO], pi[N - LO]);
+    }
+    /* coefficient of O_K: -conj(sigma) R_{3-K} + sigma R_{-1-K} (times alpha), R_{-n} = B_n = conj R_n */
+    template <int K>
+    __device__ __forceinline__ cplx c() const
+    {
+        if constexpr (K >= 3) return sg * b<K + 1>() - conj(sg) * b<K - 3>();
+        else if constexpr (K >= 0) return sg * b<K + 1>() - conj(sg * b<3 - K>());
+        else return sg * conj(b<-K - 1>()) - conj(sg * b<3 - K>());
+    }
+    /* coefficient of (2/z)^N e^{i N theta} */
+    template <int N>
+    __device__ __forceinline__ cplx l() const
+    {
+        if constexpr (N < 1) return mk(0.0, 0.0);
+        else {
+            cplx v = (0.5 * alpha * tau) * w<N - 1>();
+            if constexpr (N >= 3) v = v + (0.5 * (N - 1) * (N - 2)) * (conj(sg) * w<N - 3>());
+            return v;
+        }
+    }
+    template <int N>
+    __device__ __forceinline__ void row(double (*v)[16 * TR_PAD], int at) const
+    {
+        if constexpr (!GRAD) {
+            put<N>(c<N>(), c<-N>(), v, at);
+            const cplx p = l<N>();
+            v[4][at] = p.re;
+            v[5][at] = p.im;
+        } else {
+            /* d_x: -(alpha/2)(C_{k-1} + C_{k+1}), d_y: (i alpha/2)(C_{k-1} - C_{k+1}) */
+            const double ah = 0.5 * alpha;
+            const cplx a = c<N - 1>(), b_ = c<N + 1>(), d = c<-N - 1>(), e = c<1 - N>();
+            put<N>(-ah * (a + b_), -ah * (d + e), v, at);
+            const cplx yp = ah * (a - b_), ym = ah * (d - e);
+            put<N>(mk(-yp.im, yp.re), mk(-ym.im, ym.re), v + 4, at);
+            const cplx p = (-ah * (N - 1)) * l<N - 1>();
+            v[8][at] = p.re;
+            v[9][at] = p.im;
+        }
+    }
+    template <int N>
+    static __device__ __forceinline__ void put(cplx p, cplx m, double (*v)[16 * TR_PAD], int at)
+    {
+        const bool z = N == 0; /* K_0: one coefficient */
+        v[0][at] = z ? p.re : p.re + m.re;
+        v[1][at] = z ? 0.0 : m.im - p.im;
+        v[2][at] = z ? p.im : p.im + m.im;
+        v[3][at] = z ? 0.0 : p.re - m.re;
+    }
+};
+
+template <bool GRAD, int Z, int R>
+__device__ __forceinline__ void tree_stokes_rounds(const TreeDev &T, int k, int64_t p0, const TreeS<GRAD, Z> &b,
+                                                   double (*buf)[16 * TR_PAD])
+{
+    constexpr int NV = GRAD ? 10 : 6, RO = GRAD ? 1 : 2, N = Z * TR_NG + R;
+    if constexpr (R < TR_NG && N < TR_ROWS) {
+        const int t = threadIdx.x, at = (t >> 4) * TR_PAD + (t & 15), pp = t & 15, cb = t >> 4;
+        b.template row<N>(buf, at);
+        if constexpr (RO > 1) b.template row<N + 1>(buf + NV, at);
+        __syncthreads();
+        if (cb < RO * NV) {
+            const double *row = buf[cb] + pp * TR_PAD;
+            double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+            for (int l = 0; l < 16; l += 2) {
+                s0 += row[l];
+                s1 += row[l + 1];
+            }
+            double s = s0 + s1;
+            for (int o = 1; o < (1 << k); o <<= 1) s += __shfl_xor(s, o);
+            const int n = N + cb / NV;
+            const int64_t p = p0 + pp;
+            if ((pp & ((1 << k) - 1)) == 0 && p < T.Np && n < TR_ROWS)
+                T.mom[(T.off[k] + (p >> k)) * tr_stride(NV) + n * NV + cb % NV] = s;
+        }
+        __syncthreads();
+        tree_stokes_rounds<GRAD, Z, R + RO>(T, k, p0, b, buf);
+    }
+}
+
+template <bool GRAD, int Z>
+__device__ __forceinline__ void tree_stokes_body(const FarArgs &A, const TreeDev &T, const double *mu,
+                                                 double (*buf)[16 * TR_PAD])
+{
+    const int k = blockIdx.y, t = threadIdx.x;
+    const int64_t p0 = (int64_t)blockIdx.x * 16, j = 16 * p0 + t;
+    const bool have = j < A.N;
+    const int64_t js = have ? j : A.N - 1;
+    const int64_t c = T.off[k] + ((js >> 4) >> k);
+    const double dx = A.sx[js] - T.cc[2 * c], dy = A.sy[js] - T.cc[2 * c + 1];
+    const double wj = have ? A.sw[js] : 0.0, nx = A.snx[js], ny = A.sny[js];
+    const double m1 = have ? wj * mu[js] : 0.0, m2 = have ? wj * mu[A.N + js] : 0.0;
+    TreeS<GRAD, Z> b;
+    b.alpha = A.alpha;
+    b.tau = fma(m1, nx, m2 * ny);
+    b.sg = (0.5 * A.alpha) * (mk(m1, m2) * mk(nx, ny));
+    if (Z == 0 && k == 0) {
+        if (have) {
+            double *s = T.st + (j >> 4) * 48 + (j & 15);
+            s[0] = m1;
+            s[16] = m2;
+        }
+        if (T.flux) {
+            double f = b.tau;
+            for (int o = 1; o < 16; o <<= 1) f += __shfl_xor(f, o);
+            if ((t & 15) == 0 && have) T.flux[j >> 4] = f;
+        }
+    }
+    const double ah = 0.5 * A.alpha, wr = ah * dx, wi = -ah * dy;
+    tree_regular<TreeS<GRAD, Z>::LO, TreeS<GRAD, Z>::CNT>(wr, wi, fma(wr, wr, wi * wi), b.br, b.bi);
+    double pr = 1.0, pi = 0.0;
+#pragma unroll
+    for (int n = 0; n < TreeS<GRAD, Z>::LO + TreeS<GRAD, Z>::CNT; ++n) {
+        if (n >= TreeS<GRAD, Z>::LO) {
+            b.pr[n - TreeS<GRAD, Z>::LO] = pr;
+            b.pi[n - TreeS<GRAD, Z>::LO] = pi;
+        }
+        const double q = fma(pr, wr, -pi * wi);
+        pi = fma(pr, wi, pi * wr);
+        pr = q;
+    }
+    tree_stokes_rounds<GRAD, Z, 0>(T, k, p0, b, buf);
+}
+
+template <bool GRAD>
+__global__ __launch_bounds__(256) void tree_stokes_kernel(FarArgs A, TreeDev T)
+{
+    __shared__ double buf[12][16 * TR_PAD];
+    const double *mu;
+    if (!far_density(A, mu)) return;
+    switch (blockIdx.z) {
+    case 0: tree_stokes_body<GRAD, 0>(A, T, mu, buf); break;
+    case 1: tree_stokes_body<GRAD, 1>(A, T, mu, buf); break;
+    default: tree_stokes_body<GRAD, 2>(A, T, mu, buf); break;
+    }
 }
 
 template <bool SLP, bool DLP, bool GRAD>
@@ -544,24 +739,47 @@ __device__ __forceinline__ void tree_k01_pc(int pc, const FarConst &fc, const do
     }
 }
 
-/* f += (v of lane L of the lane's row of 16) * s: the moments of an expansion
-   sit 32 to a pair of registers, repeated in every row of 16 lanes, and reach
-   the FMA as its broadcast operand.  v comes from a load and is never written
-   by the VALU before (no DPP hazard). */
-template <int L>
-__device__ __forceinline__ void fmac_row(double &f, double v, double s)
+/* f0 += a s0, f1 += b s1 with a, b the values AT, AT + 1 (AT even; SWAP: b, a) of
+   the moment table.  The table sits 32 doubles to a register quadruple, two
+   per lane and repeated in every row of 16 lanes, and reaches the FMA as its
+   row-broadcast operand.  A register that the VALU has just written may not be
+   read so before two wait states: the s_nop covers any copy the compiler puts
+   in front. */
+template <int AT, bool SWAP = false>
+__device__ __forceinline__ void fmac_pair(double &f0, double &f1, const double2 *m, double s0, double s1)
 {
-    asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(f) : "v"(v), "v"(s), "n"(L));
+    static_assert(AT % 2 == 0, "both values lie in one lane");
+    const double a = SWAP ? m[AT / 32].y : m[AT / 32].x, b = SWAP ? m[AT / 32].x : m[AT / 32].y;
+    asm("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %2, %4 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, %3, %5 row_newbcast:%6 row_mask:0xf bank_mask:0xf"
+        : "+&v"(f0), "+&v"(f1)
+        : "v"(a), "v"(b), "v"(s0), "v"(s1), "n"((AT % 32) / 2));
+}
+
+/* two fields of a row in one go (AT a multiple of 4) */
+template <int AT>
+__device__ __forceinline__ void fmac_quad(double &f0, double &f1, double &g0, double &g1, const double2 *m, double s0,
+                                          double s1)
+{
+    static_assert(AT % 4 == 0, "the four values lie in neighbouring lanes");
+    asm("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %4, %6 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, %5, %7 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %2, %4, %6 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %3, %5, %7 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
+        : "+&v"(f0), "+&v"(f1), "+&v"(g0), "+&v"(g1)
+        : "v"(m[AT / 32].x), "v"(m[AT / 32].y), "v"(s0), "v"(s1), "n"((AT % 32) / 2), "n"((AT % 32) / 2 + 1));
 }
 
 template <int NF, int N, int F>
 __device__ __forceinline__ void tree_row(const double2 *m, double kc, double ks, double (&f0)[NF], double (&f1)[NF])
 {
-    if constexpr (F < NF) {
-        constexpr int at = N * 2 * NF + 2 * F;
-        fmac_row<(at % 32) / 2>(f0[F], m[at / 32].x, kc);
-        if (N > 0) fmac_row<(at % 32) / 2>(f1[F], m[at / 32].y, ks);
-        tree_row<NF, N, F + 1>(m, kc, ks, f0, f1);
+    if constexpr (F + 1 < NF) {
+        fmac_quad<N * 2 * NF + 2 * F>(f0[F], f1[F], f0[F + 1], f1[F + 1], m, kc, ks);
+        tree_row<NF, N, F + 2>(m, kc, ks, f0, f1);
+    } else if constexpr (F < NF) {
+        fmac_pair<N * 2 * NF + 2 * F>(f0[F], f1[F], m, kc, ks);
     }
 }
 
@@ -593,15 +811,16 @@ __device__ __forceinline__ void tree_rows(int order, const double2 *m, double c2
    load) while K0 and K1 are formed: reading them order by order through the
    scalar cache left the kernel waiting (its 16 KB serve two CUs). */
 template <int NF>
-__device__ __forceinline__ void tree_expand(const FarConst &fc, const double *fq, const TreeDev &T, uint32_t c,
+__device__ __forceinline__ void tree_expand(const double *fq, const TreeDev &T, uint32_t c,
                                             int pc, int order, double x, double y, double (&f0)[NF])
 {
-    constexpr int NL = tr_stride(NF) / 32;
-    const double2 *mp = (const double2 *)(T.mom + (int64_t)c * tr_stride(NF)) + (threadIdx.x & 15);
+    constexpr int NL = tr_stride(2 * NF) / 32;
+    const double2 *mp = (const double2 *)(T.mom + (int64_t)c * tr_stride(2 * NF)) + (threadIdx.x & 15);
     double2 m[NL];
 #pragma unroll
     for (int l = 0; l < NL; ++l) m[l] = mp[16 * l];
     const MHLP_CAS double *cc = (const MHLP_CAS double *)T.cc + 2 * (int64_t)c;
+    const FarConst fc = far_const_of(fq);
     const double ex = x - cc[0], ey = y - cc[1];
     double ri, k0, k1;
     tree_k01_pc(pc, fc, fq, fma(ex, ex, ey * ey), ri, k0, k1);
@@ -613,6 +832,81 @@ __device__ __forceinline__ void tree_expand(const FarConst &fc, const double *fq
     tree_rows<NF, 1>(order, m, 2.0 * ct, h, h, k0, k1, 1.0, ct, 0.0, st, f0, f1);
 #pragma unroll
     for (int f = 0; f < NF; ++f) f0[f] += f1[f];
+}
+
+/* orders N and on of a stresslet expansion: NC complex fields (1: velocity, 2:
+   its x and y derivatives) of the K part in f0, f1 (as tree_rows), the power
+   part's four products in g.  LAP: the power part alone. */
+template <int NC, bool LAP, int N>
+__device__ __forceinline__ void tree_stokes_rows(int order, const double2 *m, double c2, double h, double b, double km,
+                                                 double k, double cp, double cn, double sp, double sn, double rho,
+                                                 double (&f0)[2 * NC], double (&f1)[2 * NC], double (&g)[4])
+{
+    constexpr int NV = 4 * NC + 2;
+    if constexpr (N < TR_ROWS) {
+        if (N > order) return;
+        const double rc = rho * cn, rs = rho * sn;
+        fmac_pair<N * NV + 4 * NC>(g[0], g[1], m, rc, rs);
+        fmac_pair<N * NV + 4 * NC, true>(g[2], g[3], m, rc, rs);
+        double kn = 0.0;
+        if constexpr (!LAP) {
+            const double kc = k * cn, ks = k * sn;
+            fmac_pair<N * NV>(f0[0], f1[0], m, kc, ks);
+            fmac_pair<N * NV + 2>(f0[1], f1[1], m, kc, ks);
+            if constexpr (NC == 2) {
+                fmac_pair<N * NV + 4>(f0[2], f1[2], m, kc, ks);
+                fmac_pair<N * NV + 6>(f0[3], f1[3], m, kc, ks);
+            }
+            kn = fma(b, k, km);
+        }
+        tree_stokes_rows<NC, LAP, N + 1>(order, m, c2, h, b + h, k, kn, cn, fma(c2, cn, -cp), sn, fma(c2, sn, -sp),
+                                         rho * h, f0, f1, g);
+    }
+}
+
+/* a cluster's stresslet field (NC = 1: u_1, u_2) or its gradient (NC = 2:
+   d_1 u_1, d_2 u_1, d_1 u_2, d_2 u_2), times 2 pi */
+template <int NC>
+__device__ __forceinline__ void tree_expand_stokes(const double *fq, const TreeDev &T, uint32_t c,
+                                                   uint32_t fl, int order, double x, double y, double (&f)[2 * NC])
+{
+    constexpr int NV = 4 * NC + 2, NL = tr_stride(NV) / 32;
+    const double2 *mp = (const double2 *)(T.mom + (int64_t)c * tr_stride(NV)) + (threadIdx.x & 15);
+    double2 m[NL];
+#pragma unroll
+    for (int l = 0; l < NL; ++l) m[l] = mp[16 * l];
+    const MHLP_CAS double *cc = (const MHLP_CAS double *)T.cc + 2 * (int64_t)c;
+    const FarConst fc = far_const_of(fq);
+    const double ex = x - cc[0], ey = y - cc[1], r2 = fma(ex, ex, ey * ey);
+    double f0[2 * NC], f1[2 * NC], g[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int n = 0; n < 2 * NC; ++n) f0[n] = f1[n] = 0.0;
+    if (fl & TR_LAP) {
+        const double ri = lean_rsq(r2), ct = ex * ri, h = 2.0 * fc.ia * ri;
+        tree_stokes_rows<NC, true, 1>(order, m, 2.0 * ct, h, 0.0, 0.0, 0.0, 1.0, ct, 0.0, ey * ri, h, f0, f1, g);
+    } else {
+        double ri, k0, k1;
+        tree_k01_pc((int)(fl & 31) - 1, fc, fq, r2, ri, k0, k1);
+        const double ct = ex * ri, h = 2.0 * fc.ia * ri;
+        /* row 0 has no sine: its second values are zero */
+        fmac_pair<0>(f0[0], f1[0], m, k0, 0.0);
+        fmac_pair<2>(f0[1], f1[1], m, k0, 0.0);
+        if constexpr (NC == 2) {
+            fmac_pair<4>(f0[2], f1[2], m, k0, 0.0);
+            fmac_pair<6>(f0[3], f1[3], m, k0, 0.0);
+        }
+        tree_stokes_rows<NC, false, 1>(order, m, 2.0 * ct, h, h, k0, k1, 1.0, ct, 0.0, ey * ri, h, f0, f1, g);
+    }
+    const double gr = g[0] - g[1], gi = g[2] + g[3];
+    if constexpr (NC == 1) {
+        f[0] = f0[0] + f1[0] + gr;
+        f[1] = f0[1] + f1[1] + gi;
+    } else {
+        f[0] = f0[0] + f1[0] + gr;
+        f[2] = f0[1] + f1[1] + gi;
+        f[1] = f0[2] + f1[2] + gi;
+        f[3] = f0[3] + f1[3] - gr;
+    }
 }
 
 /* whether a staged charge or dipole of the cluster is infinite or NaN */
@@ -628,28 +922,31 @@ __device__ __forceinline__ bool tree_bad(const TreeDev &T, int64_t p0, int64_t p
     return __ballot(!(s == 0.0)) != 0;
 }
 
-/* What a far sum evaluates.  NF fields, EXTRA orders beyond the list's;
+/* What a far sum evaluates.  NF fields, EXTRA orders beyond the list's, blocks
+   of up to WMAX waves;
    panel<PC>: staged sources s0..s1-1 of panel p against the lane's target in
    piece PC (-1: z <= 2; KQ_NP: per pair), added to f (sources come through the
    scalar cache, two at a time); near: the correction of node jj of the listed
-   pair q; store: field f of target i.  The sums carry no 1/(2 pi) until they
-   leave the wave. */
+   pair q; store: field f of target i, common what every store of a wave shares.  The sums
+   carry no 1/(2 pi) until they leave the wave. */
 template <bool SLP, bool DLP>
 struct TreePot {
-    static constexpr int NF = (SLP ? 1 : 0) + (DLP ? 1 : 0), EXTRA = 0;
+    static constexpr int NF = (SLP ? 1 : 0) + (DLP ? 1 : 0), EXTRA = 0, WMAX = 16;
     template <int PC>
-    static __device__ __forceinline__ void panel(const FarArgs &A, const FarConst &fc, const TreeDev &D, int64_t p,
+    static __device__ __forceinline__ void panel(const FarArgs &A, const TreeDev &D, int64_t p,
                                                  int s0, int s1, double x, double y, double (&f)[NF])
     {
         constexpr int K = PC < 0 || PC >= KQ_NP ? 0 : PC;
         const MHLP_CAS double *sx = (const MHLP_CAS double *)A.sx + 16 * p;
         const MHLP_CAS double *sy = (const MHLP_CAS double *)A.sy + 16 * p;
         const MHLP_CAS double *st = (const MHLP_CAS double *)D.st + 48 * p;
-        const FarTab T = far_table();
+        FarTab T = far_table();
+        const FarConst fc = far_const_of(A.fq);
         double qa, qk;
         fine_q<K>(A.fq, qa, qk);
 #pragma unroll 1
         for (int s = s0; s < s1; s += 2) {
+            if (PC < 0 || PC >= KQ_NP) T = far_table(); /* their coefficients exceed the scalar registers */
             const double ex0 = x - sx[s], ey0 = y - sy[s];
             const double ex1 = x - sx[s + 1], ey1 = y - sy[s + 1];
             const double r20 = fma(ex0, ex0, ey0 * ey0), r21 = fma(ex1, ex1, ey1 * ey1);
@@ -670,7 +967,8 @@ struct TreePot {
         if (SLP) n[0] = fma(A.wsl[16 * q + jj], A.sigma[16 * p + jj], n[0]);
         if (DLP) n[NF - 1] = fma(A.wdl[16 * q + jj], mu[16 * p + jj], n[NF - 1]);
     }
-    static __device__ __forceinline__ void store(const FarArgs &A, const double *mu, int64_t i, int f, double v)
+    static __device__ __forceinline__ void store(const FarArgs &A, double, const double *mu, int64_t i, int f,
+                                                 double v)
     {
         const int64_t o = A.perm ? (int64_t)A.perm[i] : i;
         if (SLP && f == 0) {
@@ -684,25 +982,33 @@ struct TreePot {
     {
         return tree_bad<SLP, DLP>(T, p0, p1);
     }
+    static __device__ __forceinline__ double common(const FarArgs &, const TreeDev &) { return 0.0; }
+    static __device__ __forceinline__ void expand(const double *fq, const TreeDev &T, uint32_t c,
+                                                  uint32_t fl, double x, double y, double (&f)[NF])
+    {
+        tree_expand<NF>(fq, T, c, (int)(fl & 31) - 1, ((int)(fl >> 8) & 63) + EXTRA, x, y, f);
+    }
 };
 
 /* the target gradients: d_x S, d_y S, d_x D, d_y D (without the absent layer's) */
 template <bool SLP, bool DLP>
 struct TreeGrad {
-    static constexpr int NF = (SLP ? 2 : 0) + (DLP ? 2 : 0), EXTRA = TR_GRAD;
+    static constexpr int NF = (SLP ? 2 : 0) + (DLP ? 2 : 0), EXTRA = TR_GRAD, WMAX = 16;
     template <int PC>
-    static __device__ __forceinline__ void panel(const FarArgs &A, const FarConst &fc, const TreeDev &D, int64_t p,
+    static __device__ __forceinline__ void panel(const FarArgs &A, const TreeDev &D, int64_t p,
                                                  int s0, int s1, double x, double y, double (&f)[NF])
     {
         constexpr int K = PC < 0 || PC >= KQ_NP ? 0 : PC;
         const MHLP_CAS double *sx = (const MHLP_CAS double *)A.sx + 16 * p;
         const MHLP_CAS double *sy = (const MHLP_CAS double *)A.sy + 16 * p;
         const MHLP_CAS double *st = (const MHLP_CAS double *)D.st + 48 * p;
-        const FarTab T = far_table();
+        FarTab T = far_table();
+        const FarConst fc = far_const_of(A.fq);
         double qa, qk;
         fine_q<K>(A.fq, qa, qk);
 #pragma unroll 1
         for (int s = s0; s < s1; s += 2) {
+            if (PC < 0 || PC >= KQ_NP) T = far_table(); /* their coefficients exceed the scalar registers */
             const double ex0 = x - sx[s], ey0 = y - sy[s];
             const double ex1 = x - sx[s + 1], ey1 = y - sy[s + 1];
             const double r20 = fma(ex0, ex0, ey0 * ey0), r21 = fma(ex1, ex1, ey1 * ey1);
@@ -743,7 +1049,8 @@ struct TreeGrad {
             n[NF - 1] = fma(A.wg[3 * block + o], m, n[NF - 1]);
         }
     }
-    static __device__ __forceinline__ void store(const FarArgs &A, const double *, int64_t i, int f, double v)
+    static __device__ __forceinline__ void store(const FarArgs &A, double, const double *, int64_t i, int f,
+                                                 double v)
     {
         A.gout[SLP ? f : f + 2][A.perm ? (int64_t)A.perm[i] : i] = v;
     }
@@ -751,22 +1058,122 @@ struct TreeGrad {
     {
         return tree_bad<SLP, DLP>(T, p0, p1);
     }
+    static __device__ __forceinline__ double common(const FarArgs &, const TreeDev &) { return 0.0; }
+    static __device__ __forceinline__ void expand(const double *fq, const TreeDev &T, uint32_t c,
+                                                  uint32_t fl, double x, double y, double (&f)[NF])
+    {
+        tree_expand<NF>(fq, T, c, (int)(fl & 31) - 1, ((int)(fl >> 8) & 63) + EXTRA, x, y, f);
+    }
+};
+
+/* the stresslet double layer, and with GRAD its target gradient */
+template <bool GRAD>
+struct TreeStokes {
+    /* the gradient needs more than the 128 registers of a 16-wave block */
+    static constexpr int NF = GRAD ? 4 : 2, WMAX = GRAD ? 8 : 16;
+    template <int PC>
+    static __device__ __forceinline__ void panel(const FarArgs &A, const TreeDev &D, int64_t p,
+                                                 int s0, int s1, double x, double y, double (&f)[NF])
+    {
+        constexpr int K = PC < 0 || PC >= KQ_NP ? 0 : PC;
+        const MHLP_CAS double *sx = (const MHLP_CAS double *)A.sx + 16 * p;
+        const MHLP_CAS double *sy = (const MHLP_CAS double *)A.sy + 16 * p;
+        const MHLP_CAS double *snx = (const MHLP_CAS double *)A.snx + 16 * p;
+        const MHLP_CAS double *sny = (const MHLP_CAS double *)A.sny + 16 * p;
+        const MHLP_CAS double *st = (const MHLP_CAS double *)D.st + 48 * p;
+        FarTab T = far_table();
+        const FarConst fc = far_const_of(A.fq);
+        double qa, qk, al2, ial2;
+        far_squares_of(A.fq, al2, ial2);
+        fine_q<K>(A.fq, qa, qk);
+        double a[NF];
+#pragma unroll
+        for (int n = 0; n < NF; ++n) a[n] = 0.0;
+#pragma unroll 1
+        for (int s = s0; s < s1; s += 2) {
+            if (PC < 0 || PC >= KQ_NP) T = far_table(); /* their coefficients exceed the scalar registers */
+            const double ex[2] = {x - sx[s], x - sx[s + 1]}, ey[2] = {y - sy[s], y - sy[s + 1]};
+            const double r20 = fma(ex[0], ex[0], ey[0] * ey[0]), r21 = fma(ex[1], ex[1], ey[1] * ey[1]);
+            double Ak[2][3], Bk[2][3];
+            if constexpr (GRAD)
+                stk_far2_ab_pc<PC>(T, fc, qa, qk, al2, ial2, r20, r21, Ak[0], Bk[0], Ak[1], Bk[1]);
+            else
+                stk_far2_pc<PC>(T, fc, qa, qk, al2, ial2, r20, r21, Ak[0], Ak[1]);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const double nx = snx[s + u], ny = sny[s + u], m1 = st[s + u], m2 = st[16 + s + u];
+                const double *A_ = Ak[u];
+                const double rn = fma(ex[u], nx, ey[u] * ny);
+                const double rm = fma(ex[u], m1, ey[u] * m2);
+                const double nm = fma(nx, m1, ny * m2);
+                if constexpr (!GRAD) {
+                    const double c = fma(A_[1] * rm, rn, A_[2] * nm);
+                    a[0] -= fma(A_[0], fma(nx, rm, fma(ex[u], nm, m1 * rn)), c * ex[u]);
+                    a[1] -= fma(A_[0], fma(ny, rm, fma(ey[u], nm, m2 * rn)), c * ey[u]);
+                } else {
+                    const double *b = Bk[u];
+                    const double sr = fma(b[1] * rn, rm, (b[0] + b[2]) * nm);
+                    const double p1 = fma(b[0], fma(nx, rm, m1 * rn), ex[u] * sr);
+                    const double p2 = fma(b[0], fma(ny, rm, m2 * rn), ey[u] * sr);
+                    const double a1 = fma(A_[0], m1, A_[1] * rm * ex[u]), a2 = fma(A_[0], m2, A_[1] * rm * ey[u]);
+                    const double c1 = fma(A_[0], nx, A_[1] * rn * ex[u]), c2 = fma(A_[0], ny, A_[1] * rn * ey[u]);
+                    const double d = fma(A_[0] + A_[2], nm, A_[1] * rn * rm);
+                    a[0] -= fma(ex[u], p1, fma(nx, a1, fma(m1, c1, d)));
+                    a[1] -= fma(ey[u], p1, fma(ny, a1, m2 * c1));
+                    a[2] -= fma(ex[u], p2, fma(nx, a2, m1 * c2));
+                    a[3] -= fma(ey[u], p2, fma(ny, a2, fma(m2, c2, d)));
+                }
+            }
+        }
+#pragma unroll
+        for (int n = 0; n < NF; ++n) f[n] = fma(2.0 * PI, a[n], f[n]);
+    }
+    static __device__ __forceinline__ void expand(const double *fq, const TreeDev &T, uint32_t c,
+                                                  uint32_t fl, double x, double y, double (&f)[NF])
+    {
+        tree_expand_stokes<NF / 2>(fq, T, c, fl, ((int)(fl >> 8) & 63) + (GRAD ? TR_SGRAD : 0), x, y, f);
+    }
+    static __device__ __forceinline__ void near(const FarArgs &A, const double *mu, int64_t q, int64_t p, int jj,
+                                                double (&n)[NF])
+    {
+        /* blocks of [nnz][16]: D11 D12 D21 D22, or d_l u_i per mu_j at (2 i + l) 2 + j */
+        const double m1 = mu[16 * p + jj], m2 = mu[A.N + 16 * p + jj];
+        const int64_t block = 16 * A.nnz;
+        const double *w = A.wg + 16 * q + jj;
+#pragma unroll
+        for (int k = 0; k < NF; ++k) n[k] = fma(w[2 * k * block], m1, fma(w[(2 * k + 1) * block], m2, n[k]));
+    }
+    /* sum of the panels' fluxes over |Gamma|, the same in every lane of the (whole) wave */
+    static __device__ __forceinline__ double common(const FarArgs &A, const TreeDev &T)
+    {
+        if (GRAD || A.half_term == 0.0) return 0.0;
+        double s = 0.0;
+        for (int64_t p = threadIdx.x & 63; p < T.Np; p += 64) s += T.flux[p];
+        return wave_sum_dpp(s) * A.inv_len;
+    }
+    static __device__ __forceinline__ void store(const FarArgs &A, double flux, const double *mu, int64_t i, int f,
+                                                 double v)
+    {
+        /* on-surface operator: + 1/2 mu + n flux/|Gamma| */
+        if (!GRAD && A.half_term != 0.0) v = fma(A.half_term, mu[f * A.N + i], fma((f ? A.sny : A.snx)[i], flux, v));
+        A.gout[f][A.perm ? (int64_t)A.perm[i] : i] = v;
+    }
+    static __device__ __forceinline__ bool bad(const TreeDev &, int64_t, int64_t) { return false; }
 };
 
 template <class Op, class Args>
-__device__ __forceinline__ void tree_panel(int pc, const Args &A, const FarConst &fc, const TreeDev &T, int64_t p,
+__device__ __forceinline__ void tree_panel(int pc, const Args &A, const TreeDev &T, int64_t p,
                                            int s0, int s1, double x, double y, double (&f)[Op::NF])
 {
     switch (pc) {
 #define MHLP_TREE_PANEL(PCV) \
-    case PCV: Op::template panel<PCV>(A, fc, T, p, s0, s1, x, y, f); break;
+    case PCV: Op::template panel<PCV>(A, T, p, s0, s1, x, y, f); break;
         MHLP_PC_CASES(MHLP_TREE_PANEL)
 #undef MHLP_TREE_PANEL
-    default: Op::template panel<KQ_NP>(A, fc, T, p, s0, s1, x, y, f);
+    default: Op::template panel<KQ_NP>(A, T, p, s0, s1, x, y, f);
     }
 }
 
-constexpr int TR_WMAX = 16; /* waves of a block at most */
 
 /* One block per group of 64 targets (lane = target), in the order of the
    groups' work; the waves of the gridDim.y blocks of a group share its items:
@@ -785,10 +1192,10 @@ constexpr int TR_WMAX = 16; /* waves of a block at most */
    where the longest wave (a direct panel in one wave takes about 20 us) sets
    the time. */
 template <class Op>
-__global__ __launch_bounds__(64 * TR_WMAX) void far_tree_kernel(FarArgs A, TreeDev T)
+__global__ __launch_bounds__(64 * Op::WMAX) void far_tree_kernel(FarArgs A, TreeDev T)
 {
     constexpr int NF = Op::NF;
-    __shared__ double red[NF][TR_WMAX][64];
+    __shared__ double red[NF][Op::WMAX][64];
     const double *mu;
     if (!far_density(A, mu)) return;
     const int lane = threadIdx.x & 63, W = blockDim.x >> 6;
@@ -802,7 +1209,6 @@ __global__ __launch_bounds__(64 * TR_WMAX) void far_tree_kernel(FarArgs A, TreeD
     const int NW = W * gridDim.y, wg = w * gridDim.y + blockIdx.y;
     const int2 cnt = T.cnt[g];
     const uint2 *items = T.items + g * T.Np;
-    const FarConst fc = far_const(A.alpha);
     double acc[NF];
 #pragma unroll
     for (int f = 0; f < NF; ++f) acc[f] = 0.0;
@@ -818,7 +1224,7 @@ __global__ __launch_bounds__(64 * TR_WMAX) void far_tree_kernel(FarArgs A, TreeD
         double f[NF];
 #pragma unroll
         for (int n = 0; n < NF; ++n) f[n] = 0.0;
-        tree_panel<Op>((int)(fl & 31) - 1, A, fc, T, p, s0, s0 + nsrc, x, y, f);
+        tree_panel<Op>((int)(fl & 31) - 1, A, T, p, s0, s0 + nsrc, x, y, f);
 #pragma unroll
         for (int n = 0; n < NF; ++n) acc[n] += f[n];
     }
@@ -835,7 +1241,7 @@ __global__ __launch_bounds__(64 * TR_WMAX) void far_tree_kernel(FarArgs A, TreeD
             tree_panels_of(T, c, p0, p1);
             direct = Op::bad(T, p0, p1);
         } else {
-            tree_expand<NF>(fc, A.fq, T, c, (int)(fl & 31) - 1, ((int)(fl >> 8) & 63) + Op::EXTRA, x, y, f);
+            Op::expand(A.fq, T, c, fl, x, y, f);
             bool fin = true;
 #pragma unroll
             for (int n = 0; n < NF; ++n) fin = fin && __builtin_isfinite(f[n]);
@@ -846,7 +1252,7 @@ __global__ __launch_bounds__(64 * TR_WMAX) void far_tree_kernel(FarArgs A, TreeD
             for (int n = 0; n < NF; ++n) f[n] = 0.0;
             int64_t p0, p1;
             tree_panels_of(T, c, p0, p1);
-            for (int64_t p = p0; p < p1; ++p) Op::template panel<KQ_NP>(A, fc, T, p, 0, 16, x, y, f);
+            for (int64_t p = p0; p < p1; ++p) Op::template panel<KQ_NP>(A, T, p, 0, 16, x, y, f);
         }
 #pragma unroll
         for (int n = 0; n < NF; ++n) acc[n] += f[n];
@@ -862,6 +1268,7 @@ __global__ __launch_bounds__(64 * TR_WMAX) void far_tree_kernel(FarArgs A, TreeD
         }
 #pragma unroll
     for (int f = 0; f < NF; ++f) red[f][w][lane] = fma(INV_2PI, acc[f], nr[f]);
+    const double cm = gridDim.y > 1 ? 0.0 : Op::common(A, T); /* every lane takes part */
     __syncthreads();
     if (!valid) return;
     for (int f = w; f < NF; f += W) {
@@ -870,7 +1277,7 @@ __global__ __launch_bounds__(64 * TR_WMAX) void far_tree_kernel(FarArgs A, TreeD
         if (gridDim.y > 1)
             T.part[((int64_t)f * gridDim.y + blockIdx.y) * A.M + i] = s;
         else
-            Op::store(A, mu, i, f, s);
+            Op::store(A, cm, mu, i, f, s);
     }
 }
 
@@ -881,6 +1288,7 @@ __global__ __launch_bounds__(64) void tree_finalize(FarArgs A, TreeDev T, int ns
 {
     const double *mu;
     if (!far_density(A, mu)) return;
+    const double cm = Op::common(A, T); /* every lane takes part */
     const int64_t i = blockIdx.x * (int64_t)64 + threadIdx.x;
     if (i >= A.M) return;
     const int f = blockIdx.y;
@@ -888,7 +1296,7 @@ __global__ __launch_bounds__(64) void tree_finalize(FarArgs A, TreeDev T, int ns
     double s = 0.0;
 #pragma unroll 4
     for (int k = 0; k < nsplit; ++k) s += part[k * A.M];
-    Op::store(A, mu, i, f, s);
+    Op::store(A, cm, mu, i, f, s);
 }
 
 } // namespace mhlp

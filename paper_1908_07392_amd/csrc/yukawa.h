@@ -438,8 +438,13 @@ __device__ __forceinline__ void k01_far2_big(FarTab T, const FarConst &c, double
    of piece K through an opaque pointer, once per panel, into scalar
    registers (the compiler cannot hoist the reads of all pieces out of the
    loops, where they would stay live). */
+constexpr int FINE_SCALES = 2 * KQ_NP + 10; /* then the FarConst (far_const_of), alpha^2 and 1/alpha^2 */
 __host__ inline void fine_scales(double alpha, double *q)
 {
+    const double ia = 1.0 / alpha;
+    const double c[10] = {alpha,    0.25 * alpha * alpha, 4.0 / alpha, ia,            6.0 * ia,
+                          120.0 / 7.0 * ia, -13.0 / 7.0,  40.0 * ia,   alpha * alpha, ia * ia};
+    for (int k = 0; k < 10; ++k) q[2 * KQ_NP + k] = c[k];
     for (int k = 0; k < KQ_NP; ++k) {
         const double w = 2.0 / (KQ_UHI[k] - KQ_ULO[k]);
         q[k] = 4.0 / alpha * w;
@@ -454,6 +459,23 @@ __device__ __forceinline__ void fine_q(const double *fq, double &qa, double &qk)
     asm volatile("" : "+s"(q));
     qa = q[K];
     qk = q[KQ_NP + K];
+}
+
+/* the FarConst of fine_scales' alpha, read into scalar registers where it is
+   used (far_const forms it in vector registers, which it then occupies) */
+__device__ __forceinline__ FarConst far_const_of(const double *fq)
+{
+    const MHLP_CAS double *q = (const MHLP_CAS double *)fq;
+    asm volatile("" : "+s"(q));
+    q += 2 * KQ_NP;
+    return FarConst{q[0], q[1], q[2], q[3], q[4], q[5], q[6], q[7]};
+}
+__device__ __forceinline__ void far_squares_of(const double *fq, double &al2, double &ial2)
+{
+    const MHLP_CAS double *q = (const MHLP_CAS double *)fq;
+    asm volatile("" : "+s"(q));
+    al2 = q[2 * KQ_NP + 8];
+    ial2 = q[2 * KQ_NP + 9];
 }
 
 template <bool SLP, bool DLP, int K>

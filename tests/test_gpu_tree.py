@@ -139,3 +139,66 @@ def test_tree_gradients_vs_plain_sums(panels, m, alpha):
             bd = ((alpha ** 2 * k0 + 3 * A) * np.abs(d) * f64).sum(axis=1)
             assert (np.abs(u[c].cpu().numpy()[sel] + (A * e * q).sum(axis=1)) <= bs + 1e-300).all()
             assert (np.abs(v[c].cpu().numpy()[sel] - ((A * n - B * e) * d).sum(axis=1)) <= bd + 1e-300).all()
+
+
+def _stokeslets_T(alpha, r):
+    z = alpha * r
+    k0, zk1 = sp.k0(z), z * sp.k1(z)
+    a1 = -(2 * z * z * k0 + (z * z + 4) * zk1 - 4) / (2 * np.pi * alpha ** 2 * r ** 4)
+    a2 = (4 * z * z * k0 + (z * z + 8) * zk1 - 8) / (np.pi * alpha ** 2 * r ** 6)
+    a3 = (zk1 - 1) / (2 * np.pi * r * r)
+    return k0, zk1, a1, a2, a3
+
+
+@pytest.mark.parametrize("panels,m,alpha", [(29, 1, 6.0), (33, 900, 12.0), (64, 5500, 25.0), (31, 11000, 60.0),
+                                            (40, 41000, 9.0), (37, 77000, 300.0)])
+def test_tree_stresslet_vs_plain_sums(panels, m, alpha):
+    """Velocity and velocity gradient against the closed forms of App. B term by term.  Their brackets cancel
+    like z^2/8, in the reference and in the expansions alike: a term's bound is the potentials' times
+    1 + 16/z^2, of |m| 2/(pi r) for the velocity and of |m| 8/(pi r^2) for its derivatives."""
+    g, tx, ty, m1, m2 = _setup(panels, m, panels + m)
+    P = mhlp.Plan(mhlp.Geometry(_t(g.node_soa())), alpha, _t(tx), _t(ty), stokes=True)
+    mu = _t(np.stack([m1, m2]))
+    sel = np.unique(np.linspace(0, m - 1, min(m, 300)).astype(int))
+    e = [tx[sel][:, None] - g.x, ty[sel][:, None] - g.y]
+    r = np.hypot(*e)
+    n, d = g.normals, [g.weights * m1, g.weights * m2]
+    k0, zk1, a1, a2, a3 = _stokeslets_T(alpha, r)
+    rn, rm, nm = e[0] * n[0] + e[1] * n[1], e[0] * d[0] + e[1] * d[1], n[0] * d[0] + n[1] * d[1]
+    size = np.hypot(*d) * (3e-14 + 5e-16 * alpha * r) * (1 + 16 / (alpha * r) ** 2)
+    u = mhlp.stokes_eval(P, mu).cpu().numpy()
+    for i in range(2):
+        ref = -(a1 * (n[i] * rm + e[i] * nm + d[i] * rn) + (a2 * rm * rn + a3 * nm) * e[i]).sum(axis=1)
+        assert (np.abs(u[i][sel] - ref) <= (2 / (np.pi * r) * size).sum(axis=1)).all()
+    ak0 = alpha ** 2 * k0
+    b1 = (ak0 / (2 * np.pi) - 4 * a1) / r ** 2
+    b2 = -(ak0 + 2 * zk1 / r ** 2) / (np.pi * r ** 4) - 6 * a2 / r ** 2
+    b3 = -(ak0 / (2 * np.pi) + 2 * a3) / r ** 2
+    gr = mhlp.stokes_eval_grad(P, mu).cpu().numpy()
+    for i in range(2):
+        for l in range(2):
+            p1 = n[i] * rm + e[i] * nm + d[i] * rn
+            dp1 = n[i] * d[l] + (i == l) * nm + d[i] * n[l]
+            dp2 = (i == l) * rm * rn + e[i] * (d[l] * rn + rm * n[l])
+            ref = -(e[l] * (b1 * p1 + b2 * e[i] * rm * rn + b3 * e[i] * nm) + a1 * dp1 + a2 * dp2 +
+                    a3 * (i == l) * nm).sum(axis=1)
+            assert (np.abs(gr[i][l][sel] - ref) <= (8 / (np.pi * r * r) * size).sum(axis=1)).all()
+
+
+@pytest.mark.parametrize("panels,alpha", [(3, 3.0), (17, 40.0), (170, 8.0), (300, 200.0)])
+def test_tree_onsurface_stresslet_on_the_circle(panels, alpha):
+    """(1/2 I + D + W) mu on the circle, at target counts that are no multiple of 64 and at every split: linear,
+    and by rotational symmetry a multiple of n for mu = n."""
+    g = wl.discretize(wl.Curve("circle", R=1.0), panels)
+    P = mhlp.Plan(mhlp.Geometry(_t(g.node_soa())), alpha, stokes=True)
+    nx, ny = g.normals
+    rng = np.random.default_rng(panels)
+    c = rng.standard_normal(4)
+    a = np.stack([np.cos(2 * g.theta), np.sin(3 * g.theta)])
+    b = np.stack([nx, ny])
+    A, B, AB = (mhlp.stokes_apply_bie(P, _t(v)).cpu().numpy() for v in (a, b, c[0] * a + c[1] * b))
+    assert np.max(np.abs(AB - c[0] * A - c[1] * B)) < 1e-12 * (np.abs(A).max() + np.abs(B).max())
+    tang = B[0] * ny - B[1] * nx
+    norm = B[0] * nx + B[1] * ny
+    tol = 1e-11 if panels > 3 else 1e-6
+    assert np.max(np.abs(tang)) < tol and np.max(np.abs(norm - norm[0])) < tol
