@@ -131,6 +131,7 @@ struct mhlp_plan {
                                  mixed-precision tiles */
     double *fqd = nullptr;    /* [FINE_SCALES] fine-piece scales and constants at alpha (fine_scales) */
     mhlp::TreeDev *tree = nullptr; /* clusters, item lists, moments (tree.h) */
+    unsigned long long tr_cost = 0; /* total work of the item lists */
     int tr_waves = 0, tr_split = 1; /* waves per block and blocks per group of far_tree_kernel */
     NearParams np{};
     double near_factor = 1.2;
@@ -1097,17 +1098,15 @@ struct GsrShared {
     double col[GSF_RMAX + 2], rot[2 * GSF_RMAX];
 };
 
-/* The one-block CGS2 step on w (length N), by every thread of a GSF_T block. */
+/* CGS2 of w (length N) against V_0..V_{ncol-1}, by every thread of a GSF_T
+   block: the new vector in x, the two passes' coefficients in sh.hs and the
+   squared norm in sh.hnl. */
 template <int E>
-__device__ __forceinline__ void gsr_body(GState *__restrict__ gs, double *__restrict__ V, int64_t ld,
-                                         const double *__restrict__ w, int64_t N, double *__restrict__ H, int R,
-                                         double *__restrict__ cs, double *__restrict__ sn, double *__restrict__ gv,
-                                         GsrShared &sh)
+__device__ __forceinline__ void gsr_orth(const double *__restrict__ V, int64_t ld, const double *__restrict__ w,
+                                         int64_t N, int ncol, double (&x)[E], GsrShared &sh)
 {
     constexpr int C = 32 / E;
     const int t = threadIdx.x, wv = t >> 6, ln = t & 63;
-    const int j = gs->j, ncol = j + 1;
-    double x[E];
 #pragma unroll
     for (int k = 0; k < E; ++k) {
         const int64_t i = t + (int64_t)k * GSF_T;
@@ -1154,6 +1153,18 @@ __device__ __forceinline__ void gsr_body(GState *__restrict__ gs, double *__rest
         sh.hnl[0] = s2;
     }
     __syncthreads();
+}
+
+/* The one-block CGS2 step on w (length N), by every thread of a GSF_T block. */
+template <int E>
+__device__ __forceinline__ void gsr_body(GState *__restrict__ gs, double *__restrict__ V, int64_t ld,
+                                         const double *__restrict__ w, int64_t N, double *__restrict__ H, int R,
+                                         double *__restrict__ cs, double *__restrict__ sn, double *__restrict__ gv,
+                                         GsrShared &sh)
+{
+    const int t = threadIdx.x, j = gs->j;
+    double x[E];
+    gsr_orth<E>(V, ld, w, N, j + 1, x, sh);
     gs_finish_block(gs, H, R, cs, sn, gv, sh.hs[0], sh.hs[1], sh.hnl[0], sh.col, sh.rot);
     if (gs->done) return; /* written by thread 0 before the block's last barrier */
     const double inv = gs->inv;
@@ -1950,7 +1961,7 @@ extern "C" mhlp_status mhlp_plan_destroy(mhlp_plan *P)
     delete P->fmm;
     if (P->tree) {
         void *tp[] = {P->tree->cc, P->tree->rmin, P->tree->mom, P->tree->st, P->tree->items, P->tree->cnt, P->tree->order,
-                      P->tree->part, P->tree->flux};
+                      P->tree->part, P->tree->flux, P->tree->cost};
         for (void *p : tp)
             if (p) (void)hipFree(p);
         delete P->tree;
@@ -2008,6 +2019,7 @@ static mhlp_status tree_setup(mhlp_plan *P, hipStream_t st)
     TRY(dalloc(&T.items, G * Np));
     TRY(dalloc(&T.cnt, G));
     TRY(dalloc(&T.order, G));
+    TRY(dalloc(&T.cost, 1));
     /* waves per group of 64 targets (blocks of 8, 16 or 4 waves; direct items
        cut into 2^cut units), by the number of groups: enough waves to fill the
        chip.  Measured us per evaluation (starfish, 4096 sources, alpha = 5) with
@@ -2033,6 +2045,7 @@ static mhlp_status tree_setup(mhlp_plan *P, hipStream_t st)
                                                            P->near_factor, P->alpha, P->near_ptr, P->near_panel);
     mhlp::tree_order_kernel<<<1, 1024, 0, st>>>(T, G);
     HIPCHECK(hipGetLastError());
+    HIPCHECK(hipMemcpyAsync(&P->tr_cost, T.cost, sizeof(P->tr_cost), hipMemcpyDeviceToHost, st));
     HIPCHECK(hipStreamSynchronize(st)); /* later calls may come on other streams */
     return MHLP_OK;
 }
@@ -3740,12 +3753,14 @@ constexpr int BATCH_R_MAX = 4;
 struct BatchGeo {
     const double *x, *y, *w, *nx, *ny;
     const int32_t *nptr, *npan;
-    const double *wdl;
+    const double *wdl, *fq;
     int64_t N, Np;
     double alpha;
     int64_t voff; /* offset of the geometry's [R][N] block in batched vectors */
     int64_t poff; /* offset of its partial sums [nsplit][R][N]                 */
-    int32_t nsplit, pps;
+    int32_t nsplit, pad;
+    mhlp::TreeDev tree; /* the plan's clusters and lists with the batch's own moments ([ncl][tr_stride(2 R)])
+                           and staged dipoles ([Np][2 R][16]: alpha w mu n_x, alpha w mu n_y per right-hand side) */
 };
 
 struct BatchWork {
@@ -3772,7 +3787,8 @@ struct BState {
     int32_t done;  /* all systems converged / broken down, or kmax reached   */
     int32_t nact;  /* systems still active after the last step               */
     int32_t steps; /* lockstep steps taken in this cycle                     */
-    int32_t pad[3];
+    int32_t count, ticket; /* systems left active and systems finished by the running step */
+    int32_t pad;
 };
 
 /* density of a batched launch: fixed, or basis column bs->j; false = no-op */
@@ -3785,143 +3801,266 @@ __device__ __forceinline__ bool batch_density(const BState *bs, int64_t jstride,
     return true;
 }
 
-/* The batched far field of one work item (geometry g, target tile tb, source
-   split): TPL targets per lane (tile of FT_THREADS * TPL targets; lane t takes
-   t, t + FT_THREADS, ...), sources staged in LDS SRC at a time (a multiple of
-   16), R right-hand sides sharing every kernel value; a target skips the
-   panels it lists as near.  Partial sums per (split, right-hand side, node). */
-template <int R, int TPL, int SRC>
-__global__ __launch_bounds__(FT_THREADS) void batch_far_dlp(const BatchGeo *__restrict__ G,
-                                                            const BatchWork *__restrict__ W,
-                                                            const double *__restrict__ mu, double *__restrict__ part,
-                                                            const double *__restrict__ gate, const BState *bs,
-                                                            int64_t jstride)
+/* Moments and staged dipoles of one geometry's 16-panel chunk (work item: g,
+   chunk tb) at level blockIdx.y, orders of blockIdx.z, for its R right-hand
+   sides: tree_moments_kernel with the regular functions of a source shared. */
+template <int R, int Z, int RR, class B>
+__device__ __forceinline__ void batch_moments_rounds(const mhlp::TreeDev &T, int k, int64_t p0, const B &b,
+                                                     const double (&ex)[R], const double (&ey)[R],
+                                                     double (*buf)[16 * mhlp::TR_PAD])
 {
-    static_assert(SRC % 16 == 0 && SRC <= FT_THREADS, "whole panels, one source per thread");
-    if (batch_gated_off<R>(gate, W[blockIdx.x].g) || !batch_density(bs, jstride, mu)) return;
-    __shared__ double lx[SRC], ly[SRC];
-    __shared__ double ldx[R][SRC], ldy[R][SRC];
-    const BatchWork wk = W[blockIdx.x];
-    const BatchGeo geo = G[wk.g];
-    const int64_t pb = (int64_t)wk.split * geo.pps;
-    const int64_t pe = min(geo.Np, pb + geo.pps);
-    int64_t i[TPL];
-    bool valid[TPL];
-    double x[TPL], y[TPL];
-    int32_t k[TPL], kend[TPL], nxt[TPL];
+    constexpr int NV = 2 * R, RO = R > 2 ? 2 : 4, N = Z * mhlp::TR_NG + RR;
+    if constexpr (RR < mhlp::TR_NG && N <= mhlp::TR_PMAX) {
+        const int t = threadIdx.x, at = (t >> 4) * mhlp::TR_PAD + (t & 15), pp = t & 15, cb = t >> 4;
 #pragma unroll
-    for (int q = 0; q < TPL; ++q) {
-        i[q] = (int64_t)wk.tb * (FT_THREADS * TPL) + q * FT_THREADS + threadIdx.x;
-        valid[q] = i[q] < geo.N;
-        x[q] = valid[q] ? geo.x[i[q]] : 0.0;
-        y[q] = valid[q] ? geo.y[i[q]] : 0.0;
-        k[q] = kend[q] = 0;
-        if (valid[q]) {
-            k[q] = geo.nptr[i[q]];
-            kend[q] = geo.nptr[i[q] + 1];
-            while (k[q] < kend[q] && geo.npan[k[q]] >= 0 && geo.npan[k[q]] < pb) ++k[q];
-        }
-        nxt[q] = (k[q] < kend[q]) ? geo.npan[k[q]] : INT_MAX;
-    }
-    const FarConst fc = far_const(geo.alpha);
-    const double *mug = mu + geo.voff;
-    double acc[TPL][R];
-#pragma unroll
-    for (int q = 0; q < TPL; ++q)
-#pragma unroll
-        for (int r = 0; r < R; ++r) acc[q][r] = 0.0;
-    for (int64_t base = 16 * pb; base < 16 * pe; base += SRC) {
-        __syncthreads();
-        const int64_t j = base + threadIdx.x;
-        if (threadIdx.x < SRC && j < 16 * pe) {
-            const double wj = geo.w[j];
-            lx[threadIdx.x] = geo.x[j];
-            ly[threadIdx.x] = geo.y[j];
-            const double nxj = geo.nx[j], nyj = geo.ny[j];
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const double m = (geo.alpha * wj) * mug[r * geo.N + j]; /* the pair gives K1(z)/r */
-                ldx[r][threadIdx.x] = m * nxj;
-                ldy[r][threadIdx.x] = m * nyj;
+        for (int r = 0; r < R; ++r) {
+            const mhlp::TreeDipole<B> md{b, ex[r], ey[r]};
+            mhlp::tree_row_values<false, N>(md, 0.0, buf + 2 * r, at);
+            mhlp::tree_row_values<false, N + 1>(md, 0.0, buf + NV + 2 * r, at);
+            if constexpr (RO > 2) {
+                mhlp::tree_row_values<false, N + 2>(md, 0.0, buf + 2 * NV + 2 * r, at);
+                mhlp::tree_row_values<false, N + 3>(md, 0.0, buf + 3 * NV + 2 * r, at);
             }
         }
         __syncthreads();
-        const int32_t p0 = (int32_t)(base / 16);
-        const int npl = (pe - p0) < SRC / 16 ? (int)(pe - p0) : SRC / 16;
-        for (int pl = 0; pl < npl; ++pl) {
-            bool use[TPL];
-            bool any = false;
+        if (cb < RO * NV) {
+            const double *row = buf[cb] + pp * mhlp::TR_PAD;
+            double s0 = 0.0, s1 = 0.0;
 #pragma unroll
-            for (int q = 0; q < TPL; ++q) {
-                use[q] = p0 + pl != nxt[q];
-                if (!use[q]) {
-                    ++k[q];
-                    nxt[q] = (k[q] < kend[q]) ? geo.npan[k[q]] : INT_MAX;
-                }
-                any = any || use[q];
+            for (int l = 0; l < 16; l += 2) {
+                s0 += row[l];
+                s1 += row[l + 1];
             }
-            if (!any) continue;
-#pragma unroll 1
-            for (int s = 0; s < 16; s += 2) {
-                const FarTab T = far_table();
-                const int l0 = pl * 16 + s, l1 = l0 + 1;
-#pragma unroll
-                for (int q = 0; q < TPL; ++q) {
-                    if (!use[q]) continue;
-                    const double ex0 = x[q] - lx[l0], ey0 = y[q] - ly[l0];
-                    const double ex1 = x[q] - lx[l1], ey1 = y[q] - ly[l1];
-                    K01 o0, o1;
-                    k01_far2<false, true, true, true>(T, fc, fma(ex0, ex0, ey0 * ey0), fma(ex1, ex1, ey1 * ey1), o0,
-                                                      o1);
-#pragma unroll
-                    for (int r = 0; r < R; ++r)
-                        acc[q][r] = fma(o1.ak1r, fma(ex1, ldx[r][l1], ey1 * ldy[r][l1]),
-                                        fma(o0.ak1r, fma(ex0, ldx[r][l0], ey0 * ldy[r][l0]), acc[q][r]));
-                }
-            }
+            double s = s0 + s1;
+            for (int o = 1; o < (1 << k); o <<= 1) s += __shfl_xor(s, o);
+            const int n = N + cb / NV;
+            const int64_t p = p0 + pp;
+            if ((pp & ((1 << k) - 1)) == 0 && p < T.Np && n < mhlp::TR_ROWS)
+                T.mom[(T.off[k] + (p >> k)) * mhlp::tr_stride(NV) + n * NV + cb % NV] = s;
         }
-    }
-#pragma unroll
-    for (int q = 0; q < TPL; ++q) {
-        if (!valid[q]) continue;
-#pragma unroll
-        for (int r = 0; r < R; ++r) part[geo.poff + ((int64_t)wk.split * R + r) * geo.N + i[q]] = acc[q][r];
+        __syncthreads();
+        batch_moments_rounds<R, Z, RR + RO>(T, k, p0, b, ex, ey, buf);
     }
 }
 
-/* out = (1/2 I + D) mu for every system: split partials + corrections + identity */
-template <int R>
-__global__ void batch_finalize(const BatchGeo *__restrict__ G, const BatchWork *__restrict__ W,
-                               const double *__restrict__ part, const double *__restrict__ mu,
-                               double *__restrict__ out, const double *__restrict__ gate, const BState *bs,
-                               int64_t jstride)
+template <int R, int Z>
+__device__ __forceinline__ void batch_moments_body(const BatchGeo &geo, int64_t chunk, const double *mug,
+                                                   double (*buf)[16 * mhlp::TR_PAD])
 {
-    if (batch_gated_off<R>(gate, W[blockIdx.x].g) || !batch_density(bs, jstride, mu)) return;
-    const BatchWork wk = W[blockIdx.x];
-    const BatchGeo geo = G[wk.g];
-    const int64_t i = (int64_t)wk.tb * FT_THREADS + threadIdx.x;
-    if (i >= geo.N) return;
-    const double *mug = mu + geo.voff;
-    double v[R];
+    const mhlp::TreeDev &T = geo.tree;
+    const int k = blockIdx.y, t = threadIdx.x;
+    const int64_t p0 = 16 * chunk, j = 16 * p0 + t;
+    const bool have = j < geo.N;
+    const int64_t js = have ? j : geo.N - 1;
+    const int64_t c = T.off[k] + ((js >> 4) >> k);
+    const double aw = have ? geo.alpha * geo.w[js] : 0.0, nx = geo.nx[js], ny = geo.ny[js];
+    double ex[R], ey[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) v[r] = 0.0;
-    for (int sp = 0; sp < geo.nsplit; ++sp)
-#pragma unroll
-        for (int r = 0; r < R; ++r) v[r] += part[geo.poff + ((int64_t)sp * R + r) * geo.N + i];
-    double c[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) c[r] = 0.0;
-    for (int32_t q = geo.nptr[i]; q < geo.nptr[i + 1]; ++q) {
-        const int64_t p = geo.npan[q];
-        if (p < 0) continue;
-        for (int jj = 0; jj < 16; ++jj) {
-            const double wq = geo.wdl[16 * (int64_t)q + jj];
-#pragma unroll
-            for (int r = 0; r < R; ++r) c[r] = fma(wq, mug[r * geo.N + 16 * p + jj], c[r]);
+    for (int r = 0; r < R; ++r) {
+        const double m = have ? aw * mug[r * geo.N + js] : 0.0; /* the pair gives K1(z)/r */
+        ex[r] = m * nx;
+        ey[r] = m * ny;
+        if (Z == 0 && k == 0 && have) {
+            double *s = T.st + ((j >> 4) * 2 * R + 2 * r) * 16 + (j & 15);
+            s[0] = ex[r];
+            s[16] = ey[r];
         }
     }
+    const bool live = T.rmin[mhlp::TR_RM * c + mhlp::TR_NP - 1] < INFINITY;
+    if (__syncthreads_or(live ? 1 : 0) == 0) return;
+    const double ah = 0.5 * geo.alpha;
+    const double wr = live ? ah * (geo.x[js] - T.cc[2 * c]) : 0.0, wi = live ? -ah * (geo.y[js] - T.cc[2 * c + 1]) : 0.0;
+    mhlp::TreeB<false, Z> b;
+    mhlp::tree_regular<mhlp::TreeB<false, Z>::LO, mhlp::TreeB<false, Z>::CNT>(wr, wi, fma(wr, wr, wi * wi), b.br, b.bi);
+    batch_moments_rounds<R, Z, 0>(T, k, p0, b, ex, ey, buf);
+}
+
+template <int R>
+__global__ __launch_bounds__(256) void batch_moments_kernel(const BatchGeo *__restrict__ G,
+                                                            const BatchWork *__restrict__ W,
+                                                            const double *__restrict__ mu,
+                                                            const double *__restrict__ gate, const BState *bs,
+                                                            int64_t jstride)
+{
+    __shared__ double buf[16][16 * mhlp::TR_PAD];
+    const BatchWork wk = W[blockIdx.x];
+    if (batch_gated_off<R>(gate, wk.g) || !batch_density(bs, jstride, mu)) return;
+    const BatchGeo &geo = G[wk.g];
+    if ((int)blockIdx.y >= geo.tree.nlev) return;
+    const double *mug = mu + geo.voff;
+    switch (blockIdx.z) {
+    case 0: batch_moments_body<R, 0>(geo, wk.tb, mug, buf); break;
+    case 1: batch_moments_body<R, 1>(geo, wk.tb, mug, buf); break;
+    default: batch_moments_body<R, 2>(geo, wk.tb, mug, buf); break;
+    }
+}
+
+/* staged dipoles s0..s1-1 of panel p, R right-hand sides sharing every kernel value */
+template <int R, int PC>
+__device__ __forceinline__ void batch_panel(const BatchGeo &geo, int64_t p, int s0, int s1, double x, double y,
+                                            double (&f)[R])
+{
+    constexpr int K = PC < 0 || PC >= KQ_NP ? 0 : PC;
+    const MHLP_CAS double *sx = (const MHLP_CAS double *)geo.x + 16 * p;
+    const MHLP_CAS double *sy = (const MHLP_CAS double *)geo.y + 16 * p;
+    const MHLP_CAS double *st = (const MHLP_CAS double *)geo.tree.st + 32 * R * p;
+    FarTab T = far_table();
+    const FarConst fc = far_const_of(geo.fq);
+    double qa, qk;
+    fine_q<K>(geo.fq, qa, qk);
+#pragma unroll 1
+    for (int s = s0; s < s1; s += 2) {
+        if (PC < 0 || PC >= KQ_NP) T = far_table(); /* their coefficients exceed the scalar registers */
+        const double ex0 = x - sx[s], ey0 = y - sy[s];
+        const double ex1 = x - sx[s + 1], ey1 = y - sy[s + 1];
+        const double r20 = fma(ex0, ex0, ey0 * ey0), r21 = fma(ex1, ex1, ey1 * ey1);
+        K01 o0, o1;
+        if constexpr (PC >= KQ_NP)
+            k01_far2<false, true, true, true>(T, fc, r20, r21, o0, o1);
+        else
+            k01_far2_fixed<false, true, PC>(T, fc, qa, qk, r20, r21, o0, o1);
+        const double ax = ex0 * o0.ak1r, ay = ey0 * o0.ak1r, bx = ex1 * o1.ak1r, by = ey1 * o1.ak1r;
 #pragma unroll
-    for (int r = 0; r < R; ++r) out[geo.voff + r * geo.N + i] = fma(INV_2PI, v[r], c[r]) + 0.5 * mug[r * geo.N + i];
+        for (int r = 0; r < R; ++r) {
+            const MHLP_CAS double *q = st + 32 * r + s;
+            f[r] = fma(ax, q[0], fma(ay, q[16], fma(bx, q[1], fma(by, q[17], f[r]))));
+        }
+    }
+}
+
+/* The batched far field of one work item (geometry g, group of 64 targets tb,
+   split): the items of far_tree_kernel's lists, direct panels cut into halves,
+   shared by the BATCH_W waves of the group's nsplit blocks; R right-hand sides
+   share every kernel value and every K_n.  Partial sums per (split, right-hand
+   side, node).  Bound by VALU FP64 (per expansion 8 + 2 R instructions an
+   order, per pair 47 + 4 R): 24,656 nodes in 16 curves, R = 4, 22e6 wave
+   instructions, 50 us at 75% of their rate (the last blocks run alone), against
+   127 us for the sum over all pairs. */
+constexpr int BATCH_W = 8;
+template <int R>
+__global__ __launch_bounds__(64 * BATCH_W, 4) void batch_far_kernel(const BatchGeo *__restrict__ G,
+                                                                    const BatchWork *__restrict__ W,
+                                                                    const double *__restrict__ mu,
+                                                                    double *__restrict__ part,
+                                                                    const double *__restrict__ gate, const BState *bs,
+                                                                    int64_t jstride)
+{
+    __shared__ double red[R][BATCH_W][64];
+    const BatchWork wk = W[blockIdx.x];
+    if (batch_gated_off<R>(gate, wk.g) || !batch_density(bs, jstride, mu)) return;
+    const BatchGeo &geo = G[wk.g];
+    const mhlp::TreeDev &T = geo.tree;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t g = wk.tb, i = 64 * g + lane;
+    const bool valid = i < geo.N;
+    const int64_t iv = valid ? i : geo.N - 1;
+    const double x = geo.x[iv], y = geo.y[iv];
+    const int32_t k0 = geo.nptr[iv], k1 = geo.nptr[iv + 1];
+    const int NW = BATCH_W * geo.nsplit, wg = w * geo.nsplit + wk.split;
+    const int2 cnt = T.cnt[g];
+    const uint2 *items = T.items + g * T.Np;
+    double acc[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) acc[r] = 0.0;
+    for (int k = wg; k < 2 * cnt.x; k += NW) {
+        const uint2 it = items[k >> 1];
+        const uint32_t p = __builtin_amdgcn_readfirstlane(it.x), fl = __builtin_amdgcn_readfirstlane(it.y);
+        bool listed = false;
+        if (fl & mhlp::TR_NEAR)
+            for (int32_t q = k0; q < k1; ++q) listed = listed || geo.npan[q] == (int32_t)p;
+        if (listed) continue;
+        const int s0 = 8 * (k & 1);
+        double f[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) f[r] = 0.0;
+        switch ((int)(fl & 31) - 1) {
+#define MHLP_BATCH_PANEL(PCV) \
+    case PCV: batch_panel<R, PCV>(geo, p, s0, s0 + 8, x, y, f); break;
+            MHLP_PC_CASES(MHLP_BATCH_PANEL)
+#undef MHLP_BATCH_PANEL
+        default: batch_panel<R, KQ_NP>(geo, p, s0, s0 + 8, x, y, f);
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) acc[r] += f[r];
+    }
+    const int fb = cnt.y * (NW - 1 - wg) / NW, fe = cnt.y * (NW - wg) / NW;
+    for (int k = fb; k < fe; ++k) {
+        const uint2 it = items[T.Np - 1 - k];
+        const uint32_t c = __builtin_amdgcn_readfirstlane(it.x), fl = __builtin_amdgcn_readfirstlane(it.y);
+        int64_t p0, p1;
+        double f[R];
+        bool direct = false;
+        if (fl & mhlp::TR_ZERO) {
+            /* all pairs underflow: only a non-finite density matters */
+            mhlp::tree_panels_of(T, c, p0, p1);
+            double z = 0.0;
+            for (int64_t q = 32 * R * p0 + lane; q < 32 * R * p1; q += 64) z = fma(0.0, T.st[q], z);
+            direct = __ballot(!(z == 0.0)) != 0;
+#pragma unroll
+            for (int r = 0; r < R; ++r) f[r] = 0.0;
+        } else {
+            mhlp::tree_expand<R>(geo.fq, T, c, (int)(fl & 31) - 1, (int)(fl >> 8) & 63, x, y, f);
+            bool fin = true;
+#pragma unroll
+            for (int r = 0; r < R; ++r) fin = fin && __builtin_isfinite(f[r]);
+            direct = __ballot(!fin) != 0;
+        }
+        if (direct) {
+            mhlp::tree_panels_of(T, c, p0, p1);
+#pragma unroll
+            for (int r = 0; r < R; ++r) f[r] = 0.0;
+            for (int64_t p = p0; p < p1; ++p) batch_panel<R, KQ_NP>(geo, p, 0, 16, x, y, f);
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) acc[r] += f[r];
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) red[r][w][lane] = acc[r];
+    __syncthreads();
+    if (w >= R || !valid) return;
+    double s = 0.0;
+#pragma unroll
+    for (int v = 0; v < BATCH_W; ++v) s += red[w][v][lane];
+    part[geo.poff + ((int64_t)wk.split * R + w) * geo.N + i] = s;
+}
+
+/* out = (1/2 I + D) mu for every system: slot sum, near corrections and
+   identity.  A row of 16 lanes takes one target (16 a block of work item tb):
+   lane jj the slots jj, jj + 16, ... and source jj of the near panels, so the
+   weights are read whole and the loads of a panel are in flight together.
+   Bound by latency: 9.8 -> 6 us at 24,656 nodes with a thread per target;
+   inside the far kernel the corrections cost it 8 us. */
+template <int R>
+__global__ __launch_bounds__(256) void batch_finalize(const BatchGeo *__restrict__ G, const BatchWork *__restrict__ W,
+                                                      const double *__restrict__ part, const double *__restrict__ mu,
+                                                      double *__restrict__ out, const double *__restrict__ gate,
+                                                      const BState *bs, int64_t jstride)
+{
+    const BatchWork wk = W[blockIdx.x];
+    if (batch_gated_off<R>(gate, wk.g) || !batch_density(bs, jstride, mu)) return;
+    const BatchGeo &geo = G[wk.g];
+    const int jj = threadIdx.x & 15;
+    const int64_t i = 16 * (int64_t)wk.tb + (threadIdx.x >> 4); /* N is a multiple of 16 */
+    const double *mug = mu + geo.voff;
+    double v[R], c[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] = c[r] = 0.0;
+    for (int sp = jj; sp < geo.nsplit; sp += 16)
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[r] += part[geo.poff + ((int64_t)sp * R + r) * geo.N + i];
+    const int32_t q1 = geo.nptr[i + 1];
+    for (int32_t q = geo.nptr[i]; q < q1; ++q) {
+        const int64_t p = geo.npan[q];
+        if (p < 0) continue;
+        const double wq = geo.wdl[16 * (int64_t)q + jj];
+#pragma unroll
+        for (int r = 0; r < R; ++r) c[r] = fma(wq, mug[r * geo.N + 16 * p + jj], c[r]);
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const double s = mhlp::tree_row_sum(fma(INV_2PI, v[r], c[r]));
+        if (jj == r) out[geo.voff + r * geo.N + i] = fma(0.5, mug[r * geo.N + i], s);
+    }
 }
 
 /* per-system BLAS-1 over batched vectors: system s spans [off[s], off[s] + n[s]) */
@@ -4087,6 +4226,87 @@ __global__ void badvance_kernel(BState *__restrict__ bs)
     if (threadIdx.x == 0 && blockIdx.x == 0 && !bs->done) bs->j += 1;
 }
 
+/* The Gram-Schmidt part of one lockstep step, a block per system with the new
+   vector in registers (gsr_orth): the projections, the Hessenberg column with
+   its rotations, the system's stopping test and the next basis vector; the
+   last block to finish advances the state.  Eight launches of the split form
+   in one: 35 -> 10 us a step for 64 systems of 528-2464 unknowns. */
+template <int E>
+__global__ __launch_bounds__(GSF_T) void batch_gs_kernel(BState *__restrict__ bs, int S, int m, double *__restrict__ V,
+                                                         int64_t ld, const double *__restrict__ w,
+                                                         const int64_t *__restrict__ off,
+                                                         const int64_t *__restrict__ n, double *__restrict__ H,
+                                                         double *__restrict__ cs, double *__restrict__ sn,
+                                                         double *__restrict__ gv, const double *__restrict__ thresh,
+                                                         double *__restrict__ resest, double *__restrict__ gate,
+                                                         int32_t *__restrict__ dk)
+{
+    __shared__ GsrShared sh;
+    __shared__ double scale;
+    if (bs->done) return; /* the whole grid: only a step's last block sets it */
+    const int s = blockIdx.x, t = threadIdx.x, k = bs->j;
+    const int64_t N = n[s];
+    double *Vs = V + off[s];
+    double x[E];
+    if (gate[s] != 0.0) {
+        double *Hs = H + (int64_t)s * (m + 1) * m, *c_ = cs + (int64_t)s * m, *s_ = sn + (int64_t)s * m;
+        double *g_ = gv + (int64_t)s * (m + 1);
+        gsr_orth<E>(Vs, ld, w + off[s], N, k + 1, x, sh);
+        for (int c = t; c <= k; c += GSF_T) {
+            sh.col[c] = sh.hs[0][c] + sh.hs[1][c];
+            if (c < k) {
+                sh.rot[2 * c] = c_[c];
+                sh.rot[2 * c + 1] = s_[c];
+            }
+        }
+        __syncthreads();
+        if (t == 0) {
+            double *col = sh.col;
+            const double hk = sqrt(sh.hnl[0]);
+            for (int j = 0; j < k; ++j) {
+                const double a = col[j], c = col[j + 1];
+                col[j] = sh.rot[2 * j] * a + sh.rot[2 * j + 1] * c;
+                col[j + 1] = -sh.rot[2 * j + 1] * a + sh.rot[2 * j] * c;
+            }
+            const double a = col[k], den = hypot(a, hk);
+            c_[k] = den > 0.0 ? a / den : 1.0;
+            s_[k] = den > 0.0 ? hk / den : 0.0;
+            col[k] = den;
+            col[k + 1] = 0.0;
+            g_[k + 1] = -s_[k] * g_[k];
+            g_[k] = c_[k] * g_[k];
+            dk[s] = k + 1;
+            const double est = fabs(g_[k + 1]);
+            resest[s] = est;
+            scale = est <= thresh[s] || hk == 0.0 ? 0.0 : 1.0 / hk;
+            gate[s] = scale;
+            if (scale != 0.0) atomicAdd(&bs->count, 1);
+        }
+        __syncthreads();
+        for (int c = t; c <= k + 1; c += GSF_T) Hs[(int64_t)c * m + k] = sh.col[c];
+    } else {
+        if (t == 0) scale = 0.0;
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < E; ++e) x[e] = 0.0;
+    }
+    const double sc = scale;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int64_t i = t + (int64_t)e * GSF_T;
+        if (i < N) Vs[(int64_t)(k + 1) * ld + i] = sc * x[e];
+    }
+    if (t != 0) return;
+    __threadfence();
+    if (atomicAdd(&bs->ticket, 1) != S - 1) return;
+    const int left = atomicExch(&bs->count, 0);
+    bs->ticket = 0;
+    bs->nact = left;
+    bs->steps = k + 1;
+    bs->j = k + 1;
+    if (left == 0 || k + 1 >= bs->kmax) bs->done = 1;
+}
+
 /* y_s = R^{-1} g_s over the dk[s] leading columns; one wave per system */
 __global__ __launch_bounds__(64) void bsolve_kernel(int m, int ldh, const double *__restrict__ H,
                                                     const double *__restrict__ gv, const int32_t *__restrict__ dk,
@@ -4112,9 +4332,10 @@ struct mhlp_batch {
     int64_t total = 0, max_n = 0;
     std::vector<int64_t> off, n;
     BatchGeo *dgeo = nullptr;
-    BatchWork *dwork = nullptr, *dfin = nullptr;
-    int64_t nwork = 0, nfin = 0;
-    double *part = nullptr;
+    BatchWork *dwork = nullptr, *dfin = nullptr, *dmom = nullptr; /* far, finalize and moments items */
+    int64_t nwork = 0, nfin = 0, nmom = 0;
+    double *part = nullptr, *mom = nullptr; /* mom: moments and staged dipoles of all geometries */
+    std::vector<double> cost;               /* work of each geometry's far lists */
     int64_t *doff = nullptr, *dn = nullptr;
     /* GMRES workspace */
     int m = 0;
@@ -4153,8 +4374,8 @@ extern "C" mhlp_status mhlp_batch_destroy(mhlp_batch *B)
     for (auto &gr : B->graphs)
         if (gr.exec) (void)hipGraphExecDestroy(gr.exec);
     if (B->cap_stream) (void)hipStreamDestroy(B->cap_stream);
-    void *ptrs[] = {B->dgeo, B->dwork, B->dfin, B->part, B->doff, B->dn, B->V,
-                    B->w,    B->r,     B->dh,   B->dsc,  B->dk,   B->gd};
+    void *ptrs[] = {B->dgeo, B->dwork, B->dfin, B->part, B->doff, B->dn, B->V,   B->w,
+                    B->r,    B->dh,    B->dsc,  B->dk,   B->gd,   B->dmom, B->mom};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     if (B->hh) (void)hipHostFree(B->hh);
@@ -4179,7 +4400,8 @@ extern "C" mhlp_status mhlp_batch_create(int32_t n_geom, const mhlp_plan *const 
     B->R = n_rhs;
     B->S = n_geom * n_rhs;
     B->hgeo.resize(n_geom);
-    int64_t voff = 0;
+    int64_t voff = 0, nmom = 0;
+    std::vector<BatchWork> hm;
     for (int g = 0; g < n_geom; ++g) {
         const mhlp_plan *P = plans[g];
         const mhlp_geometry *G = P->g;
@@ -4192,6 +4414,11 @@ extern "C" mhlp_status mhlp_batch_create(int32_t n_geom, const mhlp_plan *const 
         b.nptr = P->near_ptr;
         b.npan = P->near_panel;
         b.wdl = P->wdlp;
+        b.fq = P->fqd;
+        b.tree = *P->tree;
+        B->cost.push_back((double)P->tr_cost + 1.0);
+        nmom += b.tree.ncl * mhlp::tr_stride(2 * n_rhs) + 32 * n_rhs * G->Np;
+        for (int64_t t = 0; 16 * t < G->Np; ++t) hm.push_back(BatchWork{g, (int32_t)t, 0, 0});
         b.N = G->N;
         b.Np = G->Np;
         b.alpha = P->alpha;
@@ -4205,18 +4432,30 @@ extern "C" mhlp_status mhlp_batch_create(int32_t n_geom, const mhlp_plan *const 
     }
     B->total = voff;
     mhlp_status s;
-    if ((s = dalloc(&B->dgeo, n_geom)) || (s = dalloc(&B->doff, B->S)) || (s = dalloc(&B->dn, B->S))) {
+    B->nmom = (int64_t)hm.size();
+    if ((s = dalloc(&B->dgeo, n_geom)) || (s = dalloc(&B->doff, B->S)) || (s = dalloc(&B->dn, B->S)) ||
+        (s = dalloc(&B->mom, nmom)) || (s = dalloc(&B->dmom, B->nmom))) {
         mhlp_batch_destroy(B);
         return s;
     }
-    hipError_t e = hipMemcpyAsync(B->doff, B->off.data(), sizeof(int64_t) * B->S, hipMemcpyHostToDevice, st);
+    {
+        double *m = B->mom;
+        for (BatchGeo &b : B->hgeo) {
+            b.tree.mom = m;
+            m += b.tree.ncl * mhlp::tr_stride(2 * n_rhs);
+            b.tree.st = m;
+            m += 32 * n_rhs * b.Np;
+        }
+    }
+    hipError_t e = hipMemcpyAsync(B->dmom, hm.data(), sizeof(BatchWork) * B->nmom, hipMemcpyHostToDevice, st);
+    if (e == hipSuccess) e = hipMemcpyAsync(B->doff, B->off.data(), sizeof(int64_t) * B->S, hipMemcpyHostToDevice, st);
     if (e == hipSuccess) e = hipMemcpyAsync(B->dn, B->n.data(), sizeof(int64_t) * B->S, hipMemcpyHostToDevice, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) {
         mhlp_batch_destroy(B);
         return fail(MHLP_HIP_ERROR, std::string("batch_create: ") + hipGetErrorString(e));
     }
-    if ((s = batch_build_work(B, 2048, 1, FT_SRC, st))) {
+    if ((s = batch_build_work(B, 768, 1, FT_SRC, st))) {
         mhlp_batch_destroy(B);
         return s;
     }
@@ -4225,36 +4464,33 @@ extern "C" mhlp_status mhlp_batch_create(int32_t n_geom, const mhlp_plan *const 
 }
 
 /* Work list of the grouped operator launch for about `target` blocks in total:
-   each geometry gets blocks in proportion to its share of the pair work
-   (N_g^2), as source splits of its target blocks (at least 4 panels per
-   split); items are ordered by decreasing cost so the longest start first. */
+   each geometry gets blocks in proportion to the work of its item lists, as
+   splits of its groups of 64 targets (at least one item per wave); items are
+   ordered by decreasing work, so the longest start first.  tpl and src shaped
+   the tiles of an earlier launch; they are kept and reported, no more. */
 static mhlp_status batch_build_work(mhlp_batch *B, int64_t target, int tpl, int src, hipStream_t st)
 {
     const int n_geom = B->n_geom, n_rhs = B->R;
     double tot_work = 0;
-    for (const BatchGeo &b : B->hgeo) tot_work += (double)b.N * b.N;
+    for (double c : B->cost) tot_work += c;
     std::vector<BatchWork> hw, hf;
+    std::vector<double> per((size_t)n_geom);
     int64_t poff = 0;
     for (int g = 0; g < n_geom; ++g) {
         BatchGeo &b = B->hgeo[g];
-        const int64_t tb = (b.N + FT_THREADS - 1) / FT_THREADS;            /* finalize tiles */
-        const int64_t tbf = (b.N + FT_THREADS * tpl - 1) / (FT_THREADS * tpl); /* far tiles */
-        const int64_t want = (int64_t)std::ceil((double)target * (double)b.N * b.N / tot_work);
-        int64_t ns = (want + tbf - 1) / tbf;
-        if (ns > b.Np / 4) ns = b.Np / 4;
-        if (ns < 1) ns = 1;
-        b.pps = (int32_t)((b.Np + ns - 1) / ns);
-        b.nsplit = (int32_t)((b.Np + b.pps - 1) / b.pps);
+        const int64_t tg = (b.N + 63) / 64; /* far groups */
+        int64_t ns = (int64_t)std::llround((double)target * B->cost[g] / tot_work / (double)tg);
+        ns = std::min(ns, (int64_t)(B->cost[g] / (double)tg / BATCH_W));
+        ns = std::max<int64_t>(1, std::min<int64_t>(ns, 64));
+        b.nsplit = (int32_t)ns;
+        per[g] = B->cost[g] / (double)(tg * ns);
         b.poff = poff;
         poff += (int64_t)b.nsplit * n_rhs * b.N;
-        for (int64_t t = 0; t < tbf; ++t)
+        for (int64_t t = 0; t < tg; ++t)
             for (int sp = 0; sp < b.nsplit; ++sp) hw.push_back(BatchWork{g, (int32_t)t, sp, 0});
-        for (int64_t t = 0; t < tb; ++t) hf.push_back(BatchWork{g, (int32_t)t, 0, 0});
+        for (int64_t t = 0; t < b.Np; ++t) hf.push_back(BatchWork{g, (int32_t)t, 0, 0});
     }
-    /* cost of an item ~ panels it sums over (all items have the same target tile) */
-    std::stable_sort(hw.begin(), hw.end(), [&](const BatchWork &a, const BatchWork &c) {
-        return B->hgeo[a.g].pps > B->hgeo[c.g].pps;
-    });
+    std::stable_sort(hw.begin(), hw.end(), [&](const BatchWork &a, const BatchWork &c) { return per[a.g] > per[c.g]; });
     HIPCHECK(hipStreamSynchronize(st)); /* old buffers may be in use */
     void *old[] = {B->dwork, B->dfin, B->part};
     for (void *p : old)
@@ -4295,16 +4531,10 @@ template <int R>
 static void batch_apply_t(const mhlp_batch *B, const double *mu, double *out, const double *gate,
                           const BState *bs, int64_t jstride, hipStream_t st)
 {
-    const unsigned nw = (unsigned)B->nwork;
-    if (B->tpl == 2 && B->src == 128)
-        batch_far_dlp<R, 2, 128><<<nw, FT_THREADS, 0, st>>>(B->dgeo, B->dwork, mu, B->part, gate, bs, jstride);
-    else if (B->tpl == 2)
-        batch_far_dlp<R, 2, FT_SRC><<<nw, FT_THREADS, 0, st>>>(B->dgeo, B->dwork, mu, B->part, gate, bs, jstride);
-    else if (B->src == 128)
-        batch_far_dlp<R, 1, 128><<<nw, FT_THREADS, 0, st>>>(B->dgeo, B->dwork, mu, B->part, gate, bs, jstride);
-    else
-        batch_far_dlp<R, 1, FT_SRC><<<nw, FT_THREADS, 0, st>>>(B->dgeo, B->dwork, mu, B->part, gate, bs, jstride);
-    batch_finalize<R><<<(unsigned)B->nfin, FT_THREADS, 0, st>>>(B->dgeo, B->dfin, B->part, mu, out, gate, bs,
+    batch_moments_kernel<R><<<dim3((unsigned)B->nmom, mhlp::TR_LEV, mhlp::TR_GROUPS), 256, 0, st>>>(
+        B->dgeo, B->dmom, mu, gate, bs, jstride);
+    batch_far_kernel<R><<<(unsigned)B->nwork, 64 * BATCH_W, 0, st>>>(B->dgeo, B->dwork, mu, B->part, gate, bs, jstride);
+    batch_finalize<R><<<(unsigned)B->nfin, 256, 0, st>>>(B->dgeo, B->dfin, B->part, mu, out, gate, bs,
                                                                   jstride);
 }
 
@@ -4457,6 +4687,22 @@ static mhlp_status enqueue_bstep(mhlp_batch *B, hipStream_t st)
     double *h1 = B->dh, *h2 = B->dh + (int64_t)S * ldh, *hn = B->dh + 2 * (int64_t)S * ldh;
     const dim3 gS((unsigned)((B->max_n + 255) / 256), (unsigned)S);
     TRY(batch_apply_impl(B, B->V, B->w, st, B->dsc, d.bs, T));
+    auto one = [&](auto kern) {
+        kern<<<(unsigned)S, GSF_T, 0, st>>>(d.bs, S, m, B->V, T, B->w, B->doff, B->dn, d.H, d.cs, d.sn, d.gv, d.thresh,
+                                            d.resest, B->dsc, B->dk);
+    };
+    if (B->max_n <= GSR_NMAX) { /* the new vector fits the registers of one block */
+        if (B->max_n <= GSF_T)
+            one(batch_gs_kernel<1>);
+        else if (B->max_n <= 2 * GSF_T)
+            one(batch_gs_kernel<2>);
+        else if (B->max_n <= 4 * GSF_T)
+            one(batch_gs_kernel<4>);
+        else
+            one(batch_gs_kernel<8>);
+        HIPCHECK(hipGetLastError());
+        return MHLP_OK;
+    }
     bdot_dev_kernel<<<dim3((unsigned)S, (unsigned)m), 256, 0, st>>>(d.bs, B->V, T, B->w, B->doff, B->dn, ldh, h1,
                                                                      B->dsc);
     bsub_dev_kernel<<<gS, 256, 0, st>>>(d.bs, B->V, T, h1, ldh, B->w, B->doff, B->dn, B->dsc);
@@ -4612,7 +4858,7 @@ extern "C" mhlp_status mhlp_batch_gmres_solve(mhlp_batch *B, const double *g, do
             gs_[0] = rn[s2];
             up_h[(size_t)S * (m + 1) + s2] = 0.5 * opts->tol * bn[s2];
         }
-        *bsh = BState{0, std::min(mcyc, opts->max_iter - total_it), 0, nact, 0, {0, 0, 0}};
+        *bsh = BState{0, std::min(mcyc, opts->max_iter - total_it), 0, nact, 0, 0, 0, 0};
         HIPCHECK(hipMemcpyAsync(B->dsc, sc.data(), sizeof(double) * S, hipMemcpyHostToDevice, st));
         bscale_kernel<<<gS, 256, 0, st>>>(B->r, B->dsc, B->V, B->doff, B->dn);
         HIPCHECK(hipMemcpyAsync(d.gv, up_h, sizeof(double) * (size_t)S * (m + 1), hipMemcpyHostToDevice, st));

@@ -55,6 +55,7 @@ struct TreeDev {
     uint2 *items = nullptr;                  /* [groups][Np]: direct items from the front, expansions from the back */
     int2 *cnt = nullptr;                     /* [groups]: their numbers */
     double *part = nullptr;                  /* [fields][blocks per group][M] sums of split groups */
+    unsigned long long *cost = nullptr;      /* total work of the groups (tree_cost) */
     int32_t *order = nullptr;                /* [groups] launch order: the groups with the most work first */
 };
 
@@ -298,20 +299,30 @@ __global__ __launch_bounds__(256) void tree_lists_kernel(TreeDev T, const double
     if (lane == 0) T.cnt[g] = make_int2(nd, nf);
 }
 
-/* plan time: the groups by falling work (a direct item costs about three
-   expansions), one block, a counting sort: blocks start in this order, so the
+/* work of a group in expansions (a direct item costs about three) */
+__device__ __forceinline__ int tree_cost(int2 cnt) { return 3 * cnt.x + cnt.y; }
+
+/* plan time: the groups by falling work, and its sum; one block, a counting sort: blocks start in this order, so the
    groups next to the curve, with up to five times the work of the others, do
    not start last */
 constexpr int TR_BINS = 1024;
 __global__ __launch_bounds__(1024) void tree_order_kernel(TreeDev T, int64_t G)
 {
     __shared__ int32_t pos[TR_BINS];
-    auto bin = [&](int64_t g) { return TR_BINS - 1 - min(TR_BINS - 1, 3 * T.cnt[g].x + T.cnt[g].y); };
+    __shared__ unsigned long long total;
+    auto bin = [&](int64_t g) { return TR_BINS - 1 - min(TR_BINS - 1, tree_cost(T.cnt[g])); };
     const int t = threadIdx.x;
     pos[t] = 0;
+    if (t == 0) total = 0;
     __syncthreads();
-    for (int64_t g = t; g < G; g += 1024) atomicAdd(&pos[bin(g)], 1);
+    unsigned long long sum = 0;
+    for (int64_t g = t; g < G; g += 1024) {
+        atomicAdd(&pos[bin(g)], 1);
+        sum += (unsigned long long)tree_cost(T.cnt[g]);
+    }
+    atomicAdd(&total, sum);
     __syncthreads();
+    if (t == 0) *T.cost = total;
     for (int o = 1; o < TR_BINS; o <<= 1) {
         const int32_t v = t >= o ? pos[t - o] : 0;
         __syncthreads();
@@ -757,12 +768,12 @@ __device__ __forceinline__ void fmac_pair(double &f0, double &f1, const double2 
         : "v"(a), "v"(b), "v"(s0), "v"(s1), "n"((AT % 32) / 2));
 }
 
-/* two fields of a row in one go (AT a multiple of 4) */
+/* two fields of a row in one go */
 template <int AT>
 __device__ __forceinline__ void fmac_quad(double &f0, double &f1, double &g0, double &g1, const double2 *m, double s0,
                                           double s1)
 {
-    static_assert(AT % 4 == 0, "the four values lie in neighbouring lanes");
+    static_assert(AT % 2 == 0 && AT % 32 != 30, "the four values lie in neighbouring lanes");
     asm("s_nop 1\n\t"
         "v_fmac_f64_dpp %0, %4, %6 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
         "v_fmac_f64_dpp %1, %5, %7 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
@@ -775,11 +786,12 @@ __device__ __forceinline__ void fmac_quad(double &f0, double &f1, double &g0, do
 template <int NF, int N, int F>
 __device__ __forceinline__ void tree_row(const double2 *m, double kc, double ks, double (&f0)[NF], double (&f1)[NF])
 {
-    if constexpr (F + 1 < NF) {
+    if constexpr (F + 1 < NF && (N * 2 * NF + 2 * F) % 32 != 30) {
         fmac_quad<N * 2 * NF + 2 * F>(f0[F], f1[F], f0[F + 1], f1[F + 1], m, kc, ks);
         tree_row<NF, N, F + 2>(m, kc, ks, f0, f1);
     } else if constexpr (F < NF) {
         fmac_pair<N * 2 * NF + 2 * F>(f0[F], f1[F], m, kc, ks);
+        tree_row<NF, N, F + 1>(m, kc, ks, f0, f1);
     }
 }
 
@@ -1174,6 +1186,17 @@ __device__ __forceinline__ void tree_panel(int pc, const Args &A, const TreeDev 
     }
 }
 
+
+/* sum over the 16 lanes of a row, in all of them */
+__device__ __forceinline__ double tree_row_sum(double v)
+{
+#define MHLP_ROR(N)                                                                                                  \
+    v += __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x120 + N, 0xf, 0xf, true),              \
+                          __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x120 + N, 0xf, 0xf, true));
+    MHLP_ROR(8) MHLP_ROR(4) MHLP_ROR(2) MHLP_ROR(1)
+#undef MHLP_ROR
+    return v;
+}
 
 /* One block per group of 64 targets (lane = target), in the order of the
    groups' work; the waves of the gridDim.y blocks of a group share its items:
