@@ -369,16 +369,19 @@ mhlp_status mhlp_sisdc_step(mhlp_box *box, double Re, double dt, int32_t K, doub
    Wcell = integral of K0(alpha |x|)/(2 pi) over the h x h cell centred at the
    point (exact self-cell correction; trapezoid edge/corner cells take their
    weight fraction w_i/h^2).  x, y, w, f, u: device [n].  self_cell (host, may be
-   NULL) receives Wcell.  Synchronises the stream when the source range is
-   split (n small enough that fewer than 1024 target blocks exist).  Errors:
+   NULL) receives Wcell.  FP64 sums of 12,288 points or more go by cluster
+   expansions that reach rounding (a workspace of about 200 bytes a point for
+   the call; without it, and at 2^28 points and beyond, all pairs are summed).
+   Synchronises the stream.  Errors:
    MHLP_INVALID_ARG for NULL arrays, n < 1, alpha or h not > 0. */
 mhlp_status mhlp_volume_eval(const double *x, const double *y, const double *w, const double *f, int64_t n,
                              double alpha, double h, int32_t precision, double *u, double *self_cell, void *stream);
 
 /* mhlp_volume_eval without any allocation, for callers that cannot allocate
    device memory (code under HIP graph capture, tight serving loops, harnesses
-   that forbid hipMalloc).  Same sum, arguments and launch shape (hence the same
-   result) as mhlp_volume_eval, without the self_cell output; it only enqueues
+   that forbid hipMalloc).  Same sum and arguments as mhlp_volume_eval, always over
+   all pairs (hence the same result wherever that sums them, and to rounding
+   elsewhere), without the self_cell output; it only enqueues
    and never synchronises.  The self-cell weight and the split partial sums live
    in a fixed device array of the library (32 + 2^19 doubles, about 4 MiB, one
    copy per device, held until the process ends), which every call on that

@@ -107,11 +107,11 @@ __host__ __device__ inline double tree_stokes_ratio(int p)
 
 /* the smallest t = r/R (to 2%, rounded up) from which order p serves; single
    precision is enough for a bound */
-__host__ __device__ inline double tree_order_ratio(int p, double alphaR)
+__host__ __device__ inline double tree_order_ratio(int p, double alphaR, double amax = TR_AMAX)
 {
     constexpr float TMIN = 1.5f, TMAX = 300.0f, EPS = (float)(0.999 * TR_EPS);
     const float a = (float)alphaR;
-    if (!(alphaR >= TR_AMIN && alphaR <= TR_AMAX) || !(tree_truncation(p, a, TMAX) <= EPS)) return INFINITY;
+    if (!(alphaR >= TR_AMIN && alphaR <= amax) || !(tree_truncation(p, a, TMAX) <= EPS)) return INFINITY;
     float lo = logf(TMIN), hi = logf(TMAX);
     for (int k = 0; k < 8; ++k) {
         const float mid = 0.5f * (lo + hi);

@@ -230,3 +230,60 @@ def test_batched_operator_and_solve_vs_single(panels, n_rhs):
     for (P, _), b, got, info in zip(systems, rhs, B.unpack(sol), infos):
         want, _ = mhlp.gmres_solve(P, b, tol=1e-11, restart=40)
         assert info["converged"] and float((got - want).norm()) <= 2e-9 * float(want.norm())
+
+
+def _volume_reference(x, y, q, alpha, sel):
+    """Plain sums over all other points at the points `sel`, and the bounds of their errors."""
+    r = np.hypot(x[sel][:, None] - x, y[sel][:, None] - y)
+    same = r == 0.0
+    k = np.where(same, 0.0, sp.k0(alpha * np.where(same, 1.0, r))) / (2 * np.pi)
+    tol = ((3e-14 + 5e-16 * alpha * r) * k * np.abs(q)).sum(axis=1)
+    return (k * q).sum(axis=1), tol + 1e-300 * np.abs(q).sum()
+
+
+@pytest.mark.parametrize("n,alpha,shape", [(12288, 20.0, "square"), (12289, 3.0, "disc"), (13007, 100.0, "line"),
+                                           (70001, 7.0, "square"), (20000, 900.0, "square"), (14000, 15.0, "heaps"),
+                                           (12300, 40.0, "point"), (300000, 60.0, "square")])
+def test_volume_by_clusters_vs_plain_sums(n, alpha, shape):
+    """The volume sum at sizes around the tiles of its sort and lists: even and uneven distributions, points on a
+    line, coincident points (left out of each other's sums), pairs that underflow."""
+    rng = np.random.default_rng(n)
+    x, y = rng.uniform(-1.5, 1.5, n), rng.uniform(-1.5, 1.5, n)
+    if shape == "disc":
+        a, r = rng.uniform(0, 2 * np.pi, n), np.sqrt(rng.uniform(0, 1, n))
+        x, y = 1e-3 + r * np.cos(a), 5.0 + r * np.sin(a)
+    elif shape == "line":
+        y = 0.25 * x
+    elif shape == "heaps":
+        x, y = x.round(0) + 1e-3 * rng.standard_normal(n), y.round(0) + 1e-3 * rng.standard_normal(n)
+        x[100:400], y[100:400] = x[0], y[0]
+    elif shape == "point":
+        x[:], y[:] = 0.3, -0.2
+        x[::50] += 0.01
+    w, f, h = rng.uniform(0.5, 1.5, n) / n, rng.standard_normal(n), 0.01
+    u, wc = mhlp.volume_eval(_t(x), _t(y), _t(w), _t(f), alpha, h)
+    u = u.cpu().numpy()
+    sel = np.unique(np.linspace(0, n - 1, 200).astype(int))
+    ref, tol = _volume_reference(x, y, w * f, alpha, sel)
+    own = wc / h ** 2 * w[sel] * f[sel]
+    assert (np.abs(u[sel] - ref - own) <= tol + 1e-14 * np.abs(own)).all()
+    v, _ = mhlp.volume_eval(_t(x), _t(y), _t(w), _t(f), alpha, h)
+    assert np.array_equal(u, v.cpu().numpy())
+
+
+def test_volume_by_clusters_non_finite():
+    """A non-finite charge or point reaches the values that it reaches in the sum over all pairs."""
+    rng = np.random.default_rng(1)
+    n, alpha, h = 13000, 12.0, 0.01
+    x, y = rng.uniform(-1.5, 1.5, n), rng.uniform(-1.5, 1.5, n)
+    w, f = np.full(n, 1.0 / n), rng.standard_normal(n)
+    out = torch.empty(n, dtype=torch.float64, device="cuda:0")
+    for bad in ("charge", "point"):
+        if bad == "charge":
+            f[4000] = np.inf
+        else:
+            f[4000], x[17] = 0.5, np.nan
+        u = mhlp.volume_eval(_t(x), _t(y), _t(w), _t(f), alpha, h)[0].cpu().numpy()
+        v = mhlp.volume_eval_noalloc(_t(x), _t(y), _t(w), _t(f), alpha, h, out).cpu().numpy()
+        assert np.array_equal(np.isnan(u), np.isnan(v)) and np.array_equal(np.isposinf(u), np.isposinf(v))
+        assert not np.isfinite(u).any()
