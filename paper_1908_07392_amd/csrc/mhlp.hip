@@ -119,6 +119,7 @@ struct mhlp_plan {
     bool stokes = false;      /* modified-Stokes (stresslet) plan: operator on [2][N] densities */
     double *wstk = nullptr;   /* stokes: [4][nnz][16] stresslet weights (D11, D12, D21, D22)   */
     mhlp::FmmTree *fmm = nullptr; /* off-surface scalar plans: FMM far field (mhlp_plan_set_fmm) */
+    bool fmm_serves = false;      /* it is faster than the cluster lists (fmm_is_faster) */
     double *wstkg = nullptr;  /* stokes, off-surface, built on first use: [8][nnz][16] stresslet
                                  gradient weights, block (2a + l) 2 + j = d u_a/d x_l per mu_j */
     double inv_len = 0.0;     /* 1 / |Gamma| */
@@ -2355,7 +2356,7 @@ static mhlp_status launch_far(const mhlp_plan *P, const double *sigma, const dou
     if (half_term != 0.0 && (!P->onsurf || P->M != g->N))
         return fail(MHLP_INVALID_ARG, "identity term needs an on-surface plan");
     const FarArgs A = far_args(P, sigma, mu, us, ud, half_term, gs, jstride);
-    if (P->fmm && precision == MHLP_FP64 && !gs) {
+    if (P->fmm && P->fmm_serves && precision == MHLP_FP64 && !gs) {
         if (sigma && mu)
             fmm_far_t<true, true>(P->fmm, A, st);
         else if (sigma)
@@ -3123,6 +3124,20 @@ static int fmm_auto_level(int64_t npts, int64_t per_leaf)
     return L;
 }
 
+/* Does the FMM serve an evaluation sooner than the plan's cluster lists, which
+   reach rounding whatever the order?  The lists cost their items, the FMM its
+   boxes: per evaluation of both layers, us, lists | order 40, 20, 10:
+     70,000 points, alpha = 5 (100), level 5:      63 (269) |  305  220  190
+     260,000 points, alpha = 20 (200), level 7:    218 (2057) | 1270  860  665
+     989,000 points, alpha = 20 (200), level 8:    1588 (6085) | 3680 2500 1925
+   The estimates below lie within 30% of these, above the lists' figures. */
+static bool fmm_is_faster(unsigned long long list_cost, int order, int level)
+{
+    const double lists = 60.0 + 0.75e-3 * (double)list_cost;
+    const double boxes = 9.5 * std::exp2(level) * (level >= 8 ? 1.4 : 1.0) * (0.45 + 0.55 * order / 40.0);
+    return boxes < lists;
+}
+
 extern "C" mhlp_status mhlp_plan_set_fmm(mhlp_plan *P, int32_t order, int32_t leaf_level, void *stream)
 {
     if (!P) return fail(MHLP_INVALID_ARG, "plan is NULL");
@@ -3162,6 +3177,7 @@ extern "C" mhlp_status mhlp_plan_set_fmm(mhlp_plan *P, int32_t order, int32_t le
     }
     delete P->fmm;
     P->fmm = F;
+    P->fmm_serves = fmm_is_faster(P->tr_cost, order, L);
     return MHLP_OK;
 }
 

@@ -287,3 +287,29 @@ def test_volume_by_clusters_non_finite():
         v = mhlp.volume_eval_noalloc(_t(x), _t(y), _t(w), _t(f), alpha, h, out).cpu().numpy()
         assert np.array_equal(np.isnan(u), np.isnan(v)) and np.array_equal(np.isposinf(u), np.isposinf(v))
         assert not np.isfinite(u).any()
+
+
+@pytest.mark.parametrize("alpha,order,fmm", [(5.0, 40, False), (200.0, 40, True), (200.0, 12, True)])
+def test_fmm_or_lists(alpha, order, fmm):
+    """set_fmm leaves FP64 evaluations to the cluster lists where those are shorter than the FMM's boxes (the same
+    values, bit for bit), else the FMM serves: order 40 to rounding of the largest value (as the FMM's own tests),
+    order 12 to its truncation, geometric from 1e-9 at order 20 (1e-5 with a margin)."""
+    c = wl.Curve("starfish", R=1.0, A=0.3, k=5)
+    g = wl.discretize(c, 896)
+    q = np.linspace(-1.4, 1.4, 600)
+    tx, ty = (v.ravel() for v in np.meshgrid(q, q))
+    k = c.contains(tx, ty)
+    P = mhlp.Plan(mhlp.Geometry(_t(g.node_soa())), alpha, _t(tx[k]), _t(ty[k]))
+    sigma, mu = _t(np.cos(3 * g.theta)), _t(np.sin(2 * g.theta))
+    want = mhlp.eval_layer(P, sigma=sigma, mu=mu)
+    P.set_fmm(order)
+    assert P.fmm[0] == order
+    got = mhlp.eval_layer(P, sigma=sigma, mu=mu) + (mhlp.eval_slp(P, sigma), mhlp.eval_dlp(P, mu))
+    for a, b in zip(got, want + want):
+        if fmm:
+            assert not torch.equal(a, b)
+            assert float((a - b).abs().max()) < (1e-12 if order == 40 else 1e-5) * float(b.abs().max())
+        else:
+            assert float((a - b).abs().max()) < 1e-13 * float(b.abs().max())
+    if not fmm:
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
