@@ -3397,15 +3397,6 @@ extern "C" mhlp_status mhlp_box_create(int32_t M, double x0, double y0, double L
     return MHLP_OK;
 }
 
-static void fft2_fields(const mhlp_box *B, cplx *data, int nf, double sign, hipStream_t st)
-{
-    const int M = B->M;
-    const int64_t MM = (int64_t)M * M;
-    const size_t sh = sizeof(cplx) * 2 * (size_t)M;
-    mhlp::fft_lines_kernel<<<dim3(M, nf), M / 2, sh, st>>>(data, M, 1, M, MM, B->tw, sign); /* rows (x) */
-    mhlp::fft_lines_kernel<<<dim3(M, nf), M / 2, sh, st>>>(data, M, M, 1, MM, B->tw, sign); /* columns (y) */
-}
-
 extern "C" mhlp_status mhlp_box_particular(mhlp_box *B, const double *F, double *u, double *grad, int64_t n,
                                            const double *px, const double *py, double *up, void *stream)
 {
@@ -3417,20 +3408,23 @@ extern "C" mhlp_status mhlp_box_particular(mhlp_box *B, const double *F, double 
     hipStream_t st = (hipStream_t)stream;
     const int M = B->M;
     const int64_t MM = (int64_t)M * M;
-    mhlp::fft_load_real_kernel<<<nblocks(2 * MM, 256), 256, 0, st>>>(F, 2 * MM, B->spec);
-    fft2_fields(B, B->spec, 2, -1.0, st);
-    mhlp::stokes_multiplier_kernel<<<nblocks(MM, 256), 256, 0, st>>>(B->spec, M, B->Lb, B->alpha, grad != nullptr,
-                                                                     B->uh);
+    int lg = 4;
+    while ((1 << lg) < M) ++lg;
+    const int L = mhlp::fft_rows(M), T = M / 8, G = M <= 512 ? 3 : 1;
+    const size_t line = sizeof(cplx) * mhlp::fft_line_lds(M);
+    mhlp::fft_rows_load_kernel<<<dim3(M / L, 2), L * T, L * line, st>>>(F, lg, B->tw, B->spec);
+    const int f0 = u ? 0 : 2, f1 = grad ? 6 : u ? 2 : f0; /* fields on the grid */
+    mhlp::fft_solve_kernel<<<M, G * T, G * line, st>>>(B->spec, lg, B->tw, B->Lb, B->alpha, f0, f1, n > 0, B->uh);
     if (n > 0 && B->point_method == 1) {
         TRY(box_nufft_setup(B, st));
-        const int Mf = 2 * M;
+        const int Mf = 2 * M, Lf = mhlp::fft_rows(Mf);
         const int64_t MMf = (int64_t)Mf * Mf;
-        mhlp::nufft_fine_spectrum_kernel<<<nblocks(2 * MMf, 256), 256, 0, st>>>(B->uh, M, Mf, B->corr, B->fine);
-        const size_t sh = sizeof(cplx) * 2 * (size_t)Mf;
-        mhlp::fft_lines_kernel<<<dim3(Mf, 2), Mf / 2, sh, st>>>(B->fine, Mf, 1, Mf, MMf, B->twf, 1.0);
-        mhlp::fft_lines_kernel<<<dim3(Mf, 2), Mf / 2, sh, st>>>(B->fine, Mf, Mf, 1, MMf, B->twf, 1.0);
-        mhlp::nufft_interp_kernel<<<nblocks(n, 128), 128, 0, st>>>(B->fine, Mf, B->Lb / Mf, B->x0, B->y0, px, py, n,
-                                                                  up);
+        const size_t linef = sizeof(cplx) * mhlp::fft_line_lds(Mf);
+        double *values = reinterpret_cast<double *>(B->fine + MMf); /* behind the [2][M][Mf] lines */
+        mhlp::nufft_lines_kernel<<<dim3(M, 2), Mf / 8, linef, st>>>(B->spec, lg + 1, B->corr, B->twf, B->fine);
+        mhlp::fft_rows_store_kernel<true><<<dim3(Mf / Lf, 2), Lf * Mf / 8, Lf * linef, st>>>(B->fine, lg + 1, MMf / 2,
+                                                                                           B->twf, 0, values, nullptr);
+        mhlp::nufft_interp_kernel<<<nblocks(n, 16), 256, 0, st>>>(values, Mf, B->Lb / Mf, B->x0, B->y0, px, py, n, up);
     } else if (n > 0) {
         const int nchunk = M / mhlp::FT2_R;
         const int64_t need = 2 * (int64_t)nchunk * n;
@@ -3443,17 +3437,11 @@ extern "C" mhlp_status mhlp_box_particular(mhlp_box *B, const double *F, double 
             B->part_cap = need;
         }
         mhlp::type2_points_kernel<<<dim3(nblocks(n, mhlp::FT2_T), nchunk), mhlp::FT2_T, 0, st>>>(
-            B->uh, M, B->Lb, B->x0, B->y0, px, py, n, B->part);
+            B->spec, M, B->Lb, B->x0, B->y0, px, py, n, B->part);
         mhlp::type2_reduce_kernel<<<nblocks(n, 256), 256, 0, st>>>(B->part, nchunk, n, up);
     }
-    if (u) {
-        fft2_fields(B, B->uh, 2, 1.0, st);
-        mhlp::fft_store_real_kernel<<<nblocks(2 * MM, 256), 256, 0, st>>>(B->uh, 2 * MM, u);
-    }
-    if (grad) {
-        fft2_fields(B, B->uh + 2 * MM, 4, 1.0, st);
-        mhlp::fft_store_real_kernel<<<nblocks(4 * MM, 256), 256, 0, st>>>(B->uh + 2 * MM, 4 * MM, grad);
-    }
+    if (f1 > f0)
+        mhlp::fft_rows_store_kernel<false><<<dim3(M / L, f1 - f0), L * T, L * line, st>>>(B->uh, lg, MM, B->tw, f0, u, grad);
     HIPCHECK(hipGetLastError());
     return MHLP_OK;
 }
