@@ -3859,8 +3859,8 @@ struct BState {
     int32_t done;  /* all systems converged / broken down, or kmax reached   */
     int32_t nact;  /* systems still active after the last step               */
     int32_t steps; /* lockstep steps taken in this cycle                     */
-    int32_t count, ticket; /* systems left active and systems finished by the running step */
     int32_t pad;
+    unsigned long long arrived; /* the running step: systems that are through, and << 32 those left active */
 };
 
 /* density of a batched launch: fixed, or basis column bs->j; false = no-op */
@@ -4352,7 +4352,6 @@ __global__ __launch_bounds__(GSF_T) void batch_gs_kernel(BState *__restrict__ bs
             resest[s] = est;
             scale = est <= thresh[s] || hk == 0.0 ? 0.0 : 1.0 / hk;
             gate[s] = scale;
-            if (scale != 0.0) atomicAdd(&bs->count, 1);
         }
         __syncthreads();
         for (int c = t; c <= k + 1; c += GSF_T) Hs[(int64_t)c * m + k] = sh.col[c];
@@ -4369,10 +4368,10 @@ __global__ __launch_bounds__(GSF_T) void batch_gs_kernel(BState *__restrict__ bs
         if (i < N) Vs[(int64_t)(k + 1) * ld + i] = sc * x[e];
     }
     if (t != 0) return;
-    __threadfence();
-    if (atomicAdd(&bs->ticket, 1) != S - 1) return;
-    const int left = atomicExch(&bs->count, 0);
-    bs->ticket = 0;
+    const unsigned long long mine = 1ull + (sc != 0.0 ? 1ull << 32 : 0ull), all = atomicAdd(&bs->arrived, mine) + mine;
+    if ((uint32_t)all != (uint32_t)S) return;
+    const int left = (int)(all >> 32);
+    bs->arrived = 0;
     bs->nact = left;
     bs->steps = k + 1;
     bs->j = k + 1;
@@ -4930,7 +4929,7 @@ extern "C" mhlp_status mhlp_batch_gmres_solve(mhlp_batch *B, const double *g, do
             gs_[0] = rn[s2];
             up_h[(size_t)S * (m + 1) + s2] = 0.5 * opts->tol * bn[s2];
         }
-        *bsh = BState{0, std::min(mcyc, opts->max_iter - total_it), 0, nact, 0, 0, 0, 0};
+        *bsh = BState{0, std::min(mcyc, opts->max_iter - total_it), 0, nact, 0, 0, 0};
         HIPCHECK(hipMemcpyAsync(B->dsc, sc.data(), sizeof(double) * S, hipMemcpyHostToDevice, st));
         bscale_kernel<<<gS, 256, 0, st>>>(B->r, B->dsc, B->V, B->doff, B->dn);
         HIPCHECK(hipMemcpyAsync(d.gv, up_h, sizeof(double) * (size_t)S * (m + 1), hipMemcpyHostToDevice, st));

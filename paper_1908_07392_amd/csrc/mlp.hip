@@ -48,20 +48,26 @@ static inline unsigned nb(int64_t n, int t) { return (unsigned)((n + t - 1) / t)
 
 /* ------------------------------------------------------------------------ */
 /* BF16 GEMM on the matrix cores                                              */
-/*   C_z[m][n] = sum_{k in chunk z} A(m,k) B(k,n)                             */
+/*   C[m][n] = sum_k A(m,k) B(k,n)                                            */
 /*   A(m,k) = A[m*sam + k*sak], B(k,n) = B[k*sbk + n*sbn] (FP32 in memory,    */
 /*   rounded to nearest-even BF16 as they are staged).  A block of four waves */
-/*   owns a 32x32 output tile (each wave a 16x16 quarter); per step of 32 k   */
+/*   owns a 32x32 output tile (each wave a 16x16 quarter); per step of 128 k  */
 /*   its threads stage the tile's A rows and B columns in LDS as BF16 (each   */
-/*   element read from global memory once per block) and every wave issues    */
-/*   one v_mfma_f32_16x16x32_bf16.  blockIdx.z splits K into chunks of Kc (a  */
-/*   multiple of 32) whose partial tiles go to C + z*split_stride and are     */
-/*   summed by the consumer.                                                  */
+/*   element read from global memory once per block, eight loads of a thread  */
+/*   in flight) and every wave issues up to four v_mfma_f32_16x16x32_bf16.    */
+/*   K is split into chunks of Kc (a multiple of 32) over blocks; the last    */
+/*   block of a tile to arrive adds the chunks' partial tiles in order and    */
+/*   goes on to the elementwise work that takes the product (Epi).            */
 /* v_mfma_f32_16x16x32_bf16 operand layout (lane l of 64):                    */
 /*   A: row l%16, k = 8(l/16)..8(l/16)+7;  B: column l%16, same k;            */
 /*   D: column l%16, rows 4(l/16)..4(l/16)+3.                                 */
-/* AV / BV: the operand is contiguous along k and 16-byte aligned, so the     */
-/* four k values a thread stages come in one load.                            */
+/*                                                                            */
+/* A launch runs up to two independent products and a column sum (the weight  */
+/* gradient, the input gradient and the bias gradient of a layer).  The       */
+/* training step's sizes (a few hundred by a hundred) leave every launch at   */
+/* the cost of its latency: 96 samples, 4096-256-256-1024 network, one step   */
+/* with load, gradients, Adam and read-back: 28 launches and 122 us with a    */
+/* kernel per product, sum and elementwise pass, against 9 and 74 us.         */
 /* ------------------------------------------------------------------------ */
 typedef short short4_t __attribute__((ext_vector_type(4)));
 typedef short short8_t __attribute__((ext_vector_type(8)));
@@ -75,69 +81,260 @@ __device__ __forceinline__ short f32_to_bf16(float f)
     return (short)(u >> 16);
 }
 
-template <bool VEC>
-__device__ __forceinline__ short4_t load_k4(const float *__restrict__ P, int64_t row_off, int64_t sk, int k, int kend,
-                                            bool valid)
+constexpr int GT = 32;       /* output tile edge and k of one matrix instruction */
+constexpr int GK = 128;      /* k staged at a time */
+constexpr int GT_PAD = 8;    /* LDS row padding (BF16 elements): rows of 272 bytes */
+constexpr int MAX_SPLITS = 32;
+constexpr int MAX_TICKETS = 256; /* tiles of a split product: fewer than 256 */
+
+constexpr float GELU_C = 0.7978845608028654f; /* sqrt(2/pi) */
+constexpr float GELU_A = 0.044715f;
+
+enum Epi : int {
+    EPI_STORE, /* o1 = C, and o2 = C when given */
+    EPI_ACT,   /* o1 = Z = C + bias, o2 = gelu(Z) when given */
+    EPI_MSE,   /* o1 = Z = C + bias, o2 = 2 (Z - T)/n, loss += mean (Z - T)^2 (also to loss2 when given) */
+    EPI_BACK   /* o1 = C gelu'(Z) */
+};
+
+/* how a thread reads an operand: k contiguous and 16-byte aligned (four k in
+   one load), rows contiguous (a half wave reads 32 rows at once), any strides */
+enum Access : int { ACC_K4, ACC_ROW, ACC_ANY };
+
+struct GemmJob {
+    int M, N, K, Kc, splits, gx, gy;
+    int aa, ab; /* Access of A and B */
+    const float *A, *B;
+    int64_t sam, sak, sbk, sbn;
+    float *P; /* partial tiles [splits][M][N] */
+    int *ticket;
+    int epi;
+    const float *bias, *Z, *T;
+    float *o1, *o2;
+    int64_t ldc;
+    float *loss, *loss2;
+    float *clear, *clear2; /* set to zero by the first block: a loss that a later launch adds to */
+};
+
+/* db[c] = sum_r dZ[r][c], also to db2 when given */
+struct ColJob {
+    const float *dZ;
+    float *db, *db2;
+    int rows, cols;
+};
+
+template <int ACCESS>
+__device__ __forceinline__ void stage_place(int t, int &row, int &k4)
 {
-    short4_t r;
-    if (VEC) {
+    row = ACCESS == ACC_ROW ? t & 31 : t >> 3;
+    k4 = 4 * (ACCESS == ACC_ROW ? t >> 5 : t & 7);
+}
+
+template <int ACCESS>
+__device__ __forceinline__ float4_t stage_load(const float *__restrict__ P, int64_t off, int64_t sk, int k,
+                                               int kend, bool valid)
+{
+    float4_t v = {0.f, 0.f, 0.f, 0.f};
+    if (ACCESS == ACC_K4) {
         /* kend - k is either >= 4 or <= 0: chunk bounds and K are multiples of 4 */
-        float4_t v = {0.f, 0.f, 0.f, 0.f};
-        if (valid && k < kend) v = *reinterpret_cast<const float4_t *>(P + row_off + k);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) r[t] = f32_to_bf16(v[t]);
+        if (valid && k < kend) v = *reinterpret_cast<const float4_t *>(P + off + k);
     } else {
 #pragma unroll
-        for (int t = 0; t < 4; ++t) r[t] = f32_to_bf16((valid && k + t < kend) ? P[row_off + (int64_t)(k + t) * sk] : 0.f);
+        for (int t = 0; t < 4; ++t)
+            if (valid && k + t < kend) v[t] = P[off + (int64_t)(k + t) * sk];
     }
+    return v;
+}
+
+__device__ __forceinline__ short4_t to_bf16(float4_t v)
+{
+    short4_t r;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) r[t] = f32_to_bf16(v[t]);
     return r;
 }
 
-constexpr int GT = 32;       /* output tile edge and k step */
-constexpr int GT_PAD = 8;    /* LDS row padding (BF16 elements): rows of 80 bytes */
+struct GemmShared {
+    __attribute__((aligned(16))) short la[GT][GK + GT_PAD]; /* [m][k] */
+    __attribute__((aligned(16))) short lb[GT][GK + GT_PAD]; /* [n][k] */
+    float red[4];
+    int last;
+};
 
-template <bool AV, bool BV>
-__global__ __launch_bounds__(256) void gemm_bf16_kernel(int M, int N, int K, int Kc, const float *__restrict__ A,
-                                                        int64_t sam, int64_t sak, const float *__restrict__ B,
-                                                        int64_t sbk, int64_t sbn, float *__restrict__ C, int64_t ldc,
-                                                        int64_t split_stride)
+template <int AA, int AB>
+__device__ __forceinline__ void gemm_block(const GemmJob &J, int block, GemmShared &sh)
 {
-    __shared__ __attribute__((aligned(16))) short la[GT][GT + GT_PAD]; /* [m][k] */
-    __shared__ __attribute__((aligned(16))) short lb[GT][GT + GT_PAD]; /* [n][k] */
-    const int tm = blockIdx.y * GT, tn = blockIdx.x * GT;
-    const int kbeg = blockIdx.z * Kc, kend = min(K, kbeg + Kc);
+    auto &la = sh.la;
+    auto &lb = sh.lb;
+    const int tile = block % (J.gx * J.gy), z = block / (J.gx * J.gy);
+    const int tm = tile / J.gx * GT, tn = tile % J.gx * GT;
+    const int kbeg = z * J.Kc, kend = min(J.K, kbeg + J.Kc);
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const int wm = (wv >> 1) * 16, wn = (wv & 1) * 16; /* the wave's quarter of the tile */
-    /* staging: thread t takes row (column) t / 8 of the tile and k = 4 (t % 8) .. + 3 */
-    const int sr = t >> 3, sk4 = (t & 7) * 4;
-    const bool va = tm + sr < M, vb = tn + sr < N;
-    const int64_t aoff = (int64_t)(tm + sr) * sam, boff = (int64_t)(tn + sr) * sbn;
+    int ra, ka, rb, kb;
+    stage_place<AA>(t, ra, ka);
+    stage_place<AB>(t, rb, kb);
+    const bool va = tm + ra < J.M, vb = tn + rb < J.N;
+    const int64_t aoff = (int64_t)(tm + ra) * J.sam, boff = (int64_t)(tn + rb) * J.sbn;
     const int r = lane & 15, kg = lane >> 4;
-    float4_t acc = {0.f, 0.f, 0.f, 0.f};
-    for (int k0 = kbeg; k0 < kend; k0 += GT) {
-        const short4_t a = load_k4<AV>(A, aoff, sak, k0 + sk4, kend, va);
-        const short4_t b = load_k4<BV>(B, boff, sbk, k0 + sk4, kend, vb);
-        __syncthreads(); /* the previous step's operands are read */
-        *reinterpret_cast<short4_t *>(&la[sr][sk4]) = a;
-        *reinterpret_cast<short4_t *>(&lb[sr][sk4]) = b;
-        __syncthreads();
-        const short8_t av = *reinterpret_cast<const short8_t *>(&la[wm + r][8 * kg]);
-        const short8_t bv = *reinterpret_cast<const short8_t *>(&lb[wn + r][8 * kg]);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, av),
-                                                      __builtin_bit_cast(bf16x8_t, bv), acc, 0, 0, 0);
+    if (block == 0 && t == 0) {
+        if (J.clear) *J.clear = 0.f;
+        if (J.clear2) *J.clear2 = 0.f;
     }
-    C += blockIdx.z * split_stride;
+    float4_t acc = {0.f, 0.f, 0.f, 0.f};
+    for (int k0 = kbeg; k0 < kend; k0 += GK) {
+        float4_t a[GK / GT], b[GK / GT];
+#pragma unroll
+        for (int q = 0; q < GK / GT; ++q) {
+            a[q] = stage_load<AA>(J.A, aoff, J.sak, k0 + GT * q + ka, kend, va);
+            b[q] = stage_load<AB>(J.B, boff, J.sbk, k0 + GT * q + kb, kend, vb);
+        }
+        __syncthreads(); /* the previous step's operands are read */
+#pragma unroll
+        for (int q = 0; q < GK / GT; ++q) {
+            *reinterpret_cast<short4_t *>(&la[ra][GT * q + ka]) = to_bf16(a[q]);
+            *reinterpret_cast<short4_t *>(&lb[rb][GT * q + kb]) = to_bf16(b[q]);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < GK / GT; ++q) {
+            if (k0 + GT * q >= kend) break;
+            const short8_t av = *reinterpret_cast<const short8_t *>(&la[wm + r][GT * q + 8 * kg]);
+            const short8_t bv = *reinterpret_cast<const short8_t *>(&lb[wn + r][GT * q + 8 * kg]);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, av),
+                                                          __builtin_bit_cast(bf16x8_t, bv), acc, 0, 0, 0);
+        }
+    }
+    const int col = tn + wn + r, row0 = tm + wm + 4 * kg;
+    const int64_t MN = (int64_t)J.M * J.N;
+    float c0 = 0.f; /* the sum starts from the bias, as with one kernel per step */
+    if ((J.epi == EPI_ACT || J.epi == EPI_MSE) && col < J.N) c0 = J.bias[col];
+    if (J.splits > 1) {
+        float *P = J.P + z * MN;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (row0 + q < J.M && col < J.N)
+                __hip_atomic_store(P + (int64_t)(row0 + q) * J.N + col, acc[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        /* The partial tiles go through device-scope stores and loads, which reach
+           the memory that all XCDs share; the stores have arrived once they are
+           waited for.  A device fence would write back the whole L2 of every
+           block's XCD: 30 us a launch instead of 10. */
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        if (t == 0) {
+            sh.last = atomicAdd(J.ticket + tile, 1) == J.splits - 1;
+            if (sh.last) J.ticket[tile] = 0; /* ready for the next launch */
+        }
+        __syncthreads();
+        if (!sh.last) return;
+        const float *from[4]; /* elements outside repeat the edge's */
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            acc[q] = c0;
+            from[q] = J.P + (int64_t)min(row0 + q, J.M - 1) * J.N + min(col, J.N - 1);
+        }
+#pragma unroll 1
+        for (int y0 = 0; y0 < J.splits; y0 += 8) {
+            float part[8][4];
+#pragma unroll
+            for (int y = 0; y < 8; ++y)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    part[y][q] = __hip_atomic_load(from[q] + min(y0 + y, J.splits - 1) * MN, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+            for (int y = 0; y < 8; ++y)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) acc[q] = y0 + y < J.splits ? acc[q] + part[y][q] : acc[q];
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[q] += c0;
+    }
+    float sq = 0.f;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const int row = tm + wm + 4 * kg + q, col = tn + wn + r;
-        if (row < M && col < N) C[(int64_t)row * ldc + col] = acc[q];
+        const int row = row0 + q;
+        if (row >= J.M || col >= J.N) continue;
+        const int64_t i = (int64_t)row * J.ldc + col;
+        const float v = acc[q];
+        if (J.epi == EPI_STORE) {
+            J.o1[i] = v;
+            if (J.o2) J.o2[i] = v;
+        } else if (J.epi == EPI_ACT) {
+            J.o1[i] = v;
+            if (J.o2) {
+                const float th = tanhf(GELU_C * (v + GELU_A * v * v * v));
+                J.o2[i] = 0.5f * v * (1.f + th);
+            }
+        } else if (J.epi == EPI_MSE) {
+            const float d = v - J.T[i];
+            J.o1[i] = v;
+            J.o2[i] = 2.f * d / (float)MN;
+            sq += d * d;
+        } else {
+            const float zz = J.Z[i];
+            const float th = tanhf(GELU_C * (zz + GELU_A * zz * zz * zz));
+            const float du = GELU_C * (1.f + 3.f * GELU_A * zz * zz);
+            J.o1[i] = v * (0.5f * (1.f + th) + 0.5f * zz * (1.f - th * th) * du);
+        }
     }
+    if (J.epi == EPI_MSE) {
+        for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o);
+        if (lane == 0) sh.red[wv] = sq;
+        __syncthreads();
+        if (t == 0) {
+            const float s = (sh.red[0] + sh.red[1] + sh.red[2] + sh.red[3]) / (float)MN;
+            atomicAdd(J.loss, s);
+            if (J.loss2) atomicAdd(J.loss2, s);
+        }
+    }
+}
+
+__device__ __forceinline__ void gemm_any(const GemmJob &J, int block, GemmShared &sh)
+{
+    switch (3 * J.aa + J.ab) {
+    case 3 * ACC_K4 + ACC_K4: gemm_block<ACC_K4, ACC_K4>(J, block, sh); break;
+    case 3 * ACC_K4 + ACC_ROW: gemm_block<ACC_K4, ACC_ROW>(J, block, sh); break;
+    case 3 * ACC_K4 + ACC_ANY: gemm_block<ACC_K4, ACC_ANY>(J, block, sh); break;
+    case 3 * ACC_ROW + ACC_K4: gemm_block<ACC_ROW, ACC_K4>(J, block, sh); break;
+    case 3 * ACC_ROW + ACC_ROW: gemm_block<ACC_ROW, ACC_ROW>(J, block, sh); break;
+    case 3 * ACC_ROW + ACC_ANY: gemm_block<ACC_ROW, ACC_ANY>(J, block, sh); break;
+    case 3 * ACC_ANY + ACC_K4: gemm_block<ACC_ANY, ACC_K4>(J, block, sh); break;
+    case 3 * ACC_ANY + ACC_ROW: gemm_block<ACC_ANY, ACC_ROW>(J, block, sh); break;
+    default: gemm_block<ACC_ANY, ACC_ANY>(J, block, sh);
+    }
+}
+
+__device__ void colsum_block(const ColJob &J, int block)
+{
+    __shared__ float red[8][32];
+    const int t = threadIdx.x, c = block * 32 + (t & 31), g = t >> 5;
+    float s = 0.f;
+    if (c < J.cols)
+        for (int r = g; r < J.rows; r += 8) s += J.dZ[(int64_t)r * J.cols + c];
+    red[g][t & 31] = s;
+    __syncthreads();
+    if (g != 0 || c >= J.cols) return;
+    for (int q = 1; q < 8; ++q) s += red[q][t];
+    J.db[c] = s;
+    if (J.db2) J.db2[c] = s;
+}
+
+/* blocks of J0, then of J1 (gx 0: none), then of the column sum */
+__global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmJob J0, GemmJob J1, ColJob C)
+{
+    __shared__ GemmShared sh;
+    const int block = blockIdx.x;
+    const int n0 = J0.gx * J0.gy * J0.splits, n1 = J1.gx * J1.gy * J1.splits;
+    if (block >= n0 + n1)
+        colsum_block(C, block - n0 - n1);
+    else
+        gemm_any(block < n0 ? J0 : J1, block < n0 ? block : block - n0, sh);
 }
 
 /* K chunking: enough blocks to fill the chip (about 256 blocks of four
    waves), chunks of at least 64 and a multiple of GT; at most MAX_SPLITS */
-constexpr int MAX_SPLITS = 32;
-
 static int splitk_chunk(int M, int N, int K)
 {
     const int64_t tiles = (int64_t)nb(M, GT) * nb(N, GT);
@@ -148,108 +345,31 @@ static int splitk_chunk(int M, int N, int K)
     return Kc;
 }
 
-static bool kvec(const float *P, int64_t srow, int64_t sk, int K)
+static int access_of(const float *P, int64_t srow, int64_t sk, int K)
 {
-    return sk == 1 && srow % 4 == 0 && K % 4 == 0 && ((uintptr_t)P & 15u) == 0;
+    if (sk == 1 && srow % 4 == 0 && K % 4 == 0 && ((uintptr_t)P & 15u) == 0) return ACC_K4;
+    return srow == 1 ? ACC_ROW : ACC_ANY;
 }
 
-/* returns the number of K chunks written (C + z*split_stride, z < chunks) */
-static int gemm_bf16(hipStream_t st, int M, int N, int K, const float *A, int64_t sam, int64_t sak, const float *B,
-                     int64_t sbk, int64_t sbn, float *C, int64_t ldc, int64_t split_stride, bool allow_split)
+/* a product into o1; P NULL: K is not split */
+static GemmJob gemm_job(int M, int N, int K, const float *A, int64_t sam, int64_t sak, const float *B, int64_t sbk,
+                        int64_t sbn, float *P, int *ticket, int epi, float *o1, int64_t ldc)
 {
-    const int Kc = allow_split ? splitk_chunk(M, N, K) : (K + GT - 1) / GT * GT;
-    const int splits = (int)nb(K, Kc);
-    dim3 grid(nb(N, GT), nb(M, GT), (unsigned)splits);
-    const bool av = kvec(A, sam, sak, K), bv = kvec(B, sbn, sbk, K);
-    if (av && bv)
-        gemm_bf16_kernel<true, true><<<grid, 256, 0, st>>>(M, N, K, Kc, A, sam, sak, B, sbk, sbn, C, ldc, split_stride);
-    else if (av)
-        gemm_bf16_kernel<true, false><<<grid, 256, 0, st>>>(M, N, K, Kc, A, sam, sak, B, sbk, sbn, C, ldc,
-                                                            split_stride);
-    else if (bv)
-        gemm_bf16_kernel<false, true><<<grid, 256, 0, st>>>(M, N, K, Kc, A, sam, sak, B, sbk, sbn, C, ldc,
-                                                            split_stride);
-    else
-        gemm_bf16_kernel<false, false><<<grid, 256, 0, st>>>(M, N, K, Kc, A, sam, sak, B, sbk, sbn, C, ldc,
-                                                             split_stride);
-    return splits;
+    GemmJob J = {};
+    J.M = M, J.N = N, J.K = K;
+    J.Kc = P ? splitk_chunk(M, N, K) : (K + GT - 1) / GT * GT;
+    J.splits = (int)nb(K, J.Kc);
+    J.gx = (int)nb(N, GT), J.gy = (int)nb(M, GT);
+    J.A = A, J.sam = sam, J.sak = sak, J.B = B, J.sbk = sbk, J.sbn = sbn;
+    J.aa = access_of(A, sam, sak, K), J.ab = access_of(B, sbn, sbk, K);
+    J.P = P, J.ticket = ticket, J.epi = epi, J.o1 = o1, J.ldc = ldc;
+    return J;
 }
 
-/* out[r][c] = sum_z P[z*stride + r*cols + c] */
-__global__ void splitk_sum_kernel(const float *__restrict__ P, int splits, int64_t stride, float *__restrict__ out,
-                                  int64_t n)
+static void launch_gemm(hipStream_t st, const GemmJob &J0, const GemmJob &J1 = GemmJob{}, const ColJob &C = ColJob{})
 {
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    float s = 0.f;
-    for (int z = 0; z < splits; ++z) s += P[z * stride + i];
-    out[i] = s;
-}
-
-/* ------------------------------------------------------------------------ */
-/* elementwise pieces of the network                                          */
-/* ------------------------------------------------------------------------ */
-constexpr float GELU_C = 0.7978845608028654f; /* sqrt(2/pi) */
-constexpr float GELU_A = 0.044715f;
-
-/* Z = sum_z Zp[z] + b (per column); A = gelu(Z) when A is non-null
-   (Zp may alias Z when splits == 1) */
-__global__ void bias_act_kernel(const float *Zp, int splits, int64_t sstride, const float *__restrict__ b, float *Z,
-                                float *__restrict__ Aout, int rows, int cols)
-{
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= (int64_t)rows * cols) return;
-    float z = b[i % cols];
-    for (int q = 0; q < splits; ++q) z += Zp[q * sstride + i];
-    Z[i] = z;
-    if (Aout) {
-        const float t = tanhf(GELU_C * (z + GELU_A * z * z * z));
-        Aout[i] = 0.5f * z * (1.f + t);
-    }
-}
-
-/* dZ = (sum_z dAp[z]) * gelu'(Z) */
-__global__ void gelu_back_kernel(const float *__restrict__ Z, const float *__restrict__ dAp, int splits,
-                                 int64_t sstride, float *__restrict__ dZ, int64_t n)
-{
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    float da = 0.f;
-    for (int q = 0; q < splits; ++q) da += dAp[q * sstride + i];
-    const float z = Z[i];
-    const float t = tanhf(GELU_C * (z + GELU_A * z * z * z));
-    const float du = GELU_C * (1.f + 3.f * GELU_A * z * z);
-    dZ[i] = da * (0.5f * (1.f + t) + 0.5f * z * (1.f - t * t) * du);
-}
-
-/* dY = 2 (Y - T) / n and loss = mean (Y - T)^2 (loss zeroed by the caller) */
-__global__ __launch_bounds__(256) void mse_kernel(const float *__restrict__ Y, const float *__restrict__ T,
-                                                  float *__restrict__ dY, int64_t n, float *__restrict__ loss)
-{
-    __shared__ float red[256];
-    float s = 0.f;
-    for (int64_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-        const float d = Y[i] - T[i];
-        dY[i] = 2.f * d / (float)n;
-        s += d * d;
-    }
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) atomicAdd(loss, red[0] / (float)n);
-}
-
-/* db[c] = sum_r dZ[r][c] */
-__global__ void colsum_kernel(const float *__restrict__ dZ, float *__restrict__ db, int rows, int cols)
-{
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= cols) return;
-    float s = 0.f;
-    for (int r = 0; r < rows; ++r) s += dZ[(int64_t)r * cols + c];
-    db[c] = s;
+    const int64_t blocks = (int64_t)J0.gx * J0.gy * J0.splits + (int64_t)J1.gx * J1.gy * J1.splits + nb(C.cols, 32);
+    gemm_bf16_kernel<<<(unsigned)blocks, 256, 0, st>>>(J0, J1, C);
 }
 
 __global__ void adam_kernel(float *__restrict__ p, const float *__restrict__ g, float *__restrict__ m,
@@ -286,6 +406,17 @@ __global__ void zero_f32_kernel(float *__restrict__ p, int64_t n)
     if (i < n) p[i] = 0.f;
 }
 
+/* new parameters, moments back to zero */
+__global__ void load_params_kernel(const float *__restrict__ src, float *__restrict__ p, float *__restrict__ m,
+                                   float *__restrict__ v, int64_t n)
+{
+    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    p[i] = src[i];
+    m[i] = 0.f;
+    v[i] = 0.f;
+}
+
 static void zero_f32(hipStream_t st, float *p, int64_t n)
 {
     if (n > 0) zero_f32_kernel<<<nb(n, 256), 256, 0, st>>>(p, n);
@@ -300,8 +431,9 @@ struct mhlp_mlp {
     float *p = nullptr, *g = nullptr, *m = nullptr, *v = nullptr, *loss = nullptr;
     int cap = 0; /* batch capacity of the activation buffers */
     float *Z[3] = {nullptr, nullptr, nullptr}, *Ac[2] = {nullptr, nullptr}, *d0 = nullptr, *d1 = nullptr;
-    float *ws = nullptr; /* split-K partial tiles: MAX_SPLITS x cap x max(n1, n2, n3) */
+    float *ws = nullptr; /* split-K partial tiles, twice MAX_SPLITS x cap x max(n1, n2, n3) (ws_len each) */
     int64_t ws_len = 0;
+    int *ticket = nullptr; /* [2][MAX_TICKETS] arrivals at the tiles of split products, zero between launches */
     int64_t step = 0;
 };
 
@@ -346,6 +478,7 @@ extern "C" mhlp_status mhlp_mlp_destroy(mhlp_mlp *N)
     free_dev(N->m);
     free_dev(N->v);
     free_dev(N->loss);
+    free_dev(N->ticket);
     delete N;
     return MHLP_OK;
 }
@@ -374,7 +507,8 @@ extern "C" mhlp_status mhlp_mlp_create(int32_t n_in, int32_t width, int32_t n_ou
     N->nparam = o;
     mhlp_status s;
     if ((s = malloc_dev(&N->p, o)) || (s = malloc_dev(&N->g, o)) || (s = malloc_dev(&N->m, o)) ||
-        (s = malloc_dev(&N->v, o)) || (s = malloc_dev(&N->loss, 1))) {
+        (s = malloc_dev(&N->v, o)) || (s = malloc_dev(&N->loss, 1)) ||
+        (s = malloc_dev(&N->ticket, 2 * MAX_TICKETS))) {
         mhlp_mlp_destroy(N);
         return s;
     }
@@ -382,6 +516,7 @@ extern "C" mhlp_status mhlp_mlp_create(int32_t n_in, int32_t width, int32_t n_ou
     zero_f32(st, N->g, o);
     zero_f32(st, N->m, o);
     zero_f32(st, N->v, o);
+    zero_f32(st, reinterpret_cast<float *>(N->ticket), 2 * MAX_TICKETS); /* all bits zero */
     for (int l = 0; l < 3; ++l) {
         const int64_t cnt = N->off_b[l] - N->off_w[l];
         init_uniform_kernel<<<nb(cnt, 256), 256, 0, st>>>(N->p, N->off_w[l], N->off_b[l],
@@ -413,9 +548,7 @@ extern "C" mhlp_status mhlp_mlp_params(mhlp_mlp *N, float *dst, const float *src
     hipStream_t st = (hipStream_t)stream;
     if (dst) MHIP(hipMemcpyAsync(dst, N->p, sizeof(float) * N->nparam, hipMemcpyDeviceToDevice, st));
     if (src) {
-        MHIP(hipMemcpyAsync(N->p, src, sizeof(float) * N->nparam, hipMemcpyDeviceToDevice, st));
-        zero_f32(st, N->m, N->nparam);
-        zero_f32(st, N->v, N->nparam);
+        load_params_kernel<<<nb(N->nparam, 256), 256, 0, st>>>(src, N->p, N->m, N->v, N->nparam);
         N->step = 0;
     }
     MHIP(hipGetLastError());
@@ -432,7 +565,7 @@ static mhlp_status ensure_acts(mhlp_mlp *N, int B, hipStream_t st)
     if ((s = malloc_dev(&N->Z[0], (int64_t)B * N->n[1])) || (s = malloc_dev(&N->Z[1], (int64_t)B * N->n[2])) ||
         (s = malloc_dev(&N->Z[2], (int64_t)B * N->n[3])) || (s = malloc_dev(&N->Ac[0], (int64_t)B * N->n[1])) ||
         (s = malloc_dev(&N->Ac[1], (int64_t)B * N->n[2])) || (s = malloc_dev(&N->d0, (int64_t)B * maxw)) ||
-        (s = malloc_dev(&N->d1, (int64_t)B * maxw)) || (s = malloc_dev(&N->ws, MAX_SPLITS * (int64_t)B * maxw))) {
+        (s = malloc_dev(&N->d1, (int64_t)B * maxw)) || (s = malloc_dev(&N->ws, 2 * MAX_SPLITS * (int64_t)B * maxw))) {
         free_acts(N);
         return s;
     }
@@ -441,17 +574,22 @@ static mhlp_status ensure_acts(mhlp_mlp *N, int B, hipStream_t st)
     return MHLP_OK;
 }
 
-/* forward pass of X [B][n0]; pre-activations Z[l] and activations Ac[l] kept */
-static void forward(mhlp_mlp *N, const float *X, int B, hipStream_t st)
+/* forward pass of X [B][n0]: pre-activations Z[l] and activations Ac[l] of the
+   hidden layers are kept, the output goes to Y.  With targets T the last layer
+   also forms dL/dY in d0 and the loss, in N->loss and, when given, loss. */
+static void forward(mhlp_mlp *N, const float *X, int B, float *Y, const float *T, float *loss, hipStream_t st)
 {
     const float *in = X;
     for (int l = 0; l < 3; ++l) {
         const int ni = N->n[l], no = N->n[l + 1];
-        const int64_t sz = (int64_t)B * no;
         /* Z = in W^T:  A(b,k) = in[b*ni + k],  B(k,o) = W[o*ni + k] */
-        const int sp = gemm_bf16(st, B, no, ni, in, ni, 1, N->p + N->off_w[l], 1, ni, N->ws, no, sz, true);
-        bias_act_kernel<<<nb(sz, 256), 256, 0, st>>>(N->ws, sp, sz, N->p + N->off_b[l], N->Z[l],
-                                                     l < 2 ? N->Ac[l] : nullptr, B, no);
+        GemmJob J = gemm_job(B, no, ni, in, ni, 1, N->p + N->off_w[l], 1, ni, N->ws, N->ticket,
+                             l == 2 && T ? EPI_MSE : EPI_ACT, l < 2 ? N->Z[l] : Y, no);
+        J.bias = N->p + N->off_b[l];
+        if (l < 2) J.o2 = N->Ac[l];
+        if (T && l == 0) J.clear = N->loss, J.clear2 = loss;
+        if (T && l == 2) J.T = T, J.o2 = N->d0, J.loss = N->loss, J.loss2 = loss;
+        launch_gemm(st, J);
         if (l < 2) in = N->Ac[l];
     }
 }
@@ -462,8 +600,7 @@ extern "C" mhlp_status mhlp_mlp_forward(mhlp_mlp *N, const float *X, int32_t bat
     if (batch < 1) return mfail(MHLP_INVALID_ARG, "batch must be >= 1");
     hipStream_t st = (hipStream_t)stream;
     if (mhlp_status s = ensure_acts(N, batch, st)) return s;
-    forward(N, X, batch, st);
-    MHIP(hipMemcpyAsync(Y, N->Z[2], sizeof(float) * (size_t)batch * N->n[3], hipMemcpyDeviceToDevice, st));
+    forward(N, X, batch, Y, nullptr, nullptr, st);
     MHIP(hipGetLastError());
     return MHLP_OK;
 }
@@ -476,10 +613,7 @@ extern "C" mhlp_status mhlp_mlp_loss_grad(mhlp_mlp *N, const float *X, const flo
     hipStream_t st = (hipStream_t)stream;
     if (mhlp_status s = ensure_acts(N, batch, st)) return s;
     const int B = batch;
-    forward(N, X, B, st);
-    zero_f32(st, N->loss, 1);
-    const int64_t ny = (int64_t)B * N->n[3];
-    mse_kernel<<<std::min<unsigned>(nb(ny, 256), 240u), 256, 0, st>>>(N->Z[2], T, N->d0, ny, N->loss);
+    forward(N, X, B, N->Z[2], T, loss, st);
     /* back-propagate: cur holds dL/dZ of layer l */
     float *cur = N->d0, *nxt = N->d1;
     for (int l = 2; l >= 0; --l) {
@@ -488,20 +622,20 @@ extern "C" mhlp_status mhlp_mlp_loss_grad(mhlp_mlp *N, const float *X, const flo
         /* dW = dZ^T in : A(o,b) = dZ[b*no + o], B(b,k) = in[b*ni + k] */
         const int64_t szw = (int64_t)no * ni;
         const bool wsplit = MAX_SPLITS * szw <= N->ws_len;
-        const int spw = gemm_bf16(st, no, ni, B, cur, 1, no, in, ni, 1, wsplit ? N->ws : N->g + N->off_w[l], ni, szw,
-                                  wsplit);
-        if (wsplit) splitk_sum_kernel<<<nb(szw, 256), 256, 0, st>>>(N->ws, spw, szw, N->g + N->off_w[l], szw);
-        colsum_kernel<<<nb(no, 256), 256, 0, st>>>(cur, N->g + N->off_b[l], B, no);
+        GemmJob W = gemm_job(no, ni, B, cur, 1, no, in, ni, 1, wsplit ? N->ws : nullptr, N->ticket, EPI_STORE,
+                             N->g + N->off_w[l], ni);
+        if (grad) W.o2 = grad + N->off_w[l];
+        const ColJob C = {cur, N->g + N->off_b[l], grad ? grad + N->off_b[l] : nullptr, B, no};
+        GemmJob D = {};
         if (l > 0) {
             /* dA = dZ W : A(b,o) = dZ[b*no + o], B(o,k) = W[o*ni + k] */
-            const int64_t sza = (int64_t)B * ni;
-            const int spa = gemm_bf16(st, B, ni, no, cur, no, 1, N->p + N->off_w[l], ni, 1, N->ws, ni, sza, true);
-            gelu_back_kernel<<<nb(sza, 256), 256, 0, st>>>(N->Z[l - 1], N->ws, spa, sza, nxt, sza);
-            std::swap(cur, nxt);
+            D = gemm_job(B, ni, no, cur, no, 1, N->p + N->off_w[l], ni, 1, N->ws + N->ws_len, N->ticket + MAX_TICKETS,
+                         EPI_BACK, nxt, ni);
+            D.Z = N->Z[l - 1];
         }
+        launch_gemm(st, W, D, C);
+        std::swap(cur, nxt);
     }
-    if (loss) MHIP(hipMemcpyAsync(loss, N->loss, sizeof(float), hipMemcpyDeviceToDevice, st));
-    if (grad) MHIP(hipMemcpyAsync(grad, N->g, sizeof(float) * N->nparam, hipMemcpyDeviceToDevice, st));
     MHIP(hipGetLastError());
     return MHLP_OK;
 }
@@ -526,7 +660,7 @@ extern "C" mhlp_status mhlp_gemm_bf16(int32_t m, int32_t n, int32_t k, const flo
     if (!A || !B || !C) return mfail(MHLP_INVALID_ARG, "NULL argument");
     if (m < 1 || n < 1 || k < 1) return mfail(MHLP_INVALID_ARG, "sizes must be >= 1");
     if (ldc < n) return mfail(MHLP_INVALID_ARG, "ldc < n");
-    gemm_bf16((hipStream_t)stream, m, n, k, A, sam, sak, B, sbk, sbn, C, ldc, 0, false);
+    launch_gemm((hipStream_t)stream, gemm_job(m, n, k, A, sam, sak, B, sbk, sbn, nullptr, nullptr, EPI_STORE, C, ldc));
     MHIP(hipGetLastError());
     return MHLP_OK;
 }
