@@ -647,14 +647,6 @@ __device__ __forceinline__ double wave_sum_dpp(double v)
     return __hiloint2double(hi, lo);
 }
 
-/* sum over the 64 lanes of a wave by a fixed butterfly (every lane gets it) */
-__device__ __forceinline__ double gsf_wave_sum(double v)
-{
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    return v;
-}
-
-
 /* Plan time: the fine piece of every (wave of 64 targets, panel) for the FP64
    far field (low 7 bits: piece + 1, 0 for z <= 2 everywhere, KQ_NP + 1 when
    the pairs need the per-pair selection; bit 7 set when some target of the
@@ -1003,8 +995,10 @@ constexpr int64_t GSR_NMAX = 8 * GSF_T;
    it serves the steps whose columns all fit, the slice form the later ones */
 __host__ __device__ inline int gsr_cols(int64_t N) { return N <= GSF_T ? 32 : N <= 2 * GSF_T ? 16 : N <= 4 * GSF_T ? 8 : 4; }
 /* steps take the one-block form while their basis columns exceed the register
-   capacity by at most this many (read one at a time), the slice form after */
-constexpr int GSR_EXTRA = 8;
+   capacity by at most this many (read one at a time), the slice form after.
+   Above 4096 unknowns one CU reads the columns from L2 too slowly for that:
+   8192 unknowns, step 1 11 us, step 5 20, step 12 40, the slice form 19. */
+__host__ __device__ inline int gsr_extra(int64_t N) { return N <= 4 * GSF_T ? 8 : 0; }
 
 /* v[c][k] = V_{c0+c}[t + k GSF_T] for the chunk's columns below ncol (0 elsewhere) */
 template <int C, int E>
@@ -1166,85 +1160,113 @@ __global__ __launch_bounds__(GSF_T) void gs_reg_kernel(GState *__restrict__ gs, 
 
 /* The Gram-Schmidt part of an Arnoldi step over many blocks (CGS2), for
    vectors too long for one block.  Block b owns the element slice
-   [b L, (b+1) L); a pass leaves one partial dot product per (block, column)
-   in P[b][c] (row stride pld), and the next kernel adds the partials in
-   block order, so no result depends on timing.  Column c of a slice's dot
-   products is summed by wave c % GSM_W. */
-constexpr int GSM_T = 256, GSM_W = GSM_T / 64, GSM_NBMAX = 128, GSM_HMAX = 520;
+   [b L, (b+1) L); a pass leaves one partial dot product per (column, block)
+   in P[c][b] (nb blocks, at most two per lane of a wave), and the next kernel
+   adds a column's partials over the lanes of one wave by a fixed tree, so no
+   result depends on timing.  Bound by the latency of its four launches: 8192
+   unknowns, 20 columns, 32 -> 19 us against partials added one after the other
+   and slices of 256. */
+constexpr int GSM_T = 256, GSM_W = GSM_T / 64, GSM_S = 128, GSM_NBMAX = 128, GSM_HMAX = 520;
 
-
-/* slice length: a multiple of GSM_T giving at most GSM_NBMAX blocks */
+/* slice length: a multiple of GSM_S giving at most GSM_NBMAX blocks */
 static int64_t gsm_slice(int64_t N)
 {
-    const int64_t per = (N + (int64_t)GSM_T * GSM_NBMAX - 1) / ((int64_t)GSM_T * GSM_NBMAX);
-    return GSM_T * std::max<int64_t>(1, per);
+    const int64_t per = (N + (int64_t)GSM_S * GSM_NBMAX - 1) / ((int64_t)GSM_S * GSM_NBMAX);
+    return GSM_S * std::max<int64_t>(1, per);
 }
 
-__device__ void gsm_partial_dots(const double *__restrict__ V, int64_t ld, const double *__restrict__ w, int64_t i0,
-                                 int64_t n, int ncol, double *__restrict__ Prow)
+/* P[c][block] = V_c . w over the block's slice; wave c % GSM_W takes column c,
+   four columns' loads in flight */
+__device__ __forceinline__ void gsm_partial_dots(const double *__restrict__ V, int64_t ld, const double *w, int64_t i0,
+                                                 int64_t n, int ncol, double *__restrict__ P, int nb)
 {
-    const int t = threadIdx.x, wv = t >> 6, ln = t & 63;
-    for (int c = wv; c < ncol; c += GSM_W) {
-        const double *v = V + (int64_t)c * ld + i0;
-        double sacc = 0.0;
-        for (int64_t e = ln; e < n; e += 64) sacc = fma(v[e], w[i0 + e], sacc);
-        sacc = gsf_wave_sum(sacc);
-        if (ln == 0) Prow[c] = sacc;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), ln = threadIdx.x & 63;
+    for (int c0 = wv; c0 < ncol; c0 += 4 * GSM_W) {
+        double s[4] = {0.0, 0.0, 0.0, 0.0};
+        for (int64_t e = ln; e < n; e += 64) {
+            const double we = w[i0 + e];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int c = min(c0 + k * GSM_W, ncol - 1);
+                s[k] = fma(V[(int64_t)c * ld + i0 + e], we, s[k]);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const double v = wave_sum_dpp(s[k]);
+            if (ln == 0 && c0 + k * GSM_W < ncol) P[(int64_t)(c0 + k * GSM_W) * nb + blockIdx.x] = v;
+        }
     }
 }
 
-/* first pass: P[b][c] = V_c . w over slice b, c <= j */
+/* sum of a row of nb <= 128 partials, in every lane of a wave */
+__device__ __forceinline__ double gsm_row(const double *__restrict__ P, int nb)
+{
+    const int ln = threadIdx.x & 63;
+    double v = ln < nb ? P[ln] : 0.0;
+    if (ln + 64 < nb) v += P[ln + 64];
+    return wave_sum_dpp(v);
+}
+
+/* first pass: P[c][b] = V_c . w over slice b, c <= j */
 __global__ __launch_bounds__(GSM_T) void gsm_dot_kernel(const GState *__restrict__ gs, const double *__restrict__ V,
                                                         int64_t ld, const double *__restrict__ w, int64_t N,
-                                                        int64_t L, double *__restrict__ P, int pld)
+                                                        int64_t L, double *__restrict__ P)
 {
     if (gs->done) return;
     const int64_t i0 = blockIdx.x * L;
-    gsm_partial_dots(V, ld, w, i0, min(L, N - i0), gs->j + 1, P + (int64_t)blockIdx.x * pld);
+    gsm_partial_dots(V, ld, w, i0, min(L, N - i0), gs->j + 1, P, gridDim.x);
 }
 
-/* h = sum_b Pin[b] (block 0 also stores it in hout); w -= sum_c h_c V_c on
-   the slice; then either the partial dots of the new w (NORM = false, into
-   Pout[b][c]) or its partial squared norm (NORM = true, into Pout[b]). */
+/* h = sum_b Pin[.][b] (block 0 also stores it in hout); w -= sum_c h_c V_c on
+   the slice, the columns shared by the two threads of an element; then either
+   the partial dots of the new w (NORM = false, into Pout[c][b]) or its partial
+   squared norm (NORM = true, into Pout[b]). */
 template <bool NORM>
 __global__ __launch_bounds__(GSM_T) void gsm_sub_kernel(const GState *__restrict__ gs, const double *__restrict__ V,
-                                                        int64_t ld, double *__restrict__ w, int64_t N, int64_t L,
-                                                        const double *__restrict__ Pin, int nb, int pld,
-                                                        double *__restrict__ hout, double *__restrict__ Pout)
+                                                        int64_t ld, double *w, int64_t N, int64_t L,
+                                                        const double *__restrict__ Pin, double *__restrict__ hout,
+                                                        double *__restrict__ Pout)
 {
     __shared__ double hl[GSM_HMAX];
-    __shared__ double red[GSM_W];
+    __shared__ double half[GSM_S];
+    __shared__ double red[GSM_S / 64];
     if (gs->done) return;
-    const int t = threadIdx.x;
+    const int t = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(t >> 6), nb = gridDim.x;
     const int ncol = gs->j + 1;
-    for (int c = t; c < ncol; c += GSM_T) {
-        double h = Pin[c];
-        for (int b = 1; b < nb; ++b) h += Pin[(int64_t)b * pld + c];
-        hl[c] = h;
-        if (blockIdx.x == 0) hout[c] = h;
+#pragma unroll 4
+    for (int c = wv; c < ncol; c += GSM_W) {
+        const double h = gsm_row(Pin + (int64_t)c * nb, nb);
+        if ((t & 63) == 0) {
+            hl[c] = h;
+            if (blockIdx.x == 0) hout[c] = h;
+        }
     }
     __syncthreads();
     const int64_t i0 = blockIdx.x * L, n = min(L, N - i0);
+    const int s = t & (GSM_S - 1), part = t / GSM_S; /* even or odd columns */
     double sq = 0.0;
-    for (int64_t e = t; e < n; e += GSM_T) {
-        const int64_t i = i0 + e;
-        double v = w[i];
-        for (int c = 0; c < ncol; ++c) v = fma(-hl[c], V[(int64_t)c * ld + i], v);
-        w[i] = v;
-        sq = fma(v, v, sq);
+    for (int64_t e0 = 0; e0 < n; e0 += GSM_S) {
+        const int64_t e = min(e0 + s, n - 1), i = i0 + e;
+        double v = part == 0 ? w[i] : 0.0;
+#pragma unroll 8
+        for (int c = part; c < ncol; c += 2) v = fma(-hl[c], V[(int64_t)c * ld + i], v);
+        if (part == 1) half[s] = v;
+        __syncthreads();
+        if (part == 0 && e0 + s < n) {
+            v += half[s];
+            w[i] = v;
+            sq = fma(v, v, sq);
+        }
+        __syncthreads();
     }
     if (NORM) {
-        sq = gsf_wave_sum(sq);
-        if ((t & 63) == 0) red[t >> 6] = sq;
+        sq = wave_sum_dpp(sq);
+        if ((t & 63) == 0 && part == 0) red[wv] = sq;
         __syncthreads();
-        if (t == 0) {
-            double s2 = red[0];
-            for (int q = 1; q < GSM_W; ++q) s2 += red[q];
-            Pout[blockIdx.x] = s2;
-        }
+        if (t == 0) Pout[blockIdx.x] = red[0] + red[1];
     } else {
-        __syncthreads(); /* the slice of w, written above, is read across waves */
-        gsm_partial_dots(V, ld, w, i0, n, ncol, Pout + (int64_t)blockIdx.x * pld);
+        gsm_partial_dots(V, ld, w, i0, n, ncol, Pout, nb); /* the slice of w is written: the last barrier */
     }
 }
 
@@ -1263,10 +1285,9 @@ __global__ __launch_bounds__(GSF_T) void gsm_finish_kernel(GState *__restrict__ 
     if (gs->done) return;
     const int t = threadIdx.x;
     const int j = gs->j;
-    if (t == 0) {
-        double s2 = Pn[0];
-        for (int b = 1; b < nb; ++b) s2 += Pn[b];
-        hn = s2;
+    if (t < 64) {
+        const double s2 = gsm_row(Pn, nb);
+        if (t == 0) hn = s2;
     }
     __syncthreads();
     gs_finish_block(gs, H, R, cs, sn, gv, h1, h2, hn, col, rot);
@@ -2780,9 +2801,9 @@ static mhlp_status enqueue_step(mhlp_plan *P, int32_t prec, bool one_block, hipS
     /* classical Gram-Schmidt, twice, over element slices */
     const int64_t L = gsm_slice(N);
     const int nb = (int)((N + L - 1) / L);
-    gsm_dot_kernel<<<nb, GSM_T, 0, st>>>(d.gs, V, N, w, N, L, d.p1, R + 1);
-    gsm_sub_kernel<false><<<nb, GSM_T, 0, st>>>(d.gs, V, N, w, N, L, d.p1, nb, R + 1, d.h1, d.p2);
-    gsm_sub_kernel<true><<<nb, GSM_T, 0, st>>>(d.gs, V, N, w, N, L, d.p2, nb, R + 1, d.h2, d.pn);
+    gsm_dot_kernel<<<nb, GSM_T, 0, st>>>(d.gs, V, N, w, N, L, d.p1);
+    gsm_sub_kernel<false><<<nb, GSM_T, 0, st>>>(d.gs, V, N, w, N, L, d.p1, d.h1, d.p2);
+    gsm_sub_kernel<true><<<nb, GSM_T, 0, st>>>(d.gs, V, N, w, N, L, d.p2, d.h2, d.pn);
     gsm_finish_kernel<<<1, GSF_T, 0, st>>>(d.gs, V, N, w, N, d.pn, nb, d.H, R, d.cs, d.sn, d.gv, d.h1, d.h2);
     HIPCHECK(hipGetLastError());
     return MHLP_OK;
@@ -2952,10 +2973,10 @@ static mhlp_status gmres_core(mhlp_plan *P, double *b, double bnorm, double *x, 
             const int S = std::max(1, std::min({chunk, GMRES_MAX_CHUNK, kmax - done_steps}));
             const bool tail = expect_end || S == kmax - done_steps;
             /* Gram-Schmidt in one block for the steps whose basis columns fit
-               its registers, or exceed them by at most GSR_EXTRA (step j has
+               its registers, or exceed them by at most gsr_extra (step j has
                j + 1), over slices after them */
             const int m = (N <= GSR_NMAX && R <= GSF_RMAX)
-                              ? std::max(0, std::min(S, gsr_cols(N) + GSR_EXTRA - done_steps))
+                              ? std::max(0, std::min(S, gsr_cols(N) + gsr_extra(N) - done_steps))
                               : 0;
             hipGraphExec_t ex;
             TRY(step_graph(P, prec, m, S, tail, b, x, &ex));

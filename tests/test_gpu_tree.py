@@ -313,3 +313,15 @@ def test_fmm_or_lists(alpha, order, fmm):
             assert float((a - b).abs().max()) < 1e-13 * float(b.abs().max())
     if not fmm:
         assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
+@pytest.mark.parametrize("panels,restart", [(200, 40), (257, 40), (520, 6), (1100, 60), (2100, 30)])
+def test_gram_schmidt_over_slices(panels, restart):
+    """Solves whose Gram-Schmidt runs over slices (every slice length, more than 64 of them, restarts): the residual
+    formed by the operator itself meets the tolerance, with rounding of the two operator applications on top."""
+    g = wl.discretize(wl.Curve("starfish", R=1.0, A=0.3, k=5), panels)
+    P = mhlp.Plan(mhlp.Geometry(_t(g.node_soa())), 9.0)
+    b = _t(np.cos(3 * g.theta) + np.where(np.arange(g.n_nodes) % 7 == 0, 0.5, 0.0))
+    x, info = mhlp.gmres_solve(P, b, tol=1e-11, restart=restart)
+    r = b - mhlp.apply_bie(P, x)
+    assert info["converged"] and float(r.norm()) <= 1.1e-11 * float(b.norm()) + 1e-14 * float(x.norm())
