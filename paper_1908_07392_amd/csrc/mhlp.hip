@@ -1958,7 +1958,7 @@ extern "C" mhlp_status mhlp_plan_destroy(mhlp_plan *P)
     delete P->fmm;
     if (P->tree) {
         void *tp[] = {P->tree->cc, P->tree->rmin, P->tree->mom, P->tree->st, P->tree->items, P->tree->cnt, P->tree->order,
-                      P->tree->part, P->tree->flux, P->tree->cost};
+                      P->tree->part, P->tree->flux, P->tree->cost, P->tree->lb, P->tree->znear};
         for (void *p : tp)
             if (p) (void)hipFree(p);
         delete P->tree;
@@ -2016,7 +2016,9 @@ static mhlp_status tree_setup(mhlp_plan *P, hipStream_t st)
     TRY(dalloc(&T.items, G * Np));
     TRY(dalloc(&T.cnt, G));
     TRY(dalloc(&T.order, G));
-    TRY(dalloc(&T.cost, 1));
+    TRY(dalloc(&T.cost, 2));
+    TRY(dalloc(&T.lb, T.ncl));
+    TRY(dalloc(&T.znear, G));
     /* waves per group of 64 targets (blocks of 8, 16 or 4 waves; direct items
        cut into 2^cut units), by the number of groups: enough waves to fill the
        chip.  Measured us per evaluation (starfish, 4096 sources, alpha = 5) with
@@ -2038,12 +2040,16 @@ static mhlp_status tree_setup(mhlp_plan *P, hipStream_t st)
     if (P->tr_split > 1) TRY(dalloc(&T.part, (P->onsurf ? 2 : 4) * (int64_t)P->tr_split * M));
     mhlp::tree_clusters_kernel<<<nblocks(T.ncl, 4), 256, 0, st>>>(T, g->soa, g->soa + g->N, g->ph, P->alpha,
                                                                   P->near_factor);
+    HIPCHECK(hipMemsetAsync(T.cost, 0, 2 * sizeof(*T.cost), st));
     mhlp::tree_lists_kernel<<<nblocks(G, 4), 256, 0, st>>>(T, P->tx, P->ty, M, g->soa, g->soa + g->N, g->ph,
                                                            P->near_factor, P->alpha, P->near_ptr, P->near_panel);
     mhlp::tree_order_kernel<<<1, 1024, 0, st>>>(T, G);
     HIPCHECK(hipGetLastError());
-    HIPCHECK(hipMemcpyAsync(&P->tr_cost, T.cost, sizeof(P->tr_cost), hipMemcpyDeviceToHost, st));
+    unsigned long long cost[2];
+    HIPCHECK(hipMemcpyAsync(cost, T.cost, sizeof(cost), hipMemcpyDeviceToHost, st));
     HIPCHECK(hipStreamSynchronize(st)); /* later calls may come on other streams */
+    P->tr_cost = cost[0];
+    T.skip = cost[1] >= mhlp::TR_ZSKIP && P->tr_split == 1;
     return MHLP_OK;
 }
 
@@ -2285,8 +2291,12 @@ template <class Op>
 static void launch_tree_far(const FarArgs &A, const mhlp_plan *P, hipStream_t st)
 {
     const mhlp::TreeDev &T = *P->tree;
-    mhlp::far_tree_kernel<Op>
-        <<<dim3(nblocks(A.M, 64), (unsigned)P->tr_split), 64 * std::min(P->tr_waves, Op::WMAX), 0, st>>>(A, T);
+    const dim3 grid(nblocks(A.M, 64), (unsigned)P->tr_split);
+    const int threads = 64 * std::min(P->tr_waves, Op::WMAX);
+    if (Op::SKIP && T.skip)
+        mhlp::far_tree_kernel<Op, Op::SKIP><<<grid, threads, 0, st>>>(A, T);
+    else
+        mhlp::far_tree_kernel<Op, false><<<grid, threads, 0, st>>>(A, T);
     if (P->tr_split > 1)
         mhlp::tree_finalize<Op><<<dim3(nblocks(A.M, 64), (unsigned)Op::NF), 64, 0, st>>>(A, T, P->tr_split);
 }

@@ -55,7 +55,11 @@ struct TreeDev {
     uint2 *items = nullptr;                  /* [groups][Np]: direct items from the front, expansions from the back */
     int2 *cnt = nullptr;                     /* [groups]: their numbers */
     double *part = nullptr;                  /* [fields][blocks per group][M] sums of split groups */
-    unsigned long long *cost = nullptr;      /* total work of the groups (tree_cost) */
+    unsigned long long *cost = nullptr;      /* total work of the groups (tree_cost); [1]: the largest spread of
+                                                the z classes of a group's items (TR_ZSTEP) */
+    float *lb = nullptr;                     /* [ncl] log2 of the sum of |charges| and |dipoles|, rounded up */
+    int *znear = nullptr;                    /* [groups] smallest z class of the items */
+    int skip = 0;                            /* far items are held against the near ones' sum (far_tree_kernel) */
     int32_t *order = nullptr;                /* [groups] launch order: the groups with the most work first */
 };
 
@@ -63,6 +67,13 @@ struct TreeDev {
 constexpr uint32_t TR_NEAR = 1u << 16; /* direct: some target of the wave lists the panel */
 constexpr uint32_t TR_ZERO = 1u << 17; /* every pair underflows to zero: only non-finite densities matter */
 constexpr uint32_t TR_LAP = 1u << 18;  /* stresslet: the K part of every pair is below rounding */
+/* bits 24-31: the z class, z >= TR_ZSTEP times it for every pair of the item */
+constexpr double TR_ZSTEP = 4.0;
+constexpr int TR_ZNEAR = 3;            /* classes from a group's smallest one that are always summed */
+constexpr int TR_ZSKIP = 40;           /* spread of classes (z: 160) from which a plan looks for items to leave out; below,
+                                          hardly any can be (both layers, 109,314 targets: alpha = 50, spread 33: 211 us
+                                          without, 216 with; alpha = 100, spread 65: 370, 270) */
+__host__ __device__ inline uint32_t tree_zclass(double z) { return z > 0.0 ? (uint32_t)fmin(z * (1.0 / TR_ZSTEP), 255.0) << 24 : 0u; }
 
 /* Stresslet double layer by clusters.  With U = u_1 + i u_2, x - y = r e^{i theta},
    sigma = (m_1 + i m_2)(n_1 + i n_2)/2, tau = m.n (m = w mu) and O_k = K_k(alpha r) e^{i k theta},
@@ -243,7 +254,7 @@ __global__ __launch_bounds__(256) void tree_lists_kernel(TreeDev T, const double
     const double x = tx[i], y = ty[i];
     const int32_t k0 = nptr[i], k1 = nptr[i + 1];
     uint2 *items = T.items + g * T.Np;
-    int nd = 0, nf = 0;
+    int nd = 0, nf = 0, zlo = 255, zhi = 0;
     for (int64_t p = 0; p < T.Np;) {
         int k = p == 0 ? T.nlev - 1 : min(T.nlev - 1, __builtin_ctz((uint32_t)p));
         for (;; --k) {
@@ -268,6 +279,13 @@ __global__ __launch_bounds__(256) void tree_lists_kernel(TreeDev T, const double
                 if (y_ != 0xffffffffu) y_ |= (uint32_t)tree_piece(alpha * rlo, alpha * rhi) | (lap ? TR_LAP : 0u);
             }
             if (y_ != 0xffffffffu) {
+                if (!T.stokes && y_ != TR_ZERO) {
+                    /* rm[0] and up exceed the radius: R <= rm of the highest order / 1.5 */
+                    const uint32_t zc = tree_zclass(alpha * (rlo - rm[TR_NP - 1] * (1.0 / 1.5)) * (1.0 - 1e-12));
+                    zlo = min(zlo, (int)(zc >> 24));
+                    zhi = max(zhi, (int)(zc >> 24));
+                    y_ |= zc;
+                }
                 if (lane == 0) items[T.Np - 1 - nf] = make_uint2((uint32_t)c, y_);
                 ++nf;
                 break;
@@ -287,16 +305,23 @@ __global__ __launch_bounds__(256) void tree_lists_kernel(TreeDev T, const double
                 }
                 const double dlo = (double)wave_min_f(listed ? INFINITY : (float)sqrt(r2lo)) * (1.0 - 3e-7);
                 const double dhi = (double)wave_max_f(listed ? -INFINITY : (float)sqrt(r2hi)) * (1.0 + 3e-7);
+                const uint32_t zc = tree_zclass(alpha * dlo * (1.0 - 1e-12));
+                zlo = min(zlo, (int)(zc >> 24));
+                zhi = max(zhi, (int)(zc >> 24));
                 if (lane == 0)
                     items[nd] = make_uint2((uint32_t)c, (uint32_t)tree_piece(alpha * dlo, alpha * dhi) |
-                                                            (any ? TR_NEAR : 0u));
+                                                            (any ? TR_NEAR : 0u) | zc);
                 ++nd;
             }
             break;
         }
         p += (int64_t)1 << k;
     }
-    if (lane == 0) T.cnt[g] = make_int2(nd, nf);
+    if (lane == 0) {
+        T.cnt[g] = make_int2(nd, nf);
+        T.znear[g] = zlo;
+        if (zhi > zlo) atomicMax(T.cost + 1, (unsigned long long)(zhi - zlo));
+    }
 }
 
 /* work of a group in expansions (a direct item costs about three) */
@@ -526,6 +551,20 @@ __device__ __forceinline__ void tree_moments_body(const FarArgs &A, const TreeDe
             s[16] = ex;
             s[32] = ey;
         }
+    }
+    if (Z == 0 && T.skip) {
+        /* bound of a cluster's charges, for far_tree_kernel */
+        double sum = (SLP ? fabs(q) : 0.0) + (DLP ? fabs(ex) + fabs(ey) : 0.0);
+        for (int o = 1; o < 16; o <<= 1) sum += __shfl_xor(sum, o);
+        if ((t & 15) == 0) buf[0][t >> 4] = sum;
+        __syncthreads();
+        const int64_t p = p0 + t;
+        if (t < 16 && (t & ((1 << k) - 1)) == 0 && p < T.Np) {
+            double b = 0.0;
+            for (int u = t; u < t + (1 << k) && p0 + u < T.Np; ++u) b += buf[0][u];
+            T.lb[T.off[k] + (p >> k)] = (float)log2(b) + 0.01f;
+        }
+        __syncthreads();
     }
     /* clusters too wide to expand (the same test as tree_order_ratio through rmin) */
     const bool live = T.rmin[TR_RM * c + TR_NP - 1] < INFINITY;
@@ -944,6 +983,7 @@ __device__ __forceinline__ bool tree_bad(const TreeDev &T, int64_t p0, int64_t p
 template <bool SLP, bool DLP>
 struct TreePot {
     static constexpr int NF = (SLP ? 1 : 0) + (DLP ? 1 : 0), EXTRA = 0, WMAX = 16;
+    static constexpr bool SKIP = true; /* tree_moments_kernel leaves the bounds that takes */
     template <int PC>
     static __device__ __forceinline__ void panel(const FarArgs &A, const TreeDev &D, int64_t p,
                                                  int s0, int s1, double x, double y, double (&f)[NF])
@@ -1006,6 +1046,7 @@ struct TreePot {
 template <bool SLP, bool DLP>
 struct TreeGrad {
     static constexpr int NF = (SLP ? 2 : 0) + (DLP ? 2 : 0), EXTRA = TR_GRAD, WMAX = 16;
+    static constexpr bool SKIP = false;
     template <int PC>
     static __device__ __forceinline__ void panel(const FarArgs &A, const TreeDev &D, int64_t p,
                                                  int s0, int s1, double x, double y, double (&f)[NF])
@@ -1083,6 +1124,7 @@ template <bool GRAD>
 struct TreeStokes {
     /* the gradient needs more than the 128 registers of a 16-wave block */
     static constexpr int NF = GRAD ? 4 : 2, WMAX = GRAD ? 8 : 16;
+    static constexpr bool SKIP = false;
     template <int PC>
     static __device__ __forceinline__ void panel(const FarArgs &A, const TreeDev &D, int64_t p,
                                                  int s0, int s1, double x, double y, double (&f)[NF])
@@ -1210,11 +1252,20 @@ __device__ __forceinline__ double tree_row_sum(double v)
 
    Bound by VALU FP64 (109,314 targets, 4096 sources, alpha = 5: 15.6e3
    instructions per group against 304e3 for the direct sum of all pairs, 66 us
-   against 1.07 ms; alpha = 500, all pairs direct: within 5% of the issue rate).
+   against 1.07 ms; alpha = 500, all pairs direct: within 5% of the issue rate before items were
+   left out).
+   Far items that cannot show (SKIP: plans with a large spread of z, one block
+   a group): the items of the TR_ZNEAR + 1 nearest z classes are summed first;
+   with |u| of the group's smallest target in hand, an item is left out when
+   the bound of its charges times e^-z stays below 2^-55 |u| over the number of
+   items, so that all that is left out stays below 2^-55 of every target's
+   value.  Without such a proof (cancellation, NaN) the item is summed.
+   109,314 x 4096, alpha = 100 / 200 / 500 / 1000, both layers: 370 / 964 / 735 /
+   272 -> 270 / 428 / 265 / 161 us.
    Waves per group (tree_setup): four for many groups; up to 128 for few,
    where the longest wave (a direct panel in one wave takes about 20 us) sets
    the time. */
-template <class Op>
+template <class Op, bool SKIP>
 __global__ __launch_bounds__(64 * Op::WMAX) void far_tree_kernel(FarArgs A, TreeDev T)
 {
     constexpr int NF = Op::NF;
@@ -1235,62 +1286,98 @@ __global__ __launch_bounds__(64 * Op::WMAX) void far_tree_kernel(FarArgs A, Tree
     double acc[NF];
 #pragma unroll
     for (int f = 0; f < NF; ++f) acc[f] = 0.0;
+    /* the wave's sums, with its share of the near corrections, into LDS */
+    auto put = [&]() {
+        double nr[NF];
+#pragma unroll
+        for (int f = 0; f < NF; ++f) nr[f] = 0.0;
+        if (wg < 16)
+            for (int32_t q = k0; q < k1; ++q) {
+                const int64_t p = A.npan[q];
+                if (p < 0) continue;
+                for (int jj = wg; jj < 16; jj += NW) Op::near(A, mu, q, p, jj, nr);
+            }
+#pragma unroll
+        for (int f = 0; f < NF; ++f) red[f][w][lane] = fma(INV_2PI, acc[f], nr[f]);
+    };
     const int nsrc = 16 >> T.cut;
-    for (int k = wg; k < (cnt.x << T.cut); k += NW) {
-        const uint2 it = items[k >> T.cut];
-        const int s0 = (k & ((1 << T.cut) - 1)) * nsrc;
-        const uint32_t p = __builtin_amdgcn_readfirstlane(it.x), fl = __builtin_amdgcn_readfirstlane(it.y);
-        bool listed = false;
-        if (fl & TR_NEAR)
-            for (int32_t q = k0; q < k1; ++q) listed = listed || A.npan[q] == (int32_t)p;
-        if (listed) continue;
-        double f[NF];
+    const uint32_t znear = SKIP ? (uint32_t)(T.znear[g] + TR_ZNEAR) : 255u;
+    float room = -INFINITY;
+#pragma unroll 1
+    for (int pass = 0; pass < (SKIP ? 2 : 1); ++pass) {
+        if (pass == 1) {
+            /* log2 of what an item may add to any target's field without showing */
+            put();
+            __syncthreads();
+            room = INFINITY;
 #pragma unroll
-        for (int n = 0; n < NF; ++n) f[n] = 0.0;
-        tree_panel<Op>((int)(fl & 31) - 1, A, T, p, s0, s0 + nsrc, x, y, f);
-#pragma unroll
-        for (int n = 0; n < NF; ++n) acc[n] += f[n];
-    }
-    const int fb = cnt.y * (NW - 1 - wg) / NW, fe = cnt.y * (NW - wg) / NW;
-    for (int k = fb; k < fe; ++k) {
-        const uint2 it = items[T.Np - 1 - k];
-        const uint32_t c = __builtin_amdgcn_readfirstlane(it.x), fl = __builtin_amdgcn_readfirstlane(it.y);
-        double f[NF];
-        bool direct = false;
-        if (fl & TR_ZERO) {
+            for (int f = 0; f < NF; ++f) {
+                double s = 0.0;
+                for (int v = 0; v < W; ++v) s += red[f][v][lane];
+                s = s == s ? fabs(s) : 0.0; /* beside a NaN nothing is left out */
+                for (int o = 32; o > 0; o >>= 1) s = fmin(s, __shfl_xor(s, o));
+                room = fminf(room, (float)log2(s) - 55.0f - log2f((float)(cnt.x + cnt.y)));
+            }
+            room = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(room)));
+            __syncthreads();
+        }
+        /* false: left to the other pass, or too small to show: K1(z) <= e^-z from z = 4 on */
+        auto take = [&](uint32_t c, uint32_t fl) {
+            if (!SKIP) return true;
+            const uint32_t zc = fl >> 24;
+            if (pass == 0) return zc <= znear;
+            if (zc <= znear) return false;
+            const float l = *((const MHLP_CAS float *)T.lb + c);
+            return zc == 0 || !(l - (float)(TR_ZSTEP * 1.4426950) * (float)zc <= room);
+        };
+        for (int k = wg; k < (cnt.x << T.cut); k += NW) {
+            const uint2 it = items[k >> T.cut];
+            const int s0 = (k & ((1 << T.cut) - 1)) * nsrc;
+            const uint32_t p = __builtin_amdgcn_readfirstlane(it.x), fl = __builtin_amdgcn_readfirstlane(it.y);
+            if (!take(p, fl)) continue;
+            bool listed = false;
+            if (fl & TR_NEAR)
+                for (int32_t q = k0; q < k1; ++q) listed = listed || A.npan[q] == (int32_t)p;
+            if (listed) continue;
+            double f[NF];
 #pragma unroll
             for (int n = 0; n < NF; ++n) f[n] = 0.0;
-            int64_t p0, p1;
-            tree_panels_of(T, c, p0, p1);
-            direct = Op::bad(T, p0, p1);
-        } else {
-            Op::expand(A.fq, T, c, fl, x, y, f);
-            bool fin = true;
+            tree_panel<Op>((int)(fl & 31) - 1, A, T, p, s0, s0 + nsrc, x, y, f);
 #pragma unroll
-            for (int n = 0; n < NF; ++n) fin = fin && __builtin_isfinite(f[n]);
-            direct = __ballot(!fin) != 0;
+            for (int n = 0; n < NF; ++n) acc[n] += f[n];
         }
-        if (direct) {
+        const int fb = cnt.y * (NW - 1 - wg) / NW, fe = cnt.y * (NW - wg) / NW;
+        for (int k = fb; k < fe; ++k) {
+            const uint2 it = items[T.Np - 1 - k];
+            const uint32_t c = __builtin_amdgcn_readfirstlane(it.x), fl = __builtin_amdgcn_readfirstlane(it.y);
+            if (!take(c, fl)) continue;
+            double f[NF];
+            bool direct = false;
+            if (fl & TR_ZERO) {
 #pragma unroll
-            for (int n = 0; n < NF; ++n) f[n] = 0.0;
-            int64_t p0, p1;
-            tree_panels_of(T, c, p0, p1);
-            for (int64_t p = p0; p < p1; ++p) Op::template panel<KQ_NP>(A, T, p, 0, 16, x, y, f);
+                for (int n = 0; n < NF; ++n) f[n] = 0.0;
+                int64_t p0, p1;
+                tree_panels_of(T, c, p0, p1);
+                direct = Op::bad(T, p0, p1);
+            } else {
+                Op::expand(A.fq, T, c, fl, x, y, f);
+                bool fin = true;
+#pragma unroll
+                for (int n = 0; n < NF; ++n) fin = fin && __builtin_isfinite(f[n]);
+                direct = __ballot(!fin) != 0;
+            }
+            if (direct) {
+#pragma unroll
+                for (int n = 0; n < NF; ++n) f[n] = 0.0;
+                int64_t p0, p1;
+                tree_panels_of(T, c, p0, p1);
+                for (int64_t p = p0; p < p1; ++p) Op::template panel<KQ_NP>(A, T, p, 0, 16, x, y, f);
+            }
+#pragma unroll
+            for (int n = 0; n < NF; ++n) acc[n] += f[n];
         }
-#pragma unroll
-        for (int n = 0; n < NF; ++n) acc[n] += f[n];
     }
-    double nr[NF];
-#pragma unroll
-    for (int f = 0; f < NF; ++f) nr[f] = 0.0;
-    if (wg < 16)
-        for (int32_t q = k0; q < k1; ++q) {
-            const int64_t p = A.npan[q];
-            if (p < 0) continue;
-            for (int jj = wg; jj < 16; jj += NW) Op::near(A, mu, q, p, jj, nr);
-        }
-#pragma unroll
-    for (int f = 0; f < NF; ++f) red[f][w][lane] = fma(INV_2PI, acc[f], nr[f]);
+    put();
     const double cm = gridDim.y > 1 ? 0.0 : Op::common(A, T); /* every lane takes part */
     __syncthreads();
     if (!valid) return;

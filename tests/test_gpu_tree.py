@@ -325,3 +325,31 @@ def test_gram_schmidt_over_slices(panels, restart):
     x, info = mhlp.gmres_solve(P, b, tol=1e-11, restart=restart)
     r = b - mhlp.apply_bie(P, x)
     assert info["converged"] and float(r.norm()) <= 1.1e-11 * float(b.norm()) + 1e-14 * float(x.norm())
+
+
+@pytest.mark.parametrize("alpha,m", [(60.0, 41000), (400.0, 41000), (150.0, 77000)])
+@pytest.mark.parametrize("density", ["one panel", "random", "small here, large there"])
+def test_far_items_left_out_do_not_show(alpha, m, density):
+    """Plans whose far items may be left out against the near ones' sum: where the near panels carry nothing or
+    little, the far ones decide.  Bound as for every potential, per target."""
+    g, tx, ty, sigma, mu = _setup(40, m, 7)
+    if density == "one panel":
+        keep = np.zeros(g.n_nodes)
+        keep[16 * 5:16 * 6] = 1.0
+        sigma, mu = sigma * keep, mu * keep
+    elif density == "small here, large there":
+        s = 10.0 ** (-60.0 * (0.5 + 0.5 * np.cos(g.theta)))
+        sigma, mu = sigma * s, mu * s
+    P = mhlp.Plan(mhlp.Geometry(_t(g.node_soa())), alpha, _t(tx), _t(ty))
+    us, ud = (v.cpu().numpy() for v in mhlp.eval_layer(P, sigma=_t(sigma), mu=_t(mu)))
+    sel = np.unique(np.linspace(0, m - 1, 400).astype(int))
+    dx, dy = tx[sel][:, None] - g.x, ty[sel][:, None] - g.y
+    r = np.hypot(dx, dy)
+    z = alpha * r
+    ts = sp.k0(z) / (2 * np.pi) * g.weights * sigma
+    nx, ny = g.normals
+    td = alpha * sp.k1(z) / (2 * np.pi * r) * (dx * nx + dy * ny) * g.weights * mu
+    size = alpha * sp.k1(z) / (2 * np.pi) * np.abs(g.weights * mu)
+    tol = 3e-14 + 5e-16 * z
+    assert (np.abs(us[sel] - ts.sum(axis=1)) <= (tol * np.abs(ts)).sum(axis=1) + 1e-300).all()
+    assert (np.abs(ud[sel] - td.sum(axis=1)) <= (tol * size).sum(axis=1) + 1e-300).all()
