@@ -33,51 +33,26 @@ sys.path.insert(0, ROOT)
 
 METRIC = "GPair-evals/s (SLP+DLP) and GMRES time-to-1e-10, mixed/batched/warm vs FP64"
 FP64_PEAK_TFLOPS = 78.6        # MI355X vector FP64 (published)
-# FP64 operations per (target, source) pair of the fused SLP+DLP far-field
-# kernel, per alpha, from the hardware counters of the built kernel
-# (SQ_INSTS_VALU_{FMA,MUL,ADD,TRANS}_F64 x 64 lanes / pairs, FMA = 2; lanes
-# masked off in divergent code are counted, but the kernel classifies whole
-# waves against each panel, so few are):
-# profiles/far_eval_fp64_starfish4096_grid512_valu_f64.txt.  The pairs take
-# the fitted piece of their z, K0 and K1 each from a fit of its own: at
-# alpha = 500 nearly all z > 100 (degree 6 each; the counters read 31.2 v_fma
-# (x2), 13.1 v_mul, 3.0 v_add, 2.0 v_rsq = 80.5 per pair), at alpha = 5 z of
-# 2..14 (degrees 7-12, the z <= 2 series for the nearest); e^{-z} by a table
-# of 2^(-j/64) and a 6-term polynomial.
-FLOP_PER_PAIR_FP64 = {5.0: 101.8, 50.0: 83.4, 500.0: 80.5}
-# VALU instructions per pair (all types, same counters), and the issue rate
-# they are bound by: 256 CUs x 2.4 GHz, one 64-lane VALU instruction per CU
-# per clock
-VALU_PER_PAIR_FP64 = {5.0: 73.0, 50.0: 61.1, 500.0: 59.1}
+# The far field goes through cluster expansions: what a launch executes is no
+# longer proportional to its pairs.  FP64 operations and VALU instructions (per
+# 64 lanes) of one fused SLP+DLP evaluation at the 109,314 interior targets of
+# the 512^2 grid, per alpha, from the hardware counters of the built kernels
+# (tree_moments_kernel + far_tree_kernel; SQ_INSTS_VALU_{FMA,MUL,ADD,TRANS}_F64
+# x 64 lanes, FMA = 2): profiles/far_tree_starfish4096_grid512_counters.txt.
+# alpha = 5: mostly expansions; 50: half of the work direct; 500: all direct,
+# items that cannot show left out.
+FLOP_PER_EVAL_FP64 = {5.0: 2.14e9, 50.0: 6.63e9, 500.0: 3.50e9}
+VALU_PER_EVAL_FP64 = {5.0: 26.2e6 * 64, 50.0: 81.1e6 * 64, 500.0: 44.6e6 * 64}
+COUNTED_TARGETS = 109314
+# the issue rate they are bound by: 256 CUs x 2.4 GHz, one 64-lane VALU
+# instruction per CU per clock
 VALU_ISSUE_PER_S = 256 * 2.4e9 * 64
-# the gradient kernel (grad S and grad D of the same densities) evaluates K0
-# and K1(z)/r per pair as the fused evaluation does (the fine piece of the
-# plan's (wave, panel) class table; alpha carried by the staged densities),
-# then 1/r^2, (x-y).d, (alpha K0 + 2 K1/r)/r^2 and the four accumulations:
-# FLOP per pair from the FP64 VALU counters of each alpha (2 FMA + MUL + ADD +
-# TRANS; at alpha = 500 36.3 v_fma, 17.1 v_mul, 4.0 v_add, 2.0 v_rsq),
-# profiles/far_grad_fp64_starfish4096_grid512_valu_f64.txt
-FLOP_PER_PAIR_GRAD = {5.0: 116.8, 50.0: 98.5, 500.0: 95.6}
-# modified-Stokes double layer (2x2 stresslet per pair): K0 and K1(z)/r from
-# the class table's fine piece, alpha K1/r, 1/r^2, the closed forms of
-# alpha^2 T1, alpha^4 T2, alpha^2 T3 (App. B) and the contraction D_ij w mu_j
-# into two accumulators (z <= 2: the fitted smooth parts with log z): counted
-# per alpha (at alpha = 500 45.3 v_fma, 34.1 v_mul, 6.0 v_add, 2.0 v_rsq)
-FLOP_PER_PAIR_STOKES = {5.0: 158.7, 50.0: 135.8, 500.0: 132.7}
-# target gradient of the stresslet double layer (velocity gradient, 4 outputs):
-# the same K0, K1(z)/r, 1/r^2 and A_k, B_k = A_k'(r)/r from K0 and A_k, and the
-# contraction d_l D_ij w mu_j into four accumulators: counted per alpha (at
-# alpha = 500 64.3 v_fma, 49.2 v_mul, 9.0 v_add, 2.0 v_rsq)
-FLOP_PER_PAIR_STOKES_GRAD = {5.0: 228.4, 50.0: 192.3, 500.0: 188.8}
 # launch shapes (far-field source splits) chosen by the autotuner on MI355X for
 # the plans of this benchmark
 TUNED_SPLITS = os.path.join(ROOT, "paper_1908_07392_amd", "tuning", "mi355x_far_splits.json")
-# HBM bytes per fused FP64 evaluation (FETCH_SIZE + WRITE_SIZE of far_eval_fp64
-# and far_sk_finalize, each scaled by the same counter's reading for a plain
-# 256 MiB copy), averaged over the three alphas, for the current kernels and
-# launch shape (one stream launch of 4 x the resident blocks, numbered XCD by
-# XCD) (profiles/far_eval_fp64_starfish4096_grid512_hbm_bytes.txt)
-PROFILED_TRAFFIC = 49100000
+# HBM bytes per fused FP64 evaluation (FETCH_SIZE + WRITE_SIZE of both kernels,
+# averaged over the three alphas; same profile)
+PROFILED_TRAFFIC = 9940000
 
 
 def parse():
@@ -188,8 +163,8 @@ def main():
     for a in cfg["alphas"]:
         on, off = plans[a]
         kw = dict(use_cache=True, path=args.tune_cache, write=args.tune_write)
-        # the FP64 operator and evaluation do not use source splits (symmetric
-        # tiles; stream of (target block, panel) units): the splits serve the
+        # the FP64 operator and evaluation do not use source splits (cluster
+        # lists, shaped by the number of target groups): the splits serve the
         # mixed-precision leg's operator and evaluation, tuned for those
         r_on = autotune.tune(on, "bie", precision=mhlp.MIXED, reps=5, **kw)
         r_off = autotune.tune(off, "both", precision=mhlp.MIXED, reps=5, **kw)
@@ -204,7 +179,7 @@ def main():
     events = []  # (alpha, start, end) around every fused evaluation of the timed region
 
     def step(record=False):
-        pairs = [0, 0]  # kernel evaluations, pair terms
+        pairs = [0, 0]  # pairs of the sums (unordered on the curve), their terms
         for a in cfg["alphas"]:
             on, off = plans[a]
             if record:
@@ -223,8 +198,9 @@ def main():
                                                     residual=info["rel_residual"]))
             # operator applications of a zero-guess solve: one per Arnoldi step and
             # one true-residual check per cycle (the first residual is g itself);
-            # the FP64 operator evaluates each unordered pair once (N(N-1)/2
-            # kernel evaluations give its N^2 terms)
+            # a pair of nodes counts once for the operator's two terms.  Pairs are
+            # those of the sums delivered, whether they were summed one by one or
+            # through cluster expansions
             napp = info["iters"] + info["restarts"]
             pairs[0] += napp * (N * (N - 1) // 2) + M * N
             pairs[1] += napp * N * N + M * N
@@ -254,19 +230,20 @@ def main():
     eval_pairs = M * N
     # FLOPs and VALU instructions of every timed launch over the sum of their durations
     t_sum = sum(sum(v) for v in per_a.values()) * 1e-3
-    flops = sum(len(v) * eval_pairs * FLOP_PER_PAIR_FP64[a] for a, v in per_a.items())
-    valus = sum(len(v) * eval_pairs * VALU_PER_PAIR_FP64[a] for a, v in per_a.items())
+    share = M / COUNTED_TARGETS  # the counts are the 512^2 grid's
+    flops = sum(len(v) * share * FLOP_PER_EVAL_FP64[a] for a, v in per_a.items())
+    valus = sum(len(v) * share * VALU_PER_EVAL_FP64[a] for a, v in per_a.items())
     achieved_tf = flops / t_sum / 1e12
     roofline = {"bound": "alu", "achieved": round(achieved_tf, 3), "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(achieved_tf / FP64_PEAK_TFLOPS, 4),
                 "traffic": PROFILED_TRAFFIC,
-                "kernel": "far_eval_fp64<SLP,DLP> + far_sk_finalize",
+                "kernel": "tree_moments_kernel + far_tree_kernel<SLP,DLP>",
                 "launch_ms": round(launch_ms, 4),
                 "launch_ms_by_alpha": {f"alpha={a:g}": round(float(np.mean(v)), 4) for a, v in per_a.items()},
                 "pairs_per_launch": eval_pairs,
-                "flop_per_pair_by_alpha": {f"alpha={a:g}": f for a, f in FLOP_PER_PAIR_FP64.items()},
+                "flop_per_launch_by_alpha": {f"alpha={a:g}": f * share for a, f in FLOP_PER_EVAL_FP64.items()},
                 "eval_gpair_per_s": round(eval_pairs / (launch_ms * 1e-3) / 1e9, 3),
-                "valu_per_pair_by_alpha": {f"alpha={a:g}": f for a, f in VALU_PER_PAIR_FP64.items()},
+                "valu_per_launch_by_alpha": {f"alpha={a:g}": f * share for a, f in VALU_PER_EVAL_FP64.items()},
                 "valu_issue_frac": round(valus / t_sum / VALU_ISSUE_PER_S, 4)}
     a_r = 50.0
     on, off = plans[a_r]
@@ -534,7 +511,7 @@ def bench_grad(mhlp, plans, gdev, cfg, args, torch):
     (builds the 64 gradient weights per near pair) and the steady launch."""
     print("# gradient leg", file=sys.stderr, flush=True)
     from paper_1908_07392_amd import autotune
-    res = {"flop_per_pair_by_alpha": {f"alpha={a:g}": f for a, f in FLOP_PER_PAIR_GRAD.items()}}
+    res = {}
     launch = {}
     for a in cfg["alphas"]:
         on, off = plans[a]
@@ -558,13 +535,9 @@ def bench_grad(mhlp, plans, gdev, cfg, args, torch):
                                   "nsplit": r["nsplit"], "near_pairs": off.n_near_pairs}
     ms = float(np.mean([v["launch_ms"] for v in launch.values()]))
     pairs = off.n_targets * off.n_sources
-    # the counted FLOPs of every alpha's launch over their summed durations
-    tf = pairs * sum(FLOP_PER_PAIR_GRAD[a] for a in cfg["alphas"]) / (
-        sum(launch[f"alpha={a:g}"]["launch_ms"] for a in cfg["alphas"]) * 1e-3) / 1e12
     res.update({"by_alpha": launch, "pairs_per_launch": pairs, "launch_ms": round(ms, 4),
-                "gpair_per_s": round(pairs / (ms * 1e-3) / 1e9, 3), "achieved_tflops": round(tf, 3),
-                "frac_of_fp64_peak": round(tf / FP64_PEAK_TFLOPS, 4),
-                "kernel": "far_grad_fp64<gradS,gradD> (+ grad_finalize when split)"})
+                "gpair_per_s": round(pairs / (ms * 1e-3) / 1e9, 3),
+                "kernel": "tree_moments_kernel + far_tree_kernel<gradS,gradD>"})
     return res
 
 
@@ -579,7 +552,7 @@ def bench_stokes(mhlp, wl, cfg, G, tx, ty, t, args, torch):
     from paper_1908_07392_amd import autotune
     g = cfg["geom"]
     sources = [(2.2 + 0.4j, (1.0, 0.3)), (-0.5 - 2.1j, (-0.4, 0.8))]
-    res = {"flop_per_pair_by_alpha": {f"alpha={a:g}": f for a, f in FLOP_PER_PAIR_STOKES.items()}}
+    res = {}
     by = {}
     for a in cfg["alphas"]:
         gb = np.zeros((2, g.n_nodes))
@@ -638,19 +611,12 @@ def bench_stokes(mhlp, wl, cfg, G, tx, ty, t, args, torch):
     ms = float(np.mean([v["eval_launch_ms"] for v in by.values()]))
     gms = float(np.mean([v["grad_launch_ms"] for v in by.values()]))
     pairs = off.n_targets * off.n_sources
-    al = [float(k.split("=")[1]) for k in by]
-    tf = pairs * sum(FLOP_PER_PAIR_STOKES[a] for a in al) / (sum(v["eval_launch_ms"] for v in by.values()) * 1e-3) / 1e12
-    gtf = pairs * sum(FLOP_PER_PAIR_STOKES_GRAD[a] for a in al) / (
-        sum(v["grad_launch_ms"] for v in by.values()) * 1e-3) / 1e12
     res.update({"by_alpha": by, "pairs_per_launch": pairs, "eval_launch_ms": round(ms, 4),
-                "eval_gpair_per_s": round(pairs / (ms * 1e-3) / 1e9, 3), "achieved_tflops": round(tf, 3),
-                "frac_of_fp64_peak": round(tf / FP64_PEAK_TFLOPS, 4),
-                "kernel": "far_stokes_fp64 (+ stk_finalize when split)",
-                "grad": {"flop_per_pair_by_alpha": {f"alpha={a:g}": f for a, f in FLOP_PER_PAIR_STOKES_GRAD.items()},
-                         "launch_ms": round(gms, 4),
-                         "gpair_per_s": round(pairs / (gms * 1e-3) / 1e9, 3), "achieved_tflops": round(gtf, 3),
-                         "frac_of_fp64_peak": round(gtf / FP64_PEAK_TFLOPS, 4),
-                         "kernel": "far_stokes_grad_fp64 (+ stkg_finalize when split)"}})
+                "eval_gpair_per_s": round(pairs / (ms * 1e-3) / 1e9, 3),
+                "kernel": "tree_stokes_kernel + far_tree_kernel<stresslet>",
+                "grad": {"launch_ms": round(gms, 4),
+                         "gpair_per_s": round(pairs / (gms * 1e-3) / 1e9, 3),
+                         "kernel": "tree_stokes_kernel<grad> + far_tree_kernel<stresslet gradient>"}})
     return res
 
 

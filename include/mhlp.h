@@ -411,12 +411,12 @@ mhlp_status mhlp_batch_info(const mhlp_batch *batch, int64_t *total_len, int32_t
                             int64_t *lengths);
 /* out = (1/2 I + D) mu for every system in one grouped launch (kernel values
    shared by the right-hand sides of a geometry); FP64.  The launch runs a
-   work list of (geometry, 256 targets, source split) items, longest first. */
+   work list of (geometry, 64 targets, split) items over the plans' cluster
+   lists, longest first. */
 mhlp_status mhlp_batch_apply_bie(const mhlp_batch *batch, const double *mu, double *out, void *stream);
-/* Autotuner of the grouped operator's launch shape: for every tile shape
-   (1 or 2 targets per lane, i.e. target tiles of 256 or 512 nodes; 128 or
-   256 sources staged in LDS per step) and a total of 512, 1024, ..., 16384
-   blocks, rebuild the work list and time the operator (reps launches after a
+/* Autotuner of the grouped operator's launch shape: for every pair of 1 or 2
+   targets per lane and 128 or 256 sources per step (kept and reported; they
+   no longer shape the launch) and a total of 512, 1024, ..., 16384 blocks, rebuild the work list and time the operator (reps launches after a
    warm-up, HIP events on `stream`); keep the fewest blocks within 1% of the
    fastest.  best_target and best_ms (host) may be NULL.  Synchronises the
    stream. */

@@ -72,7 +72,7 @@ constexpr double TR_ZSTEP = 4.0;
 constexpr int TR_ZNEAR = 3;            /* classes from a group's smallest one that are always summed */
 constexpr int TR_ZSKIP = 40;           /* spread of classes (z: 160) from which a plan looks for items to leave out; below,
                                           hardly any can be (both layers, 109,314 targets: alpha = 50, spread 33: 211 us
-                                          without, 216 with; alpha = 100, spread 65: 370, 270) */
+                                          without, 216 with; alpha = 100, spread 65: 370, 233) */
 __host__ __device__ inline uint32_t tree_zclass(double z) { return z > 0.0 ? (uint32_t)fmin(z * (1.0 / TR_ZSTEP), 255.0) << 24 : 0u; }
 
 /* Stresslet double layer by clusters.  With U = u_1 + i u_2, x - y = r e^{i theta},
@@ -1261,7 +1261,7 @@ __device__ __forceinline__ double tree_row_sum(double v)
    items, so that all that is left out stays below 2^-55 of every target's
    value.  Without such a proof (cancellation, NaN) the item is summed.
    109,314 x 4096, alpha = 100 / 200 / 500 / 1000, both layers: 370 / 964 / 735 /
-   272 -> 270 / 428 / 265 / 161 us.
+   272 -> 233 / 365 / 239 / 142 us.
    Waves per group (tree_setup): four for many groups; up to 128 for few,
    where the longest wave (a direct panel in one wave takes about 20 us) sets
    the time. */
@@ -1321,36 +1321,20 @@ __global__ __launch_bounds__(64 * Op::WMAX) void far_tree_kernel(FarArgs A, Tree
             room = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(room)));
             __syncthreads();
         }
-        /* false: left to the other pass, or too small to show: K1(z) <= e^-z from z = 4 on */
-        auto take = [&](uint32_t c, uint32_t fl) {
-            if (!SKIP) return true;
-            const uint32_t zc = fl >> 24;
-            if (pass == 0) return zc <= znear;
-            if (zc <= znear) return false;
-            const float l = *((const MHLP_CAS float *)T.lb + c);
-            return zc == 0 || !(l - (float)(TR_ZSTEP * 1.4426950) * (float)zc <= room);
-        };
-        for (int k = wg; k < (cnt.x << T.cut); k += NW) {
-            const uint2 it = items[k >> T.cut];
+        auto direct_item = [&](int k, uint32_t p, uint32_t fl) {
             const int s0 = (k & ((1 << T.cut) - 1)) * nsrc;
-            const uint32_t p = __builtin_amdgcn_readfirstlane(it.x), fl = __builtin_amdgcn_readfirstlane(it.y);
-            if (!take(p, fl)) continue;
             bool listed = false;
             if (fl & TR_NEAR)
                 for (int32_t q = k0; q < k1; ++q) listed = listed || A.npan[q] == (int32_t)p;
-            if (listed) continue;
+            if (listed) return;
             double f[NF];
 #pragma unroll
             for (int n = 0; n < NF; ++n) f[n] = 0.0;
             tree_panel<Op>((int)(fl & 31) - 1, A, T, p, s0, s0 + nsrc, x, y, f);
 #pragma unroll
             for (int n = 0; n < NF; ++n) acc[n] += f[n];
-        }
-        const int fb = cnt.y * (NW - 1 - wg) / NW, fe = cnt.y * (NW - wg) / NW;
-        for (int k = fb; k < fe; ++k) {
-            const uint2 it = items[T.Np - 1 - k];
-            const uint32_t c = __builtin_amdgcn_readfirstlane(it.x), fl = __builtin_amdgcn_readfirstlane(it.y);
-            if (!take(c, fl)) continue;
+        };
+        auto far_item = [&](uint32_t c, uint32_t fl) {
             double f[NF];
             bool direct = false;
             if (fl & TR_ZERO) {
@@ -1375,6 +1359,42 @@ __global__ __launch_bounds__(64 * Op::WMAX) void far_tree_kernel(FarArgs A, Tree
             }
 #pragma unroll
             for (int n = 0; n < NF; ++n) acc[n] += f[n];
+        };
+        const int ndir = cnt.x << T.cut;
+        const int fb = cnt.y * (NW - 1 - wg) / NW, fe = cnt.y * (NW - wg) / NW;
+        if constexpr (SKIP) {
+            /* a lane's item; false: left to the other pass, or too small to show: K1(z) <= e^-z from z = 4 on */
+            auto take = [&](uint2 it) {
+                const uint32_t zc = it.y >> 24;
+                if (pass == 0) return zc <= znear;
+                if (zc <= znear) return false;
+                return zc == 0 || !(T.lb[it.x] - (float)(TR_ZSTEP * 1.4426950) * (float)zc <= room);
+            };
+            /* the wave's items come 64 at a time, one a lane */
+            for (int kb = wg; kb < ndir; kb += 64 * NW) {
+                const int kl = kb + lane * NW;
+                const uint2 it = items[min(kl, ndir - 1) >> T.cut];
+                for (uint64_t todo = __ballot(kl < ndir && take(it)); todo; todo &= todo - 1) {
+                    const int b = __builtin_ctzll(todo);
+                    direct_item(kb + b * NW, __builtin_amdgcn_readlane(it.x, b), __builtin_amdgcn_readlane(it.y, b));
+                }
+            }
+            for (int kb = fb; kb < fe; kb += 64) {
+                const uint2 it = items[T.Np - 1 - min(kb + lane, fe - 1)];
+                for (uint64_t todo = __ballot(kb + lane < fe && take(it)); todo; todo &= todo - 1) {
+                    const int b = __builtin_ctzll(todo);
+                    far_item(__builtin_amdgcn_readlane(it.x, b), __builtin_amdgcn_readlane(it.y, b));
+                }
+            }
+        } else {
+            for (int k = wg; k < ndir; k += NW) {
+                const uint2 it = items[k >> T.cut];
+                direct_item(k, __builtin_amdgcn_readfirstlane(it.x), __builtin_amdgcn_readfirstlane(it.y));
+            }
+            for (int k = fb; k < fe; ++k) {
+                const uint2 it = items[T.Np - 1 - k];
+                far_item(__builtin_amdgcn_readfirstlane(it.x), __builtin_amdgcn_readfirstlane(it.y));
+            }
         }
     }
     put();
