@@ -219,7 +219,7 @@ __device__ __forceinline__ void gemm_block(const GemmJob &J, int block, GemmShar
            the memory that all XCDs share; the stores have arrived once they are
            waited for.  A device fence would write back the whole L2 of every
            block's XCD: 30 us a launch instead of 10. */
-        __builtin_amdgcn_s_waitcnt(0);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         if (t == 0) {
             sh.last = atomicAdd(J.ticket + tile, 1) == J.splits - 1;
