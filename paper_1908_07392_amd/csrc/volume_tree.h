@@ -272,10 +272,11 @@ __global__ __launch_bounds__(64) void vol_scatter_kernel(VolTree V)
     }
 }
 
-/* centre, box and distances of each cluster, one wave per cluster.  A point
-   that is not finite keeps its clusters from every expansion and makes their
-   boxes unbounded; a charge that is not finite keeps them from being left out
-   where all pairs underflow. */
+/* centre, box and distances of each cluster, one wave per cluster.  A distance
+   that never serves is NaN, which no comparison passes, not even that of an
+   infinite distance.  A point that is not finite keeps its clusters from every
+   expansion and from being left out, and makes their boxes unbounded; a charge
+   that is not finite keeps them from being left out where all pairs underflow. */
 __global__ __launch_bounds__(256) void vol_clusters_kernel(VolTree V, TreeDev T)
 {
     const int64_t c = blockIdx.x * (int64_t)4 + (threadIdx.x >> 6);
@@ -303,11 +304,12 @@ __global__ __launch_bounds__(256) void vol_clusters_kernel(VolTree V, TreeDev T)
     for (int64_t j = 16 * p0 + lane; j < 16 * p1; j += 64) R = fmax(R, hypot(V.xs[j] - cx, V.ys[j] - cy));
     for (int o = 32; o > 0; o >>= 1) R = fmax(R, __shfl_xor(R, o));
     R *= 1.0 + 1e-12;
+    bad = bad || !__builtin_isfinite(R); /* finite points may lie further apart than a double holds */
     const double a = V.alpha * R;
     if (lane < 2) T.cc[2 * c + lane] = lane ? cy : cx;
     if (lane < 4) V.cbox[4 * c + lane] = bad ? (lane & 1 ? INFINITY : -INFINITY) : lane == 0 ? xl : lane == 1 ? xh : lane == 2 ? yl : yh;
     if (lane < TR_RM) {
-        double v = INFINITY;
+        double v = __builtin_nan("");
         if (!bad && lane == TR_RM - 1 && !badq) v = R + TR_ZZERO * (1.0 + 1e-12) / V.alpha;
         if (!bad && lane < TR_NP && a >= TR_AMIN && a <= VT_AMAX) {
             const int bin = (int)(3.0f * (log2f((float)a) + 20.0f));
