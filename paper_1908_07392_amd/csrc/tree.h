@@ -1256,10 +1256,11 @@ __device__ __forceinline__ double tree_row_sum(double v)
    left out).
    Far items that cannot show (SKIP: plans with a large spread of z, one block
    a group): the items of the TR_ZNEAR + 1 nearest z classes are summed first;
-   with |u| of the group's smallest target in hand, an item is left out when
-   the bound of its charges times e^-z stays below 2^-55 |u| over the number of
-   items, so that all that is left out stays below 2^-55 of every target's
-   value.  Without such a proof (cancellation, NaN) the item is summed.
+   with the smallest |u| of the group's targets so far in hand, an item is left
+   out when the bound of its charges times e^-z stays below 2^-55 |u| over the
+   number of items, so that all that is left out stays below 2^-55 of the nearest
+   classes' sum at every target, whose own rounding is larger.  Where that sum
+   is small (cancellation) or not finite, the item is summed.
    109,314 x 4096, alpha = 100 / 200 / 500 / 1000, both layers: 370 / 964 / 735 /
    272 -> 233 / 365 / 239 / 142 us.
    Waves per group (tree_setup): four for many groups; up to 128 for few,
@@ -1314,7 +1315,7 @@ __global__ __launch_bounds__(64 * Op::WMAX) void far_tree_kernel(FarArgs A, Tree
             for (int f = 0; f < NF; ++f) {
                 double s = 0.0;
                 for (int v = 0; v < W; ++v) s += red[f][v][lane];
-                s = s == s ? fabs(s) : 0.0; /* beside a NaN nothing is left out */
+                s = __builtin_isfinite(s) ? fabs(s) : 0.0; /* beside a NaN or an infinity nothing is left out */
                 for (int o = 32; o > 0; o >>= 1) s = fmin(s, __shfl_xor(s, o));
                 room = fminf(room, (float)log2(s) - 55.0f - log2f((float)(cnt.x + cnt.y)));
             }

@@ -30,3 +30,28 @@ def test_volume_points_at_infinity(px, py):
     assert np.array_equal(np.isnan(u), np.isnan(v)) and np.array_equal(np.isposinf(u), np.isposinf(v))
     ok = np.isfinite(v)
     assert (np.abs(u[ok] - v[ok]) <= 1e-12 * np.abs(v[ok]).max(initial=0.0)).all()
+
+
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+def test_opposite_infinities_near_and_far(sign):
+    """A plan whose far items may be left out, an infinite charge near a group of targets and the opposite one far from
+    it: every pair of both has K0 > 0, so the sum is NaN at every target, and with one of them alone it is infinite."""
+    rng = np.random.default_rng(3)
+    m, alpha = 41000, 150.0
+    g = wl.discretize(wl.Curve("ellipse", a=1.2, b=0.7), 40)
+    # targets within 4.3 of every node (z < 650, above the underflow) and away from the near panels
+    tx, ty = rng.uniform(-2.4, 2.4, 3 * m), rng.uniform(-1.6, 1.6, 3 * m)
+    clear = 1.3 * g.weights.reshape(-1, 16).sum(axis=1).max()
+    far = np.ones(3 * m, bool)
+    for j in range(0, g.n_nodes, 3):
+        far &= np.hypot(tx - g.x[j], ty - g.y[j]) > clear
+    tx, ty = tx[far][:m], ty[far][:m]
+    P = mhlp.Plan(mhlp.Geometry(_t(g.node_soa())), alpha, _t(tx), _t(ty))
+    assert P.n_targets == m and P.n_near_pairs == 0
+    left, right = int(np.argmin(g.x)), int(np.argmax(g.x))
+    for bad in ((left,), (right,), (left, right)):
+        sg = rng.standard_normal(g.n_nodes)
+        for k, j in enumerate(bad):
+            sg[j] = sign * np.inf * (-1) ** k
+        u = mhlp.eval_slp(P, _t(sg)).cpu().numpy()
+        assert np.isnan(u).all() if len(bad) == 2 else (u == sign * np.inf).all()
