@@ -321,11 +321,12 @@ __device__ void colsum_block(const ColJob &J, int block)
     if (J.db2) J.db2[c] = s;
 }
 
-/* blocks of J0, then of J1 (gx 0: none), then of the column sum */
+/* blocks of J0, then of J1 (gx 0: none), then of the column sum; numbered over
+   the rows of the grid, whose last row may run past the end (GRID_ROW) */
 __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmJob J0, GemmJob J1, ColJob C)
 {
     __shared__ GemmShared sh;
-    const int block = blockIdx.x;
+    const int block = blockIdx.y * gridDim.x + blockIdx.x;
     const int n0 = J0.gx * J0.gy * J0.splits, n1 = J1.gx * J1.gy * J1.splits;
     if (block >= n0 + n1)
         colsum_block(C, block - n0 - n1);
@@ -366,10 +367,13 @@ static GemmJob gemm_job(int M, int N, int K, const float *A, int64_t sam, int64_
     return J;
 }
 
+/* blocks of a row of the grid: a dimension of a launch holds fewer than 2^32 threads */
+constexpr int64_t GRID_ROW = (int64_t)1 << 20;
+
 static void launch_gemm(hipStream_t st, const GemmJob &J0, const GemmJob &J1 = GemmJob{}, const ColJob &C = ColJob{})
 {
     const int64_t blocks = (int64_t)J0.gx * J0.gy * J0.splits + (int64_t)J1.gx * J1.gy * J1.splits + nb(C.cols, 32);
-    gemm_bf16_kernel<<<(unsigned)blocks, 256, 0, st>>>(J0, J1, C);
+    gemm_bf16_kernel<<<dim3((unsigned)std::min(blocks, GRID_ROW), nb(blocks, (int)GRID_ROW)), 256, 0, st>>>(J0, J1, C);
 }
 
 __global__ void adam_kernel(float *__restrict__ p, const float *__restrict__ g, float *__restrict__ m,

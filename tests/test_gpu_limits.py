@@ -55,3 +55,16 @@ def test_opposite_infinities_near_and_far(sign):
             sg[j] = sign * np.inf * (-1) ** k
         u = mhlp.eval_slp(P, _t(sg)).cpu().numpy()
         assert np.isnan(u).all() if len(bad) == 2 else (u == sign * np.inf).all()
+
+
+def test_gemm_of_more_tiles_than_a_grid_dimension_holds():
+    """131,072 x 131,072 from one column and one row (4096^2 tiles of 256 threads: 2^32 threads); products of small
+    whole numbers are exact."""
+    n = 131072
+    if torch.cuda.mem_get_info()[0] < 80 << 30:
+        pytest.skip("needs 69 GB for the product")
+    a = torch.arange(n, device="cuda:0") % 13 - 6
+    b = torch.arange(n, device="cuda:0") % 7 - 3
+    c = mhlp.gemm_bf16(a.float()[:, None].contiguous(), b.float()[None, :].contiguous())
+    for i in (0, 31, 32, 65535, 65536, n - 33, n - 1):
+        assert torch.equal(c[i], (a[i] * b).float()) and torch.equal(c[:, i], (a * b[i]).float())
