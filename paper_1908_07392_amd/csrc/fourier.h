@@ -372,13 +372,15 @@ __device__ __forceinline__ double nu_phi(double z)
 /* u at the points from the fine-grid values b [2][Mf][Mf], NU_W x NU_W stencil: a
    row of 16 lanes per point, lane a its column a of the stencil (42 -> 5 us for
    1024 points with a thread each, whose 28 exponentials and 392 loads came one
-   after the other) */
+   after the other).  The blocks fill rows of
+   NU_ROW: a dimension of a launch holds fewer than 2^32 threads. */
+constexpr int NU_ROW = 1 << 20;
 __global__ __launch_bounds__(256) void nufft_interp_kernel(const double *__restrict__ fine, int Mf, double hf, double x0,
                                                            double y0, const double *__restrict__ px,
                                                            const double *__restrict__ py, int64_t n,
                                                            double *__restrict__ up)
 {
-    const int64_t p = blockIdx.x * (int64_t)16 + (threadIdx.x >> 4);
+    const int64_t p = (blockIdx.y * (int64_t)gridDim.x + blockIdx.x) * 16 + (threadIdx.x >> 4);
     const int64_t i = min(p, n - 1); /* rows past the end repeat the last point */
     const int a = threadIdx.x & 15, row = threadIdx.x & 48;
     const double xf = (px[i] - x0) / hf, yf = (py[i] - y0) / hf;

@@ -3455,7 +3455,9 @@ extern "C" mhlp_status mhlp_box_particular(mhlp_box *B, const double *F, double 
         mhlp::nufft_lines_kernel<<<dim3(M, 2), Mf / 8, linef, st>>>(B->spec, lg + 1, B->corr, B->twf, B->fine);
         mhlp::fft_rows_store_kernel<true><<<dim3(Mf / Lf, 2), Lf * Mf / 8, Lf * linef, st>>>(B->fine, lg + 1, MMf / 2,
                                                                                            B->twf, 0, values, nullptr);
-        mhlp::nufft_interp_kernel<<<nblocks(n, 16), 256, 0, st>>>(values, Mf, B->Lb / Mf, B->x0, B->y0, px, py, n, up);
+        const int64_t pb = nblocks(n, 16);
+        mhlp::nufft_interp_kernel<<<dim3((unsigned)std::min<int64_t>(pb, mhlp::NU_ROW), nblocks(pb, mhlp::NU_ROW)), 256, 0,
+                                    st>>>(values, Mf, B->Lb / Mf, B->x0, B->y0, px, py, n, up);
     } else if (n > 0) {
         const int nchunk = M / mhlp::FT2_R;
         const int64_t need = 2 * (int64_t)nchunk * n;

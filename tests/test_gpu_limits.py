@@ -68,3 +68,20 @@ def test_gemm_of_more_tiles_than_a_grid_dimension_holds():
     c = mhlp.gemm_bf16(a.float()[:, None].contiguous(), b.float()[None, :].contiguous())
     for i in (0, 31, 32, 65535, 65536, n - 33, n - 1):
         assert torch.equal(c[i], (a[i] * b).float()) and torch.equal(c[:, i], (a * b[i]).float())
+
+
+def test_box_values_at_more_points_than_a_grid_dimension_holds():
+    """2^28 + 5 points, 16 lanes each: the first and last ones as in a small call."""
+    n = (1 << 28) + 5
+    if torch.cuda.mem_get_info()[0] < 16 << 30:
+        pytest.skip("needs 9 GB for the points and values")
+    M = 16
+    B = mhlp.Box(M, -1.0, 0.5, 2.0, 3.0)
+    gen = torch.Generator(device="cuda:0").manual_seed(5)
+    F = torch.randn(2, M, M, dtype=torch.float64, device="cuda:0", generator=gen)
+    px = torch.rand(n, dtype=torch.float64, device="cuda:0", generator=gen)
+    py = torch.rand(n, dtype=torch.float64, device="cuda:0", generator=gen)
+    up = B.particular(F, want_u=False, px=px, py=py)[2]
+    for cut in (slice(0, 1000), slice(n - 1000, n)):
+        small = B.particular(F, want_u=False, px=px[cut].clone(), py=py[cut].clone())[2]
+        assert torch.equal(up[:, cut], small)
