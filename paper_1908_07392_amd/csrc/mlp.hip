@@ -86,6 +86,8 @@ constexpr int GK = 128;      /* k staged at a time */
 constexpr int GT_PAD = 8;    /* LDS row padding (BF16 elements): rows of 272 bytes */
 constexpr int MAX_SPLITS = 32;
 constexpr int MAX_TICKETS = 256; /* tiles of a split product: fewer than 256 */
+/* partial tiles of a split product: splitk_chunk's splits times its tiles stay below 256 + tiles <= 512 */
+constexpr int64_t WS_LEN = (int64_t)512 * GT * GT;
 
 constexpr float GELU_C = 0.7978845608028654f; /* sqrt(2/pi) */
 constexpr float GELU_A = 0.044715f;
@@ -435,8 +437,7 @@ struct mhlp_mlp {
     float *p = nullptr, *g = nullptr, *m = nullptr, *v = nullptr, *loss = nullptr;
     int cap = 0; /* batch capacity of the activation buffers */
     float *Z[3] = {nullptr, nullptr, nullptr}, *Ac[2] = {nullptr, nullptr}, *d0 = nullptr, *d1 = nullptr;
-    float *ws = nullptr; /* split-K partial tiles, twice MAX_SPLITS x cap x max(n1, n2, n3) (ws_len each) */
-    int64_t ws_len = 0;
+    float *ws = nullptr; /* split-K partial tiles of two products, WS_LEN each */
     int *ticket = nullptr; /* [2][MAX_TICKETS] arrivals at the tiles of split products, zero between launches */
     int64_t step = 0;
 };
@@ -468,7 +469,6 @@ static void free_acts(mhlp_mlp *N)
     free_dev(N->d0);
     free_dev(N->d1);
     free_dev(N->ws);
-    N->ws_len = 0;
     N->cap = 0;
 }
 
@@ -569,11 +569,10 @@ static mhlp_status ensure_acts(mhlp_mlp *N, int B, hipStream_t st)
     if ((s = malloc_dev(&N->Z[0], (int64_t)B * N->n[1])) || (s = malloc_dev(&N->Z[1], (int64_t)B * N->n[2])) ||
         (s = malloc_dev(&N->Z[2], (int64_t)B * N->n[3])) || (s = malloc_dev(&N->Ac[0], (int64_t)B * N->n[1])) ||
         (s = malloc_dev(&N->Ac[1], (int64_t)B * N->n[2])) || (s = malloc_dev(&N->d0, (int64_t)B * maxw)) ||
-        (s = malloc_dev(&N->d1, (int64_t)B * maxw)) || (s = malloc_dev(&N->ws, 2 * MAX_SPLITS * (int64_t)B * maxw))) {
+        (s = malloc_dev(&N->d1, (int64_t)B * maxw)) || (s = malloc_dev(&N->ws, 2 * WS_LEN))) {
         free_acts(N);
         return s;
     }
-    N->ws_len = MAX_SPLITS * (int64_t)B * maxw;
     N->cap = B;
     return MHLP_OK;
 }
@@ -625,7 +624,8 @@ extern "C" mhlp_status mhlp_mlp_loss_grad(mhlp_mlp *N, const float *X, const flo
         const float *in = l > 0 ? N->Ac[l - 1] : X;
         /* dW = dZ^T in : A(o,b) = dZ[b*no + o], B(b,k) = in[b*ni + k] */
         const int64_t szw = (int64_t)no * ni;
-        const bool wsplit = MAX_SPLITS * szw <= N->ws_len;
+        /* split where the weights are no more than the activations kept */
+        const bool wsplit = szw <= (int64_t)N->cap * std::max(std::max(N->n[1], N->n[2]), N->n[3]);
         GemmJob W = gemm_job(no, ni, B, cur, 1, no, in, ni, 1, wsplit ? N->ws : nullptr, N->ticket, EPI_STORE,
                              N->g + N->off_w[l], ni);
         if (grad) W.o2 = grad + N->off_w[l];
@@ -633,7 +633,7 @@ extern "C" mhlp_status mhlp_mlp_loss_grad(mhlp_mlp *N, const float *X, const flo
         GemmJob D = {};
         if (l > 0) {
             /* dA = dZ W : A(b,o) = dZ[b*no + o], B(o,k) = W[o*ni + k] */
-            D = gemm_job(B, ni, no, cur, no, 1, N->p + N->off_w[l], ni, 1, N->ws + N->ws_len, N->ticket + MAX_TICKETS,
+            D = gemm_job(B, ni, no, cur, no, 1, N->p + N->off_w[l], ni, 1, N->ws + WS_LEN, N->ticket + MAX_TICKETS,
                          EPI_BACK, nxt, ni);
             D.Z = N->Z[l - 1];
         }

@@ -85,3 +85,18 @@ def test_box_values_at_more_points_than_a_grid_dimension_holds():
     for cut in (slice(0, 1000), slice(n - 1000, n)):
         small = B.particular(F, want_u=False, px=px[cut].clone(), py=py[cut].clone())[2]
         assert torch.equal(up[:, cut], small)
+
+
+def test_network_workspace_does_not_grow_with_the_batch():
+    """Besides the seven activation buffers of a network (batch x its widest layer) a training step allocates the
+    partial tiles of its split products, which stay below 2 x 512 tiles of 4 KB."""
+    batch, wide = 32768, 256
+    N = mhlp.MLP(64, wide, wide, seed=3)
+    X, T = torch.randn(batch, 64, device="cuda:0"), torch.randn(batch, wide, device="cuda:0")
+    N.loss_grad(X[:16], T[:16])  # code and torch's own buffers in place
+    N.loss_grad(X[:16].clone(), T[:16].clone())
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    N.loss_grad(X, T)
+    torch.cuda.synchronize()
+    assert free - torch.cuda.mem_get_info()[0] <= 7 * batch * wide * 4 + (64 << 20)
