@@ -152,9 +152,11 @@ mhlp_status mhlp_plan_info(const mhlp_plan *plan, int64_t *n_targets, int64_t *n
    plus the current value, reps timed launches each after one warm-up,
    with HIP events on `stream`, keeps the fewest splits within 1% of the
    fastest and reports it with its time (host outputs; cand/cand_ms receive up
-   to cap candidates and their ms per launch).  Where the FP64 launch does not
-   use the split (layers 1-4), FP64 requests time the MIXED launch of the same layers, the one the split
-   serves (layers 5-7 time the same launch for every candidate).  Synchronises the stream.  Errors: MHLP_INVALID_ARG. */
+   to cap candidates and their ms per launch).  The FP64 launches do not use the
+   split: for layers 1-4 FP64 requests time the MIXED launch of the same layers,
+   the one the split serves; layers 5-7 time their launch at the plan's split,
+   the only candidate, and leave it as it is.  Synchronises the stream.  Errors:
+   MHLP_INVALID_ARG. */
 mhlp_status mhlp_plan_set_split(mhlp_plan *plan, int32_t nsplit);
 mhlp_status mhlp_plan_get_split(const mhlp_plan *plan, int32_t *nsplit);
 mhlp_status mhlp_plan_autotune(mhlp_plan *plan, int32_t layers, int32_t precision, int32_t reps, void *stream,
@@ -414,11 +416,11 @@ mhlp_status mhlp_batch_info(const mhlp_batch *batch, int64_t *total_len, int32_t
    work list of (geometry, 64 targets, split) items over the plans' cluster
    lists, longest first. */
 mhlp_status mhlp_batch_apply_bie(const mhlp_batch *batch, const double *mu, double *out, void *stream);
-/* Autotuner of the grouped operator's launch shape: for every pair of 1 or 2
-   targets per lane and 128 or 256 sources per step (kept and reported; they
-   no longer shape the launch) and a total of 512, 1024, ..., 16384 blocks, rebuild the work list and time the operator (reps launches after a
-   warm-up, HIP events on `stream`); keep the fewest blocks within 1% of the
-   fastest.  best_target and best_ms (host) may be NULL.  Synchronises the
+/* Autotuner of the grouped operator's launch shape: for a total of 512, 1024,
+   ..., 16384 blocks, rebuild the work list and time the operator (reps launches
+   after a warm-up, HIP events on `stream`); keep the fewest blocks within 1% of
+   the fastest.  Each time is reported for every pair of 1 or 2 targets per lane
+   and 128 or 256 sources per step, which do not shape the launch.  best_target and best_ms (host) may be NULL.  Synchronises the
    stream. */
 mhlp_status mhlp_batch_autotune(mhlp_batch *batch, int32_t reps, void *stream, int64_t *best_target, double *best_ms);
 /* The batch's launch shape (block target, targets per lane, sources per LDS

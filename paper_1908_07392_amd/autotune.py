@@ -42,7 +42,11 @@ def _load(path):
 def tune(plan: mhlp.Plan, layers: str = "both", precision: int = mhlp.FP64, reps: int = 5,
          use_cache: bool = True, path: str | None = None, write: bool = True) -> dict:
     """Set the plan's split count from the cache or by timing; returns the record.
-    path: cache file (default cache_path()); write=False never modifies it."""
+    path: cache file (default cache_path()); write=False never modifies it.
+    The gradients and the stresslet do not use the split: they are timed afresh
+    and the plan's split, which shapes its mixed-precision launches, stays."""
+    if layers in ("grad", "stokes", "stokes_grad"):
+        use_cache = False
     path = path or cache_path()
     key = _key(plan, layers, precision)
     cache = _load(path) if use_cache else {}

@@ -2455,12 +2455,14 @@ extern "C" mhlp_status mhlp_plan_autotune(mhlp_plan *P, int32_t layers, int32_t 
     if (cap < 0 || (cap > 0 && (!cand || !cand_ms))) return fail(MHLP_INVALID_ARG, "candidate arrays");
     hipStream_t st = (hipStream_t)stream;
     const int64_t N = P->g->N, M = P->M, Np = P->g->Np;
-    /* The FP64 single and double layers run by cluster expansions (tree.h) and
-       do not use the split.  For them the split serves the MIXED launch of the
-       same layers, which is what gets timed. */
+    /* The FP64 launches run by cluster expansions (tree.h) and do not use the
+       split.  For the potentials it serves the MIXED launch of the same layers,
+       which is what gets timed; the gradients and the stresslet are timed as they
+       stand, and the split, which shapes the plan's MIXED launches, is left alone. */
     if (precision == MHLP_FP64 && layers <= 4) precision = MHLP_MIXED;
     std::vector<int> cs;
-    for (int64_t ns = 1; ns <= Np && ns <= 256; ns *= 2) cs.push_back((int)ns);
+    if (layers <= 4)
+        for (int64_t ns = 1; ns <= Np && ns <= 256; ns *= 2) cs.push_back((int)ns);
     if (std::find(cs.begin(), cs.end(), P->nsplit) == cs.end()) cs.push_back(P->nsplit);
     double *dens = nullptr, *out = nullptr;
     TRY(dalloc(&dens, 2 * N));
@@ -4684,22 +4686,23 @@ extern "C" mhlp_status mhlp_batch_autotune(mhlp_batch *B, int32_t reps, void *st
         double ms;
     };
     std::vector<Cand> tim;
-    for (int tpl : {1, 2})
-        for (int src : {128, FT_SRC})
-            for (int64_t tg : {512LL, 1024LL, 2048LL, 4096LL, 8192LL, 16384LL}) {
-                if (s) break;
-                if ((s = batch_build_work(B, tg, tpl, src, st))) break;
-                if ((s = batch_apply_impl(B, mu, out, st))) break;
-                float ms = 0.f;
-                hipError_t e = hipEventRecord(e0, st);
-                for (int r = 0; r < reps && e == hipSuccess && s == MHLP_OK; ++r) s = batch_apply_impl(B, mu, out, st);
-                if (e == hipSuccess) e = hipEventRecord(e1, st);
-                if (e == hipSuccess) e = hipEventSynchronize(e1);
-                if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
-                if (e != hipSuccess && s == MHLP_OK)
-                    s = fail(MHLP_HIP_ERROR, std::string("batch autotune: ") + hipGetErrorString(e));
+    for (int64_t tg : {512LL, 1024LL, 2048LL, 4096LL, 8192LL, 16384LL}) {
+        if (s) break;
+        if ((s = batch_build_work(B, tg, B->tpl, B->src, st))) break;
+        if ((s = batch_apply_impl(B, mu, out, st))) break;
+        float ms = 0.f;
+        hipError_t e = hipEventRecord(e0, st);
+        for (int r = 0; r < reps && e == hipSuccess && s == MHLP_OK; ++r) s = batch_apply_impl(B, mu, out, st);
+        if (e == hipSuccess) e = hipEventRecord(e1, st);
+        if (e == hipSuccess) e = hipEventSynchronize(e1);
+        if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
+        if (e != hipSuccess && s == MHLP_OK)
+            s = fail(MHLP_HIP_ERROR, std::string("batch autotune: ") + hipGetErrorString(e));
+        /* the tile shapes do not change the launch: one measurement stands for all four */
+        for (int tpl : {1, 2})
+            for (int src : {128, FT_SRC})
                 if (s == MHLP_OK) tim.push_back(Cand{tg, tpl, src, (double)ms / reps});
-            }
+    }
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
     (void)hipStreamSynchronize(st);
@@ -4708,8 +4711,7 @@ extern "C" mhlp_status mhlp_batch_autotune(mhlp_batch *B, int32_t reps, void *st
     if (s) return s;
     double bms = 1e300;
     for (const auto &t : tim) bms = std::min(bms, t.ms);
-    /* fewest blocks within 1% of the fastest (the first such in the search
-       order: one target per lane and the larger stage first) */
+    /* fewest blocks within 1% of the fastest, with the first of the shapes */
     const Cand *best = nullptr;
     for (const auto &t : tim)
         if (t.ms <= 1.01 * bms && (!best || t.target < best->target)) best = &t;

@@ -100,3 +100,30 @@ def test_network_workspace_does_not_grow_with_the_batch():
     N.loss_grad(X, T)
     torch.cuda.synchronize()
     assert free - torch.cuda.mem_get_info()[0] <= 7 * batch * wide * 4 + (64 << 20)
+
+
+def test_tuning_launches_without_a_split_leaves_it():
+    """The gradients and the stresslet do not use a plan's source split: tuning them keeps the one that shapes the
+    plan's mixed-precision launches, whether timed or asked of the cache."""
+    from paper_1908_07392_amd import autotune
+    g = wl.discretize(wl.starfish_curve(), 64)
+    G = mhlp.Geometry(_t(g.node_soa()))
+    tx, ty = (_t(v) for v in wl.grid_targets(60, -0.6, 0.6))
+    for stokes, layers in ((False, ("grad",)), (True, ("stokes", "stokes_grad"))):
+        P = mhlp.Plan(G, 20.0, tx, ty, stokes=stokes)
+        for split in (16, 32):
+            P.set_split(split)
+            for name in layers:
+                best, ms, table = P.autotune(layers=autotune.LAYERS[name], reps=1)
+                assert best == P.nsplit == split and list(table) == [split] and ms == table[split]
+                assert autotune.tune(P, name, reps=1)["nsplit"] == P.nsplit == split
+
+
+def test_batch_shapes_of_one_launch_share_a_time():
+    g = wl.discretize(wl.starfish_curve(), 40)
+    B = mhlp.Batch([mhlp.Plan(mhlp.Geometry(_t(g.node_soa())), 9.0)], 2)
+    B.autotune(reps=2)
+    rows = B.tile()["candidates"]
+    for target in {r[0] for r in rows}:
+        same = [r for r in rows if r[0] == target]
+        assert len(same) == 4 and len({r[3] for r in same}) == 1
