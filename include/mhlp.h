@@ -68,11 +68,8 @@ typedef struct {
     double tol;         /* stop when ||g - A mu||_2 / ||g||_2 <= tol (true residual) */
     int32_t max_iter;   /* total Arnoldi steps                                        */
     int32_t restart;    /* Krylov dimension before a restart (<= 512)                 */
-    int32_t precision;  /* MHLP_FP64 or MHLP_MIXED (mixed: inner solves of iterative
-                           refinement: each cycle's Arnoldi steps stop at 0.5e-6 of
-                           the residual the cycle started from; each cycle ends with
-                           the FP64 true residual, from which the next starts; the
-                           operator itself is FP64 in both)                           */
+    int32_t precision;  /* MHLP_FP64 or MHLP_MIXED: the same solve, since the operator
+                           by cluster expansions is FP64 and faster than in FP32      */
     int32_t use_x0;     /* 1: mu holds the initial guess on entry; 0: zero guess      */
 } mhlp_gmres_opts;
 

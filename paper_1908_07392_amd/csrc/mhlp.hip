@@ -155,7 +155,7 @@ struct mhlp_plan {
     /* keyed by (precision, chunk length S = 0..GMRES_MAX_CHUNK, steps m <= S
        whose Gram-Schmidt runs in one block, end-of-cycle tail or not) */
     std::map<int, StepGraph> graphs;
-    int gm_first_steps[2] = {0, 0}; /* steps of the last solve's first cycle, per precision */
+    int gm_first_steps = 0; /* steps of the last solve's first cycle */
 };
 
 /* ------------------------------------------------------------------------ */
@@ -2682,14 +2682,13 @@ extern "C" mhlp_status mhlp_stokes_eval_grad(const mhlp_plan *Pc, const double *
    stresslet (2N, component-major) */
 static int64_t vlen(const mhlp_plan *P) { return P->stokes ? 2 * P->g->N : P->g->N; }
 
-static mhlp_status apply_op(mhlp_plan *P, const double *x, double *out, int32_t prec, hipStream_t st,
-                            const GState *gs = nullptr, int64_t jstride = 0)
+/* the FP64 operator, in mixed-precision solves too: by expansions it takes a
+   third of the FP32 tiles' time (N = 4096: 18 against 61 + 5 us) and is the more
+   accurate */
+static mhlp_status apply_op(mhlp_plan *P, const double *x, double *out, hipStream_t st, const GState *gs = nullptr,
+                            int64_t jstride = 0)
 {
     if (P->stokes) return launch_stokes(P, x, out, P->g->N, true, st, gs, jstride);
-    /* also the inner steps of a mixed-precision solve: the FP64 operator by
-       expansions takes a third of the FP32 tiles' time (N = 4096: 18 against
-       61 + 5 us) and is the more accurate */
-    (void)prec;
     return launch_far(P, nullptr, x, nullptr, out, 0.5, MHLP_FP64, st, gs, jstride);
 }
 
@@ -2791,13 +2790,13 @@ static hipError_t spin_sync(hipStream_t st)
 
 /* One Arnoldi step of the device-driven GMRES, enqueued on st (one_block: the
    Gram-Schmidt part in one block, else over element slices). */
-static mhlp_status enqueue_step(mhlp_plan *P, int32_t prec, bool one_block, hipStream_t st)
+static mhlp_status enqueue_step(mhlp_plan *P, bool one_block, hipStream_t st)
 {
     const int64_t N = vlen(P);
     const int R = P->gdev_R;
     double *V = P->ws, *w = P->ws + (int64_t)(R + 1) * N;
     const GmresDev d = gdev_view(P);
-    TRY(apply_op(P, V, w, prec, st, d.gs, N));
+    TRY(apply_op(P, V, w, st, d.gs, N));
     if (one_block) {
         if (N <= GSF_T)
             gs_reg_kernel<1><<<1, GSF_T, 0, st>>>(d.gs, V, N, w, N, d.H, R, d.cs, d.sn, d.gv);
@@ -2823,8 +2822,7 @@ static mhlp_status enqueue_step(mhlp_plan *P, int32_t prec, bool one_block, hipS
 
 /* End of a cycle (each kernel a no-op unless the state says done): y from
    the rotated Hessenberg system, x += V y, and the true residual r = b - A x
-   with the FP64 operator (whatever the precision of the cycle's Arnoldi
-   steps) and its squared norm in the state, so that the host reads the
+   and its squared norm in the state, so that the host reads the
    outcome of the cycle with the state itself.  x and b are the solve's own
    vectors. */
 static mhlp_status enqueue_tail(mhlp_plan *P, const double *b, double *x, hipStream_t st)
@@ -2836,7 +2834,7 @@ static mhlp_status enqueue_tail(mhlp_plan *P, const double *b, double *x, hipStr
     gs_solve_kernel<<<1, 64, 0, st>>>(d.gs, d.tail, d.H, R, d.gv, d.y);
     gs_addcols_kernel<<<nblocks(N, 256), 256, 0, st>>>(d.gs, V, N, d.y, x, N);
     HIPCHECK(hipGetLastError());
-    TRY(apply_op(P, x, w, MHLP_FP64, st, d.tail, 0));
+    TRY(apply_op(P, x, w, st, d.tail, 0));
     tail_residual_kernel<<<1, GSF_T, 0, st>>>(d.tail, b, w, x, r, N, d.gs);
     HIPCHECK(hipGetLastError());
     return MHLP_OK;
@@ -2849,11 +2847,9 @@ constexpr int GMRES_MAX_CHUNK = 16;
    the first m of them with the one-block Gram-Schmidt, followed by the end of
    the cycle when `tail` is set; captured once per plan state (workspace,
    split, restart, the solve's x and b) on a private stream. */
-static mhlp_status step_graph(mhlp_plan *P, int32_t prec, int m, int S, bool tail, const double *b, double *x,
-                              hipGraphExec_t *out)
+static mhlp_status step_graph(mhlp_plan *P, int m, int S, bool tail, const double *b, double *x, hipGraphExec_t *out)
 {
-    const int key = (((prec == MHLP_MIXED ? 1 : 0) * (GMRES_MAX_CHUNK + 1) + S) * (GMRES_MAX_CHUNK + 1) + m) * 2 +
-                    (tail ? 1 : 0);
+    const int key = (S * (GMRES_MAX_CHUNK + 1) + m) * 2 + (tail ? 1 : 0);
     mhlp_plan::StepGraph &G = P->graphs[key];
     if (G.exec && G.ws == P->ws && G.part == P->part && G.gdev == P->gdev && G.R == P->gdev_R &&
         G.nsplit == P->nsplit && G.x == x && G.b == b) {
@@ -2867,7 +2863,7 @@ static mhlp_status step_graph(mhlp_plan *P, int32_t prec, int m, int S, bool tai
     if (!P->cap_stream) HIPCHECK(hipStreamCreateWithFlags(&P->cap_stream, hipStreamNonBlocking));
     HIPCHECK(hipStreamBeginCapture(P->cap_stream, hipStreamCaptureModeThreadLocal));
     mhlp_status s = MHLP_OK;
-    for (int k = 0; k < S && s == MHLP_OK; ++k) s = enqueue_step(P, prec, k < m, P->cap_stream);
+    for (int k = 0; k < S && s == MHLP_OK; ++k) s = enqueue_step(P, k < m, P->cap_stream);
     if (tail && s == MHLP_OK) s = enqueue_tail(P, b, x, P->cap_stream);
     hipGraph_t graph = nullptr;
     hipError_t e = hipStreamEndCapture(P->cap_stream, &graph);
@@ -2894,13 +2890,11 @@ static mhlp_status step_graph(mhlp_plan *P, int32_t prec, int m, int S, bool tai
 }
 
 /* One restarted-GMRES solve of A x = b to relative tolerance `tol` (relative
-   to bnorm), FP64 Arnoldi with CGS2 on the operator in `prec`, each cycle
-   ended by the true residual with the FP64 operator.  A cycle stops once its
-   residual estimate is below 0.5 tol bnorm or, when larger, cycle_rel times
-   the residual it started from: with the mixed-precision operator (cycle_rel
-   = 0.5e-6, the FP32 far field resolving the operator to ~1e-7) this is
-   iterative refinement, each cycle an inner solve of A d = r corrected by the
-   FP64 residual.  x and b belong to
+   to bnorm), FP64 Arnoldi with CGS2, each cycle ended by the true residual.  A
+   cycle stops once its residual estimate is below 0.5 tol bnorm.  Both
+   precisions take this path: the operator is FP64 in either, so cycles that
+   stop early to be refined would only repeat work (N = 4096, alpha = 50:
+   0.33 ms in two cycles, 0.23 in one).  x and b belong to
    the plan's workspace (captured graphs refer to them); x is updated in
    place.  The Arnoldi steps, the Givens rotations, the stopping test and the
    end of each cycle (x += V y, the true residual, and a copy of x into xout
@@ -2913,11 +2907,11 @@ static mhlp_status step_graph(mhlp_plan *P, int32_t prec, int m, int S, bool tai
    the solve starts from x = 0 with ||b|| formed on the device from bsrc,
    which is copied into b. */
 static mhlp_status gmres_core(mhlp_plan *P, double *b, double bnorm, double *x, double tol, int restart,
-                              int max_iter, int32_t prec, hipStream_t st, int *iters, int *cycles, double *relres,
+                              int max_iter, hipStream_t st, int *iters, int *cycles, double *relres,
                               const double *r_first, double beta_first, bool first_dev_in = false,
-                              const double *bsrc = nullptr, double *xout = nullptr, double cycle_rel = 0.0)
+                              const double *bsrc = nullptr, double *xout = nullptr)
 {
-    const double half_tol = std::max(0.5 * tol, cycle_rel); /* first cycle of a device-normed solve */
+    const double half_tol = 0.5 * tol;
     const int64_t N = vlen(P);
     TRY(ensure_gdev(P, restart));
     const int R = P->gdev_R;
@@ -2926,7 +2920,6 @@ static mhlp_status gmres_core(mhlp_plan *P, double *b, double bnorm, double *x, 
     double *r = w + N;
     const GmresDev d = gdev_view(P);
     const unsigned nbN = nblocks(N, 256);
-    const int pi = prec == MHLP_MIXED ? 1 : 0;
     int it = 0;
     *cycles = 0;
     double beta_tail = 0.0;
@@ -2944,7 +2937,7 @@ static mhlp_status gmres_core(mhlp_plan *P, double *b, double bnorm, double *x, 
             beta = beta_first;
             rr = r_first;
         } else if (*cycles == 0) {
-            TRY(apply_op(P, x, w, MHLP_FP64, st));
+            TRY(apply_op(P, x, w, st));
             residual_kernel<<<nbN, 256, 0, st>>>(b, w, r, N);
             TRY(dnorm(P, r, N, st, &beta));
             rr = r;
@@ -2969,17 +2962,16 @@ static mhlp_status gmres_core(mhlp_plan *P, double *b, double bnorm, double *x, 
             }
         } else {
             scale_kernel<<<nbN, 256, 0, st>>>(rr, 1.0 / beta, V, N);
-            gs_init_kernel<<<1, 256, 0, st>>>(d.gs, d.gv, R, kmax, beta,
-                                              std::max(0.5 * tol * bnorm, cycle_rel * beta), xout);
+            gs_init_kernel<<<1, 256, 0, st>>>(d.gs, d.gv, R, kmax, beta, half_tol * bnorm, xout);
         }
         HIPCHECK(hipGetLastError());
         int done_steps = 0;
         /* the first cycle starts with the previous solve's count and its end
            appended; otherwise GMRES_FIRST_CHUNK steps */
-        const bool hist = *cycles == 1 && P->gm_first_steps[pi] > 0;
-        int chunk = hist ? P->gm_first_steps[pi] : GMRES_FIRST_CHUNK;
+        const bool hist = *cycles == 1 && P->gm_first_steps > 0;
+        int chunk = hist ? P->gm_first_steps : GMRES_FIRST_CHUNK;
         bool expect_end = hist;
-        double last_est = beta, thresh = std::max(0.5 * tol * bnorm, cycle_rel * beta);
+        double last_est = beta, thresh = half_tol * bnorm;
         GState gsh;
         for (;;) {
             const int S = std::max(1, std::min({chunk, GMRES_MAX_CHUNK, kmax - done_steps}));
@@ -2991,7 +2983,7 @@ static mhlp_status gmres_core(mhlp_plan *P, double *b, double bnorm, double *x, 
                               ? std::max(0, std::min(S, gsr_cols(N) + gsr_extra(N) - done_steps))
                               : 0;
             hipGraphExec_t ex;
-            TRY(step_graph(P, prec, m, S, tail, b, x, &ex));
+            TRY(step_graph(P, m, S, tail, b, x, &ex));
             HIPCHECK(hipGraphLaunch(ex, st));
             HIPCHECK(hipMemcpyAsync(P->gstate_host, d.gs, sizeof(GState), hipMemcpyDeviceToHost, st));
             HIPCHECK(spin_sync(st));
@@ -3009,7 +3001,7 @@ static mhlp_status gmres_core(mhlp_plan *P, double *b, double bnorm, double *x, 
             }
             if (gsh.done) {
                 if (!tail) { /* the cycle ended before its end was enqueued */
-                    TRY(step_graph(P, prec, 0, 0, true, b, x, &ex));
+                    TRY(step_graph(P, 0, 0, true, b, x, &ex));
                     HIPCHECK(hipGraphLaunch(ex, st));
                     HIPCHECK(hipMemcpyAsync(P->gstate_host, d.gs, sizeof(GState), hipMemcpyDeviceToHost, st));
                     HIPCHECK(spin_sync(st));
@@ -3034,7 +3026,7 @@ static mhlp_status gmres_core(mhlp_plan *P, double *b, double bnorm, double *x, 
             chunk = need;
         }
         it += gsh.steps;
-        if (*cycles == 1) P->gm_first_steps[pi] = std::max(1, gsh.steps);
+        if (*cycles == 1) P->gm_first_steps = std::max(1, gsh.steps);
         beta_tail = std::sqrt(gsh.rn2);
     }
     *iters = it;
@@ -3064,7 +3056,6 @@ static mhlp_status gmres_solve_impl(const mhlp_plan *Pc, const double *g, double
     TRY(ensure_gdev(P, opts->restart));
     const int R = P->gdev_R;
     TRY(ensure_ws(P, R + 1));
-    const bool mixed = opts->precision == MHLP_MIXED;
     double *xw = P->ws + (int64_t)(R + 5) * N, *bw = P->ws + (int64_t)(R + 6) * N;
     /* a solve from zero forms ||g|| on the device and reads it with the first
        read of the GMRES state (one host round trip fewer); the others need it
@@ -3079,14 +3070,14 @@ static mhlp_status gmres_solve_impl(const mhlp_plan *Pc, const double *g, double
         info->converged = 1;
         return MHLP_OK;
     }
-    /* residual of the initial guess (FP64 operator), kept in the residual slot
+    /* residual of the initial guess, kept in the residual slot
        of the first GMRES cycle (basis V_0..V_R, then w, r) so the cycle does
        not recompute it */
     double *r0 = P->ws + (int64_t)(R + 2) * N;
     double r0n = 0.0;
     if (opts->use_x0) {
         double *w = P->ws + (int64_t)(R + 1) * N;
-        TRY(apply_op(P, mu, w, MHLP_FP64, st));
+        TRY(apply_op(P, mu, w, st));
         residual_kernel<<<nblocks(N, 256), 256, 0, st>>>(g, w, r0, N);
         TRY(dnorm(P, r0, N, st, &r0n));
         info->x0_residual = r0n / bnorm;
@@ -3104,12 +3095,10 @@ static mhlp_status gmres_solve_impl(const mhlp_plan *Pc, const double *g, double
     double rel = 1.0;
     /* the solve runs on its own copies of g and mu (xw, bw), which the captured
        graphs refer to; the start kernel of a device-normed solve makes them,
-       else they are copied here.  Mixed precision: each cycle an inner solve to 1e-6 of the residual it started
-       from, its end the FP64 true residual (iterative refinement). */
+       else they are copied here. */
     if (!bnorm_dev) HIPCHECK(hipMemcpyAsync(bw, g, sizeof(double) * N, hipMemcpyDeviceToDevice, st));
-    TRY(gmres_core(P, bw, bnorm, xw, opts->tol, opts->restart, opts->max_iter, mixed ? MHLP_MIXED : MHLP_FP64, st,
-                   &iters, &cycles, &rel, info->used_x0 ? r0 : bw, info->used_x0 ? r0n : bnorm, bnorm_dev, g, mu,
-                   mixed ? 0.5e-6 : 0.0));
+    TRY(gmres_core(P, bw, bnorm, xw, opts->tol, opts->restart, opts->max_iter, st, &iters, &cycles, &rel,
+                   info->used_x0 ? r0 : bw, info->used_x0 ? r0n : bnorm, bnorm_dev, g, mu));
     /* every cycle's end copies x into mu; without a cycle x is the start */
     if (cycles == 0) HIPCHECK(hipMemcpyAsync(mu, xw, sizeof(double) * N, hipMemcpyDeviceToDevice, st));
     info->iters = iters;

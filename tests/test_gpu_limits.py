@@ -127,3 +127,14 @@ def test_batch_shapes_of_one_launch_share_a_time():
     for target in {r[0] for r in rows}:
         same = [r for r in rows if r[0] == target]
         assert len(same) == 4 and len({r[3] for r in same}) == 1
+
+
+@pytest.mark.parametrize("alpha", [5.0, 200.0])
+def test_mixed_solve_is_the_fp64_solve(alpha):
+    """The operator is FP64 in both precisions, so a mixed-precision solve takes the same single cycle."""
+    g = wl.discretize(wl.starfish_curve(), 96)
+    P = mhlp.Plan(mhlp.Geometry(_t(g.node_soa())), alpha)
+    b = _t(np.cos(3 * g.theta) + 0.5)
+    mu64, i64 = mhlp.gmres_solve(P, b, tol=1e-10)
+    mu32, i32 = mhlp.gmres_solve(P, b, tol=1e-10, precision=mhlp.MIXED)
+    assert i64 == i32 and i32["converged"] and torch.equal(mu64, mu32)
