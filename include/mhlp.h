@@ -286,9 +286,10 @@ mhlp_status mhlp_gmres_solve(const mhlp_plan *onsurf, const double *g, double *m
    in [4, 60] builds the tree for the plan's nodes and targets, after which
    mhlp_eval_layer / _slp / _dlp with MHLP_FP64 evaluate the far field by the
    FMM (near-panel corrections unchanged; the direct part skips each target's
-   near panels) wherever it is estimated to be faster than the plan's own cluster
-   lists (large plans with large alpha, low orders; the lists reach rounding
-   whatever the order); MHLP_MIXED keeps the direct FP32 tiles.  leaf_level -1 picks the
+   near panels): always with an explicit leaf_level, with -1 wherever it is
+   estimated to be faster than the plan's own cluster lists (large plans with
+   large alpha, low orders; the lists reach rounding whatever the order);
+   MHLP_MIXED keeps the direct FP32 tiles.  leaf_level -1 picks the
    finest level <= 8 (about 32 points per leaf or more) at which every node of
    each target's near panels lies in the target's 3x3 leaf neighbourhood; an
    explicit level must satisfy that (MHLP_INVALID_ARG otherwise).  Builds on the

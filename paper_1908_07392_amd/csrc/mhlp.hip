@@ -3147,7 +3147,8 @@ static int fmm_auto_level(int64_t npts, int64_t per_leaf)
 }
 
 /* Does the FMM serve an evaluation sooner than the plan's cluster lists, which
-   reach rounding whatever the order?  The lists cost their items, the FMM its
+   reach rounding whatever the order?  (Where the caller leaves the level to the
+   library; a level asked for is served by the FMM.)  The lists cost their items, the FMM its
    boxes: per evaluation of both layers, us, lists | order 40, 20, 10:
      70,000 points, alpha = 5 (100), level 5:      63 (269) |  305  220  190
      260,000 points, alpha = 20 (200), level 7:    218 (2057) | 1270  860  665
@@ -3199,7 +3200,7 @@ extern "C" mhlp_status mhlp_plan_set_fmm(mhlp_plan *P, int32_t order, int32_t le
     }
     delete P->fmm;
     P->fmm = F;
-    P->fmm_serves = fmm_is_faster(P->tr_cost, order, L);
+    P->fmm_serves = leaf_level >= 0 || fmm_is_faster(P->tr_cost, order, L);
     return MHLP_OK;
 }
 

@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 from paper_1908_07392_amd import mhlp
 from paper_1908_07392_amd import workloads as wl
 
@@ -138,3 +139,26 @@ def test_mixed_solve_is_the_fp64_solve(alpha):
     mu64, i64 = mhlp.gmres_solve(P, b, tol=1e-10)
     mu32, i32 = mhlp.gmres_solve(P, b, tol=1e-10, precision=mhlp.MIXED)
     assert i64 == i32 and i32["converged"] and torch.equal(mu64, mu32)
+
+
+@pytest.mark.parametrize("alpha", [0.05, 5.0, 50.0, 500.0])
+def test_fmm_at_a_level_that_the_caller_asks_for(alpha):
+    """An explicit leaf level is served by the FMM whatever the lists would take: not the lists' values bit for bit,
+    yet as near to the oracle's (1e-11) and to theirs (1e-12) as the FMM's own tests ask, from level 0 to the finest."""
+    curve = wl.starfish_curve()
+    g = wl.discretize(curve, 128)
+    rng = np.random.default_rng(int(alpha * 100) + 9)
+    th = rng.uniform(0, 2 * np.pi, 60)
+    z, dz, _ = curve.eval(th)
+    pts = np.concatenate([z + d * 1j * dz / np.abs(dz) for d in (3e-2, 1e-4, -1e-3)] +
+                         [rng.uniform(-1.6, 1.6, 300) + 1j * rng.uniform(-1.6, 1.6, 300)])
+    mu = wl.fourier_density(g.theta, wl.random_fourier_coeffs(rng, 8))
+    P = mhlp.Plan(mhlp.Geometry(_t(g.node_soa())), alpha, _t(pts.real), _t(pts.imag))
+    lists = mhlp.eval_layer(P, sigma=_t(mu), mu=_t(mu))
+    exact = oracle.eval_potentials(g.x, g.y, alpha, pts.real, pts.imag, sigma=mu, mu=mu)
+    P.set_fmm(40)
+    for level in range(P.fmm[1] + 1):
+        P.set_fmm(40, level)
+        for u, v, w in zip(mhlp.eval_layer(P, sigma=_t(mu), mu=_t(mu)), lists, exact):
+            assert not torch.equal(u, v) and float((u - v).abs().max()) < 1e-12 * float(v.abs().max())
+            assert np.max(np.abs(u.cpu().numpy() - w)) < 1e-11 * np.max(np.abs(w))
