@@ -132,6 +132,8 @@ struct mhlp_plan {
                                  mixed-precision tiles */
     double *fqd = nullptr;    /* [FINE_SCALES] fine-piece scales and constants at alpha (fine_scales) */
     mhlp::TreeDev *tree = nullptr; /* clusters, item lists, moments (tree.h) */
+    char *tree_mem = nullptr;      /* its arrays but for the partial sums and, unless small, the lists */
+    uint2 *tree_items = nullptr;   /* the lists where they have memory of their own */
     unsigned long long tr_cost = 0; /* total work of the item lists */
     int tr_waves = 0, tr_split = 1; /* waves per block and blocks per group of far_tree_kernel */
     NearParams np{};
@@ -1957,8 +1959,7 @@ extern "C" mhlp_status mhlp_plan_destroy(mhlp_plan *P)
         if (p) (void)hipFree(p);
     delete P->fmm;
     if (P->tree) {
-        void *tp[] = {P->tree->cc, P->tree->rmin, P->tree->mom, P->tree->st, P->tree->items, P->tree->cnt, P->tree->order,
-                      P->tree->part, P->tree->flux, P->tree->cost, P->tree->lb, P->tree->znear};
+        void *tp[] = {P->tree_mem, P->tree_items, P->tree->part};
         for (void *p : tp)
             if (p) (void)hipFree(p);
         delete P->tree;
@@ -2007,18 +2008,38 @@ static mhlp_status tree_setup(mhlp_plan *P, hipStream_t st)
         T.ncl += (Np + ((int64_t)1 << T.nlev) - 1) >> T.nlev;
         ++T.nlev;
     }
-    TRY(dalloc(&T.cc, 2 * T.ncl));
-    TRY(dalloc(&T.rmin, mhlp::TR_RM * T.ncl));
     T.stokes = P->stokes ? 1 : 0;
-    TRY(dalloc(&T.mom, T.ncl * mhlp::tr_stride(P->stokes ? (P->onsurf ? 6 : 10) : (P->onsurf ? 4 : 8))));
-    if (P->stokes && P->onsurf) TRY(dalloc(&T.flux, Np));
-    TRY(dalloc(&T.st, 48 * Np));
-    TRY(dalloc(&T.items, G * Np));
-    TRY(dalloc(&T.cnt, G));
-    TRY(dalloc(&T.order, G));
-    TRY(dalloc(&T.cost, 2));
-    TRY(dalloc(&T.lb, T.ncl));
-    TRY(dalloc(&T.znear, G));
+    int64_t bytes = 0;
+    auto take = [&](int64_t n) {
+        const int64_t o = bytes;
+        bytes += (n + 255) / 256 * 256;
+        return o;
+    };
+    const int64_t nmom = T.ncl * mhlp::tr_stride(P->stokes ? (P->onsurf ? 6 : 10) : (P->onsurf ? 4 : 8));
+    const int64_t o_cc = take(16 * T.ncl), o_rmin = take(8 * mhlp::TR_RM * T.ncl), o_mom = take(8 * nmom);
+    const int64_t o_st = take(8 * 48 * Np), o_flux = take(P->stokes && P->onsurf ? 8 * Np : 0), o_lb = take(4 * T.ncl);
+    const int64_t o_at = take(16 * G), o_cnt = take(8 * G), o_order = take(4 * G), o_znear = take(4 * G), o_cost = take(24);
+    /* the lists are counted, then filled into storage of their size; they pass
+       through slots of one entry a panel, for as many groups at a time as 64 MB
+       hold (more than one such part: listed once to count and again to fill).
+       Small plans keep slots and room for all entries, at most 8 MB, with the
+       rest: allocations are most of what their creation costs here */
+    const int64_t nrun = mhlp::tree_nrun(Np), slot = mhlp::TR_RUN * (int64_t)sizeof(uint2), per = nrun * (slot + 4);
+    const int64_t Gc = std::min(G, std::max<int64_t>(1, ((int64_t)64 << 20) / per));
+    const bool small = G * nrun * slot <= (int64_t)4 << 20;
+    const int64_t o_tmp = take(small ? G * per : 0), o_items = take(small ? G * nrun * slot : 0);
+    TRY(dalloc(&P->tree_mem, bytes));
+    T.cc = reinterpret_cast<double *>(P->tree_mem + o_cc);
+    T.rmin = reinterpret_cast<double *>(P->tree_mem + o_rmin);
+    T.mom = reinterpret_cast<double *>(P->tree_mem + o_mom);
+    T.st = reinterpret_cast<double *>(P->tree_mem + o_st);
+    if (P->stokes && P->onsurf) T.flux = reinterpret_cast<double *>(P->tree_mem + o_flux);
+    T.lb = reinterpret_cast<float *>(P->tree_mem + o_lb);
+    T.at = reinterpret_cast<longlong2 *>(P->tree_mem + o_at);
+    T.cnt = reinterpret_cast<int2 *>(P->tree_mem + o_cnt);
+    T.order = reinterpret_cast<int32_t *>(P->tree_mem + o_order);
+    T.znear = reinterpret_cast<int *>(P->tree_mem + o_znear);
+    T.cost = reinterpret_cast<unsigned long long *>(P->tree_mem + o_cost);
     /* waves per group of 64 targets (blocks of 8, 16 or 4 waves; direct items
        cut into 2^cut units), by the number of groups: enough waves to fill the
        chip.  Measured us per evaluation (starfish, 4096 sources, alpha = 5) with
@@ -2040,14 +2061,56 @@ static mhlp_status tree_setup(mhlp_plan *P, hipStream_t st)
     if (P->tr_split > 1) TRY(dalloc(&T.part, (P->onsurf ? 2 : 4) * (int64_t)P->tr_split * M));
     mhlp::tree_clusters_kernel<<<nblocks(T.ncl, 4), 256, 0, st>>>(T, g->soa, g->soa + g->N, g->ph, P->alpha,
                                                                   P->near_factor);
-    HIPCHECK(hipMemsetAsync(T.cost, 0, 2 * sizeof(*T.cost), st));
-    mhlp::tree_lists_kernel<<<nblocks(G, 4), 256, 0, st>>>(T, P->tx, P->ty, M, g->soa, g->soa + g->N, g->ph,
-                                                           P->near_factor, P->alpha, P->near_ptr, P->near_panel);
-    mhlp::tree_order_kernel<<<1, 1024, 0, st>>>(T, G);
-    HIPCHECK(hipGetLastError());
-    unsigned long long cost[2];
-    HIPCHECK(hipMemcpyAsync(cost, T.cost, sizeof(cost), hipMemcpyDeviceToHost, st));
-    HIPCHECK(hipStreamSynchronize(st)); /* later calls may come on other streams */
+    HIPCHECK(hipMemsetAsync(T.cost, 0, 3 * sizeof(*T.cost), st));
+    char *tmp = small ? P->tree_mem + o_tmp : nullptr;
+    bool have = small || hipMalloc((void **)&tmp, (size_t)(Gc * per)) == hipSuccess;
+    uint2 *slots = reinterpret_cast<uint2 *>(tmp);
+    uint32_t *runs = reinterpret_cast<uint32_t *>(slots + Gc * nrun * mhlp::TR_RUN);
+    auto list = [&](int64_t g0) {
+        const int64_t ng = std::min(Gc, G - g0);
+        mhlp::tree_lists_kernel<<<nblocks(ng * nrun, 4), 256, 0, st>>>(T, P->tx, P->ty, M, g->soa, g->soa + g->N, P->alpha,
+                                                                       P->near_ptr, P->near_panel, g0, ng, slots, runs);
+        return (unsigned)ng;
+    };
+    unsigned long long cost[3] = {3ull * (unsigned long long)Np * (unsigned long long)G, 0, (unsigned long long)Np};
+    hipError_t e = hipSuccess;
+    if (have) {
+        for (int64_t g0 = 0; g0 < G; g0 += Gc) {
+            const unsigned ng = list(g0);
+            mhlp::tree_count_kernel<<<ng, 64, 0, st>>>(T, g0, runs);
+        }
+        mhlp::tree_order_kernel<<<1, 1024, 0, st>>>(T, G);
+        e = hipGetLastError();
+        unsigned long long c[3];
+        if (e == hipSuccess) e = hipMemcpyAsync(c, T.cost, sizeof(c), hipMemcpyDeviceToHost, st);
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        if (e == hipSuccess) {
+            const size_t n = (size_t)std::max<unsigned long long>(1, c[2]);
+            have = small || hipMalloc((void **)&P->tree_items, sizeof(uint2) * n) == hipSuccess;
+            T.items = small ? reinterpret_cast<uint2 *>(P->tree_mem + o_items) : P->tree_items;
+            if (have) std::copy(c, c + 3, cost);
+        }
+    }
+    if (have && e == hipSuccess) {
+        for (int64_t g0 = 0; g0 < G; g0 += Gc) {
+            const unsigned ng = Gc < G ? list(g0) : (unsigned)G; /* else they are in the slots */
+            mhlp::tree_fill_kernel<<<ng, 64, 0, st>>>(T, g0, slots, runs);
+        }
+        e = hipGetLastError();
+        if (e == hipSuccess) e = hipStreamSynchronize(st); /* later calls may come on other streams */
+    }
+    if (tmp && !small) (void)hipFree(tmp);
+    if (e != hipSuccess) return fail(MHLP_HIP_ERROR, std::string("plan_create lists: ") + hipGetErrorString(e));
+    if (!have) {
+        /* no memory for them: one list serves every group, all pairs one by one */
+        (void)hipGetLastError();
+        P->tree_items = nullptr;
+        TRY(dalloc(&P->tree_items, Np));
+        T.items = P->tree_items;
+        mhlp::tree_direct_kernel<<<nblocks(std::max(G, Np), 256), 256, 0, st>>>(T, G);
+        HIPCHECK(hipGetLastError());
+        HIPCHECK(hipStreamSynchronize(st));
+    }
     P->tr_cost = cost[0];
     T.skip = cost[1] >= mhlp::TR_ZSKIP && P->tr_split == 1;
     return MHLP_OK;
@@ -2291,12 +2354,17 @@ template <class Op>
 static void launch_tree_far(const FarArgs &A, const mhlp_plan *P, hipStream_t st)
 {
     const mhlp::TreeDev &T = *P->tree;
-    const dim3 grid(nblocks(A.M, 64), (unsigned)P->tr_split);
     const int threads = 64 * std::min(P->tr_waves, Op::WMAX);
-    if (Op::SKIP && T.skip)
-        mhlp::far_tree_kernel<Op, Op::SKIP><<<grid, threads, 0, st>>>(A, T);
-    else
-        mhlp::far_tree_kernel<Op, false><<<grid, threads, 0, st>>>(A, T);
+    const int64_t G = nblocks(A.M, 64), most = (int64_t)1 << 20; /* groups a launch: below 2^32 threads along the grid */
+    for (int64_t g0 = 0; g0 < G; g0 += most) {
+        mhlp::TreeDev S = T;
+        S.order += g0;
+        const dim3 grid((unsigned)std::min(most, G - g0), (unsigned)P->tr_split);
+        if (Op::SKIP && T.skip)
+            mhlp::far_tree_kernel<Op, Op::SKIP><<<grid, threads, 0, st>>>(A, S);
+        else
+            mhlp::far_tree_kernel<Op, false><<<grid, threads, 0, st>>>(A, S);
+    }
     if (P->tr_split > 1)
         mhlp::tree_finalize<Op><<<dim3(nblocks(A.M, 64), (unsigned)Op::NF), 64, 0, st>>>(A, T, P->tr_split);
 }
@@ -4055,7 +4123,8 @@ __global__ __launch_bounds__(64 * BATCH_W, 4) void batch_far_kernel(const BatchG
     const int32_t k0 = geo.nptr[iv], k1 = geo.nptr[iv + 1];
     const int NW = BATCH_W * geo.nsplit, wg = w * geo.nsplit + wk.split;
     const int2 cnt = T.cnt[g];
-    const uint2 *items = T.items + g * T.Np;
+    const longlong2 at = T.at[g];
+    const uint2 *items = T.items + at.x, *back = T.items + at.y - 1;
     double acc[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) acc[r] = 0.0;
@@ -4082,7 +4151,7 @@ __global__ __launch_bounds__(64 * BATCH_W, 4) void batch_far_kernel(const BatchG
     }
     const int fb = cnt.y * (NW - 1 - wg) / NW, fe = cnt.y * (NW - wg) / NW;
     for (int k = fb; k < fe; ++k) {
-        const uint2 it = items[T.Np - 1 - k];
+        const uint2 it = back[-k];
         const uint32_t c = __builtin_amdgcn_readfirstlane(it.x), fl = __builtin_amdgcn_readfirstlane(it.y);
         int64_t p0, p1;
         double f[R];

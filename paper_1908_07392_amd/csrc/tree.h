@@ -52,11 +52,12 @@ struct TreeDev {
     double *mom = nullptr;                   /* [ncl][tr_stride]: rows of the coefficients of K_n cos n theta
                                                 and K_n sin n theta per field (stresslet: then of r^-n) */
     double *st = nullptr;                    /* staged sources [Np][3][16]: w sigma, alpha w mu n_x, alpha w mu n_y */
-    uint2 *items = nullptr;                  /* [groups][Np]: direct items from the front, expansions from the back */
-    int2 *cnt = nullptr;                     /* [groups]: their numbers */
+    uint2 *items = nullptr;                  /* the groups' lists: direct items from the front, expansions from the back */
+    longlong2 *at = nullptr;                 /* [groups]: begin and end of a group's list */
+    int2 *cnt = nullptr;                     /* [groups]: numbers of direct items and expansions */
     double *part = nullptr;                  /* [fields][blocks per group][M] sums of split groups */
     unsigned long long *cost = nullptr;      /* total work of the groups (tree_cost); [1]: the largest spread of
-                                                the z classes of a group's items (TR_ZSTEP) */
+                                                the z classes of a group's items (TR_ZSTEP); [2]: all items */
     float *lb = nullptr;                     /* [ncl] log2 of the sum of |charges| and |dipoles|, rounded up */
     int *znear = nullptr;                    /* [groups] smallest z class of the items */
     int skip = 0;                            /* far items are held against the near ones' sum (far_tree_kernel) */
@@ -237,26 +238,36 @@ __device__ __forceinline__ int tree_piece(double zlo, double zhi)
     return KQ_NP + 1;
 }
 
-/* plan time: the item lists of each group of 64 targets, one wave per group.
-   Panels are visited in order; at each, the largest aligned cluster is tried
-   first, then its halves. */
+/* plan time: the items of each group of 64 targets, one wave per group and run
+   of 16 panels (the widest cluster), of the groups g0 on: into 16 slots of tmp
+   per run, direct items from the front, expansions from the back, and their
+   numbers and z classes into runs.  Panels are visited in order; at each, the
+   largest aligned cluster is tried first, then its halves.  A wave per group
+   alone left a plan of few groups waiting: 1024 panels all direct, 313 groups,
+   2 ms. */
+constexpr int TR_RUN = 1 << (TR_LEV - 1);
+__host__ __device__ inline int tree_nrun(int64_t Np) { return (int)((Np + TR_RUN - 1) / TR_RUN); }
+__device__ __forceinline__ uint32_t tree_run_word(int nd, int nf, int zlo, int zhi)
+{
+    return (uint32_t)(nd | nf << 5 | zlo << 10 | zhi << 18);
+}
 __global__ __launch_bounds__(256) void tree_lists_kernel(TreeDev T, const double *__restrict__ tx,
                                                          const double *__restrict__ ty, int64_t M,
                                                          const double *__restrict__ sx, const double *__restrict__ sy,
-                                                         const double *__restrict__ ph, double near_factor,
                                                          double alpha, const int32_t *__restrict__ nptr,
-                                                         const int32_t *__restrict__ npan)
+                                                         const int32_t *__restrict__ npan, int64_t g0, int64_t ng,
+                                                         uint2 *__restrict__ tmp, uint32_t *__restrict__ runs)
 {
-    const int64_t g = blockIdx.x * (int64_t)4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (64 * g >= M) return;
-    const int64_t i = min(64 * g + lane, M - 1);
+    const int64_t u = blockIdx.x * (int64_t)4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, nrun = tree_nrun(T.Np);
+    if (u >= ng * nrun) return;
+    const int64_t run = u % nrun, i = min(64 * (g0 + u / nrun) + lane, M - 1);
     const double x = tx[i], y = ty[i];
     const int32_t k0 = nptr[i], k1 = nptr[i + 1];
-    uint2 *items = T.items + g * T.Np;
+    uint2 *items = tmp + u * TR_RUN;
     int nd = 0, nf = 0, zlo = 255, zhi = 0;
-    for (int64_t p = 0; p < T.Np;) {
-        int k = p == 0 ? T.nlev - 1 : min(T.nlev - 1, __builtin_ctz((uint32_t)p));
+    for (int64_t p = TR_RUN * run, pe = min(T.Np, p + TR_RUN); p < pe;) {
+        int k = min(T.nlev - 1, __builtin_ctz((uint32_t)p | TR_RUN));
         for (;; --k) {
             const int64_t c = T.off[k] + (p >> k);
             const double dx = x - T.cc[2 * c], dy = y - T.cc[2 * c + 1], r = sqrt(fma(dx, dx, dy * dy));
@@ -286,7 +297,7 @@ __global__ __launch_bounds__(256) void tree_lists_kernel(TreeDev T, const double
                     zhi = max(zhi, (int)(zc >> 24));
                     y_ |= zc;
                 }
-                if (lane == 0) items[T.Np - 1 - nf] = make_uint2((uint32_t)c, y_);
+                if (lane == 0) items[TR_RUN - 1 - nf] = make_uint2((uint32_t)c, y_);
                 ++nf;
                 break;
             }
@@ -317,23 +328,85 @@ __global__ __launch_bounds__(256) void tree_lists_kernel(TreeDev T, const double
         }
         p += (int64_t)1 << k;
     }
-    if (lane == 0) {
-        T.cnt[g] = make_int2(nd, nf);
-        T.znear[g] = zlo;
-        if (zhi > zlo) atomicMax(T.cost + 1, (unsigned long long)(zhi - zlo));
+    if (lane == 0) runs[u] = tree_run_word(nd, nf, zlo, zhi);
+}
+
+/* plan time: a group's counts and z classes from its runs', one wave per group */
+__global__ __launch_bounds__(64) void tree_count_kernel(TreeDev T, int64_t g0, const uint32_t *__restrict__ runs)
+{
+    const int lane = threadIdx.x, nrun = tree_nrun(T.Np);
+    const int64_t g = g0 + blockIdx.x;
+    const uint32_t *w = runs + blockIdx.x * (int64_t)nrun;
+    int nd = 0, nf = 0, zlo = 255, zhi = 0;
+    for (int r = lane; r < nrun; r += 64) {
+        const uint32_t v = w[r];
+        nd += v & 31;
+        nf += (v >> 5) & 31;
+        zlo = min(zlo, (int)((v >> 10) & 255));
+        zhi = max(zhi, (int)(v >> 18));
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        nd += __shfl_xor(nd, o), nf += __shfl_xor(nf, o);
+        zlo = min(zlo, __shfl_xor(zlo, o)), zhi = max(zhi, __shfl_xor(zhi, o));
+    }
+    if (lane != 0) return;
+    T.cnt[g] = make_int2(nd, nf);
+    T.znear[g] = zlo;
+    if (zhi > zlo) atomicMax(T.cost + 1, (unsigned long long)(zhi - zlo));
+}
+
+/* plan time: the runs' items to their places in the groups' lists, one wave per
+   group, a lane per run */
+__global__ __launch_bounds__(64) void tree_fill_kernel(TreeDev T, int64_t g0, const uint2 *__restrict__ tmp,
+                                                       const uint32_t *__restrict__ runs)
+{
+    const int lane = threadIdx.x, nrun = tree_nrun(T.Np);
+    const int64_t u0 = blockIdx.x * (int64_t)nrun;
+    const longlong2 at = T.at[g0 + blockIdx.x];
+    int64_t front = at.x, back = at.y;
+    for (int r0 = 0; r0 < nrun; r0 += 64) {
+        const int r = r0 + lane;
+        const uint32_t v = r < nrun ? runs[u0 + r] : 0u;
+        const uint32_t mine = (v & 31) | ((v >> 5) & 31) << 16; /* at most 1024 of either in 64 runs */
+        uint32_t inc = mine;
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t q = __shfl_up(inc, o);
+            if (lane >= o) inc += q;
+        }
+        const uint32_t all = __shfl(inc, 63), before = inc - mine;
+        const uint2 *src = tmp + (u0 + r) * TR_RUN;
+        for (int k = 0; k < (int)(mine & 0xffff); ++k) T.items[front + (before & 0xffff) + k] = src[k];
+        for (int k = 0; k < (int)(mine >> 16); ++k) T.items[back - 1 - (before >> 16) - k] = src[TR_RUN - 1 - k];
+        front += all & 0xffff;
+        back -= all >> 16;
     }
 }
+
+/* plan time, where the lists are not to be had: one list for all groups, every
+   panel direct and per pair */
+__global__ void tree_direct_kernel(TreeDev T, int64_t G)
+{
+    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (i < T.Np) T.items[i] = make_uint2((uint32_t)i, (uint32_t)(KQ_NP + 1) | TR_NEAR);
+    if (i >= G) return;
+    T.at[i] = make_longlong2(0, T.Np);
+    T.cnt[i] = make_int2((int)T.Np, 0);
+    T.znear[i] = 0;
+    T.order[i] = (int32_t)i;
+}
+
 
 /* work of a group in expansions (a direct item costs about three) */
 __device__ __forceinline__ int tree_cost(int2 cnt) { return 3 * cnt.x + cnt.y; }
 
-/* plan time: the groups by falling work, and its sum; one block, a counting sort: blocks start in this order, so the
-   groups next to the curve, with up to five times the work of the others, do
-   not start last */
+/* plan time: the groups by falling work, its sum, and the places of their lists;
+   one block, a counting sort: blocks start in this order, so the groups next to
+   the curve, with up to five times the work of the others, do not start last */
 constexpr int TR_BINS = 1024;
 __global__ __launch_bounds__(1024) void tree_order_kernel(TreeDev T, int64_t G)
 {
     __shared__ int32_t pos[TR_BINS];
+    __shared__ unsigned long long start[1024];
     __shared__ unsigned long long total;
     auto bin = [&](int64_t g) { return TR_BINS - 1 - min(TR_BINS - 1, tree_cost(T.cnt[g])); };
     const int t = threadIdx.x;
@@ -359,6 +432,24 @@ __global__ __launch_bounds__(1024) void tree_order_kernel(TreeDev T, int64_t G)
     pos[t] = before;
     __syncthreads();
     for (int64_t g = t; g < G; g += 1024) T.order[atomicAdd(&pos[bin(g)], 1)] = (int32_t)g;
+    /* places: a thread takes a run of groups */
+    const int64_t per = (G + 1023) / 1024, ga = min(G, t * per), gb = min(G, ga + per);
+    unsigned long long n = 0;
+    for (int64_t g = ga; g < gb; ++g) n += (unsigned long long)(T.cnt[g].x + T.cnt[g].y);
+    unsigned long long inc = n;
+    for (int o = 1; o < 1024; o <<= 1) {
+        start[t] = inc;
+        __syncthreads();
+        if (t >= o) inc += start[t - o];
+        __syncthreads();
+    }
+    if (t == 1023) T.cost[2] = inc;
+    inc -= n;
+    for (int64_t g = ga; g < gb; ++g) {
+        const unsigned long long end = inc + (unsigned long long)(T.cnt[g].x + T.cnt[g].y);
+        T.at[g] = make_longlong2((long long)inc, (long long)end);
+        inc = end;
+    }
 }
 
 /* ------------------------------------------------------------------------ */
@@ -1283,7 +1374,8 @@ __global__ __launch_bounds__(64 * Op::WMAX) void far_tree_kernel(FarArgs A, Tree
     const int32_t k0 = A.nptr[iv], k1 = A.nptr[iv + 1];
     const int NW = W * gridDim.y, wg = w * gridDim.y + blockIdx.y;
     const int2 cnt = T.cnt[g];
-    const uint2 *items = T.items + g * T.Np;
+    const longlong2 at = T.at[g];
+    const uint2 *items = T.items + at.x, *back = T.items + at.y - 1;
     double acc[NF];
 #pragma unroll
     for (int f = 0; f < NF; ++f) acc[f] = 0.0;
@@ -1381,7 +1473,7 @@ __global__ __launch_bounds__(64 * Op::WMAX) void far_tree_kernel(FarArgs A, Tree
                 }
             }
             for (int kb = fb; kb < fe; kb += 64) {
-                const uint2 it = items[T.Np - 1 - min(kb + lane, fe - 1)];
+                const uint2 it = back[-min(kb + lane, fe - 1)];
                 for (uint64_t todo = __ballot(kb + lane < fe && take(it)); todo; todo &= todo - 1) {
                     const int b = __builtin_ctzll(todo);
                     far_item(__builtin_amdgcn_readlane(it.x, b), __builtin_amdgcn_readlane(it.y, b));
@@ -1393,7 +1485,7 @@ __global__ __launch_bounds__(64 * Op::WMAX) void far_tree_kernel(FarArgs A, Tree
                 direct_item(k, __builtin_amdgcn_readfirstlane(it.x), __builtin_amdgcn_readfirstlane(it.y));
             }
             for (int k = fb; k < fe; ++k) {
-                const uint2 it = items[T.Np - 1 - k];
+                const uint2 it = back[-k];
                 far_item(__builtin_amdgcn_readfirstlane(it.x), __builtin_amdgcn_readfirstlane(it.y));
             }
         }

@@ -162,3 +162,54 @@ def test_fmm_at_a_level_that_the_caller_asks_for(alpha):
         for u, v, w in zip(mhlp.eval_layer(P, sigma=_t(mu), mu=_t(mu)), lists, exact):
             assert not torch.equal(u, v) and float((u - v).abs().max()) < 1e-12 * float(v.abs().max())
             assert np.max(np.abs(u.cpu().numpy() - w)) < 1e-11 * np.max(np.abs(w))
+
+
+def test_lists_take_the_memory_of_their_items():
+    """A million targets and 2048 panels at small alpha: the lists hold a few hundred items a group, not an entry a
+    panel (256 MB), and are built in several parts.  The values are those of the same targets in a small plan: each
+    good to about 30 roundings of the sum of absolute values, which for these positive terms is the value."""
+    g = wl.discretize(wl.starfish_curve(), 2048)
+    G = mhlp.Geometry(_t(g.node_soa()))
+    tx, ty = (_t(v) for v in wl.grid_targets(1000, -1.7, 1.7))
+    mhlp.Plan(G, 3.0, tx, ty)  # the runtime's own memory for these launches is in place after it
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    P = mhlp.Plan(G, 3.0, tx, ty)
+    torch.cuda.synchronize()
+    near = P.n_near_pairs * (2 * 16 * 8 + 24)
+    # 96 MB of partial sums and 32 MB of classes of the mixed tiles, 40 MB of targets and their lists' places
+    assert free - torch.cuda.mem_get_info()[0] < near + (256 << 20)
+    u = mhlp.eval_slp(P, _t(np.cos(3 * g.theta) + 1.5))
+    pick = torch.randint(0, tx.numel(), (3000,), device="cuda:0", generator=torch.Generator("cuda:0").manual_seed(1))
+    v = mhlp.eval_slp(mhlp.Plan(G, 3.0, tx[pick].clone(), ty[pick].clone()), _t(np.cos(3 * g.theta) + 1.5))
+    assert float(((u[pick] - v) / v).abs().max()) < 1e-13
+
+
+@pytest.mark.parametrize("stokes", [False, True])
+def test_plan_without_memory_for_its_lists(stokes):
+    """With memory left for what a plan holds but not for building its lists beside it, the plan still comes about,
+    its pairs summed one by one: the values of the plan with lists (for the scalar alpha all its items are pairs, too)
+    to the roundings of 16,384 terms."""
+    g = wl.discretize(wl.starfish_curve(), 1024)
+    G = mhlp.Geometry(_t(g.node_soa()))
+    alpha, rng = (1e-5, 4.0)[stokes], np.random.default_rng(8)
+    tx, ty = _t(rng.uniform(-1.5, 1.5, 300000)), _t(rng.uniform(-1.5, 1.5, 300000))
+    mu = _t(np.stack([np.cos(3 * g.theta) + 1.5, np.sin(g.theta)])) if stokes else _t(np.cos(3 * g.theta) + 1.5)
+    run = mhlp.stokes_eval if stokes else mhlp.eval_slp
+    want = run(mhlp.Plan(G, alpha, tx, ty, stokes=stokes), mu)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    free = torch.cuda.mem_get_info()[0]
+    P = mhlp.Plan(G, alpha, tx, ty, stokes=stokes)
+    torch.cuda.synchronize()
+    holds = free - torch.cuda.mem_get_info()[0]
+    del P
+    # the lists pass through slots of 40 MB
+    rest = torch.empty(torch.cuda.mem_get_info()[0] - holds - (10 << 20), dtype=torch.uint8, device="cuda:0")
+    try:
+        P = mhlp.Plan(G, alpha, tx, ty, stokes=stokes)
+    finally:
+        del rest
+        torch.cuda.empty_cache()
+    got = run(P, mu)
+    assert float((got - want).abs().max()) < 1e-12 * float(want.abs().max())
