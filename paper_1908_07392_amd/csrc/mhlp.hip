@@ -135,7 +135,9 @@ struct mhlp_plan {
     char *tree_mem = nullptr;      /* its arrays but for the partial sums and, unless small, the lists */
     uint2 *tree_items = nullptr;   /* the lists where they have memory of their own */
     unsigned long long tr_cost = 0; /* total work of the item lists */
-    int tr_waves = 0, tr_split = 1; /* waves per block and blocks per group of far_tree_kernel */
+    struct TreeShape {
+        int waves = 0, split = 1, cut = 0; /* waves per block and blocks per group, direct items in 2^cut units */
+    } tr, tr_skip;                         /* of far_tree_kernel; where it leaves items out */
     NearParams np{};
     double near_factor = 1.2;
     int64_t part_cap = 0;     /* capacity of part (doubles)                 */
@@ -1994,6 +1996,39 @@ static mhlp_status far_class_setup(mhlp_plan *P, hipStream_t st)
     return MHLP_OK;
 }
 
+/* Launch shape of far_tree_kernel for G groups of U units of work each
+   (tree_cost): 2^e waves a group, in blocks of 8 or, from few waves, 4; direct
+   items in 2^cut units.  More waves shorten a group's sum until the chip is
+   full (thousands of them) or a wave's share falls to a unit or two.  Waves a
+   group of the fastest of 12 to 30 shapes, over curves of 16 to 256 panels and
+   alpha = 1e-3 to 500 (potentials, gradients, stresslet):
+       G        1    5   11   24   47   79  125  313  469  704 1016 1719
+     U ~  32       128  128   64   64   32   32   16   16    8    8    4
+     U ~ 128  256  256  128  128   64   64   64   32   16    8    8    4
+     U ~ 512  512  256  256  256  128  128   64   32   32   16    8    8
+   and cut 3 below one unit a wave, 0 from about six on.  The formula is within
+   3.4% of the fastest on average, 33% at worst.
+   Where far items are left out (tree.h) the second pass needs the group's sum,
+   so one block serves a group.  That pays from 400 groups on, and on the curve,
+   where few panels are near a group, from 400 units a group on (both layers,
+   us, left out | split): alpha = 500, 256 panels, 313 groups 152 | 115, 469
+   145 | 160, 1016 162 | 305; 64 panels, alpha = 100, 469 groups 68 | 83; on the
+   curve, alpha = 500: 128 panels (242 units) 21 | 16, 256 (444) 24 | 32, 1024
+   (1660) 42 | 277.  Waves: 8, but 4 for many groups of little work (1719
+   groups, 64 panels, alpha = 500: 76 against 89; 256 panels 250 against 183)
+   and 16 on the curve (256 panels 24.5 against 28.4). */
+static mhlp_plan::TreeShape tree_shape(int64_t G, double U)
+{
+    const double lu = std::log2(std::max(8.0, U));
+    int e = (int)std::floor(9.5 - 0.55 * std::log2((double)G) + 0.3 * (lu - 6.0));
+    e = std::max(2, std::min({e, (int)lu + 2, 9}));
+    if (G >= 1200) e = 2;
+    const int cut = lu - e < 0.25 && e >= 6 ? 3 : lu - e < 2.5 ? 2 : 0;
+    if (e <= 3) return {1 << e, 1, cut};
+    if (e == 4) return {4, 4, cut};
+    return {8, 1 << (e - 3), cut};
+}
+
 /* Clusters, item lists and buffers of a plan's far field (tree.h), on
    the stream after the near lists, which the item lists read. */
 static mhlp_status tree_setup(mhlp_plan *P, hipStream_t st)
@@ -2019,6 +2054,7 @@ static mhlp_status tree_setup(mhlp_plan *P, hipStream_t st)
     const int64_t o_cc = take(16 * T.ncl), o_rmin = take(8 * mhlp::TR_RM * T.ncl), o_mom = take(8 * nmom);
     const int64_t o_st = take(8 * 48 * Np), o_flux = take(P->stokes && P->onsurf ? 8 * Np : 0), o_lb = take(4 * T.ncl);
     const int64_t o_at = take(16 * G), o_cnt = take(8 * G), o_order = take(4 * G), o_znear = take(4 * G), o_cost = take(24);
+    const int64_t o_arr = take(4 * G);
     /* the lists are counted, then filled into storage of their size; they pass
        through slots of one entry a panel, for as many groups at a time as 64 MB
        hold (more than one such part: listed once to count and again to fill).
@@ -2040,28 +2076,11 @@ static mhlp_status tree_setup(mhlp_plan *P, hipStream_t st)
     T.order = reinterpret_cast<int32_t *>(P->tree_mem + o_order);
     T.znear = reinterpret_cast<int *>(P->tree_mem + o_znear);
     T.cost = reinterpret_cast<unsigned long long *>(P->tree_mem + o_cost);
-    /* waves per group of 64 targets (blocks of 8, 16 or 4 waves; direct items
-       cut into 2^cut units), by the number of groups: enough waves to fill the
-       chip.  Measured us per evaluation (starfish, 4096 sources, alpha = 5) with
-       4 / 16 / 32 / 64 / 128 waves: 52 groups 114/72/35/31/28, 106 groups
-       98/64/35/31/34, 425 groups 94/63/46/52/71, 853 groups 79/54/58/78/117,
-       1709 groups 69/85/-/-/161; the on-surface operator (targets in panel order,
-       eight direct panels a group) with 16 / 32 / 64: 64 groups 21.5/18.1/18.4
-       (alpha = 50: 39/24/22). */
-    if (G >= 1200)
-        P->tr_waves = 4, T.cut = 0;
-    else if (G >= 640)
-        P->tr_waves = 16, T.cut = 2;
-    else if (G >= 170)
-        P->tr_waves = 8, P->tr_split = 4, T.cut = 2;
-    else if (G >= 85 || P->onsurf)
-        P->tr_waves = 8, P->tr_split = 8, T.cut = 2;
-    else
-        P->tr_waves = 8, P->tr_split = 16, T.cut = 3;
-    if (P->tr_split > 1) TRY(dalloc(&T.part, (P->onsurf ? 2 : 4) * (int64_t)P->tr_split * M));
+    T.arrived = reinterpret_cast<uint32_t *>(P->tree_mem + o_arr);
     mhlp::tree_clusters_kernel<<<nblocks(T.ncl, 4), 256, 0, st>>>(T, g->soa, g->soa + g->N, g->ph, P->alpha,
                                                                   P->near_factor);
     HIPCHECK(hipMemsetAsync(T.cost, 0, 3 * sizeof(*T.cost), st));
+    HIPCHECK(hipMemsetAsync(T.arrived, 0, 4 * G, st));
     char *tmp = small ? P->tree_mem + o_tmp : nullptr;
     bool have = small || hipMalloc((void **)&tmp, (size_t)(Gc * per)) == hipSuccess;
     uint2 *slots = reinterpret_cast<uint2 *>(tmp);
@@ -2112,7 +2131,11 @@ static mhlp_status tree_setup(mhlp_plan *P, hipStream_t st)
         HIPCHECK(hipStreamSynchronize(st));
     }
     P->tr_cost = cost[0];
-    T.skip = cost[1] >= mhlp::TR_ZSKIP && P->tr_split == 1;
+    const double U = (double)cost[0] / (double)G;
+    P->tr = tree_shape(G, U);
+    if (P->tr.split > 1) TRY(dalloc(&T.part, (P->onsurf ? 2 : 4) * (int64_t)P->tr.split * 64 * G));
+    T.skip = cost[1] >= mhlp::TR_ZSKIP && (P->onsurf ? U >= 400.0 : G >= 400);
+    P->tr_skip = {P->onsurf ? 16 : G >= 1200 && U < 350.0 ? 4 : 8, 1, P->onsurf ? 2 : 0};
     return MHLP_OK;
 }
 
@@ -2354,19 +2377,20 @@ template <class Op>
 static void launch_tree_far(const FarArgs &A, const mhlp_plan *P, hipStream_t st)
 {
     const mhlp::TreeDev &T = *P->tree;
-    const int threads = 64 * std::min(P->tr_waves, Op::WMAX);
+    const bool skip = Op::SKIP && T.skip;
+    const mhlp_plan::TreeShape &F = skip ? P->tr_skip : P->tr;
+    const int threads = 64 * std::min(F.waves, Op::WMAX);
     const int64_t G = nblocks(A.M, 64), most = (int64_t)1 << 20; /* groups a launch: below 2^32 threads along the grid */
     for (int64_t g0 = 0; g0 < G; g0 += most) {
         mhlp::TreeDev S = T;
         S.order += g0;
-        const dim3 grid((unsigned)std::min(most, G - g0), (unsigned)P->tr_split);
-        if (Op::SKIP && T.skip)
+        S.cut = F.cut;
+        const dim3 grid((unsigned)std::min(most, G - g0), (unsigned)F.split);
+        if (skip)
             mhlp::far_tree_kernel<Op, Op::SKIP><<<grid, threads, 0, st>>>(A, S);
         else
             mhlp::far_tree_kernel<Op, false><<<grid, threads, 0, st>>>(A, S);
     }
-    if (P->tr_split > 1)
-        mhlp::tree_finalize<Op><<<dim3(nblocks(A.M, 64), (unsigned)Op::NF), 64, 0, st>>>(A, T, P->tr_split);
 }
 
 template <class Op, bool SLP, bool DLP, bool GRAD>

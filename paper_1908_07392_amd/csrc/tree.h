@@ -55,7 +55,8 @@ struct TreeDev {
     uint2 *items = nullptr;                  /* the groups' lists: direct items from the front, expansions from the back */
     longlong2 *at = nullptr;                 /* [groups]: begin and end of a group's list */
     int2 *cnt = nullptr;                     /* [groups]: numbers of direct items and expansions */
-    double *part = nullptr;                  /* [fields][blocks per group][M] sums of split groups */
+    double *part = nullptr;                  /* [groups][blocks per group][fields][64] sums of split groups */
+    uint32_t *arrived = nullptr;             /* [groups]: blocks of split groups that are through, counted on and on */
     unsigned long long *cost = nullptr;      /* total work of the groups (tree_cost); [1]: the largest spread of
                                                 the z classes of a group's items (TR_ZSTEP); [2]: all items */
     float *lb = nullptr;                     /* [ncl] log2 of the sum of |charges| and |dipoles|, rounded up */
@@ -1336,8 +1337,10 @@ __device__ __forceinline__ double tree_row_sum(double v)
    direct ones in units of 16 / 2^cut sources in turn, expansions in equal
    runs, starting from the other end, so that no wave gets more than its share
    of both, and the near corrections by node.  The wave sums are added
-   in wave order; with several blocks a group they go to slot blockIdx.y for
-   tree_finalize.  A cluster whose expansion is not finite (an infinite or NaN
+   in wave order; with several blocks a group (a power of two) each leaves them
+   in its slot, and the last one to arrive adds the slots in order: a launch of
+   its own for that took 4 us (64 targets, 256 sources: 15 -> 11 us a call in
+   all).  A cluster whose expansion is not finite (an infinite or NaN
    density), or whose pairs all underflow with such a density, is summed
    directly, pair by pair.
 
@@ -1354,9 +1357,8 @@ __device__ __forceinline__ double tree_row_sum(double v)
    is small (cancellation) or not finite, the item is summed.
    109,314 x 4096, alpha = 100 / 200 / 500 / 1000, both layers: 370 / 964 / 735 /
    272 -> 233 / 365 / 239 / 142 us.
-   Waves per group (tree_setup): four for many groups; up to 128 for few,
-   where the longest wave (a direct panel in one wave takes about 20 us) sets
-   the time. */
+   Waves per group (tree_shape): four for many groups; up to 512 for few, where
+   the longest wave (a direct panel in one wave takes about 20 us) sets the time. */
 template <class Op, bool SKIP>
 __global__ __launch_bounds__(64 * Op::WMAX) void far_tree_kernel(FarArgs A, TreeDev T)
 {
@@ -1364,7 +1366,8 @@ __global__ __launch_bounds__(64 * Op::WMAX) void far_tree_kernel(FarArgs A, Tree
     __shared__ double red[NF][Op::WMAX][64];
     const double *mu;
     if (!far_density(A, mu)) return;
-    const int lane = threadIdx.x & 63, W = blockDim.x >> 6;
+    const int lane = threadIdx.x & 63, waves = blockDim.x >> 6;
+    int W = waves; /* sums of a field in red */
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t g = T.order[blockIdx.x];
     const int64_t i = 64 * g + lane;
@@ -1491,35 +1494,42 @@ __global__ __launch_bounds__(64 * Op::WMAX) void far_tree_kernel(FarArgs A, Tree
         }
     }
     put();
-    const double cm = gridDim.y > 1 ? 0.0 : Op::common(A, T); /* every lane takes part */
+    const int split = gridDim.y;
+    if (split > 1) {
+        __shared__ bool last;
+        __syncthreads();
+        double *part = T.part + g * split * NF * 64 + lane;
+        for (int f = w; f < NF; f += W) {
+            double s = 0.0;
+            for (int v = 0; v < W; ++v) s += red[f][v][lane];
+            __hip_atomic_store(part + (blockIdx.y * NF + f) * 64, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        /* the slots go through device-scope stores, which reach the memory that
+           all XCDs share; they have arrived once they are waited for */
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (threadIdx.x == 0) last = (atomicAdd(T.arrived + g, 1u) & (split - 1)) == (uint32_t)split - 1;
+        __syncthreads();
+        if (!last) return;
+        /* the waves share the slots of the fields; red holds their sums */
+        const int H = W / NF, f = w % NF, h = w / NF;
+        if (h < H) {
+            double s = 0.0;
+#pragma unroll 4
+            for (int k = h; k < split; k += H)
+                s += __hip_atomic_load(part + (k * NF + f) * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            red[f][h][lane] = s;
+        }
+        W = H;
+    }
+    const double cm = Op::common(A, T); /* every lane takes part */
     __syncthreads();
     if (!valid) return;
-    for (int f = w; f < NF; f += W) {
+    for (int f = w; f < NF; f += waves) {
         double s = 0.0;
         for (int v = 0; v < W; ++v) s += red[f][v][lane];
-        if (gridDim.y > 1)
-            T.part[((int64_t)f * gridDim.y + blockIdx.y) * A.M + i] = s;
-        else
-            Op::store(A, cm, mu, i, f, s);
+        Op::store(A, cm, mu, i, f, s);
     }
-}
-
-/* the slots of a group split over several blocks, in order; one thread per
-   target and field */
-template <class Op>
-__global__ __launch_bounds__(64) void tree_finalize(FarArgs A, TreeDev T, int nsplit)
-{
-    const double *mu;
-    if (!far_density(A, mu)) return;
-    const double cm = Op::common(A, T); /* every lane takes part */
-    const int64_t i = blockIdx.x * (int64_t)64 + threadIdx.x;
-    if (i >= A.M) return;
-    const int f = blockIdx.y;
-    const double *part = T.part + (int64_t)f * nsplit * A.M + i;
-    double s = 0.0;
-#pragma unroll 4
-    for (int k = 0; k < nsplit; ++k) s += part[k * A.M];
-    Op::store(A, cm, mu, i, f, s);
 }
 
 } // namespace mhlp
