@@ -38,6 +38,7 @@
 #include <map>
 #include <mutex>
 #include <numeric>
+#include <type_traits>
 
 #include "mhlp.h"
 #include "nearfield.h"
@@ -2052,6 +2053,7 @@ static mhlp_status tree_setup(mhlp_plan *P, hipStream_t st)
     };
     const int64_t nmom = T.ncl * mhlp::tr_stride(P->stokes ? (P->onsurf ? 6 : 10) : (P->onsurf ? 4 : 8));
     const int64_t o_cc = take(16 * T.ncl), o_rmin = take(8 * mhlp::TR_RM * T.ncl), o_mom = take(8 * nmom);
+    const int64_t o_small = take(P->stokes ? 8 * T.ncl * mhlp::tr_stride(P->onsurf ? 4 : 8) : 0);
     const int64_t o_st = take(8 * 48 * Np), o_flux = take(P->stokes && P->onsurf ? 8 * Np : 0), o_lb = take(4 * T.ncl);
     const int64_t o_at = take(16 * G), o_cnt = take(8 * G), o_order = take(4 * G), o_znear = take(4 * G), o_cost = take(24);
     const int64_t o_arr = take(4 * G);
@@ -2131,6 +2133,7 @@ static mhlp_status tree_setup(mhlp_plan *P, hipStream_t st)
         HIPCHECK(hipStreamSynchronize(st));
     }
     P->tr_cost = cost[0];
+    if (P->stokes && cost[1] > 0) T.small = reinterpret_cast<double *>(P->tree_mem + o_small);
     const double U = (double)cost[0] / (double)G;
     P->tr = tree_shape(G, U);
     if (P->tr.split > 1) TRY(dalloc(&T.part, (P->onsurf ? 2 : 4) * (int64_t)P->tr.split * 64 * G));
@@ -2405,8 +2408,13 @@ template <bool GRAD>
 static void launch_tree_stokes(const FarArgs &A, const mhlp_plan *P, hipStream_t st)
 {
     const mhlp::TreeDev &T = *P->tree;
-    mhlp::tree_stokes_kernel<GRAD><<<moments_grid(A, T), 256, 0, st>>>(A, T);
-    launch_tree_far<mhlp::TreeStokes<GRAD>>(A, P, st);
+    dim3 grid = moments_grid(A, T);
+    if (T.small) grid.z *= 2; /* the rows of the powers, too */
+    mhlp::tree_stokes_kernel<GRAD><<<grid, 256, 0, st>>>(A, T);
+    if (T.small)
+        launch_tree_far<mhlp::TreeStokes<GRAD, true>>(A, P, st);
+    else
+        launch_tree_far<mhlp::TreeStokes<GRAD, false>>(A, P, st);
 }
 
 template <bool SLP, bool DLP>

@@ -51,6 +51,8 @@ struct TreeDev {
                                                 (k < TR_NP; INFINITY: never); last: from which every pair underflows */
     double *mom = nullptr;                   /* [ncl][tr_stride]: rows of the coefficients of K_n cos n theta
                                                 and K_n sin n theta per field (stresslet: then of r^-n) */
+    double *small = nullptr;                 /* stresslet lists with TR_SMALL items: rows of their powers' coefficients,
+                                                [ncl][tr_stride(4 or, for gradients, 8)] */
     double *st = nullptr;                    /* staged sources [Np][3][16]: w sigma, alpha w mu n_x, alpha w mu n_y */
     uint2 *items = nullptr;                  /* the groups' lists: direct items from the front, expansions from the back */
     longlong2 *at = nullptr;                 /* [groups]: begin and end of a group's list */
@@ -58,7 +60,8 @@ struct TreeDev {
     double *part = nullptr;                  /* [groups][blocks per group][fields][64] sums of split groups */
     uint32_t *arrived = nullptr;             /* [groups]: blocks of split groups that are through, counted on and on */
     unsigned long long *cost = nullptr;      /* total work of the groups (tree_cost); [1]: the largest spread of
-                                                the z classes of a group's items (TR_ZSTEP); [2]: all items */
+                                                the z classes of a group's items (TR_ZSTEP), of a stresslet plan whether
+                                                it has TR_SMALL items; [2]: all items */
     float *lb = nullptr;                     /* [ncl] log2 of the sum of |charges| and |dipoles|, rounded up */
     int *znear = nullptr;                    /* [groups] smallest z class of the items */
     int skip = 0;                            /* far items are held against the near ones' sum (far_tree_kernel) */
@@ -69,6 +72,7 @@ struct TreeDev {
 constexpr uint32_t TR_NEAR = 1u << 16; /* direct: some target of the wave lists the panel */
 constexpr uint32_t TR_ZERO = 1u << 17; /* every pair underflows to zero: only non-finite densities matter */
 constexpr uint32_t TR_LAP = 1u << 18;  /* stresslet: the K part of every pair is below rounding */
+constexpr uint32_t TR_SMALL = 1u << 19; /* stresslet: some pair has z < TR_SZ, singular parts with the powers */
 /* bits 24-31: the z class, z >= TR_ZSTEP times it for every pair of the item */
 constexpr double TR_ZSTEP = 4.0;
 constexpr int TR_ZNEAR = 3;            /* classes from a group's smallest one that are always summed */
@@ -83,10 +87,13 @@ __host__ __device__ inline uint32_t tree_zclass(double z) { return z > 0.0 ? (ui
      2 pi U = conj(sigma) [8/(alpha^2 conj(x - y)^3) - alpha O_3] + sigma alpha O_{-1} + tau/conj(x - y):
    derivatives of K0 and of log r, each of which has its expansion about the
    cluster's centre (Graf's theorem; powers of 1/conj(x - c)).  The two parts
-   in brackets cancel like z^2/8 for small z, so a cluster is expanded only
-   from alpha (r - R) >= TR_SZ on; from TR_SLAP on the K part is below
-   rounding against the other's 1/r and left out (K_3(42) = 1e-19), for
-   clusters of any alpha R.  Order: the terms of the bracket differ by the
+   in brackets cancel like z^2/8 for small z.  Below alpha (r - R) = TR_SZ the
+   singular part S_n = (n-1)!/2 (2/z)^n of every K_n, n >= 1, therefore goes with
+   the powers: K_n - S_n falls by z^2 against K_n, follows K_n's recurrence
+   stably (K_{n+1} - S_{n+1} = K_{n-1} + 2n/z (K_n - S_n)), and the powers'
+   coefficients with it are formed without the cancelling parts (TreeSmall).
+   From TR_SLAP on the K part is below rounding against the other's 1/r and left
+   out (K_3(42) = 1e-19), for clusters of any alpha R.  Order: the terms of the bracket differ by the
    factor z^2/(4 n) once n > z^2/4, so the neglected terms are below
    n t^{n-3}/r in every regime (t = R/r). */
 constexpr double TR_SZ = 2.0, TR_SLAP = 42.0, TR_SAMAX = 1e7;
@@ -277,18 +284,19 @@ __global__ __launch_bounds__(256) void tree_lists_kernel(TreeDev T, const double
             const double rhi = (double)wave_max_f((float)r) * (1.0 + 3e-7);
             const double *rm = T.rmin + TR_RM * c;
             uint32_t y_ = 0xffffffffu;
-            bool expand = true, lap = false;
+            bool expand = true, lap = false, small = false;
             if (T.stokes) {
                 const double R = rm[TR_RM - 1], a = alpha * R, zc = alpha * (rlo - R);
                 lap = zc >= TR_SLAP;
-                expand = a >= TR_AMIN && (lap ? a <= TR_SAMAX : a <= TR_AMAX && zc >= TR_SZ);
+                small = zc < TR_SZ;
+                expand = a >= TR_AMIN && a <= (lap ? TR_SAMAX : TR_AMAX);
             }
             if (!T.stokes && rlo >= rm[TR_RM - 1]) {
                 y_ = TR_ZERO;
             } else if (expand) {
                 for (int q = TR_NP - 1 - T.stokes; /* the stresslet has one order fewer */ q >= 0 && rlo >= rm[q]; --q) /* rm falls with the order */
                     y_ = (uint32_t)(TR_PMIN + TR_PSTEP * q) << 8;
-                if (y_ != 0xffffffffu) y_ |= (uint32_t)tree_piece(alpha * rlo, alpha * rhi) | (lap ? TR_LAP : 0u);
+                if (y_ != 0xffffffffu) y_ |= (uint32_t)tree_piece(alpha * rlo, alpha * rhi) | (lap ? TR_LAP : small ? TR_SMALL : 0u);
             }
             if (y_ != 0xffffffffu) {
                 if (!T.stokes && y_ != TR_ZERO) {
@@ -297,6 +305,8 @@ __global__ __launch_bounds__(256) void tree_lists_kernel(TreeDev T, const double
                     zlo = min(zlo, (int)(zc >> 24));
                     zhi = max(zhi, (int)(zc >> 24));
                     y_ |= zc;
+                } else if (T.stokes && small) {
+                    zlo = 0, zhi = 1; /* no z classes here: the plan has such items */
                 }
                 if (lane == 0) items[TR_RUN - 1 - nf] = make_uint2((uint32_t)c, y_);
                 ++nf;
@@ -318,8 +328,10 @@ __global__ __launch_bounds__(256) void tree_lists_kernel(TreeDev T, const double
                 const double dlo = (double)wave_min_f(listed ? INFINITY : (float)sqrt(r2lo)) * (1.0 - 3e-7);
                 const double dhi = (double)wave_max_f(listed ? -INFINITY : (float)sqrt(r2hi)) * (1.0 + 3e-7);
                 const uint32_t zc = tree_zclass(alpha * dlo * (1.0 - 1e-12));
-                zlo = min(zlo, (int)(zc >> 24));
-                zhi = max(zhi, (int)(zc >> 24));
+                if (!T.stokes) {
+                    zlo = min(zlo, (int)(zc >> 24));
+                    zhi = max(zhi, (int)(zc >> 24));
+                }
                 if (lane == 0)
                     items[nd] = make_uint2((uint32_t)c, (uint32_t)tree_piece(alpha * dlo, alpha * dhi) |
                                                             (any ? TR_NEAR : 0u) | zc);
@@ -344,7 +356,7 @@ __global__ __launch_bounds__(64) void tree_count_kernel(TreeDev T, int64_t g0, c
         nd += v & 31;
         nf += (v >> 5) & 31;
         zlo = min(zlo, (int)((v >> 10) & 255));
-        zhi = max(zhi, (int)(v >> 18));
+        zhi = max(zhi, (int)((v >> 18) & 255));
     }
     for (int o = 32; o > 0; o >>= 1) {
         nd += __shfl_xor(nd, o), nf += __shfl_xor(nf, o);
@@ -501,6 +513,31 @@ __device__ __forceinline__ void tree_regular(double wr, double wi, double q, dou
     }
     bi[CNT - 1] = pi * br[CNT - 1];
     br[CNT - 1] *= pr;
+}
+
+/* S_n and S_n - 1 of B_n = w^n/n! S_n, n = N0 .. N0 + CNT - 1, as tree_regular
+   forms S_n; all terms positive */
+template <int N0, int CNT>
+__device__ __forceinline__ void tree_regular_series(double q, double (&s)[CNT], double (&d)[CNT])
+{
+    constexpr int top = N0 + CNT - 1;
+    double u1 = 1.0, u0 = 1.0;
+#pragma unroll
+    for (int k = 10; k >= 2; --k) {
+        u1 = fma(q * (1.0 / ((double)k * (top + 1 + k))), u1, 1.0);
+        u0 = fma(q * (1.0 / ((double)k * (top + k))), u0, 1.0);
+    }
+    double s1 = fma(q * (1.0 / (top + 2)), u1, 1.0); /* S_{top+1} */
+    double d0 = q * (1.0 / (top + 1)) * u0;
+#pragma unroll
+    for (int n = top; n >= N0; --n) {
+        d[n - N0] = d0;
+        s[n - N0] = 1.0 + d0;
+        if (n > 0) {
+            d0 = fma(q * (1.0 / ((double)n * (n + 1))), s1, d0);
+            s1 = s[n - N0];
+        }
+    }
 }
 
 /* B_n is kept for n = N0 - H .. N0 + TR_NG - 1 + H: the potential of a dipole
@@ -737,18 +774,104 @@ struct TreeS {
     }
 };
 
-template <bool GRAD, int Z, int R>
-__device__ __forceinline__ void tree_stokes_rounds(const TreeDev &T, int k, int64_t p0, const TreeS<GRAD, Z> &b,
+/* The powers' rows of TR_SMALL items: 4 values (8 with GRAD: the x and y
+   derivatives) in the K part's layout, of
+     l~_k = l_k + (k-1)!/2 c_k  at (2/z)^k e^{i k theta},
+     (k-1)!/2 c_{-k}            at (2/z)^k e^{-i k theta}   (k >= 1)
+   with c and l as in TreeS.  The parts of l_k and c_k that cancel leave S_n - 1
+   of the regular functions B_n = w^n/n! S_n; all factorials are ratios of near
+   ones. */
+template <bool GRAD, int Z>
+struct TreeSmall {
+    static constexpr int H = GRAD ? 4 : 3, N0 = Z * TR_NG, LO = N0 < H ? 0 : N0 - H, CNT = N0 + TR_NG + H - LO;
+    double s[CNT], d[CNT], pr[CNT], pi[CNT]; /* S_n, S_n - 1 and w^n */
+    cplx sg;                                 /* alpha sigma */
+    double tau, alpha;
+    template <int N>
+    __device__ __forceinline__ cplx w() const
+    {
+        return mk(pr[N - LO], pi[N - LO]);
+    }
+    /* w^N S_N / D */
+    template <int N>
+    __device__ __forceinline__ cplx ws(double D) const
+    {
+        return (s[N - LO] * (1.0 / D)) * w<N>();
+    }
+    /* l~_K */
+    template <int K>
+    __device__ __forceinline__ cplx l() const
+    {
+        if constexpr (K < 1) return mk(0.0, 0.0);
+        else {
+            cplx v = (0.5 * alpha * tau) * w<K - 1>() + 0.5 * (sg * ws<K + 1>((double)K * (K + 1)));
+            if constexpr (K >= 3) v = v - (0.5 * (K - 1) * (K - 2) * d[K - 3 - LO]) * (conj(sg) * w<K - 3>());
+            else v = v - 0.5 * conj(sg * ws<3 - K>(K == 1 ? 2.0 : 1.0));
+            return v;
+        }
+    }
+    /* (K-1)!/2 c_{-K} */
+    template <int K>
+    __device__ __forceinline__ cplx m() const
+    {
+        return 0.5 * (sg * conj(ws<K - 1>(1.0))) - 0.5 * conj(sg * ws<K + 3>((double)K * (K + 1) * (K + 2) * (K + 3)));
+    }
+    /* c_0 / 2 */
+    __device__ __forceinline__ cplx c0() const { return 0.5 * (sg * ws<1>(1.0)) - 0.5 * conj(sg * ws<3>(6.0)); }
+    template <int N>
+    __device__ __forceinline__ void row(double (*v)[16 * TR_PAD], int at) const
+    {
+        if constexpr (N == 0) {
+            for (int k = 0; k < (GRAD ? 8 : 4); ++k) v[k][at] = 0.0;
+        } else if constexpr (!GRAD) {
+            TreeS<false, Z>::template put<N>(l<N>(), m<N>(), v, at);
+        } else {
+            /* d_x: -(alpha/2)(C_{k-1} + C_{k+1}), d_y: (i alpha/2)(C_{k-1} - C_{k+1}), each times (N-1)!/2, with
+               (N-1) l_{N-1} in the upper ones */
+            const double ah = 0.5 * alpha;
+            cplx up, uq, lp, lq; /* of e^{i N theta}: neighbours N - 1 and N + 1; of e^{-i N theta}: -N - 1 and 1 - N */
+            if constexpr (N == 1) {
+                up = c0();
+                uq = 0.5 * (sg * ws<3>(6.0)) - 0.5 * conj(sg * ws<1>(1.0));
+                lq = up;
+            } else {
+                up = (double)(N - 1) * l<N - 1>();
+                uq = 0.5 * (sg * ws<N + 2>((double)N * (N + 1) * (N + 2))) -
+                     (0.5 * (N - 1)) * (conj(sg) * ws<N - 2>(1.0));
+                lq = (0.5 * (N - 1)) * (sg * conj(ws<N - 2>(1.0))) -
+                     0.5 * conj(sg * ws<N + 2>((double)N * (N + 1) * (N + 2)));
+            }
+            lp = 0.5 * (sg * conj(ws<N>((double)N))) -
+                 0.5 * conj(sg * ws<N + 4>((double)N * (N + 1) * (N + 2) * (N + 3) * (N + 4)));
+            TreeS<true, Z>::template put<N>(-ah * (up + uq), -ah * (lp + lq), v, at);
+            const cplx yp = ah * (up - uq), ym = ah * (lp - lq);
+            TreeS<true, Z>::template put<N>(mk(-yp.im, yp.re), mk(-ym.im, ym.re), v + 4, at);
+        }
+    }
+};
+
+/* sums of the rows of B (NV values each, RO rows a round) over the sources of each
+   cluster, into mom.  Bound by the latency of its rounds: two rows a round took
+   9.0 us at 64 panels, four 8.3 (GRAD: two instead of one) */
+template <int NV, int RO, int Z, int R, class B>
+__device__ __forceinline__ void tree_stokes_rounds(const TreeDev &T, double *mom, int k, int64_t p0, const B &b,
                                                    double (*buf)[16 * TR_PAD])
 {
-    constexpr int NV = GRAD ? 10 : 6, RO = GRAD ? 1 : 2, N = Z * TR_NG + R;
+    constexpr int N = Z * TR_NG + R;
     if constexpr (R < TR_NG && N < TR_ROWS) {
         const int t = threadIdx.x, at = (t >> 4) * TR_PAD + (t & 15), pp = t & 15, cb = t >> 4;
         b.template row<N>(buf, at);
-        if constexpr (RO > 1) b.template row<N + 1>(buf + NV, at);
+        b.template row<N + 1>(buf + NV, at);
+        if constexpr (RO > 2) {
+            b.template row<N + 2>(buf + 2 * NV, at);
+            b.template row<N + 3>(buf + 3 * NV, at);
+        }
         __syncthreads();
-        if (cb < RO * NV) {
-            const double *row = buf[cb] + pp * TR_PAD;
+#pragma unroll
+        for (int c0 = 0; c0 < RO * NV; c0 += 16) {
+            const int c = c0 + cb;
+            if (c >= RO * NV) continue;
+            const double *row = buf[c] + pp * TR_PAD;
             double s0 = 0.0, s1 = 0.0;
 #pragma unroll
             for (int l = 0; l < 16; l += 2) {
@@ -757,17 +880,17 @@ __device__ __forceinline__ void tree_stokes_rounds(const TreeDev &T, int k, int6
             }
             double s = s0 + s1;
             for (int o = 1; o < (1 << k); o <<= 1) s += __shfl_xor(s, o);
-            const int n = N + cb / NV;
+            const int n = N + c / NV;
             const int64_t p = p0 + pp;
             if ((pp & ((1 << k) - 1)) == 0 && p < T.Np && n < TR_ROWS)
-                T.mom[(T.off[k] + (p >> k)) * tr_stride(NV) + n * NV + cb % NV] = s;
+                mom[(T.off[k] + (p >> k)) * tr_stride(NV) + n * NV + c % NV] = s;
         }
         __syncthreads();
-        tree_stokes_rounds<GRAD, Z, R + RO>(T, k, p0, b, buf);
+        tree_stokes_rounds<NV, RO, Z, R + RO>(T, mom, k, p0, b, buf);
     }
 }
 
-template <bool GRAD, int Z>
+template <bool GRAD, int Z, bool SMALL>
 __device__ __forceinline__ void tree_stokes_body(const FarArgs &A, const TreeDev &T, const double *mu,
                                                  double (*buf)[16 * TR_PAD])
 {
@@ -779,11 +902,11 @@ __device__ __forceinline__ void tree_stokes_body(const FarArgs &A, const TreeDev
     const double dx = A.sx[js] - T.cc[2 * c], dy = A.sy[js] - T.cc[2 * c + 1];
     const double wj = have ? A.sw[js] : 0.0, nx = A.snx[js], ny = A.sny[js];
     const double m1 = have ? wj * mu[js] : 0.0, m2 = have ? wj * mu[A.N + js] : 0.0;
-    TreeS<GRAD, Z> b;
+    typename std::conditional<SMALL, TreeSmall<GRAD, Z>, TreeS<GRAD, Z>>::type b;
     b.alpha = A.alpha;
     b.tau = fma(m1, nx, m2 * ny);
     b.sg = (0.5 * A.alpha) * (mk(m1, m2) * mk(nx, ny));
-    if (Z == 0 && k == 0) {
+    if (Z == 0 && k == 0 && !SMALL) {
         if (have) {
             double *s = T.st + (j >> 4) * 48 + (j & 15);
             s[0] = m1;
@@ -795,8 +918,11 @@ __device__ __forceinline__ void tree_stokes_body(const FarArgs &A, const TreeDev
             if ((t & 15) == 0 && have) T.flux[j >> 4] = f;
         }
     }
-    const double ah = 0.5 * A.alpha, wr = ah * dx, wi = -ah * dy;
-    tree_regular<TreeS<GRAD, Z>::LO, TreeS<GRAD, Z>::CNT>(wr, wi, fma(wr, wr, wi * wi), b.br, b.bi);
+    const double ah = 0.5 * A.alpha, wr = ah * dx, wi = -ah * dy, q2 = fma(wr, wr, wi * wi);
+    if constexpr (SMALL)
+        tree_regular_series<TreeS<GRAD, Z>::LO, TreeS<GRAD, Z>::CNT>(q2, b.s, b.d);
+    else
+        tree_regular<TreeS<GRAD, Z>::LO, TreeS<GRAD, Z>::CNT>(wr, wi, q2, b.br, b.bi);
     double pr = 1.0, pi = 0.0;
 #pragma unroll
     for (int n = 0; n < TreeS<GRAD, Z>::LO + TreeS<GRAD, Z>::CNT; ++n) {
@@ -808,19 +934,22 @@ __device__ __forceinline__ void tree_stokes_body(const FarArgs &A, const TreeDev
         pi = fma(pr, wi, pi * wr);
         pr = q;
     }
-    tree_stokes_rounds<GRAD, Z, 0>(T, k, p0, b, buf);
+    tree_stokes_rounds<SMALL ? (GRAD ? 8 : 4) : (GRAD ? 10 : 6), GRAD ? 2 : 4, Z, 0>(T, SMALL ? T.small : T.mom, k, p0, b, buf);
 }
 
 template <bool GRAD>
 __global__ __launch_bounds__(256) void tree_stokes_kernel(FarArgs A, TreeDev T)
 {
-    __shared__ double buf[12][16 * TR_PAD];
+    __shared__ double buf[24][16 * TR_PAD];
     const double *mu;
     if (!far_density(A, mu)) return;
-    switch (blockIdx.z) {
-    case 0: tree_stokes_body<GRAD, 0>(A, T, mu, buf); break;
-    case 1: tree_stokes_body<GRAD, 1>(A, T, mu, buf); break;
-    default: tree_stokes_body<GRAD, 2>(A, T, mu, buf); break;
+    switch (blockIdx.z) { /* from TR_GROUPS on the rows of TR_SMALL items */
+    case 0: tree_stokes_body<GRAD, 0, false>(A, T, mu, buf); break;
+    case 1: tree_stokes_body<GRAD, 1, false>(A, T, mu, buf); break;
+    case 2: tree_stokes_body<GRAD, 2, false>(A, T, mu, buf); break;
+    case 3: tree_stokes_body<GRAD, 0, true>(A, T, mu, buf); break;
+    case 4: tree_stokes_body<GRAD, 1, true>(A, T, mu, buf); break;
+    default: tree_stokes_body<GRAD, 2, true>(A, T, mu, buf); break;
     }
 }
 
@@ -1004,6 +1133,99 @@ __device__ __forceinline__ void tree_stokes_rows(int order, const double2 *m, do
         }
         tree_stokes_rows<NC, LAP, N + 1>(order, m, c2, h, b + h, k, kn, cn, fma(c2, cn, -cp), sn, fma(c2, sn, -sp),
                                          rho * h, f0, f1, g);
+    }
+}
+
+/* orders N and on of a TR_SMALL item: K_n - S_n (kt, the next one in kt1) with the
+   K part's rows in m, the powers with theirs in ms, into the same sums */
+template <int NC, int N>
+__device__ __forceinline__ void tree_small_rows(int order, const double2 *m, const double2 *ms, double c2, double h,
+                                                double b, double k, double k1, double kt, double kt1, double cp,
+                                                double cn, double sp, double sn, double rho, double (&f0)[2 * NC],
+                                                double (&f1)[2 * NC])
+{
+    constexpr int NV = 4 * NC + 2, NS = 4 * NC;
+    if constexpr (N < TR_ROWS) {
+        if (N > order) return;
+        const double kc = kt * cn, ks = kt * sn, rc = rho * cn, rs = rho * sn;
+        fmac_pair<N * NV>(f0[0], f1[0], m, kc, ks);
+        fmac_pair<N * NV + 2>(f0[1], f1[1], m, kc, ks);
+        fmac_pair<N * NS>(f0[0], f1[0], ms, rc, rs);
+        fmac_pair<N * NS + 2>(f0[1], f1[1], ms, rc, rs);
+        if constexpr (NC == 2) {
+            fmac_pair<N * NV + 4>(f0[2], f1[2], m, kc, ks);
+            fmac_pair<N * NV + 6>(f0[3], f1[3], m, kc, ks);
+            fmac_pair<N * NS + 4>(f0[2], f1[2], ms, rc, rs);
+            fmac_pair<N * NS + 6>(f0[3], f1[3], ms, rc, rs);
+        }
+        /* k, k1: K_N and K_{N+1}; b: 2 (N + 1)/z */
+        tree_small_rows<NC, N + 1>(order, m, ms, c2, h, b + h, k1, fma(b, k1, k), kt1, fma(b, kt1, k), cn,
+                                   fma(c2, cn, -cp), sn, fma(c2, sn, -sp), rho * h, f0, f1);
+    }
+}
+
+/* K_0, K_1, K_1 - 1/z and K_2 - 2/z^2 at distance^2 r2.  z <= 2: from the fitted
+   smooth parts T1, T3 of the stresslet, z K_1 - 1 = 2 pi z^2 T3 and
+   K_2 - 2/z^2 = -1/2 - pi z^2 (T1 + T3), where nothing cancels. */
+__device__ __forceinline__ void tree_k_small(const double *fq, double r2, double &ri, double &k0, double &k1, double &kt1,
+                                             double &kt2)
+{
+    const FarTab T = far_table();
+    const FarConst fc = far_const_of(fq);
+    ri = lean_rsq(r2);
+    const double z = fc.a * (r2 * ri), zi = fc.ia * ri, q = fc.a2q * r2;
+    if (q <= 1.0) {
+        const double lz = fma(0.5, lean_log01(T, q), LN2);
+        const double t1 = fma(hornerc<14>(T->stk[3], q), lz, hornerc<14>(T->stk[0], q));
+        const double t3 = fma(hornerc<14>(T->stk[5], q), lz, hornerc<14>(T->stk[2], q));
+        kt1 = (2.0 * PI * z) * t3;
+        kt2 = fma(-PI * (z * z), t1 + t3, -0.5);
+        k0 = fma(-4.0 * PI, t3, kt2);
+        k1 = zi + kt1;
+    } else {
+        K01 o, o2;
+        k01_far2<true, true, true, true>(T, fc, r2, r2, o, o2);
+        k0 = o.k0;
+        k1 = o.ak1r * (r2 * ri);
+        kt1 = k1 - zi;
+        kt2 = fma(2.0 * zi, kt1, k0);
+    }
+}
+
+template <int NC>
+__device__ __forceinline__ void tree_expand_small(const double *fq, const TreeDev &T, uint32_t c, int order, double x,
+                                                  double y, double (&f0)[2 * NC])
+{
+    constexpr int NV = 4 * NC + 2, NS = 4 * NC, NL = tr_stride(NV) / 32, NLS = tr_stride(NS) / 32;
+    const double2 *mp = (const double2 *)(T.mom + (int64_t)c * tr_stride(NV)) + (threadIdx.x & 15);
+    const double2 *sp = (const double2 *)(T.small + (int64_t)c * tr_stride(NS)) + (threadIdx.x & 15);
+    double2 m[NL], ms[NLS];
+#pragma unroll
+    for (int l = 0; l < NL; ++l) m[l] = mp[16 * l];
+#pragma unroll
+    for (int l = 0; l < NLS; ++l) ms[l] = sp[16 * l];
+    const MHLP_CAS double *cc = (const MHLP_CAS double *)T.cc + 2 * (int64_t)c;
+    const double ex = x - cc[0], ey = y - cc[1];
+    double ri, k0, k1, kt1, kt2;
+    tree_k_small(fq, fma(ex, ex, ey * ey), ri, k0, k1, kt1, kt2);
+    const double ct = ex * ri, h = 2.0 * far_const_of(fq).ia * ri;
+    double f1[2 * NC];
+#pragma unroll
+    for (int n = 0; n < 2 * NC; ++n) f0[n] = f1[n] = 0.0;
+    fmac_pair<0>(f0[0], f1[0], m, k0, 0.0);
+    fmac_pair<2>(f0[1], f1[1], m, k0, 0.0);
+    if constexpr (NC == 2) {
+        fmac_pair<4>(f0[2], f1[2], m, k0, 0.0);
+        fmac_pair<6>(f0[3], f1[3], m, k0, 0.0);
+    }
+    tree_small_rows<NC, 1>(order, m, ms, 2.0 * ct, h, 2.0 * h, k1, fma(h, k1, k0), kt1, kt2, 1.0, ct, 0.0, ey * ri, h, f0,
+                           f1);
+#pragma unroll
+    for (int n = 0; n < 2 * NC; ++n) f0[n] += f1[n];
+    if constexpr (NC == 2) { /* x derivatives of u_1, u_2, then y: to d_1 u_1, d_2 u_1, d_1 u_2, d_2 u_2 */
+        const double t = f0[1];
+        f0[1] = f0[2];
+        f0[2] = t;
     }
 }
 
@@ -1211,11 +1433,12 @@ struct TreeGrad {
     }
 };
 
-/* the stresslet double layer, and with GRAD its target gradient */
-template <bool GRAD>
+/* the stresslet double layer, and with GRAD its target gradient; SMALL: for plans
+   with TR_SMALL items (their rows take registers that the others need not pay for) */
+template <bool GRAD, bool SMALL>
 struct TreeStokes {
-    /* the gradient needs more than the 128 registers of a 16-wave block */
-    static constexpr int NF = GRAD ? 4 : 2, WMAX = GRAD ? 8 : 16;
+    /* the gradient and SMALL need more than the 128 registers of a 16-wave block */
+    static constexpr int NF = GRAD ? 4 : 2, WMAX = GRAD || SMALL ? 8 : 16;
     static constexpr bool SKIP = false;
     template <int PC>
     static __device__ __forceinline__ void panel(const FarArgs &A, const TreeDev &D, int64_t p,
@@ -1277,7 +1500,11 @@ struct TreeStokes {
     static __device__ __forceinline__ void expand(const double *fq, const TreeDev &T, uint32_t c,
                                                   uint32_t fl, double x, double y, double (&f)[NF])
     {
-        tree_expand_stokes<NF / 2>(fq, T, c, fl, ((int)(fl >> 8) & 63) + (GRAD ? TR_SGRAD : 0), x, y, f);
+        const int order = ((int)(fl >> 8) & 63) + (GRAD ? TR_SGRAD : 0);
+        if (SMALL && fl & TR_SMALL)
+            tree_expand_small<NF / 2>(fq, T, c, order, x, y, f);
+        else
+            tree_expand_stokes<NF / 2>(fq, T, c, fl, order, x, y, f);
     }
     static __device__ __forceinline__ void near(const FarArgs &A, const double *mu, int64_t q, int64_t p, int jj,
                                                 double (&n)[NF])
