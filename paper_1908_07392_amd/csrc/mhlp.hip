@@ -2055,7 +2055,7 @@ static mhlp_status tree_setup(mhlp_plan *P, hipStream_t st)
     const int64_t o_cc = take(16 * T.ncl), o_rmin = take(8 * mhlp::TR_RM * T.ncl), o_mom = take(8 * nmom);
     const int64_t o_small = take(P->stokes ? 8 * T.ncl * mhlp::tr_stride(P->onsurf ? 4 : 8) : 0);
     const int64_t o_st = take(8 * 48 * Np), o_flux = take(P->stokes && P->onsurf ? 8 * Np : 0), o_lb = take(4 * T.ncl);
-    const int64_t o_at = take(16 * G), o_cnt = take(8 * G), o_order = take(4 * G), o_znear = take(4 * G), o_cost = take(24);
+    const int64_t o_at = take(16 * G), o_cnt = take(8 * G), o_order = take(4 * G), o_znear = take(4 * G), o_cost = take(32);
     const int64_t o_arr = take(4 * G);
     /* the lists are counted, then filled into storage of their size; they pass
        through slots of one entry a panel, for as many groups at a time as 64 MB
@@ -2081,7 +2081,7 @@ static mhlp_status tree_setup(mhlp_plan *P, hipStream_t st)
     T.arrived = reinterpret_cast<uint32_t *>(P->tree_mem + o_arr);
     mhlp::tree_clusters_kernel<<<nblocks(T.ncl, 4), 256, 0, st>>>(T, g->soa, g->soa + g->N, g->ph, P->alpha,
                                                                   P->near_factor);
-    HIPCHECK(hipMemsetAsync(T.cost, 0, 3 * sizeof(*T.cost), st));
+    HIPCHECK(hipMemsetAsync(T.cost, 0, 4 * sizeof(*T.cost), st));
     HIPCHECK(hipMemsetAsync(T.arrived, 0, 4 * G, st));
     char *tmp = small ? P->tree_mem + o_tmp : nullptr;
     bool have = small || hipMalloc((void **)&tmp, (size_t)(Gc * per)) == hipSuccess;
@@ -2093,7 +2093,7 @@ static mhlp_status tree_setup(mhlp_plan *P, hipStream_t st)
                                                                        P->near_ptr, P->near_panel, g0, ng, slots, runs);
         return (unsigned)ng;
     };
-    unsigned long long cost[3] = {3ull * (unsigned long long)Np * (unsigned long long)G, 0, (unsigned long long)Np};
+    unsigned long long cost[4] = {3ull * (unsigned long long)Np * (unsigned long long)G, 0, (unsigned long long)Np, 0};
     hipError_t e = hipSuccess;
     if (have) {
         for (int64_t g0 = 0; g0 < G; g0 += Gc) {
@@ -2102,14 +2102,14 @@ static mhlp_status tree_setup(mhlp_plan *P, hipStream_t st)
         }
         mhlp::tree_order_kernel<<<1, 1024, 0, st>>>(T, G);
         e = hipGetLastError();
-        unsigned long long c[3];
+        unsigned long long c[4];
         if (e == hipSuccess) e = hipMemcpyAsync(c, T.cost, sizeof(c), hipMemcpyDeviceToHost, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);
         if (e == hipSuccess) {
             const size_t n = (size_t)std::max<unsigned long long>(1, c[2]);
             have = small || hipMalloc((void **)&P->tree_items, sizeof(uint2) * n) == hipSuccess;
             T.items = small ? reinterpret_cast<uint2 *>(P->tree_mem + o_items) : P->tree_items;
-            if (have) std::copy(c, c + 3, cost);
+            if (have) std::copy(c, c + 4, cost);
         }
     }
     if (have && e == hipSuccess) {
@@ -2133,6 +2133,7 @@ static mhlp_status tree_setup(mhlp_plan *P, hipStream_t st)
         HIPCHECK(hipStreamSynchronize(st));
     }
     P->tr_cost = cost[0];
+    T.expands = cost[3] != 0;
     if (P->stokes && cost[1] > 0) T.small = reinterpret_cast<double *>(P->tree_mem + o_small);
     const double U = (double)cost[0] / (double)G;
     P->tr = tree_shape(G, U);
@@ -2373,7 +2374,8 @@ extern "C" mhlp_status mhlp_plan_info(const mhlp_plan *P, int64_t *n_targets, in
    <SLP, DLP, GRAD> the moments it reads. */
 static dim3 moments_grid(const FarArgs &A, const mhlp::TreeDev &T)
 {
-    return dim3(nblocks(A.Np, 16), (unsigned)T.nlev, mhlp::TR_GROUPS);
+    /* without expansions only the staging at level 0 is left: 6 -> 2.5 us */
+    return T.expands ? dim3(nblocks(A.Np, 16), (unsigned)T.nlev, mhlp::TR_GROUPS) : dim3(nblocks(A.Np, 16));
 }
 
 template <class Op>

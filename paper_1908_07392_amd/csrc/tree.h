@@ -61,9 +61,10 @@ struct TreeDev {
     uint32_t *arrived = nullptr;             /* [groups]: blocks of split groups that are through, counted on and on */
     unsigned long long *cost = nullptr;      /* total work of the groups (tree_cost); [1]: the largest spread of
                                                 the z classes of a group's items (TR_ZSTEP), of a stresslet plan whether
-                                                it has TR_SMALL items; [2]: all items */
+                                                it has TR_SMALL items; [2]: all items; [3]: whether there are expansions */
     float *lb = nullptr;                     /* [ncl] log2 of the sum of |charges| and |dipoles|, rounded up */
     int *znear = nullptr;                    /* [groups] smallest z class of the items */
+    int expands = 1;                         /* some item is an expansion (else the moments kernel only stages) */
     int skip = 0;                            /* far items are held against the near ones' sum (far_tree_kernel) */
     int32_t *order = nullptr;                /* [groups] launch order: the groups with the most work first */
 };
@@ -255,9 +256,9 @@ __device__ __forceinline__ int tree_piece(double zlo, double zhi)
    2 ms. */
 constexpr int TR_RUN = 1 << (TR_LEV - 1);
 __host__ __device__ inline int tree_nrun(int64_t Np) { return (int)((Np + TR_RUN - 1) / TR_RUN); }
-__device__ __forceinline__ uint32_t tree_run_word(int nd, int nf, int zlo, int zhi)
+__device__ __forceinline__ uint32_t tree_run_word(int nd, int nf, int zlo, int zhi, bool expands)
 {
-    return (uint32_t)(nd | nf << 5 | zlo << 10 | zhi << 18);
+    return (uint32_t)(nd | nf << 5 | zlo << 10 | zhi << 18) | (expands ? 1u << 26 : 0u);
 }
 __global__ __launch_bounds__(256) void tree_lists_kernel(TreeDev T, const double *__restrict__ tx,
                                                          const double *__restrict__ ty, int64_t M,
@@ -274,6 +275,7 @@ __global__ __launch_bounds__(256) void tree_lists_kernel(TreeDev T, const double
     const int32_t k0 = nptr[i], k1 = nptr[i + 1];
     uint2 *items = tmp + u * TR_RUN;
     int nd = 0, nf = 0, zlo = 255, zhi = 0;
+    bool expands = false;
     for (int64_t p = TR_RUN * run, pe = min(T.Np, p + TR_RUN); p < pe;) {
         int k = min(T.nlev - 1, __builtin_ctz((uint32_t)p | TR_RUN));
         for (;; --k) {
@@ -308,6 +310,7 @@ __global__ __launch_bounds__(256) void tree_lists_kernel(TreeDev T, const double
                 } else if (T.stokes && small) {
                     zlo = 0, zhi = 1; /* no z classes here: the plan has such items */
                 }
+                expands = expands || y_ != TR_ZERO;
                 if (lane == 0) items[TR_RUN - 1 - nf] = make_uint2((uint32_t)c, y_);
                 ++nf;
                 break;
@@ -341,7 +344,7 @@ __global__ __launch_bounds__(256) void tree_lists_kernel(TreeDev T, const double
         }
         p += (int64_t)1 << k;
     }
-    if (lane == 0) runs[u] = tree_run_word(nd, nf, zlo, zhi);
+    if (lane == 0) runs[u] = tree_run_word(nd, nf, zlo, zhi, expands);
 }
 
 /* plan time: a group's counts and z classes from its runs', one wave per group */
@@ -351,8 +354,10 @@ __global__ __launch_bounds__(64) void tree_count_kernel(TreeDev T, int64_t g0, c
     const int64_t g = g0 + blockIdx.x;
     const uint32_t *w = runs + blockIdx.x * (int64_t)nrun;
     int nd = 0, nf = 0, zlo = 255, zhi = 0;
+    bool expands = false;
     for (int r = lane; r < nrun; r += 64) {
         const uint32_t v = w[r];
+        expands = expands || v >> 26;
         nd += v & 31;
         nf += (v >> 5) & 31;
         zlo = min(zlo, (int)((v >> 10) & 255));
@@ -362,7 +367,9 @@ __global__ __launch_bounds__(64) void tree_count_kernel(TreeDev T, int64_t g0, c
         nd += __shfl_xor(nd, o), nf += __shfl_xor(nf, o);
         zlo = min(zlo, __shfl_xor(zlo, o)), zhi = max(zhi, __shfl_xor(zhi, o));
     }
+    expands = __ballot(expands) != 0;
     if (lane != 0) return;
+    if (expands) T.cost[3] = 1; /* all that write it write this */
     T.cnt[g] = make_int2(nd, nf);
     T.znear[g] = zlo;
     if (zhi > zlo) atomicMax(T.cost + 1, (unsigned long long)(zhi - zlo));
@@ -695,6 +702,7 @@ __device__ __forceinline__ void tree_moments_body(const FarArgs &A, const TreeDe
         }
         __syncthreads();
     }
+    if (!T.expands) return;
     /* clusters too wide to expand (the same test as tree_order_ratio through rmin) */
     const bool live = T.rmin[TR_RM * c + TR_NP - 1] < INFINITY;
     if (__syncthreads_or(live ? 1 : 0) == 0) return;
@@ -918,6 +926,7 @@ __device__ __forceinline__ void tree_stokes_body(const FarArgs &A, const TreeDev
             if ((t & 15) == 0 && have) T.flux[j >> 4] = f;
         }
     }
+    if (!T.expands) return;
     const double ah = 0.5 * A.alpha, wr = ah * dx, wi = -ah * dy, q2 = fma(wr, wr, wi * wi);
     if constexpr (SMALL)
         tree_regular_series<TreeS<GRAD, Z>::LO, TreeS<GRAD, Z>::CNT>(q2, b.s, b.d);

@@ -2,6 +2,7 @@
 memory that a call may need, and which launch shapes and paths a call leaves behind."""
 import numpy as np
 import pytest
+import scipy.special as sp
 import torch
 
 import oracle
@@ -213,3 +214,53 @@ def test_plan_without_memory_for_its_lists(stokes):
         torch.cuda.empty_cache()
     got = run(P, mu)
     assert float((got - want).abs().max()) < 1e-12 * float(want.abs().max())
+
+
+@pytest.mark.parametrize("panels,alpha", [(300, 500.0), (600, 900.0), (257, 300.0)])
+def test_items_left_out_on_the_curve(panels, alpha):
+    """cos(n theta) is an eigenfunction of 1/2 I + D on the circle, with -alpha I_n K_n', on plans whose operator
+    leaves far items out (one block a group, a large spread of z); a density that lives on one panel leaves the far
+    targets what the far items bring: there the panel's plain sum."""
+    g = wl.discretize(wl.Curve("circle", R=1.0), panels)
+    P = mhlp.Plan(mhlp.Geometry(_t(g.node_soa())), alpha)
+    lam = -alpha * sp.ive(2, alpha) * np.exp(alpha) * sp.kvp(2, alpha) if alpha < 700 else None
+    mu = np.cos(2 * g.theta)
+    if lam is not None:
+        out = mhlp.apply_bie(P, _t(mu)).cpu().numpy()
+        assert np.max(np.abs(out - lam * mu)) < 1e-11 * abs(lam)
+    one = np.zeros(g.n_nodes)
+    one[16 * 40:16 * 41] = 1.0 + np.arange(16) / 7.0
+    out = mhlp.apply_bie(P, _t(one)).cpu().numpy()
+    k = np.arange(g.n_nodes)
+    far = np.minimum(np.abs(k - 648), g.n_nodes - np.abs(k - 648)) > 16 * 6
+    ex, ey = g.x[far][:, None] - g.x[16 * 40:16 * 41], g.y[far][:, None] - g.y[16 * 40:16 * 41]
+    r = np.hypot(ex, ey)
+    nx, ny = (n[16 * 40:16 * 41] for n in g.normals)
+    size = alpha * sp.k1(alpha * r) / (2 * np.pi) * (g.weights * one)[16 * 40:16 * 41]
+    d = size / r * (ex * nx + ey * ny)
+    assert (np.abs(out[far] - d.sum(axis=1)) <= ((3e-14 + 5e-16 * alpha * r) * size).sum(axis=1) + 1e-300).all()
+
+
+@pytest.mark.parametrize("panels,m", [(16, 60), (64, 300), (256, 60), (40, 9000), (64, 20000)])
+def test_split_groups_finish_alike(panels, m):
+    """Groups summed by several blocks, the last of which adds the slots: the same bits whichever that is, in calls
+    of either layer, gradients and both in turn, and in replays of a captured graph between them."""
+    g = wl.discretize(wl.starfish_curve(), panels)
+    rng = np.random.default_rng(m)
+    P = mhlp.Plan(mhlp.Geometry(_t(g.node_soa())), 15.0, _t(rng.uniform(-1.5, 1.5, m)), _t(rng.uniform(-1.5, 1.5, m)))
+    sg = _t(np.cos(3 * g.theta) + 0.5)
+    first = [mhlp.eval_slp(P, sg), *mhlp.eval_layer(P, sigma=sg, mu=sg), *mhlp.eval_grad(P, sigma=sg, mu=sg)]
+    out = torch.empty_like(first[0])
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side), torch.cuda.graph(graph, stream=side):
+        mhlp.eval_slp(P, sg, out=out)
+    torch.cuda.synchronize()
+    for k in range(20):
+        out.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, first[0])
+        again = [mhlp.eval_slp(P, sg), *mhlp.eval_layer(P, sigma=sg, mu=sg), *mhlp.eval_grad(P, sigma=sg, mu=sg)]
+        assert all(torch.equal(a, b) for a, b in zip(first, again))
