@@ -139,6 +139,7 @@ struct mhlp_plan {
     struct TreeShape {
         int waves = 0, split = 1, cut = 0; /* waves per block and blocks per group, direct items in 2^cut units */
     } tr, tr_skip;                         /* of far_tree_kernel; where it leaves items out */
+    bool tr_raw = false;                   /* no staging launch (TREE_RAW_MAX) */
     NearParams np{};
     double near_factor = 1.2;
     int64_t part_cap = 0;     /* capacity of part (doubles)                 */
@@ -2030,6 +2031,17 @@ static mhlp_plan::TreeShape tree_shape(int64_t G, double U)
     return {8, 1 << (e - 3), cut};
 }
 
+/* Up to TREE_DIRECT_MAX (group, panel) pairs an off-surface plan is summed pair by
+   pair, which takes no longer than moments and expansions (us, single layer |
+   stresslet, lists and direct, alpha = 1: 320 pairs 16.2, 10.9 | 23.9, 17.4; 752
+   17.1, 12.2 | 29.1, 21.2; 1280 16.8, 21.0 | 26.1, 39.4; with 16 panels, whose
+   clusters gather little, 2000 pairs 19.8, 15.7 | 35.9, 32.2); batches share the
+   lists of plans on the curve, whose many groups run at once, so these keep their
+   expansions.  Without expansions, charges are formed where they are read up to
+   TREE_RAW_MAX pairs: a launch less (11.0 -> 8.5 us at 16 panels), up to four
+   multiplications a source and lane more, 2 us at 8000 pairs. */
+constexpr int64_t TREE_DIRECT_MAX = 1024, TREE_RAW_MAX = 16384;
+
 /* Clusters, item lists and buffers of a plan's far field (tree.h), on
    the stream after the near lists, which the item lists read. */
 static mhlp_status tree_setup(mhlp_plan *P, hipStream_t st)
@@ -2039,6 +2051,7 @@ static mhlp_status tree_setup(mhlp_plan *P, hipStream_t st)
     P->tree = new mhlp::TreeDev();
     mhlp::TreeDev &T = *P->tree;
     T.Np = Np;
+    T.expands = (P->onsurf && !P->stokes) || G * Np > (Np <= 24 ? 2 : 1) * TREE_DIRECT_MAX;
     while (T.nlev < mhlp::TR_LEV && ((int64_t)1 << T.nlev) <= Np) {
         T.off[T.nlev] = T.ncl;
         T.ncl += (Np + ((int64_t)1 << T.nlev) - 1) >> T.nlev;
@@ -2139,6 +2152,7 @@ static mhlp_status tree_setup(mhlp_plan *P, hipStream_t st)
     P->tr = tree_shape(G, U);
     if (P->tr.split > 1) TRY(dalloc(&T.part, (P->onsurf ? 2 : 4) * (int64_t)P->tr.split * 64 * G));
     T.skip = cost[1] >= mhlp::TR_ZSKIP && (P->onsurf ? U >= 400.0 : G >= 400);
+    P->tr_raw = !T.expands && !T.skip && !T.flux && G * Np <= TREE_RAW_MAX;
     P->tr_skip = {P->onsurf ? 16 : G >= 1200 && U < 350.0 ? 4 : 8, 1, P->onsurf ? 2 : 0};
     return MHLP_OK;
 }
@@ -2370,8 +2384,8 @@ extern "C" mhlp_status mhlp_plan_info(const mhlp_plan *P, int64_t *n_targets, in
 /* ------------------------------------------------------------------------ */
 /* evaluation                                                                */
 /* ------------------------------------------------------------------------ */
-/* The launches of one far sum by cluster expansions: Op what it evaluates,
-   <SLP, DLP, GRAD> the moments it reads. */
+/* The launches of one far sum by cluster expansions: Op<SLP, DLP, RAW> what it
+   evaluates, <SLP, DLP, GRAD> the moments it reads. */
 static dim3 moments_grid(const FarArgs &A, const mhlp::TreeDev &T)
 {
     /* without expansions only the staging at level 0 is left: 6 -> 2.5 us */
@@ -2398,18 +2412,20 @@ static void launch_tree_far(const FarArgs &A, const mhlp_plan *P, hipStream_t st
     }
 }
 
-template <class Op, bool SLP, bool DLP, bool GRAD>
+template <template <bool, bool, bool> class Op, bool SLP, bool DLP, bool GRAD>
 static void launch_tree(const FarArgs &A, const mhlp_plan *P, hipStream_t st)
 {
+    if (P->tr_raw) return launch_tree_far<Op<SLP, DLP, true>>(A, P, st);
     const mhlp::TreeDev &T = *P->tree;
     mhlp::tree_moments_kernel<SLP, DLP, GRAD><<<moments_grid(A, T), 256, 0, st>>>(A, T);
-    launch_tree_far<Op>(A, P, st);
+    launch_tree_far<Op<SLP, DLP, false>>(A, P, st);
 }
 
 template <bool GRAD>
 static void launch_tree_stokes(const FarArgs &A, const mhlp_plan *P, hipStream_t st)
 {
     const mhlp::TreeDev &T = *P->tree;
+    if (P->tr_raw) return launch_tree_far<mhlp::TreeStokes<GRAD, false, true>>(A, P, st);
     dim3 grid = moments_grid(A, T);
     if (T.small) grid.z *= 2; /* the rows of the powers, too */
     mhlp::tree_stokes_kernel<GRAD><<<grid, 256, 0, st>>>(A, T);
@@ -2423,7 +2439,7 @@ template <bool SLP, bool DLP>
 static void launch_far_t(const FarArgs &A, const mhlp_plan *P, int32_t precision, hipStream_t st)
 {
     if (precision == MHLP_FP64) {
-        launch_tree<mhlp::TreePot<SLP, DLP>, SLP, DLP, false>(A, P, st);
+        launch_tree<mhlp::TreePot, SLP, DLP, false>(A, P, st);
         return;
     }
     const int nsplit = P->nsplit;
@@ -2695,11 +2711,11 @@ extern "C" mhlp_status mhlp_eval_grad(const mhlp_plan *Pc, const double *sigma, 
     double *out[4] = {gs_x, gs_y, gd_x, gd_y};
     for (int f = 0; f < 4; ++f) A.gout[f] = out[f];
     if (gs && gd)
-        launch_tree<mhlp::TreeGrad<true, true>, true, true, true>(A, P, st);
+        launch_tree<mhlp::TreeGrad, true, true, true>(A, P, st);
     else if (gs)
-        launch_tree<mhlp::TreeGrad<true, false>, true, false, true>(A, P, st);
+        launch_tree<mhlp::TreeGrad, true, false, true>(A, P, st);
     else
-        launch_tree<mhlp::TreeGrad<false, true>, false, true, true>(A, P, st);
+        launch_tree<mhlp::TreeGrad, false, true, true>(A, P, st);
     HIPCHECK(hipGetLastError());
     return MHLP_OK;
 }

@@ -64,7 +64,8 @@ struct TreeDev {
                                                 it has TR_SMALL items; [2]: all items; [3]: whether there are expansions */
     float *lb = nullptr;                     /* [ncl] log2 of the sum of |charges| and |dipoles|, rounded up */
     int *znear = nullptr;                    /* [groups] smallest z class of the items */
-    int expands = 1;                         /* some item is an expansion (else the moments kernel only stages) */
+    int expands = 1;                         /* some item is (while the lists are built: may be) an expansion; else the
+                                                moments kernel only stages, if it runs at all */
     int skip = 0;                            /* far items are held against the near ones' sum (far_tree_kernel) */
     int32_t *order = nullptr;                /* [groups] launch order: the groups with the most work first */
 };
@@ -286,12 +287,12 @@ __global__ __launch_bounds__(256) void tree_lists_kernel(TreeDev T, const double
             const double rhi = (double)wave_max_f((float)r) * (1.0 + 3e-7);
             const double *rm = T.rmin + TR_RM * c;
             uint32_t y_ = 0xffffffffu;
-            bool expand = true, lap = false, small = false;
+            bool expand = T.expands, lap = false, small = false;
             if (T.stokes) {
                 const double R = rm[TR_RM - 1], a = alpha * R, zc = alpha * (rlo - R);
                 lap = zc >= TR_SLAP;
                 small = zc < TR_SZ;
-                expand = a >= TR_AMIN && a <= (lap ? TR_SAMAX : TR_AMAX);
+                expand = expand && a >= TR_AMIN && a <= (lap ? TR_SAMAX : TR_AMAX);
             }
             if (!T.stokes && rlo >= rm[TR_RM - 1]) {
                 y_ = TR_ZERO;
@@ -1283,15 +1284,69 @@ __device__ __forceinline__ void tree_expand_stokes(const double *fq, const TreeD
     }
 }
 
-/* whether a staged charge or dipole of the cluster is infinite or NaN */
-template <bool SLP, bool DLP>
-__device__ __forceinline__ bool tree_bad(const TreeDev &T, int64_t p0, int64_t p1)
+/* the density that far_density gives, from scalar registers */
+__device__ __forceinline__ const double *tree_density(const FarArgs &A)
+{
+    return A.gs ? A.mu + (int64_t)__builtin_amdgcn_readfirstlane(A.gs->j) * A.jstride : A.mu;
+}
+
+/* Charges and dipoles of panel p for the direct pairs: staged by the moments
+   kernel, or, RAW, formed where they are read, with the same roundings (small
+   plans without expansions: a launch less; 1 to 4 multiplications a source and
+   lane more).  GRAD: the charges carry alpha. */
+template <bool SLP, bool DLP, bool GRAD, bool RAW>
+struct TreeSrc {
+    const MHLP_CAS double *st, *w, *sg, *mu, *nx, *ny;
+    double alpha;
+    __device__ __forceinline__ TreeSrc(const FarArgs &A, const TreeDev &D, int64_t p)
+    {
+        if constexpr (RAW) {
+            w = (const MHLP_CAS double *)A.sw + 16 * p;
+            sg = (const MHLP_CAS double *)A.sigma + 16 * p;
+            if (DLP) mu = (const MHLP_CAS double *)tree_density(A) + 16 * p;
+            nx = (const MHLP_CAS double *)A.snx + 16 * p;
+            ny = (const MHLP_CAS double *)A.sny + 16 * p;
+            alpha = A.alpha;
+        } else {
+            st = (const MHLP_CAS double *)D.st + 48 * p;
+        }
+    }
+    __device__ __forceinline__ double q(int s) const
+    {
+        if constexpr (!RAW) return st[s];
+        else if constexpr (GRAD) return alpha * (w[s] * sg[s]);
+        else return w[s] * sg[s];
+    }
+    __device__ __forceinline__ void d(int s, double &dx, double &dy) const
+    {
+        if constexpr (!RAW) {
+            dx = st[16 + s];
+            dy = st[32 + s];
+        } else {
+            const double m = (alpha * w[s]) * mu[s];
+            dx = m * nx[s];
+            dy = m * ny[s];
+        }
+    }
+};
+
+/* whether a charge or dipole of the cluster is infinite or NaN */
+template <bool SLP, bool DLP, bool RAW>
+__device__ __forceinline__ bool tree_bad(const FarArgs &A, const TreeDev &T, int64_t p0, int64_t p1)
 {
     double s = 0.0;
     for (int64_t j = 16 * p0 + (threadIdx.x & 63); j < 16 * p1; j += 64) {
-        const double *q = T.st + (j >> 4) * 48 + (j & 15);
-        if (SLP) s = fma(0.0, q[0], s);
-        if (DLP) s = fma(0.0, q[16], fma(0.0, q[32], s));
+        if constexpr (RAW) {
+            if (SLP) s = fma(0.0, A.sw[j] * A.sigma[j], s);
+            if (DLP) {
+                const double m = (A.alpha * A.sw[j]) * tree_density(A)[j];
+                s = fma(0.0, m * A.snx[j], fma(0.0, m * A.sny[j], s));
+            }
+        } else {
+            const double *q = T.st + (j >> 4) * 48 + (j & 15);
+            if (SLP) s = fma(0.0, q[0], s);
+            if (DLP) s = fma(0.0, q[16], fma(0.0, q[32], s));
+        }
     }
     return __ballot(!(s == 0.0)) != 0;
 }
@@ -1303,10 +1358,10 @@ __device__ __forceinline__ bool tree_bad(const TreeDev &T, int64_t p0, int64_t p
    scalar cache, two at a time); near: the correction of node jj of the listed
    pair q; store: field f of target i, common what every store of a wave shares.  The sums
    carry no 1/(2 pi) until they leave the wave. */
-template <bool SLP, bool DLP>
+template <bool SLP, bool DLP, bool RAW = false>
 struct TreePot {
     static constexpr int NF = (SLP ? 1 : 0) + (DLP ? 1 : 0), EXTRA = 0, WMAX = 16;
-    static constexpr bool SKIP = true; /* tree_moments_kernel leaves the bounds that takes */
+    static constexpr bool SKIP = !RAW; /* tree_moments_kernel leaves the bounds that takes */
     template <int PC>
     static __device__ __forceinline__ void panel(const FarArgs &A, const TreeDev &D, int64_t p,
                                                  int s0, int s1, double x, double y, double (&f)[NF])
@@ -1314,7 +1369,7 @@ struct TreePot {
         constexpr int K = PC < 0 || PC >= KQ_NP ? 0 : PC;
         const MHLP_CAS double *sx = (const MHLP_CAS double *)A.sx + 16 * p;
         const MHLP_CAS double *sy = (const MHLP_CAS double *)A.sy + 16 * p;
-        const MHLP_CAS double *st = (const MHLP_CAS double *)D.st + 48 * p;
+        const TreeSrc<SLP, DLP, false, RAW> src(A, D, p);
         FarTab T = far_table();
         const FarConst fc = far_const_of(A.fq);
         double qa, qk;
@@ -1330,10 +1385,13 @@ struct TreePot {
                 k01_far2<SLP, DLP, true, true>(T, fc, r20, r21, o0, o1);
             else
                 k01_far2_fixed<SLP, DLP, PC>(T, fc, qa, qk, r20, r21, o0, o1);
-            if (SLP) f[0] = fma(o1.k0, st[s + 1], fma(o0.k0, st[s], f[0]));
-            if (DLP)
-                f[NF - 1] = fma(o1.ak1r, fma(ex1, st[16 + s + 1], ey1 * st[32 + s + 1]),
-                                fma(o0.ak1r, fma(ex0, st[16 + s], ey0 * st[32 + s]), f[NF - 1]));
+            if (SLP) f[0] = fma(o1.k0, src.q(s + 1), fma(o0.k0, src.q(s), f[0]));
+            if (DLP) {
+                double dx0, dy0, dx1, dy1;
+                src.d(s, dx0, dy0);
+                src.d(s + 1, dx1, dy1);
+                f[NF - 1] = fma(o1.ak1r, fma(ex1, dx1, ey1 * dy1), fma(o0.ak1r, fma(ex0, dx0, ey0 * dy0), f[NF - 1]));
+            }
         }
     }
     static __device__ __forceinline__ void near(const FarArgs &A, const double *mu, int64_t q, int64_t p, int jj,
@@ -1353,9 +1411,9 @@ struct TreePot {
             A.ud[o] = v;
         }
     }
-    static __device__ __forceinline__ bool bad(const TreeDev &T, int64_t p0, int64_t p1)
+    static __device__ __forceinline__ bool bad(const FarArgs &A, const TreeDev &T, int64_t p0, int64_t p1)
     {
-        return tree_bad<SLP, DLP>(T, p0, p1);
+        return tree_bad<SLP, DLP, RAW>(A, T, p0, p1);
     }
     static __device__ __forceinline__ double common(const FarArgs &, const TreeDev &) { return 0.0; }
     static __device__ __forceinline__ void expand(const double *fq, const TreeDev &T, uint32_t c,
@@ -1366,7 +1424,7 @@ struct TreePot {
 };
 
 /* the target gradients: d_x S, d_y S, d_x D, d_y D (without the absent layer's) */
-template <bool SLP, bool DLP>
+template <bool SLP, bool DLP, bool RAW = false>
 struct TreeGrad {
     static constexpr int NF = (SLP ? 2 : 0) + (DLP ? 2 : 0), EXTRA = TR_GRAD, WMAX = 16;
     static constexpr bool SKIP = false;
@@ -1377,7 +1435,7 @@ struct TreeGrad {
         constexpr int K = PC < 0 || PC >= KQ_NP ? 0 : PC;
         const MHLP_CAS double *sx = (const MHLP_CAS double *)A.sx + 16 * p;
         const MHLP_CAS double *sy = (const MHLP_CAS double *)A.sy + 16 * p;
-        const MHLP_CAS double *st = (const MHLP_CAS double *)D.st + 48 * p;
+        const TreeSrc<SLP, DLP, true, RAW> src(A, D, p);
         FarTab T = far_table();
         const FarConst fc = far_const_of(A.fq);
         double qa, qk;
@@ -1394,19 +1452,22 @@ struct TreeGrad {
             else
                 k01_far2_fixed<DLP, true, PC>(T, fc, qa, qk, r20, r21, o0, o1);
             if (SLP) {
-                const double c0 = o0.ak1r * st[s], c1 = o1.ak1r * st[s + 1];
+                const double c0 = o0.ak1r * src.q(s), c1 = o1.ak1r * src.q(s + 1);
                 f[0] = fma(-c1, ex1, fma(-c0, ex0, f[0]));
                 f[1] = fma(-c1, ey1, fma(-c0, ey0, f[1]));
             }
             if (DLP) {
                 /* (alpha^2 K0 + 2 alpha K1/r) (x-y).d / r^2, alpha from the dipole */
-                const double n0 = fma(ex0, st[16 + s], ey0 * st[32 + s]);
-                const double n1 = fma(ex1, st[16 + s + 1], ey1 * st[32 + s + 1]);
+                double dx0, dy0, dx1, dy1;
+                src.d(s, dx0, dy0);
+                src.d(s + 1, dx1, dy1);
+                const double n0 = fma(ex0, dx0, ey0 * dy0);
+                const double n1 = fma(ex1, dx1, ey1 * dy1);
                 const double b0 = n0 * fma(A.alpha, o0.k0, 2.0 * o0.ak1r) * o0.ri2;
                 const double b1 = n1 * fma(A.alpha, o1.k0, 2.0 * o1.ak1r) * o1.ri2;
                 double &gx = f[NF - 2], &gy = f[NF - 1];
-                gx = fma(-b1, ex1, fma(o1.ak1r, st[16 + s + 1], fma(-b0, ex0, fma(o0.ak1r, st[16 + s], gx))));
-                gy = fma(-b1, ey1, fma(o1.ak1r, st[32 + s + 1], fma(-b0, ey0, fma(o0.ak1r, st[32 + s], gy))));
+                gx = fma(-b1, ex1, fma(o1.ak1r, dx1, fma(-b0, ex0, fma(o0.ak1r, dx0, gx))));
+                gy = fma(-b1, ey1, fma(o1.ak1r, dy1, fma(-b0, ey0, fma(o0.ak1r, dy0, gy))));
             }
         }
     }
@@ -1430,9 +1491,9 @@ struct TreeGrad {
     {
         A.gout[SLP ? f : f + 2][A.perm ? (int64_t)A.perm[i] : i] = v;
     }
-    static __device__ __forceinline__ bool bad(const TreeDev &T, int64_t p0, int64_t p1)
+    static __device__ __forceinline__ bool bad(const FarArgs &A, const TreeDev &T, int64_t p0, int64_t p1)
     {
-        return tree_bad<SLP, DLP>(T, p0, p1);
+        return tree_bad<SLP, DLP, RAW>(A, T, p0, p1);
     }
     static __device__ __forceinline__ double common(const FarArgs &, const TreeDev &) { return 0.0; }
     static __device__ __forceinline__ void expand(const double *fq, const TreeDev &T, uint32_t c,
@@ -1443,8 +1504,9 @@ struct TreeGrad {
 };
 
 /* the stresslet double layer, and with GRAD its target gradient; SMALL: for plans
-   with TR_SMALL items (their rows take registers that the others need not pay for) */
-template <bool GRAD, bool SMALL>
+   with TR_SMALL items (their rows take registers that the others need not pay for);
+   RAW as in TreeSrc */
+template <bool GRAD, bool SMALL, bool RAW = false>
 struct TreeStokes {
     /* the gradient and SMALL need more than the 128 registers of a 16-wave block */
     static constexpr int NF = GRAD ? 4 : 2, WMAX = GRAD || SMALL ? 8 : 16;
@@ -1459,6 +1521,8 @@ struct TreeStokes {
         const MHLP_CAS double *snx = (const MHLP_CAS double *)A.snx + 16 * p;
         const MHLP_CAS double *sny = (const MHLP_CAS double *)A.sny + 16 * p;
         const MHLP_CAS double *st = (const MHLP_CAS double *)D.st + 48 * p;
+        const MHLP_CAS double *w = (const MHLP_CAS double *)A.sw + 16 * p;
+        const MHLP_CAS double *mu = (const MHLP_CAS double *)tree_density(A) + 16 * p;
         FarTab T = far_table();
         const FarConst fc = far_const_of(A.fq);
         double qa, qk, al2, ial2;
@@ -1479,7 +1543,9 @@ struct TreeStokes {
                 stk_far2_pc<PC>(T, fc, qa, qk, al2, ial2, r20, r21, Ak[0], Ak[1]);
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
-                const double nx = snx[s + u], ny = sny[s + u], m1 = st[s + u], m2 = st[16 + s + u];
+                const double nx = snx[s + u], ny = sny[s + u];
+                const double m1 = RAW ? w[s + u] * mu[s + u] : st[s + u];
+                const double m2 = RAW ? w[s + u] * mu[A.N + s + u] : st[16 + s + u];
                 const double *A_ = Ak[u];
                 const double rn = fma(ex[u], nx, ey[u] * ny);
                 const double rm = fma(ex[u], m1, ey[u] * m2);
@@ -1540,7 +1606,7 @@ struct TreeStokes {
         if (!GRAD && A.half_term != 0.0) v = fma(A.half_term, mu[f * A.N + i], fma((f ? A.sny : A.snx)[i], flux, v));
         A.gout[f][A.perm ? (int64_t)A.perm[i] : i] = v;
     }
-    static __device__ __forceinline__ bool bad(const TreeDev &, int64_t, int64_t) { return false; }
+    static __device__ __forceinline__ bool bad(const FarArgs &, const TreeDev &, int64_t, int64_t) { return false; }
 };
 
 template <class Op, class Args>
@@ -1674,7 +1740,7 @@ __global__ __launch_bounds__(64 * Op::WMAX) void far_tree_kernel(FarArgs A, Tree
                 for (int n = 0; n < NF; ++n) f[n] = 0.0;
                 int64_t p0, p1;
                 tree_panels_of(T, c, p0, p1);
-                direct = Op::bad(T, p0, p1);
+                direct = Op::bad(A, T, p0, p1);
             } else {
                 Op::expand(A.fq, T, c, fl, x, y, f);
                 bool fin = true;

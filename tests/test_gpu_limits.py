@@ -264,3 +264,42 @@ def test_split_groups_finish_alike(panels, m):
         assert torch.equal(out, first[0])
         again = [mhlp.eval_slp(P, sg), *mhlp.eval_layer(P, sigma=sg, mu=sg), *mhlp.eval_grad(P, sigma=sg, mu=sg)]
         assert all(torch.equal(a, b) for a, b in zip(first, again))
+
+
+@pytest.mark.parametrize("panels,m", [(16, 1), (16, 64 * 64), (17, 64 * 63), (64, 64 * 16), (63, 64 * 16 + 1),
+                                      (40, 26000), (40, 27000)])
+def test_small_plans_summed_pair_by_pair(panels, m):
+    """Plans on both sides of the sizes up to which all pairs are summed and charges are formed where they are read:
+    each of the potentials, gradients and the stresslet as the same targets give beside others in a larger plan with
+    expansions (which the plain sums of their own tests check): 30 roundings of the sum of absolute values, here the
+    largest value times 1e-12."""
+    g = wl.discretize(wl.starfish_curve(), panels)
+    rng = np.random.default_rng(m)
+    G = mhlp.Geometry(_t(g.node_soa()))
+    k = max(m, 30000)
+    tx, ty = rng.uniform(-1.5, 1.5, k), rng.uniform(-1.5, 1.5, k)
+    mu = _t(np.cos(3 * g.theta) + 0.5)
+    mu2 = _t(np.stack([np.cos(2 * g.theta), np.sin(g.theta)]))
+    for alpha in (2.0, 150.0):
+        small, large = (mhlp.Plan(G, alpha, _t(tx[:n]), _t(ty[:n])) for n in (m, k))
+        got = [*mhlp.eval_layer(small, sigma=mu, mu=mu), mhlp.eval_slp(small, mu), mhlp.eval_dlp(small, mu),
+               *mhlp.eval_grad(small, sigma=mu, mu=mu), mhlp.eval_grad(small, sigma=mu)[0], mhlp.eval_grad(small, mu=mu)[1]]
+        want = [*mhlp.eval_layer(large, sigma=mu, mu=mu), mhlp.eval_slp(large, mu), mhlp.eval_dlp(large, mu),
+                *mhlp.eval_grad(large, sigma=mu, mu=mu), mhlp.eval_grad(large, sigma=mu)[0], mhlp.eval_grad(large, mu=mu)[1]]
+        small, large = (mhlp.Plan(G, alpha, _t(tx[:n]), _t(ty[:n]), stokes=True) for n in (m, k))
+        got += [mhlp.stokes_eval(small, mu2), mhlp.stokes_eval_grad(small, mu2)]
+        want += [mhlp.stokes_eval(large, mu2), mhlp.stokes_eval_grad(large, mu2)]
+        for a, b in zip(got, want):
+            assert float((a - b[..., :m]).abs().max()) <= 1e-12 * float(b.abs().max())
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), -float("inf")])
+def test_non_finite_densities_of_small_plans(bad):
+    """As in larger plans: a NaN or infinite charge or dipole reaches every target, also where its pairs underflow."""
+    g = wl.discretize(wl.starfish_curve(), 20)
+    rng = np.random.default_rng(2)
+    P = mhlp.Plan(mhlp.Geometry(_t(g.node_soa())), 900.0, _t(rng.uniform(-1.5, 1.5, 500)), _t(rng.uniform(-1.5, 1.5, 500)))
+    v = np.ones(g.n_nodes)
+    v[77] = bad
+    for u in (mhlp.eval_slp(P, _t(v)), mhlp.eval_dlp(P, _t(v)), *mhlp.eval_grad(P, sigma=_t(v), mu=_t(v))):
+        assert not torch.isfinite(u).any()
