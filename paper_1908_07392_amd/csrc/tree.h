@@ -1813,9 +1813,11 @@ __global__ __launch_bounds__(64 * Op::WMAX) void far_tree_kernel(FarArgs A, Tree
         if (threadIdx.x == 0) last = (atomicAdd(T.arrived + g, 1u) & (split - 1)) == (uint32_t)split - 1;
         __syncthreads();
         if (!last) return;
-        /* the waves share the slots of the fields; red holds their sums */
-        const int H = W / NF, f = w % NF, h = w / NF;
-        if (h < H) {
+        /* the waves share the slots of the fields, as many sums for a field
+           whatever NF, so that one alone gets the bits it has beside others */
+        const int H = W > 1 ? W / 2 : 1;
+        for (int t = w; t < NF * H; t += W) {
+            const int f = t % NF, h = t / NF;
             double s = 0.0;
 #pragma unroll 4
             for (int k = h; k < split; k += H)

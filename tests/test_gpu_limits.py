@@ -250,6 +250,7 @@ def test_split_groups_finish_alike(panels, m):
     P = mhlp.Plan(mhlp.Geometry(_t(g.node_soa())), 15.0, _t(rng.uniform(-1.5, 1.5, m)), _t(rng.uniform(-1.5, 1.5, m)))
     sg = _t(np.cos(3 * g.theta) + 0.5)
     first = [mhlp.eval_slp(P, sg), *mhlp.eval_layer(P, sigma=sg, mu=sg), *mhlp.eval_grad(P, sigma=sg, mu=sg)]
+    assert torch.equal(first[0], first[1])  # one layer alone as beside the other
     out = torch.empty_like(first[0])
     side = torch.cuda.Stream()
     side.wait_stream(torch.cuda.current_stream())
