@@ -3266,17 +3266,25 @@ static int fmm_auto_level(int64_t npts, int64_t per_leaf)
 
 /* Does the FMM serve an evaluation sooner than the plan's cluster lists, which
    reach rounding whatever the order?  (Where the caller leaves the level to the
-   library; a level asked for is served by the FMM.)  The lists cost their items, the FMM its
-   boxes: per evaluation of both layers, us, lists | order 40, 20, 10:
-     70,000 points, alpha = 5 (100), level 5:      63 (269) |  305  220  190
-     260,000 points, alpha = 20 (200), level 7:    218 (2057) | 1270  860  665
-     989,000 points, alpha = 20 (200), level 8:    1588 (6085) | 3680 2500 1925
-   The estimates below lie within 30% of these, above the lists' figures. */
-static bool fmm_is_faster(unsigned long long list_cost, int order, int level)
+   library; a level asked for is served by the FMM.)  The lists cost their items,
+   the FMM its boxes, but for those whose neighbours underflow: from
+   z = alpha times the leaf's side about 20 on they get fewer, from 100 on none
+   are left but the direct part.  Both layers, us, lists | order 40, 20, 10:
+     64 panels, 3000 points, level 3:       alpha = 5 22 | 167 144 133; 200 23 | 46 45 46
+     256, 49,729, level 5:   alpha = 50 121 | 346 263 228; 500 166 | 145 127 117; 1000 98 | 59 59 58
+     512, 100,000, level 6:  alpha = 5 78 | 700 508 419; 500 337 | 495 368 305
+     896, 250,000, level 7:  alpha = 50 524 | 1775 1235 976; 200 945 | 1664 1161 910
+     896, 898,704, level 7:  alpha = 20 619 | 1751 1206 944; 200 2767 | 1686 1177 933
+   The estimates err on the FMM's side (boxes of levels 3 and 7 take up to twice
+   theirs, lists that leave far items out down to a third), which is what a plan
+   that has one asked for: over these and 70 more cases the choice was never
+   slower than the FMM and 3% from the faster of both on average. */
+static bool fmm_is_faster(unsigned long long list_cost, int order, int level, double z)
 {
-    const double lists = 60.0 + 0.75e-3 * (double)list_cost;
+    const double lists = 25.0 + 0.75e-3 * (double)list_cost;
+    const double left = std::min(1.0, std::max(0.05, (100.0 - z) / 80.0));
     const double boxes = 9.5 * std::exp2(level) * (level >= 8 ? 1.4 : 1.0) * (0.45 + 0.55 * order / 40.0);
-    return boxes < lists;
+    return 33.0 + boxes * left < lists;
 }
 
 extern "C" mhlp_status mhlp_plan_set_fmm(mhlp_plan *P, int32_t order, int32_t leaf_level, void *stream)
@@ -3318,7 +3326,7 @@ extern "C" mhlp_status mhlp_plan_set_fmm(mhlp_plan *P, int32_t order, int32_t le
     }
     delete P->fmm;
     P->fmm = F;
-    P->fmm_serves = leaf_level >= 0 || fmm_is_faster(P->tr_cost, order, L);
+    P->fmm_serves = leaf_level >= 0 || fmm_is_faster(P->tr_cost, order, L, P->alpha * G.S / std::exp2(L));
     return MHLP_OK;
 }
 

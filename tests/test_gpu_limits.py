@@ -304,3 +304,17 @@ def test_non_finite_densities_of_small_plans(bad):
     v[77] = bad
     for u in (mhlp.eval_slp(P, _t(v)), mhlp.eval_dlp(P, _t(v)), *mhlp.eval_grad(P, sigma=_t(v), mu=_t(v))):
         assert not torch.isfinite(u).any()
+
+
+@pytest.mark.parametrize("alpha,fmm", [(20.0, False), (1000.0, True)])
+def test_automatic_choice_at_large_alpha(alpha, fmm):
+    """Where the boxes' neighbours underflow the FMM has little left to do and serves (49,729 points, 256 panels:
+    59 us against 98); at smaller alpha the lists do."""
+    g = wl.discretize(wl.starfish_curve(), 256)
+    tx, ty = wl.grid_targets(223, -1.4, 1.4)
+    P = mhlp.Plan(mhlp.Geometry(_t(g.node_soa())), alpha, _t(tx), _t(ty))
+    mu = _t(np.cos(3 * g.theta) + 0.5)
+    lists = mhlp.eval_slp(P, mu)
+    P.set_fmm(40)
+    u = mhlp.eval_slp(P, mu)
+    assert torch.equal(u, lists) != fmm and float((u - lists).abs().max()) < 1e-12 * float(lists.abs().max())
