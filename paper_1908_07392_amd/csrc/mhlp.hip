@@ -139,7 +139,7 @@ struct mhlp_plan {
     struct TreeShape {
         int waves = 0, split = 1, cut = 0; /* waves per block and blocks per group, direct items in 2^cut units */
     } tr, tr_skip;                         /* of far_tree_kernel; where it leaves items out */
-    bool tr_raw = false;                   /* no staging launch (TREE_RAW_MAX) */
+    int64_t tr_pairs = 0;                  /* (group, panel) pairs of a plan that may do without staging; 0: none may */
     NearParams np{};
     double near_factor = 1.2;
     int64_t part_cap = 0;     /* capacity of part (doubles)                 */
@@ -2038,9 +2038,14 @@ static mhlp_plan::TreeShape tree_shape(int64_t G, double U)
    clusters gather little, 2000 pairs 19.8, 15.7 | 35.9, 32.2); batches share the
    lists of plans on the curve, whose many groups run at once, so these keep their
    expansions.  Without expansions, charges are formed where they are read up to
-   TREE_RAW_MAX pairs: a launch less (11.0 -> 8.5 us at 16 panels), up to four
-   multiplications a source and lane more, 2 us at 8000 pairs. */
-constexpr int64_t TREE_DIRECT_MAX = 1024, TREE_RAW_MAX = 16384;
+   tree_raw_max pairs: a launch less, 2.5 us, for a multiplication a source and lane
+   with a charge, four with a dipole (us, 50 panels at alpha = 95, formed and
+   staged, single layer | double | both: 1000 pairs 12.2, 14.8 | 13.4, 14.6 | 15.8,
+   16.5; 2500 15.7, 18.1 | 16.6, 17.8 | 20.8, 20.6; 5000 22.2, 24.2 | 24.7, 23.9 |
+   30.8, 28.2; 16000 40.3, 41.4 | 47.7, 42.6 | 62.2, 52.2; gradients alike, the
+   stresslet 22.8, 22.8 at 2500). */
+constexpr int64_t TREE_DIRECT_MAX = 1024;
+constexpr int64_t tree_raw_max(bool sigma, bool mu) { return !mu ? 16384 : sigma ? 2048 : 3072; }
 
 /* Clusters, item lists and buffers of a plan's far field (tree.h), on
    the stream after the near lists, which the item lists read. */
@@ -2152,7 +2157,7 @@ static mhlp_status tree_setup(mhlp_plan *P, hipStream_t st)
     P->tr = tree_shape(G, U);
     if (P->tr.split > 1) TRY(dalloc(&T.part, (P->onsurf ? 2 : 4) * (int64_t)P->tr.split * 64 * G));
     T.skip = cost[1] >= mhlp::TR_ZSKIP && (P->onsurf ? U >= 400.0 : G >= 400);
-    P->tr_raw = !T.expands && !T.skip && !T.flux && G * Np <= TREE_RAW_MAX;
+    P->tr_pairs = !T.expands && !T.skip && !T.flux ? G * Np : 0;
     P->tr_skip = {P->onsurf ? 16 : G >= 1200 && U < 350.0 ? 4 : 8, 1, P->onsurf ? 2 : 0};
     return MHLP_OK;
 }
@@ -2415,7 +2420,7 @@ static void launch_tree_far(const FarArgs &A, const mhlp_plan *P, hipStream_t st
 template <template <bool, bool, bool> class Op, bool SLP, bool DLP, bool GRAD>
 static void launch_tree(const FarArgs &A, const mhlp_plan *P, hipStream_t st)
 {
-    if (P->tr_raw) return launch_tree_far<Op<SLP, DLP, true>>(A, P, st);
+    if (P->tr_pairs && P->tr_pairs <= tree_raw_max(SLP, DLP)) return launch_tree_far<Op<SLP, DLP, true>>(A, P, st);
     const mhlp::TreeDev &T = *P->tree;
     mhlp::tree_moments_kernel<SLP, DLP, GRAD><<<moments_grid(A, T), 256, 0, st>>>(A, T);
     launch_tree_far<Op<SLP, DLP, false>>(A, P, st);
@@ -2425,7 +2430,8 @@ template <bool GRAD>
 static void launch_tree_stokes(const FarArgs &A, const mhlp_plan *P, hipStream_t st)
 {
     const mhlp::TreeDev &T = *P->tree;
-    if (P->tr_raw) return launch_tree_far<mhlp::TreeStokes<GRAD, false, true>>(A, P, st);
+    if (P->tr_pairs && P->tr_pairs <= tree_raw_max(true, true))
+        return launch_tree_far<mhlp::TreeStokes<GRAD, false, true>>(A, P, st);
     dim3 grid = moments_grid(A, T);
     if (T.small) grid.z *= 2; /* the rows of the powers, too */
     mhlp::tree_stokes_kernel<GRAD><<<grid, 256, 0, st>>>(A, T);

@@ -318,3 +318,17 @@ def test_automatic_choice_at_large_alpha(alpha, fmm):
     P.set_fmm(40)
     u = mhlp.eval_slp(P, mu)
     assert torch.equal(u, lists) != fmm and float((u - lists).abs().max()) < 1e-12 * float(lists.abs().max())
+
+
+@pytest.mark.parametrize("groups", [40, 41, 61, 62, 327, 328])
+def test_charges_formed_where_read_or_staged(groups):
+    """Plans without expansions on both sides of the sizes up to which charges are formed where they are read, which
+    depend on the layers: the single layer, and the double layer's gradient, have the same bits alone as beside the
+    other (a double layer alone rounds K1 otherwise, as it needs no K0)."""
+    g = wl.discretize(wl.starfish_curve(), 50)
+    rng = np.random.default_rng(groups)
+    m = 64 * groups
+    P = mhlp.Plan(mhlp.Geometry(_t(g.node_soa())), 95.0, _t(rng.uniform(-1.6, 1.6, m)), _t(rng.uniform(-1.6, 1.6, m)))
+    sg, mu = _t(np.cos(3 * g.theta) + 0.5), _t(np.sin(2 * g.theta) + 0.25)
+    assert torch.equal(mhlp.eval_slp(P, sg), mhlp.eval_layer(P, sigma=sg, mu=mu)[0])
+    assert torch.equal(mhlp.eval_grad(P, mu=mu)[1], mhlp.eval_grad(P, sigma=sg, mu=mu)[1])
