@@ -2008,24 +2008,46 @@ static mhlp_status far_class_setup(mhlp_plan *P, hipStream_t st)
      U ~  32       128  128   64   64   32   32   16   16    8    8    4
      U ~ 128  256  256  128  128   64   64   64   32   16    8    8    4
      U ~ 512  512  256  256  256  128  128   64   32   32   16    8    8
-   and cut 3 below one unit a wave, 0 from about six on.  The formula is within
+   and cut 3 below one unit a wave, 0 from nine on (the stresslet from six on; potentials,
+   512 panels on the curve, 528 units, 6 a wave, 58 against 53).  The formula is within
    3.4% of the fastest on average, 33% at worst.
    Where far items are left out (tree.h) the second pass needs the group's sum,
    so one block serves a group.  That pays from 400 groups on, and on the curve,
-   where few panels are near a group, from 400 units a group on (both layers,
+   where few panels are near a group, if almost half of a group's panels are summed
+   directly, in 400 units or more, over 150 classes of z, or 500 over 90 (operator, left
+   out | split: 61 classes, 198 panels 41 | 31, 400 panels 61 | 45; 122 classes, 139 panels
+   (417 units) 25 | 20, 198 (594) 27 | 30, 400 (1200) 39 | 93; 512 panels, a third of them
+   direct, 58 | 53).  (Both layers,
    us, left out | split): alpha = 500, 256 panels, 313 groups 152 | 115, 469
    145 | 160, 1016 162 | 305; 64 panels, alpha = 100, 469 groups 68 | 83; on the
    curve, alpha = 500: 128 panels (242 units) 21 | 16, 256 (444) 24 | 32, 1024
    (1660) 42 | 277.  Waves: 8, but 4 for many groups of little work (1719
    groups, 64 panels, alpha = 500: 76 against 89; 256 panels 250 against 183)
-   and 16 on the curve (256 panels 24.5 against 28.4). */
-static mhlp_plan::TreeShape tree_shape(int64_t G, double U)
+   and 16 on the curve (256 panels 24.5 against 28.4).
+   Up to 50 groups, 85 on the curve: one block of 16 waves a CU, up to 100 two of 8,
+   in place of powers of two, where some CUs get a block more than others (us,
+   formula and this; on the curve, double layer: 139 panels, 35 groups, alpha = 100:
+   26.0, 20.6; 198 panels 36.8, 29.8; 70 panels, alpha = 350: 14.5, 11.1; 300 panels,
+   alpha = 1: 21.3, 17.3, but 100 groups 20.8, 21.1; off it, 12 to 45 shapes at 180
+   plans: 15% off the fastest at 30 to 60 groups, 4% with this, 13% and 6% at 60 to
+   100), and from there to 280 groups of less than 150 units four blocks of 8 (10%, 5%
+   at 250), six up to 134 with 100 panels and more (118 groups, alpha = 5, 256 panels
+   28.2, 25.2; 24 panels 20.6, 23.5).  On the curve, units of 2 sources below 100 units a group (128 panels,
+   alpha = 20: 15.1, of 4 16.3).  The stresslet's kernels hold fewer waves. */
+constexpr int TREE_CUS = 256;
+static mhlp_plan::TreeShape tree_shape(int64_t G, double U, int64_t Np, bool curve, bool stokes)
 {
+    if (!stokes && G >= (curve ? 1 : 12)) {
+        if (G <= (curve ? 85 : 50))
+            return {16, (int)std::min<int64_t>(curve ? 14 : 16, TREE_CUS / G), curve && U < 100.0 ? 3 : U < 480.0 ? 2 : 1};
+        if (!curve && G <= 100) return {8, (int)(2 * TREE_CUS / G), 2};
+        if (!curve && G <= 280 && U < 150.0) return {8, G < 135 && Np >= 100 ? 6 : 4, 2};
+    }
     const double lu = std::log2(std::max(8.0, U));
     int e = (int)std::floor(9.5 - 0.55 * std::log2((double)G) + 0.3 * (lu - 6.0));
     e = std::max(2, std::min({e, (int)lu + 2, 9}));
     if (G >= 1200) e = 2;
-    const int cut = lu - e < 0.25 && e >= 6 ? 3 : lu - e < 2.5 ? 2 : 0;
+    const int cut = lu - e < 0.25 && e >= 6 ? 3 : lu - e < (stokes ? 2.5 : 3.1) ? 2 : 0;
     if (e <= 3) return {1 << e, 1, cut};
     if (e == 4) return {4, 4, cut};
     return {8, 1 << (e - 3), cut};
@@ -2154,9 +2176,10 @@ static mhlp_status tree_setup(mhlp_plan *P, hipStream_t st)
     T.expands = cost[3] != 0;
     if (P->stokes && cost[1] > 0) T.small = reinterpret_cast<double *>(P->tree_mem + o_small);
     const double U = (double)cost[0] / (double)G;
-    P->tr = tree_shape(G, U);
+    P->tr = tree_shape(G, U, Np, P->onsurf, P->stokes);
     if (P->tr.split > 1) TRY(dalloc(&T.part, (P->onsurf ? 2 : 4) * (int64_t)P->tr.split * 64 * G));
-    T.skip = cost[1] >= mhlp::TR_ZSKIP && (P->onsurf ? U >= 400.0 : G >= 400);
+    const double least = std::max(1.35 * (double)Np, cost[1] >= 150 ? 400.0 : 500.0);
+    T.skip = P->onsurf ? cost[1] >= 90 && U >= least : cost[1] >= mhlp::TR_ZSKIP && G >= 400;
     P->tr_pairs = !T.expands && !T.skip && !T.flux ? G * Np : 0;
     P->tr_skip = {P->onsurf ? 16 : G >= 1200 && U < 350.0 ? 4 : 8, 1, P->onsurf ? 2 : 0};
     return MHLP_OK;

@@ -58,7 +58,7 @@ struct TreeDev {
     longlong2 *at = nullptr;                 /* [groups]: begin and end of a group's list */
     int2 *cnt = nullptr;                     /* [groups]: numbers of direct items and expansions */
     double *part = nullptr;                  /* [groups][blocks per group][fields][64] sums of split groups */
-    uint32_t *arrived = nullptr;             /* [groups]: blocks of split groups that are through, counted on and on */
+    uint32_t *arrived = nullptr;             /* [groups]: blocks of split groups that are through, counted round and round */
     unsigned long long *cost = nullptr;      /* total work of the groups (tree_cost); [1]: the largest spread of
                                                 the z classes of a group's items (TR_ZSTEP), of a stresslet plan whether
                                                 it has TR_SMALL items; [2]: all items; [3]: whether there are expansions */
@@ -1639,7 +1639,7 @@ __device__ __forceinline__ double tree_row_sum(double v)
    direct ones in units of 16 / 2^cut sources in turn, expansions in equal
    runs, starting from the other end, so that no wave gets more than its share
    of both, and the near corrections by node.  The wave sums are added
-   in wave order; with several blocks a group (a power of two) each leaves them
+   in wave order; with several blocks a group each leaves them
    in its slot, and the last one to arrive adds the slots in order: a launch of
    its own for that took 4 us (64 targets, 256 sources: 15 -> 11 us a call in
    all).  A cluster whose expansion is not finite (an infinite or NaN
@@ -1810,7 +1810,7 @@ __global__ __launch_bounds__(64 * Op::WMAX) void far_tree_kernel(FarArgs A, Tree
            all XCDs share; they have arrived once they are waited for */
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        if (threadIdx.x == 0) last = (atomicAdd(T.arrived + g, 1u) & (split - 1)) == (uint32_t)split - 1;
+        if (threadIdx.x == 0) last = atomicInc(T.arrived + g, (uint32_t)split - 1) == (uint32_t)split - 1;
         __syncthreads();
         if (!last) return;
         /* the waves share the slots of the fields, as many sums for a field

@@ -241,7 +241,8 @@ def test_items_left_out_on_the_curve(panels, alpha):
     assert (np.abs(out[far] - d.sum(axis=1)) <= ((3e-14 + 5e-16 * alpha * r) * size).sum(axis=1) + 1e-300).all()
 
 
-@pytest.mark.parametrize("panels,m", [(16, 60), (64, 300), (256, 60), (40, 9000), (64, 20000)])
+@pytest.mark.parametrize("panels,m", [(16, 60), (64, 300), (256, 60), (64, 960), (64, 2500), (50, 5000), (40, 9000),
+                                      (64, 20000)])
 def test_split_groups_finish_alike(panels, m):
     """Groups summed by several blocks, the last of which adds the slots: the same bits whichever that is, in calls
     of either layer, gradients and both in turn, and in replays of a captured graph between them."""
@@ -332,3 +333,17 @@ def test_charges_formed_where_read_or_staged(groups):
     sg, mu = _t(np.cos(3 * g.theta) + 0.5), _t(np.sin(2 * g.theta) + 0.25)
     assert torch.equal(mhlp.eval_slp(P, sg), mhlp.eval_layer(P, sigma=sg, mu=mu)[0])
     assert torch.equal(mhlp.eval_grad(P, mu=mu)[1], mhlp.eval_grad(P, sigma=sg, mu=mu)[1])
+
+
+@pytest.mark.parametrize("panels", [16, 70, 139, 341, 344])
+def test_operator_of_any_number_of_blocks_a_group(panels):
+    """cos(2 theta) is an eigenfunction of 1/2 I + D on the circle, with -alpha I_n K_n', where a group's blocks are as
+    many as fill the chip: the same bits each time, and within 1e-11 of it."""
+    g = wl.discretize(wl.Curve("circle", R=1.0), panels)
+    P = mhlp.Plan(mhlp.Geometry(_t(g.node_soa())), 20.0)
+    lam = -20.0 * sp.iv(2, 20.0) * sp.kvp(2, 20.0)
+    mu = np.cos(2 * g.theta)
+    first = mhlp.apply_bie(P, _t(mu))
+    for k in range(20):
+        assert torch.equal(mhlp.apply_bie(P, _t(mu)), first)
+    assert np.max(np.abs(first.cpu().numpy() - lam * mu)) < 1e-11 * abs(lam)
