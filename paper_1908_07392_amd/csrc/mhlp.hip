@@ -1963,7 +1963,7 @@ extern "C" mhlp_status mhlp_plan_destroy(mhlp_plan *P)
         if (p) (void)hipFree(p);
     delete P->fmm;
     if (P->tree) {
-        void *tp[] = {P->tree_mem, P->tree_items, P->tree->part};
+        void *tp[] = {P->tree_mem, P->tree_items, P->tree->part, P->tree->base};
         for (void *p : tp)
             if (p) (void)hipFree(p);
         delete P->tree;
@@ -2011,19 +2011,18 @@ static mhlp_status far_class_setup(mhlp_plan *P, hipStream_t st)
    and cut 3 below one unit a wave, 0 from nine on (the stresslet from six on; potentials,
    512 panels on the curve, 528 units, 6 a wave, 58 against 53).  The formula is within
    3.4% of the fastest on average, 33% at worst.
-   Where far items are left out (tree.h) the second pass needs the group's sum,
-   so one block serves a group.  That pays from 400 groups on, and on the curve,
-   where few panels are near a group, if almost half of a group's panels are summed
-   directly, in 400 units or more, over 150 classes of z, or 500 over 90 (operator, left
-   out | split: 61 classes, 198 panels 41 | 31, 400 panels 61 | 45; 122 classes, 139 panels
-   (417 units) 25 | 20, 198 (594) 27 | 30, 400 (1200) 39 | 93; 512 panels, a third of them
-   direct, 58 | 53).  (Both layers,
-   us, left out | split): alpha = 500, 256 panels, 313 groups 152 | 115, 469
-   145 | 160, 1016 162 | 305; 64 panels, alpha = 100, 469 groups 68 | 83; on the
-   curve, alpha = 500: 128 panels (242 units) 21 | 16, 256 (444) 24 | 32, 1024
-   (1660) 42 | 277.  Waves: 8, but 4 for many groups of little work (1719
-   groups, 64 panels, alpha = 500: 76 against 89; 256 panels 250 against 183)
-   and 16 on the curve (256 panels 24.5 against 28.4).
+   Where far items are left out (tree.h) the second pass needs the group's sum.  Off
+   the curve one block makes both, which pays from 400 groups on (both layers, us, left
+   out | split: alpha = 500, 256 panels, 313 groups 152 | 115, 469 145 | 160, 1016 162 |
+   305; 64 panels, alpha = 100, 469 groups 68 | 83), of 8 waves, or 4 for many groups of
+   little work (1719 groups, 64 panels, alpha = 500: 76 against 89; 256 panels 250
+   against 183).  On the curve, where few panels are near a group, each pass is a
+   launch: if almost half of a group's panels are summed directly, in 400 units or
+   more, over 150 classes of z, or 500 over 90 (double layer, smooth density | one that
+   spans 300 decades, of which little can be left out | split; one launch for both made
+   the second twice the third: alpha = 500, 256 panels 22 | 26 | 36, 512 29 | 37 | 93,
+   1024 44 | 76 | 344; alpha = 200, 198 panels 25 | 37 | 38; 61 classes, 400 panels, one
+   launch 61 | . | 45; 512 panels, a third of them direct, one launch 58 | . | 53).
    Up to 50 groups, 85 on the curve: one block of 16 waves a CU, up to 100 two of 8,
    in place of powers of two, where some CUs get a block more than others (us,
    formula and this; on the curve, double layer: 139 panels, 35 groups, alpha = 100:
@@ -2177,11 +2176,17 @@ static mhlp_status tree_setup(mhlp_plan *P, hipStream_t st)
     if (P->stokes && cost[1] > 0) T.small = reinterpret_cast<double *>(P->tree_mem + o_small);
     const double U = (double)cost[0] / (double)G;
     P->tr = tree_shape(G, U, Np, P->onsurf, P->stokes);
-    if (P->tr.split > 1) TRY(dalloc(&T.part, (P->onsurf ? 2 : 4) * (int64_t)P->tr.split * 64 * G));
     const double least = std::max(1.35 * (double)Np, cost[1] >= 150 ? 400.0 : 500.0);
     T.skip = P->onsurf ? cost[1] >= 90 && U >= least : cost[1] >= mhlp::TR_ZSKIP && G >= 400;
     P->tr_pairs = !T.expands && !T.skip && !T.flux ? G * Np : 0;
-    P->tr_skip = {P->onsurf ? 16 : G >= 1200 && U < 350.0 ? 4 : 8, 1, P->onsurf ? 2 : 0};
+    P->tr_skip = {G >= 1200 && U < 350.0 ? 4 : 8, 1, 0};
+    if (P->onsurf) P->tr_skip = 3 * G <= TREE_CUS ? P->tr : mhlp_plan::TreeShape{16, 2 * G <= TREE_CUS ? 2 : 1, 1};
+    const int split = std::max(P->tr.split, P->tr_skip.split);
+    if (split > 1) TRY(dalloc(&T.part, (P->onsurf ? 2 : 4) * (int64_t)split * 64 * G));
+    if (T.skip && P->onsurf) {
+        TRY(dalloc(&T.base, 2 * (64 + 1) * G)); /* two fields, and their room */
+        T.room = reinterpret_cast<float *>(T.base + 2 * 64 * G);
+    }
     return MHLP_OK;
 }
 
@@ -2433,10 +2438,18 @@ static void launch_tree_far(const FarArgs &A, const mhlp_plan *P, hipStream_t st
         S.order += g0;
         S.cut = F.cut;
         const dim3 grid((unsigned)std::min(most, G - g0), (unsigned)F.split);
-        if (skip)
-            mhlp::far_tree_kernel<Op, Op::SKIP><<<grid, threads, 0, st>>>(A, S);
-        else
-            mhlp::far_tree_kernel<Op, false><<<grid, threads, 0, st>>>(A, S);
+        if constexpr (Op::SKIP) {
+            if (skip && P->onsurf) {
+                mhlp::far_tree_kernel<Op, mhlp::TREE_NEAREST><<<grid, threads, 0, st>>>(A, S);
+                mhlp::far_tree_kernel<Op, mhlp::TREE_REST><<<grid, threads, 0, st>>>(A, S);
+                continue;
+            }
+            if (skip) {
+                mhlp::far_tree_kernel<Op, mhlp::TREE_BOTH><<<grid, threads, 0, st>>>(A, S);
+                continue;
+            }
+        }
+        mhlp::far_tree_kernel<Op, mhlp::TREE_ALL><<<grid, threads, 0, st>>>(A, S);
     }
 }
 

@@ -58,6 +58,8 @@ struct TreeDev {
     longlong2 *at = nullptr;                 /* [groups]: begin and end of a group's list */
     int2 *cnt = nullptr;                     /* [groups]: numbers of direct items and expansions */
     double *part = nullptr;                  /* [groups][blocks per group][fields][64] sums of split groups */
+    double *base = nullptr;                  /* [groups][fields][64] sums of the items always summed (TREE_NEAREST) */
+    float *room = nullptr;                   /* [groups][fields]: log2 of what an item may then add without showing */
     uint32_t *arrived = nullptr;             /* [groups]: blocks of split groups that are through, counted round and round */
     unsigned long long *cost = nullptr;      /* total work of the groups (tree_cost); [1]: the largest spread of
                                                 the z classes of a group's items (TR_ZSTEP), of a stresslet plan whether
@@ -1650,8 +1652,9 @@ __device__ __forceinline__ double tree_row_sum(double v)
    instructions per group against 304e3 for the direct sum of all pairs, 66 us
    against 1.07 ms; alpha = 500, all pairs direct: within 5% of the issue rate before items were
    left out).
-   Far items that cannot show (SKIP: plans with a large spread of z, one block
-   a group): the items of the TR_ZNEAR + 1 nearest z classes are summed first;
+   Far items that cannot show (plans with a large spread of z; off the curve one
+   block a group makes both passes, on it, where groups are few, each pass is a
+   launch of split groups): the items of the TR_ZNEAR + 1 nearest z classes are summed first;
    with the smallest |u| of the group's targets so far in hand, an item is left
    out when the bound of its charges times e^-z stays below 2^-55 |u| over the
    number of items, so that all that is left out stays below 2^-55 of the nearest
@@ -1661,10 +1664,13 @@ __device__ __forceinline__ double tree_row_sum(double v)
    272 -> 233 / 365 / 239 / 142 us.
    Waves per group (tree_shape): four for many groups; up to 512 for few, where
    the longest wave (a direct panel in one wave takes about 20 us) sets the time. */
-template <class Op, bool SKIP>
+enum TreePass { TREE_ALL, TREE_BOTH, TREE_NEAREST, TREE_REST }; /* every item; those that show: in two passes, or the first, the second */
+
+template <class Op, TreePass PASS>
 __global__ __launch_bounds__(64 * Op::WMAX) void far_tree_kernel(FarArgs A, TreeDev T)
 {
     constexpr int NF = Op::NF;
+    constexpr bool SKIP = PASS != TREE_ALL;
     __shared__ double red[NF][Op::WMAX][64];
     const double *mu;
     if (!far_density(A, mu)) return;
@@ -1689,7 +1695,7 @@ __global__ __launch_bounds__(64 * Op::WMAX) void far_tree_kernel(FarArgs A, Tree
         double nr[NF];
 #pragma unroll
         for (int f = 0; f < NF; ++f) nr[f] = 0.0;
-        if (wg < 16)
+        if (PASS != TREE_REST && wg < 16)
             for (int32_t q = k0; q < k1; ++q) {
                 const int64_t p = A.npan[q];
                 if (p < 0) continue;
@@ -1701,10 +1707,20 @@ __global__ __launch_bounds__(64 * Op::WMAX) void far_tree_kernel(FarArgs A, Tree
     const int nsrc = 16 >> T.cut;
     const uint32_t znear = SKIP ? (uint32_t)(T.znear[g] + TR_ZNEAR) : 255u;
     float room = -INFINITY;
+    /* log2 of what an item may add to field sums s of the group's targets without showing */
+    auto room_of = [&](double s) {
+        s = __builtin_isfinite(s) ? fabs(s) : 0.0; /* beside a NaN or an infinity nothing is left out */
+        for (int o = 32; o > 0; o >>= 1) s = fmin(s, __shfl_xor(s, o));
+        return (float)log2(s) - 55.0f - log2f((float)(cnt.x + cnt.y));
+    };
+    if constexpr (PASS == TREE_REST) {
+        room = INFINITY;
+        for (int f = 0; f < NF; ++f) room = fminf(room, T.room[g * NF + f]);
+        room = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(room)));
+    }
 #pragma unroll 1
-    for (int pass = 0; pass < (SKIP ? 2 : 1); ++pass) {
-        if (pass == 1) {
-            /* log2 of what an item may add to any target's field without showing */
+    for (int pass = PASS == TREE_REST; pass < (PASS == TREE_BOTH || PASS == TREE_REST ? 2 : 1); ++pass) {
+        if (PASS == TREE_BOTH && pass == 1) {
             put();
             __syncthreads();
             room = INFINITY;
@@ -1712,9 +1728,7 @@ __global__ __launch_bounds__(64 * Op::WMAX) void far_tree_kernel(FarArgs A, Tree
             for (int f = 0; f < NF; ++f) {
                 double s = 0.0;
                 for (int v = 0; v < W; ++v) s += red[f][v][lane];
-                s = __builtin_isfinite(s) ? fabs(s) : 0.0; /* beside a NaN or an infinity nothing is left out */
-                for (int o = 32; o > 0; o >>= 1) s = fmin(s, __shfl_xor(s, o));
-                room = fminf(room, (float)log2(s) - 55.0f - log2f((float)(cnt.x + cnt.y)));
+                room = fminf(room, room_of(s));
             }
             room = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(room)));
             __syncthreads();
@@ -1826,12 +1840,24 @@ __global__ __launch_bounds__(64 * Op::WMAX) void far_tree_kernel(FarArgs A, Tree
         }
         W = H;
     }
+    if constexpr (PASS == TREE_NEAREST) {
+        __syncthreads();
+        for (int f = w; f < NF; f += waves) {
+            double s = 0.0;
+            for (int v = 0; v < W; ++v) s += red[f][v][lane];
+            T.base[(g * NF + f) * 64 + lane] = s;
+            const float r = room_of(s);
+            if (lane == 0) T.room[g * NF + f] = r;
+        }
+        return;
+    }
     const double cm = Op::common(A, T); /* every lane takes part */
     __syncthreads();
     if (!valid) return;
     for (int f = w; f < NF; f += waves) {
         double s = 0.0;
         for (int v = 0; v < W; ++v) s += red[f][v][lane];
+        if constexpr (PASS == TREE_REST) s += T.base[(g * NF + f) * 64 + lane];
         Op::store(A, cm, mu, i, f, s);
     }
 }

@@ -347,3 +347,17 @@ def test_operator_of_any_number_of_blocks_a_group(panels):
     for k in range(20):
         assert torch.equal(mhlp.apply_bie(P, _t(mu)), first)
     assert np.max(np.abs(first.cpu().numpy() - lam * mu)) < 1e-11 * abs(lam)
+
+
+@pytest.mark.parametrize("panels,alpha", [(198, 200.0), (256, 500.0), (360, 350.0), (700, 500.0)])
+def test_items_left_out_beside_tiny_sums(panels, alpha):
+    """On the curve, a density over 260 decades: where it is tiny, the items of the panels where it is not have to be
+    summed, whatever the nearest ones give.  The kernel has one sign on the circle, so that the values of the loud and
+    the quiet part of the density add up to those of the whole to 1e-12 at every node (left out: 2^-55)."""
+    g = wl.discretize(wl.Curve("circle", R=1.0), panels)
+    P = mhlp.Plan(mhlp.Geometry(_t(g.node_soa())), alpha)
+    mu = np.exp(-600.0 * np.sin(g.theta / 2) ** 2)
+    loud = np.where(mu > 1e-20, mu, 0.0)
+    whole, again, a, b = (mhlp.eval_dlp(P, _t(v)) for v in (mu, mu, loud, mu - loud))
+    assert torch.equal(whole, again)
+    assert bool(torch.all(torch.abs(whole - a - b) <= 1e-12 * torch.abs(whole)))
