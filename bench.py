@@ -41,18 +41,18 @@ FP64_PEAK_TFLOPS = 78.6        # MI355X vector FP64 (published)
 # x 64 lanes, FMA = 2): profiles/far_tree_starfish4096_grid512_counters.txt.
 # alpha = 5: mostly expansions; 50: half of the work direct; 500: all direct,
 # items that cannot show left out.
-FLOP_PER_EVAL_FP64 = {5.0: 2.14e9, 50.0: 6.63e9, 500.0: 3.50e9}
-VALU_PER_EVAL_FP64 = {5.0: 26.2e6 * 64, 50.0: 81.1e6 * 64, 500.0: 44.6e6 * 64}
+FLOP_PER_EVAL_FP64 = {5.0: 2.14e9, 50.0: 6.63e9, 500.0: 3.58e9}
+VALU_PER_EVAL_FP64 = {5.0: 26.5e6 * 64, 50.0: 81.2e6 * 64, 500.0: 49.2e6 * 64}
 COUNTED_TARGETS = 109314
 # the issue rate they are bound by: 256 CUs x 2.4 GHz, one 64-lane VALU
 # instruction per CU per clock
 VALU_ISSUE_PER_S = 256 * 2.4e9 * 64
-# launch shapes (far-field source splits) chosen by the autotuner on MI355X for
-# the plans of this benchmark
+# launch shapes (source splits of the mixed-precision tiles) chosen by the
+# autotuner on MI355X for the plans of this benchmark
 TUNED_SPLITS = os.path.join(ROOT, "paper_1908_07392_amd", "tuning", "mi355x_far_splits.json")
 # HBM bytes per fused FP64 evaluation (FETCH_SIZE + WRITE_SIZE of both kernels,
 # averaged over the three alphas; same profile)
-PROFILED_TRAFFIC = 9940000
+PROFILED_TRAFFIC = 10070000
 
 
 def parse():
@@ -165,7 +165,7 @@ def main():
         kw = dict(use_cache=True, path=args.tune_cache, write=args.tune_write)
         # the FP64 operator and evaluation do not use source splits (cluster
         # lists, shaped by the number of target groups): the splits serve the
-        # mixed-precision leg's operator and evaluation, tuned for those
+        # mixed-precision tiles, tuned for those
         r_on = autotune.tune(on, "bie", precision=mhlp.MIXED, reps=5, **kw)
         r_off = autotune.tune(off, "both", precision=mhlp.MIXED, reps=5, **kw)
         tuned[f"alpha={a:g}"] = {"bie_nsplit": r_on["nsplit"], "eval_nsplit": r_off["nsplit"],
@@ -270,7 +270,7 @@ def main():
                       "n_sources": N, "n_targets": M, "alphas": list(cfg["alphas"]), "precision": "fp64"},
            "pair_terms_per_s": round(total_terms / elapsed / 1e9, 4),
            "gmres": gm, "plan_build_ms": round(plan_ms, 1), "autotune": tuned, "roofline": roofline}
-    # ---- mixed precision (FP32 far field, FP64 near/identity/Arnoldi, GMRES-IR) on the same step
+    # ---- mixed precision on the same step: its evaluations sum FP32 pairs; its solves are the FP64 path
     def mixed_step():
         tm = {}
         for a in cfg["alphas"]:

@@ -75,7 +75,7 @@ typedef struct {
 
 typedef struct {
     int32_t iters;        /* Arnoldi steps taken                                   */
-    int32_t restarts;     /* outer cycles (restarts or refinement steps)           */
+    int32_t restarts;     /* outer cycles                                         */
     double rel_residual;  /* true ||g - A mu|| / ||g|| at exit (FP64 operator)     */
     double x0_residual;   /* true relative residual of the initial guess           */
     int32_t converged;    /* 1 if rel_residual <= tol                              */

@@ -653,8 +653,8 @@ __device__ __forceinline__ double wave_sum_dpp(double v)
     return __hiloint2double(hi, lo);
 }
 
-/* Plan time: the fine piece of every (wave of 64 targets, panel) for the FP64
-   far field (low 7 bits: piece + 1, 0 for z <= 2 everywhere, KQ_NP + 1 when
+/* Plan time: the fine piece of every (wave of 64 targets, panel) for the
+   mixed-precision tiles (low 7 bits: piece + 1, 0 for z <= 2 everywhere, KQ_NP + 1 when
    the pairs need the per-pair selection; bit 7 set when some target of the
    wave lists the panel as near), from the exact extreme distances of the
    wave's targets to the panel's nodes; targets that list the panel do not vote
@@ -2019,10 +2019,11 @@ static mhlp_status far_class_setup(mhlp_plan *P, hipStream_t st)
    against 183).  On the curve, where few panels are near a group, each pass is a
    launch: if almost half of a group's panels are summed directly, in 400 units or
    more, over 150 classes of z, or 500 over 90 (double layer, smooth density | one that
-   spans 300 decades, of which little can be left out | split; one launch for both made
-   the second twice the third: alpha = 500, 256 panels 22 | 26 | 36, 512 29 | 37 | 93,
-   1024 44 | 76 | 344; alpha = 200, 198 panels 25 | 37 | 38; 61 classes, 400 panels, one
-   launch 61 | . | 45; 512 panels, a third of them direct, one launch 58 | . | 53).
+   spans 300 decades, of which little can be left out | split, nothing left out: alpha =
+   500, 256 panels 22 | 26 | 36, 512 29 | 37 | 93, 1024 44 | 76 | 344; alpha = 200, 198
+   panels 25 | 37 | 38; both passes in one launch, smooth: 61 classes, 400 panels 61 | . |
+   45; 512 panels, a third of them direct, 58 | . | 53; a solve whose density spans
+   decades 0.32 ms, 0.23 with nothing left out, 0.20 in two launches).
    Up to 50 groups, 85 on the curve: one block of 16 waves a CU, up to 100 two of 8,
    in place of powers of two, where some CUs get a block more than others (us,
    formula and this; on the curve, double layer: 139 panels, 35 groups, alpha = 100:
@@ -4731,8 +4732,8 @@ extern "C" mhlp_status mhlp_batch_create(int32_t n_geom, const mhlp_plan *const 
 /* Work list of the grouped operator launch for about `target` blocks in total:
    each geometry gets blocks in proportion to the work of its item lists, as
    splits of its groups of 64 targets (at least one item per wave); items are
-   ordered by decreasing work, so the longest start first.  tpl and src shaped
-   the tiles of an earlier launch; they are kept and reported, no more. */
+   ordered by decreasing work, so the longest start first.  tpl and src do not
+   shape the launch; they are kept and reported, no more. */
 static mhlp_status batch_build_work(mhlp_batch *B, int64_t target, int tpl, int src, hipStream_t st)
 {
     const int n_geom = B->n_geom, n_rhs = B->R;

@@ -105,7 +105,9 @@ __global__ __launch_bounds__(256) void vol_box_kernel(VolTree V, VolSetup S)
     if (t < 4) V.box[4 * blockIdx.x + t] = red[t][0];
 }
 
-/* place of a cell along the Hilbert curve: unlike Morton order its runs of any
+/* place of a cell along the Hilbert curve (the well-known iteration over the
+   bits from the top that takes a quadrant's two bits, then undoes its
+   reflection and transposition): unlike Morton order its runs of any
    start and length are connected, so panels and clusters stay compact whatever
    the grid (the figures are at vol_far_kernel) */
 __device__ __forceinline__ uint32_t vol_curve(uint32_t x, uint32_t y, int bits)
